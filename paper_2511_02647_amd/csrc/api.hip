@@ -60,7 +60,13 @@ bool use_mfma_prefill(const fedattn_params* p) {
   return p->dtype == FEDATTN_BF16 && (p->head_dim == 64 || p->head_dim == 128);
 }
 
-// keep chunks that are not whole 64-row tiles: the MFMA path packs the kept rows first
+int elem_bytes(const fedattn_params* p) { return p->dtype == FEDATTN_BF16 ? 2 : 4; }
+
+// prefill on the matrix cores in fp32 products and sums; a keep-list needs the workspace there, without
+// one these shapes run on the general kernel, which reads the flags itself
+bool use_f32_prefill(const fedattn_params* p) { return p->dtype == FEDATTN_F32; }
+
+// keep chunks that are not whole 64-row tiles: the tile kernels pack the kept rows first
 bool needs_row_packing(int chunk_tokens) { return chunk_tokens > 0 && chunk_tokens % kKvTile != 0; }
 
 // Decode splits every participant's cache segment into chunks of `rows` cache rows (a
@@ -98,7 +104,7 @@ int decode_chunk_rows(int64_t total_rows, int Hkv) {
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 // prefill workspace: [kept_cum: (kMaxP+1) int32, padded][kept_tiles: int2 per 64-row tile]
-// and, for keep chunks finer than a tile on the MFMA path:
+// and, for keep chunks finer than a tile where a tile kernel runs:
 // [kept_rows: kMaxP int32][src_index: int32 per token][packed K][packed V]
 constexpr size_t kKeptCumBytes = 1024;
 constexpr size_t kKeptRowsBytes = 512;
@@ -111,8 +117,8 @@ PrefillWs prefill_ws_layout(const fedattn_params* p, int32_t tokens, int32_t chu
   w.tiles_off = kKeptCumBytes;
   w.rows_off = w.tiles_off + align_up(max_tiles * sizeof(int2), 256);
   w.index_off = w.k_off = w.v_off = w.total = w.rows_off;
-  if (use_mfma_prefill(p) && needs_row_packing(chunk_tokens)) {
-    const size_t kv_bytes = (size_t)tokens * (size_t)p->n_kv_heads * (size_t)p->head_dim * 2;
+  if ((use_mfma_prefill(p) || use_f32_prefill(p)) && needs_row_packing(chunk_tokens)) {
+    const size_t kv_bytes = (size_t)tokens * (size_t)p->n_kv_heads * (size_t)p->head_dim * (size_t)elem_bytes(p);
     w.index_off = w.rows_off + kKeptRowsBytes;
     w.k_off = w.index_off + align_up((size_t)tokens * 4, 256);
     w.v_off = w.k_off + align_up(kv_bytes, 256);
@@ -185,24 +191,15 @@ fedattn_status run_prefill(const fedattn_params* p, int32_t block_idx0, int32_t 
   a.v_list = v;
   const int G = a.Hq / a.Hkv;
   a.heads_per_wg = (G % 4 == 0) ? 4 : ((G % 2 == 0) ? 2 : 1);
-  a.q_tile_rows = kWaveRows * (4 / a.heads_per_wg);
-  int64_t tiles = 0, chunks = 0, pairs = 0;
+  int64_t chunks = 0;
   for (int n = 0; n <= N; ++n) {
     a.seg.seg_off[n] = seg[n];
-    a.seg.tile_cum[n] = (int32_t)tiles;
     a.seg.chunk_cum[n] = (int32_t)chunks;
-    a.seg.pair_cum[n] = (int32_t)pairs;
-    if (n < N) {
-      const int64_t len = seg[n + 1] - seg[n];
-      const int64_t tn = (len + a.q_tile_rows - 1) / a.q_tile_rows;
-      tiles += tn;
-      pairs += (tn + 1) / 2;
-      if (has_keep) chunks += (len + chunk_tokens - 1) / chunk_tokens;
-    }
+    if (n < N && has_keep) chunks += ((int64_t)seg[n + 1] - seg[n] + chunk_tokens - 1) / chunk_tokens;
   }
-  a.n_q_tiles = (int32_t)tiles;
+  lay_out_query_tiles(a, kWaveRows * (4 / a.heads_per_wg));
   a.n_cus = device_cus();
-  if (tiles * a.Hkv * (G / a.heads_per_wg) > 0x7fffffffLL) return fail(FEDATTN_EUNSUPPORTED, "too many query tiles");
+  if ((int64_t)a.n_q_tiles * a.Hkv * (G / a.heads_per_wg) > 0x7fffffffLL) return fail(FEDATTN_EUNSUPPORTED, "too many query tiles");
 
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   // a block reads the keep-list only if it is a sync block
@@ -211,14 +208,17 @@ fedattn_status run_prefill(const fedattn_params* p, int32_t block_idx0, int32_t 
     for (int b = 0; b < n_blocks && !any_sync; ++b) any_sync = sync_block_rule(p->sync_interval, block_idx0 + b);
   if (!has_keep || !any_sync) a.keep_chunks = nullptr;
 
-  if (mfma) {
-    if (a.keep_chunks) {
-      if (n_blocks != 1) return fail(FEDATTN_EUNSUPPORTED, "a keep-list applies to one block per call");
-      const PrefillWs w = prefill_ws_layout(p, total, chunk_tokens);
-      if (!workspace || workspace_bytes < w.total)
-        return fail(FEDATTN_EWORKSPACE, "prefill with a keep-list needs %zu workspace bytes, got %zu", w.total,
-                    workspace_bytes);
-      if (!aligned16(workspace)) return fail(FEDATTN_EINVAL, "workspace must be 16-byte aligned");
+  bool tiled = mfma || use_f32_prefill(p);
+  if (tiled && a.keep_chunks) {
+    if (n_blocks != 1) return fail(FEDATTN_EUNSUPPORTED, "a keep-list applies to one block per call");
+    const PrefillWs w = prefill_ws_layout(p, total, chunk_tokens);
+    const bool have_ws = workspace && workspace_bytes >= w.total;
+    if (mfma && !have_ws)
+      return fail(FEDATTN_EWORKSPACE, "prefill with a keep-list needs %zu workspace bytes, got %zu", w.total,
+                  workspace_bytes);
+    if (mfma && !aligned16(workspace)) return fail(FEDATTN_EINVAL, "workspace must be 16-byte aligned");
+    tiled = have_ws && aligned16(workspace);
+    if (tiled) {
       unsigned char* ws = reinterpret_cast<unsigned char*>(workspace);
       int32_t* kept_cum = reinterpret_cast<int32_t*>(ws);
       int2* kept_tiles = reinterpret_cast<int2*>(ws + w.tiles_off);
@@ -228,7 +228,7 @@ fedattn_status run_prefill(const fedattn_params* p, int32_t block_idx0, int32_t 
       if (needs_row_packing(chunk_tokens)) {
         a.k_list = ws + w.k_off;
         a.v_list = ws + w.v_off;
-        e = launch_pack_kept_rows(a, reinterpret_cast<int32_t*>(ws + w.rows_off),
+        e = launch_pack_kept_rows(a, a.Hkv * a.D * elem_bytes(p), reinterpret_cast<int32_t*>(ws + w.rows_off),
                                   reinterpret_cast<int32_t*>(ws + w.index_off), ws + w.k_off, ws + w.v_off,
                                   kept_tiles, kept_cum, s);
       } else {
@@ -236,12 +236,13 @@ fedattn_status run_prefill(const fedattn_params* p, int32_t block_idx0, int32_t 
       }
       if (e != hipSuccess) return fail(FEDATTN_ELAUNCH, "keep-list compaction: %s", hipGetErrorString(e));
     }
-    hipError_t e = launch_prefill_mfma(a, n_blocks, s);
-    if (e != hipSuccess) return fail(FEDATTN_ELAUNCH, "prefill (mfma): %s", hipGetErrorString(e));
-  } else {
-    hipError_t e = launch_prefill_generic(a, n_blocks, p->dtype, s);
-    if (e != hipSuccess) return fail(FEDATTN_ELAUNCH, "prefill (general): %s", hipGetErrorString(e));
   }
+  hipError_t e;
+  if (!tiled)
+    e = launch_prefill_generic(a, n_blocks, p->dtype, s);
+  else
+    e = mfma ? launch_prefill_mfma(a, n_blocks, s) : launch_prefill_f32(a, n_blocks, s);
+  if (e != hipSuccess) return fail(FEDATTN_ELAUNCH, "prefill: %s", hipGetErrorString(e));
   return FEDATTN_OK;
 }
 
@@ -313,10 +314,12 @@ fedattn_status fedattn_prefill_sync_local_kv(const fedattn_params* params, const
                   "the participants' K/V do not lie back to back: aggregating them needs %zu workspace bytes, got %zu",
                   2 * copy, workspace_bytes);
     if (!aligned16(workspace)) return fail(FEDATTN_EINVAL, "workspace must be 16-byte aligned");
-    if (keep_chunks && chunk_tokens > 0 &&
-        workspace_bytes < 2 * copy + prefill_ws_layout(params, total, chunk_tokens).total)
-      return fail(FEDATTN_EWORKSPACE, "workspace too small for the aggregated copy and the keep-list (%zu bytes needed)",
-                  2 * copy + prefill_ws_layout(params, total, chunk_tokens).total);
+    if (keep_chunks && chunk_tokens > 0) {
+      const PrefillWs w = prefill_ws_layout(params, total, chunk_tokens);
+      const size_t need = 2 * copy + (use_mfma_prefill(params) ? w.total : w.rows_off);
+      if (workspace_bytes < need)
+        return fail(FEDATTN_EWORKSPACE, "workspace too small for the aggregated copy and the keep-list (%zu bytes needed)", need);
+    }
     k_base = ws;
     v_base = ws + copy;
     ws += 2 * copy;

@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <atomic>
 
 #include "fedattn.h"
@@ -55,6 +56,7 @@ struct PrefillArgs {
   int32_t warm_kv;          // MFMA kernel: every workgroup pulls the K, V rows of its own query rows into L2 first
   int32_t one_tile_heavy_first;  // MFMA kernel, causal launch of several rounds of workgroups: one query tile per
                                  // workgroup, heaviest first (seg.pair_cum then counts tiles in seg_order's order)
+  int32_t short_half_ascending;  // fp32 kernel: workgroups of the shorter half of the walks in ascending order
   SegLayout seg;
   uint16_t tile_order[kMaxOrderedTiles];
   uint8_t seg_order[kMaxP];      // participants by decreasing length (local blocks of a heavy-first launch)
@@ -101,12 +103,46 @@ struct AggregateArgs {
   int32_t row_bytes;        // Hkv * D * element size, multiple of 16
 };
 
+// Host side: cuts every segment into query tiles of `rows` rows (tiles never straddle segments).
+inline void lay_out_query_tiles(PrefillArgs& a, int rows) {
+  a.q_tile_rows = rows;
+  int32_t tiles = 0, pairs = 0;
+  for (int n = 0; n <= a.seg.n; ++n) {
+    a.seg.tile_cum[n] = tiles;
+    a.seg.pair_cum[n] = pairs;
+    if (n == a.seg.n) break;
+    const int32_t tn = (int32_t)(((int64_t)a.seg.seg_off[n + 1] - a.seg.seg_off[n] + rows - 1) / rows);
+    tiles += tn;
+    pairs += (tn + 1) / 2;
+  }
+  a.n_q_tiles = tiles;
+}
+
+// Host side: seg_order = participants by decreasing number of query tiles, pair_cum = cumulative
+// number of query tiles in that order.
+inline void order_segments_by_length(PrefillArgs& a) {
+  const int N = a.seg.n;
+  int order[kMaxP];
+  for (int n = 0; n < N; ++n) order[n] = n;
+  std::stable_sort(order, order + N, [&](int x, int y) {
+    return a.seg.tile_cum[x + 1] - a.seg.tile_cum[x] > a.seg.tile_cum[y + 1] - a.seg.tile_cum[y];
+  });
+  int run = 0;
+  for (int i = 0; i < N; ++i) {
+    a.seg_order[i] = (uint8_t)order[i];
+    a.seg.pair_cum[i] = run;
+    run += a.seg.tile_cum[order[i] + 1] - a.seg.tile_cum[order[i]];
+  }
+  a.seg.pair_cum[N] = run;
+}
+
 // Host-side launchers (one per kernel family); each returns the hipError_t of the launch.
 hipError_t launch_prefill_generic(const PrefillArgs& a, int n_blocks, int dtype, hipStream_t s);
 hipError_t launch_prefill_mfma(const PrefillArgs& a, int n_blocks, hipStream_t s);
+hipError_t launch_prefill_f32(const PrefillArgs& a, int n_blocks, hipStream_t s);
 hipError_t launch_build_kept_tiles(const PrefillArgs& a, int2* kept_tiles, int32_t* kept_cum,
                                    hipStream_t s);
-hipError_t launch_pack_kept_rows(const PrefillArgs& a, int32_t* kept_rows, int32_t* src_index, void* k_packed,
+hipError_t launch_pack_kept_rows(const PrefillArgs& a, int row_bytes, int32_t* kept_rows, int32_t* src_index, void* k_packed,
                                  void* v_packed, int2* kept_tiles, int32_t* kept_cum, hipStream_t s);
 hipError_t launch_decode(const DecodeArgs& a, int dtype, int n_z, hipStream_t s);
 hipError_t launch_decode_zero_counters(int32_t* counters, int n, int slices, int64_t slice_bytes, hipStream_t s);

@@ -30,20 +30,6 @@ constexpr int kDecodeStages = 3;
 template <int D>
 constexpr int decode_smem_bytes() { return kDecodeStages * 2 * KvTile<D, 0>::TILEB; }
 
-// value of x maximised / summed over the 4 lanes (lane%16 + 16 k) that share a query column
-__device__ inline float max_over_kgroups(float x) {
-  const unsigned u = __float_as_uint(x);
-  const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-  const unsigned a = r[0], b = r[1];
-  return max_across_halves(fmaxf(__uint_as_float(a), __uint_as_float(b)));
-}
-__device__ inline float sum_over_kgroups(float x) {
-  const unsigned u = __float_as_uint(x);
-  const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-  const unsigned a = r[0], b = r[1];
-  return sum_across_halves(__uint_as_float(a) + __uint_as_float(b));
-}
-
 // COLSPLIT = false (at most 16 query columns, e.g. the G heads of one participant in a
 // local block): 4 wavefronts, wavefront w takes tile rows 16w..16w+15; they are merged
 // through LDS at the end.  COLSPLIT = true (up to 64 query columns, sync blocks): 8

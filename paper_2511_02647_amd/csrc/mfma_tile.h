@@ -86,6 +86,21 @@ __device__ inline float sum_across_halves(float x) {
   return lo + hi;
 }
 
+// value of x maximised / summed over the 4 lanes (lane%16 + 16 k) that share a query
+// column of a 16x16 product
+__device__ inline float max_over_kgroups(float x) {
+  const unsigned u = __float_as_uint(x);
+  const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  const unsigned a = r[0], b = r[1];
+  return max_across_halves(fmaxf(__uint_as_float(a), __uint_as_float(b)));
+}
+__device__ inline float sum_over_kgroups(float x) {
+  const unsigned u = __float_as_uint(x);
+  const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  const unsigned a = r[0], b = r[1];
+  return sum_across_halves(__uint_as_float(a) + __uint_as_float(b));
+}
+
 // VSWZ selects the chunk swizzle of V tiles: the transposing reads of the 32x32x16
 // product touch 4 rows x 4 chunks per 32 lanes (VSWZ = 1: f = 4 (row mod 4)), those of the
 // 16x16x16 product 8 rows x 2 chunks (VSWZ = 0: f = 2 (row mod 8)).

@@ -1,8 +1,7 @@
 // General prefill attention kernel (plain ALU, fp32 arithmetic): one wavefront per
-// (query row, query head).  Covers every shape the boundary accepts (any head_dim
-// that is a multiple of 8 up to 256, fp32 or bf16 storage, token-granular
-// keep-lists, bidirectional attention); the MFMA kernel takes over for the bf16
-// shapes that matter for throughput.
+// (query row, query head).  It reads token-granular keep flags as they are and needs no
+// workspace, so it takes the keep-list calls that come without one, and the bf16 head
+// dimensions other than 64 and 128; everything else runs on the matrix cores.
 //
 // Visibility of key j for query i (Section III-B causal mask; Phase I / Phase II;
 // adaptive KV aggregation): own segment always, remote segments only in a sync

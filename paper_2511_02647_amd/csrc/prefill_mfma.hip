@@ -21,11 +21,11 @@
 // Tiles entirely above the diagonal or in other participants' segments of a local
 // block are never visited; only diagonal and ragged tiles apply an element mask.
 #include <algorithm>
-#include <climits>
 #include <type_traits>
 
 #include "common.h"
 #include "mfma_tile.h"
+#include "prefill_walk.h"
 
 namespace fedattn {
 
@@ -65,39 +65,12 @@ __global__ __launch_bounds__(256 * NG, 2) void prefill_mfma_kernel(PrefillArgs a
   const int G = Hq / Hkv;
   const int HS = a.heads_per_wg;
   const int HG = G / HS;
-  const int BM = a.q_tile_rows;
   const int N = a.seg.n;
   const int T = a.n_q_tiles;
 
-  // The segment tables sit in the kernel-argument buffer.  Walking them entry by entry costs
-  // one scalar-cache miss after another while nothing else is in flight, so every lane
-  // fetches the entries of segment `lane` (and `lane + 64`) of all tables in one go and the
-  // searches below run on ballots.  Entry 0 of every table is 0.
-  struct Tab {
-    int lo, hi;  // table[lane + 1], table[lane + 65]; INT_MAX past the last segment
-  };
-  auto load_tab = [&](const int32_t* t) __attribute__((always_inline)) {
-    // the tables have kMaxP + 1 entries whatever N is: fetch first (nothing to wait for), select after
-    const int lo = t[lane + 1], hi = t[lane + 65];
-    Tab r;
-    r.lo = lane < N ? lo : INT_MAX;
-    r.hi = lane + 64 < N ? hi : INT_MAX;
-    return r;
-  };
-  // table[idx] for a wave-uniform idx in [0, N]
-  auto tab_at = [&](const Tab& t, int idx) __attribute__((always_inline)) {
-    if (idx == 0) return 0;
-    return idx <= 64 ? __builtin_amdgcn_readlane(t.lo, idx - 1) : __builtin_amdgcn_readlane(t.hi, idx - 65);
-  };
-  // number of segments s with x >= table[s + 1], i.e. the segment a cumulative index falls in
-  auto tab_find = [&](const Tab& t, int x) __attribute__((always_inline)) {
-    int n = __builtin_popcountll(__builtin_amdgcn_ballot_w64(x >= t.lo));
-    if (N > 64) n += __builtin_popcountll(__builtin_amdgcn_ballot_w64(x >= t.hi));
-    return n;
-  };
-  const Tab seg_tab = load_tab(a.seg.seg_off);
-  const Tab tile_tab = load_tab(a.seg.tile_cum);
-  const Tab pair_tab = load_tab(a.seg.pair_cum);
+  const SegTab seg_tab = load_seg_tab(a.seg.seg_off, lane, N);
+  const SegTab tile_tab = load_seg_tab(a.seg.tile_cum, lane, N);
+  const SegTab pair_tab = load_seg_tab(a.seg.pair_cum, lane, N);
   const int order_lo = a.seg_order[lane], order_hi = a.seg_order[lane + 64];
 
   // workgroup -> (kv head, head subgroup, query tile pair); kv head fastest so that the
@@ -139,20 +112,20 @@ __global__ __launch_bounds__(256 * NG, 2) void prefill_mfma_kernel(PrefillArgs a
     if (is_sync) {
       tile_a = T - 1 - p;
     } else {
-      const int s = tab_find(pair_tab, p);   // position in the length order
-      const int pi = p - tab_at(pair_tab, s);
+      const int s = seg_tab_find(pair_tab, p, N);   // position in the length order
+      const int pi = p - seg_tab_at(pair_tab, s);
       const int n = s < 64 ? __builtin_amdgcn_readlane(order_lo, s) : __builtin_amdgcn_readlane(order_hi, s - 64);
-      tile_a = tab_at(tile_tab, n + 1) - 1 - pi;
+      tile_a = seg_tab_at(tile_tab, n + 1) - 1 - pi;
     }
   } else if (is_sync) {
     if (p >= (T + 1) / 2) return;
     tile_a = T - 1 - p;
     if (p < T - 1 - p) tile_b = p;
   } else {
-    if (p >= tab_at(pair_tab, N)) return;
-    const int n = tab_find(pair_tab, p);
-    const int pi = p - tab_at(pair_tab, n);
-    const int t0 = tab_at(tile_tab, n), tn = tab_at(tile_tab, n + 1) - t0;
+    if (p >= seg_tab_at(pair_tab, N)) return;
+    const int n = seg_tab_find(pair_tab, p, N);
+    const int pi = p - seg_tab_at(pair_tab, n);
+    const int t0 = seg_tab_at(tile_tab, n), tn = seg_tab_at(tile_tab, n + 1) - t0;
     tile_a = t0 + tn - 1 - pi;
     if (pi < tn - 1 - pi) tile_b = t0 + pi;
   }
@@ -169,52 +142,18 @@ __global__ __launch_bounds__(256 * NG, 2) void prefill_mfma_kernel(PrefillArgs a
   TL tile_io;
   tile_io.init(lane, wave, row_elems);
 
-  // One query tile's walk through its KV tiles (all members wave-uniform): two runs of
-  // the kept-tile list, then a dense range [dlo, dhi).
-  struct Walk {
-    int seg_hi, row0w, la_n, lb0, n_list, dlo, dhi, nt;
+  struct Walk : KvWalk {
+    int row0w;  // first query row of this wavefront
   };
   auto make_walk = [&](int tile, Walk& w) __attribute__((always_inline)) {
-    const int n = tab_find(tile_tab, tile);
-    const int seg_lo = tab_at(seg_tab, n);
-    w.seg_hi = tab_at(seg_tab, n + 1);
-    const int q0 = seg_lo + (tile - tab_at(tile_tab, n)) * BM;
-    w.row0w = q0 + kWaveRows * (wave / HS);
-    const int i_last = min(q0 + BM, w.seg_hi) - 1;
-    int la_n = 0, lb0 = 0, lb_n = 0;
-    if (sparse) {
-      la_n = a.kept_cum[n];
-      if (!causal) {
-        lb0 = a.kept_cum[n + 1];
-        lb_n = a.kept_cum[N] - lb0;
-      }
-    }
-    w.la_n = la_n;
-    w.lb0 = lb0;
-    w.n_list = la_n + lb_n;
-    w.dlo = (is_sync && !sparse) ? 0 : seg_lo;
-    w.dhi = causal ? i_last + 1 : ((is_sync && !sparse) ? a.total : w.seg_hi);
-    w.nt = w.n_list + (w.dhi - w.dlo + kKvTile - 1) / kKvTile;  // >= 1: the tile has a row
-  };
-  auto tile_desc = [&](const Walk& w, int it, int& kv0, int& len, bool& causal_tile)
-                       __attribute__((always_inline)) {
-    if (it < w.n_list) {
-      const int idx = it < w.la_n ? it : w.lb0 + (it - w.la_n);
-      const int2 t = a.kept_tiles[idx];
-      kv0 = __builtin_amdgcn_readfirstlane(t.x);
-      len = __builtin_amdgcn_readfirstlane(t.y);
-      causal_tile = false;
-    } else {
-      kv0 = w.dlo + kKvTile * (it - w.n_list);
-      len = min(kKvTile, w.dhi - kv0);
-      causal_tile = causal;
-    }
+    static_cast<KvWalk&>(w) = make_kv_walk(a, seg_tab, tile_tab, tile, is_sync, sparse);
+    w.row0w = w.q0 + kWaveRows * (wave / HS);
   };
   // K and V tile `it` of walk w into the stage at byte offset st of this group
   auto fetch_tile = [&](const Walk& w, int it, int st) __attribute__((always_inline)) {
     int kv0, len;
     bool ct;
-    tile_desc(w, it, kv0, len, ct);
+    kv_tile_desc(a, w, it, kv0, len, ct);
     const bool listed = it < w.n_list;
     tile_io.template dma<false>((listed ? kp_list : kp) + (int64_t)kv0 * row_elems, lds_base + st, len);
     tile_io.template dma<true>((listed ? vp_list : vp) + (int64_t)kv0 * row_elems, lds_base + 2 * TILEB + st, len);
@@ -337,7 +276,7 @@ __global__ __launch_bounds__(256 * NG, 2) void prefill_mfma_kernel(PrefillArgs a
       if (j < cur.nt) {
         int kv0, len;
         bool causal_tile;
-        tile_desc(cur, j, kv0, len, causal_tile);
+        kv_tile_desc(a, cur, j, kv0, len, causal_tile);
         f32x16 s_cur[2];
         tile_io.scores(lds0, st_cur, qf, neg_ref, s_cur);
 
@@ -550,10 +489,10 @@ __global__ __launch_bounds__(kMaxP) void build_packed_tiles_kernel(PrefillArgs a
   }
 }
 
-// Packed row p of K and V = row src_index[p] of the block's K and V (16 bytes per thread).
-__global__ __launch_bounds__(256) void gather_kept_rows_kernel(PrefillArgs a, const int32_t* src_index,
-                                                               uint4* k_packed, uint4* v_packed) {
-  const int row_vecs = a.Hkv * a.D / 8;  // 16-byte pieces per bf16 row
+// Packed row p of K and V = row src_index[p] of the block's K and V (row_vecs 16-byte pieces, one per thread).
+__global__ __launch_bounds__(256) void gather_kept_rows_kernel(PrefillArgs a, int row_vecs,
+                                                               const int32_t* src_index, uint4* k_packed,
+                                                               uint4* v_packed) {
   const int rows_per_wg = max(1, 256 / row_vecs);
   const uint4* src = reinterpret_cast<const uint4*>(blockIdx.y == 0 ? a.k : a.v);
   uint4* dst = blockIdx.y == 0 ? k_packed : v_packed;
@@ -567,7 +506,7 @@ __global__ __launch_bounds__(256) void gather_kept_rows_kernel(PrefillArgs a, co
 
 }  // namespace
 
-hipError_t launch_pack_kept_rows(const PrefillArgs& a, int32_t* kept_rows, int32_t* src_index, void* k_packed,
+hipError_t launch_pack_kept_rows(const PrefillArgs& a, int row_bytes, int32_t* kept_rows, int32_t* src_index, void* k_packed,
                                  void* v_packed, int2* kept_tiles, int32_t* kept_cum, hipStream_t s) {
   hipLaunchKernelGGL(scan_kept_rows_kernel, dim3((unsigned)a.seg.n), dim3(256), 0, s, a, kept_rows, src_index);
   hipError_t e = hipGetLastError();
@@ -575,10 +514,10 @@ hipError_t launch_pack_kept_rows(const PrefillArgs& a, int32_t* kept_rows, int32
   hipLaunchKernelGGL(build_packed_tiles_kernel, dim3(1), dim3(kMaxP), 0, s, a, kept_rows, kept_tiles, kept_cum);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const int row_vecs = a.Hkv * a.D / 8;
+  const int row_vecs = row_bytes / 16;
   const int rows_per_wg = row_vecs >= 256 ? 1 : 256 / row_vecs;
   hipLaunchKernelGGL(gather_kept_rows_kernel, dim3((unsigned)((a.total + rows_per_wg - 1) / rows_per_wg), 2), dim3(256),
-                     0, s, a, src_index, reinterpret_cast<uint4*>(k_packed), reinterpret_cast<uint4*>(v_packed));
+                     0, s, a, row_vecs, src_index, reinterpret_cast<uint4*>(k_packed), reinterpret_cast<uint4*>(v_packed));
   return hipGetLastError();
 }
 
@@ -653,21 +592,7 @@ hipError_t launch_prefill_mfma(const PrefillArgs& a_in, int n_blocks, hipStream_
   if (!wide && n_blocks == 1 && a.causal && a.n_ordered == 0 && (int64_t)grid.x > 2 * (int64_t)a.n_cus) {
     const bool is_sync = a.sync_override >= 0 ? a.sync_override != 0 : sync_block_rule(a.sync_interval, a.block_idx0);
     a.one_tile_heavy_first = 1;
-    if (!is_sync) {
-      const int N = a.seg.n;
-      int order[kMaxP];
-      for (int n = 0; n < N; ++n) order[n] = n;
-      std::stable_sort(order, order + N, [&](int x, int y) {
-        return a.seg.tile_cum[x + 1] - a.seg.tile_cum[x] > a.seg.tile_cum[y + 1] - a.seg.tile_cum[y];
-      });
-      int run = 0;
-      for (int i = 0; i < N; ++i) {
-        a.seg_order[i] = (uint8_t)order[i];
-        a.seg.pair_cum[i] = run;
-        run += a.seg.tile_cum[order[i] + 1] - a.seg.tile_cum[order[i]];
-      }
-      a.seg.pair_cum[N] = run;
-    }
+    if (!is_sync) order_segments_by_length(a);
     grid.x = (unsigned)(a.n_q_tiles * per_tile);
   }
   // scale folded into Q only up to the usual 1/sqrt(D): its rounding error grows with the scale

@@ -1,0 +1,87 @@
+// Where a query tile's workgroup finds its segment and which KV tiles it walks: shared by the
+// prefill kernels on the matrix cores.
+//
+// The segment tables sit in the kernel-argument buffer.  Walking them entry by entry costs
+// one scalar-cache miss after another while nothing else is in flight, so every lane
+// fetches the entries of segment `lane` (and `lane + 64`) of all tables in one go and the
+// searches run on ballots.  Entry 0 of every table is 0.
+#pragma once
+
+#include <climits>
+
+#include "common.h"
+
+namespace fedattn {
+
+struct SegTab {
+  int lo, hi;  // table[lane + 1], table[lane + 65]; INT_MAX past the last segment
+};
+__device__ __attribute__((always_inline)) inline SegTab load_seg_tab(const int32_t* t, int lane, int n_seg) {
+  // the tables have kMaxP + 1 entries whatever N is: fetch first (nothing to wait for), select after
+  const int lo = t[lane + 1], hi = t[lane + 65];
+  SegTab r;
+  r.lo = lane < n_seg ? lo : INT_MAX;
+  r.hi = lane + 64 < n_seg ? hi : INT_MAX;
+  return r;
+}
+// table[idx] for a wave-uniform idx in [0, N]
+__device__ __attribute__((always_inline)) inline int seg_tab_at(const SegTab& t, int idx) {
+  if (idx == 0) return 0;
+  return idx <= 64 ? __builtin_amdgcn_readlane(t.lo, idx - 1) : __builtin_amdgcn_readlane(t.hi, idx - 65);
+}
+// number of segments s with x >= table[s + 1], i.e. the segment a cumulative index falls in
+__device__ __attribute__((always_inline)) inline int seg_tab_find(const SegTab& t, int x, int n_seg) {
+  int n = __builtin_popcountll(__builtin_amdgcn_ballot_w64(x >= t.lo));
+  if (n_seg > 64) n += __builtin_popcountll(__builtin_amdgcn_ballot_w64(x >= t.hi));
+  return n;
+}
+
+// One query tile's walk through its KV tiles (all members wave-uniform): two runs of the
+// kept-tile list (sparse exchange: remote participants before and after the own one), then a
+// dense range [dlo, dhi).
+struct KvWalk {
+  int seg_hi, q0, la_n, lb0, n_list, dlo, dhi, nt;
+};
+__device__ __attribute__((always_inline)) inline KvWalk make_kv_walk(const PrefillArgs& a, const SegTab& seg_tab,
+                                                                     const SegTab& tile_tab, int tile, bool is_sync,
+                                                                     bool sparse) {
+  const int N = a.seg.n, BM = a.q_tile_rows;
+  const bool causal = a.causal != 0;
+  KvWalk w;
+  const int n = seg_tab_find(tile_tab, tile, N);
+  const int seg_lo = seg_tab_at(seg_tab, n);
+  w.seg_hi = seg_tab_at(seg_tab, n + 1);
+  w.q0 = seg_lo + (tile - seg_tab_at(tile_tab, n)) * BM;
+  const int i_last = min(w.q0 + BM, w.seg_hi) - 1;
+  int la_n = 0, lb0 = 0, lb_n = 0;
+  if (sparse) {
+    la_n = a.kept_cum[n];
+    if (!causal) {
+      lb0 = a.kept_cum[n + 1];
+      lb_n = a.kept_cum[N] - lb0;
+    }
+  }
+  w.la_n = la_n;
+  w.lb0 = lb0;
+  w.n_list = la_n + lb_n;
+  w.dlo = (is_sync && !sparse) ? 0 : seg_lo;
+  w.dhi = causal ? i_last + 1 : ((is_sync && !sparse) ? a.total : w.seg_hi);
+  w.nt = w.n_list + (w.dhi - w.dlo + kKvTile - 1) / kKvTile;  // >= 1: the tile has a row
+  return w;
+}
+__device__ __attribute__((always_inline)) inline void kv_tile_desc(const PrefillArgs& a, const KvWalk& w, int it,
+                                                                   int& kv0, int& len, bool& causal_tile) {
+  if (it < w.n_list) {
+    const int idx = it < w.la_n ? it : w.lb0 + (it - w.la_n);
+    const int2 t = a.kept_tiles[idx];
+    kv0 = __builtin_amdgcn_readfirstlane(t.x);
+    len = __builtin_amdgcn_readfirstlane(t.y);
+    causal_tile = false;
+  } else {
+    kv0 = w.dlo + kKvTile * (it - w.n_list);
+    len = min(kKvTile, w.dhi - kv0);
+    causal_tile = a.causal != 0;
+  }
+}
+
+}  // namespace fedattn

@@ -1,0 +1,56 @@
+"""GPU parity of the shapes outside bf16 x head dimension 64 / 128: fp32 prefill on the matrix
+cores, in every split of the work that its launcher chooses, at head dimensions on and between
+the padded sizes."""
+import numpy as np
+import pytest
+import torch
+
+import fedattn_inputs as fi
+import oracle
+import paper_2511_02647_amd as fa
+from gpu_util import check, dev, host, prefill, say
+from test_gpu_parity import rand_block
+
+pytestmark = pytest.mark.gpu
+BF16, F32 = torch.bfloat16, torch.float32
+
+# (lengths, Hq, Hkv): 16-row tiles; 32-row tiles with the keys split over a workgroup (at least 512
+# of them on 256 CUs); heads sharing a workgroup (at least 1536 of them).  Ragged ends, an empty and
+# a one-token segment, groups of 1, 2 and 4 heads per KV head.
+LAYOUTS = {"narrow": ([70, 0, 63, 1, 258], 4, 1), "split": ([500, 33, 484], 16, 8), "shared": ([3101, 2, 3137], 32, 8)}
+
+
+@pytest.mark.parametrize("layout", sorted(LAYOUTS))
+@pytest.mark.parametrize("D", [8, 40, 64, 88, 128, 136, 256])
+def test_f32_prefill(layout, D):
+    lens, Hq, Hkv = LAYOUTS[layout]
+    seg = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    total = int(seg[-1])
+    q, k, v = rand_block(41, total, Hq, Hkv, D, bf16=False)
+    rows, heads = fi.sample_rows(seg, Hq, 64, fi.DEFAULT_SEED, salt=D, tile=32, max_boundary_rows=200)
+    for sync, causal in [(0, True), (1, True), (1, False)]:
+        what = "f32 %s D=%d sync=%d causal=%d" % (layout, D, sync, causal)
+        say(what)
+        got = prefill(q, k, v, seg, Hq=Hq, Hkv=Hkv, D=D, H=0, block=0, dtype=F32, causal=causal, sync_override=sync)
+        ref = oracle.attend_rows(q, k, v, seg, rows, heads, is_sync=bool(sync), causal=causal)
+        check(got[rows, heads], ref, F32, what)
+
+
+@pytest.mark.parametrize("chunk", [1, 20, 64])
+@pytest.mark.parametrize("causal", [True, False])
+def test_f32_prefill_keep_lists_with_and_without_workspace(chunk, causal):
+    seg = np.array([0, 130, 130, 321, 402], dtype=np.int32)
+    Hq, Hkv, D = 4, 2, 72
+    q, k, v = rand_block(42, 402, Hq, Hkv, D, bf16=False)
+    flags = (np.random.default_rng(7).random(int(fi.chunk_counts(np.diff(seg), chunk).sum())) < 0.4).astype(np.uint8)
+    ref = oracle.attend_block(q, k, v, seg, is_sync=True, causal=causal, keep_tok=oracle.expand_keep_chunks(flags, seg, chunk))
+    say("f32 keep-list chunk=%d causal=%d" % (chunk, causal))
+    got = prefill(q, k, v, seg, Hq=Hq, Hkv=Hkv, D=D, H=1, block=0, dtype=F32, causal=causal, keep_chunks=flags, chunk_tokens=chunk)
+    check(got, ref, F32, "f32 keep-list chunk=%d" % chunk)
+    # without a workspace the flags are read by the general kernel
+    p = fa.make_params(4, Hq, Hkv, D, 1, F32, causal=causal)
+    tq = dev(q, F32)
+    out = torch.full_like(tq, float("nan"))
+    fa.fedattn_prefill(p, 0, tq, dev(k, F32), dev(v, F32), out, seg, keep_chunks=torch.from_numpy(flags).to("cuda"), chunk_tokens=chunk)
+    torch.cuda.synchronize()
+    check(host(out), ref, F32, "f32 keep-list chunk=%d, no workspace" % chunk)
