@@ -96,7 +96,8 @@ FEDATTN_API size_t fedattn_workspace_bytes(const fedattn_params* params, int32_t
  *   second product (the row sum is taken over the rounded weights); when the softmax scale does
  *   not exceed 1/sqrt(D) it is folded into the query operand (q * scale * log2(e), rounded to
  *   bf16), otherwise applied to the fp32 scores.  Other bf16 shapes: fp32 arithmetic on the
- *   bf16 values.
+ *   bf16 values (on bf16 MFMA: the products of bf16 values are exact in fp32, and a weight enters
+ *   the second product as the three bf16 values that it is the exact sum of).
  *
  *   block_idx      0-based block index; with sync_override = -1 the block is a sync
  *                  block iff fedattn_is_sync_block(params->sync_interval, block_idx).

@@ -62,10 +62,6 @@ bool use_mfma_prefill(const fedattn_params* p) {
 
 int elem_bytes(const fedattn_params* p) { return p->dtype == FEDATTN_BF16 ? 2 : 4; }
 
-// prefill on the matrix cores in fp32 products and sums; a keep-list needs the workspace there, without
-// one these shapes run on the general kernel, which reads the flags itself
-bool use_f32_prefill(const fedattn_params* p) { return p->dtype == FEDATTN_F32; }
-
 // keep chunks that are not whole 64-row tiles: the tile kernels pack the kept rows first
 bool needs_row_packing(int chunk_tokens) { return chunk_tokens > 0 && chunk_tokens % kKvTile != 0; }
 
@@ -117,7 +113,7 @@ PrefillWs prefill_ws_layout(const fedattn_params* p, int32_t tokens, int32_t chu
   w.tiles_off = kKeptCumBytes;
   w.rows_off = w.tiles_off + align_up(max_tiles * sizeof(int2), 256);
   w.index_off = w.k_off = w.v_off = w.total = w.rows_off;
-  if ((use_mfma_prefill(p) || use_f32_prefill(p)) && needs_row_packing(chunk_tokens)) {
+  if (needs_row_packing(chunk_tokens)) {
     const size_t kv_bytes = (size_t)tokens * (size_t)p->n_kv_heads * (size_t)p->head_dim * (size_t)elem_bytes(p);
     w.index_off = w.rows_off + kKeptRowsBytes;
     w.k_off = w.index_off + align_up((size_t)tokens * 4, 256);
@@ -208,8 +204,10 @@ fedattn_status run_prefill(const fedattn_params* p, int32_t block_idx0, int32_t 
     for (int b = 0; b < n_blocks && !any_sync; ++b) any_sync = sync_block_rule(p->sync_interval, block_idx0 + b);
   if (!has_keep || !any_sync) a.keep_chunks = nullptr;
 
-  bool tiled = mfma || use_f32_prefill(p);
-  if (tiled && a.keep_chunks) {
+  // fp32 and bf16 with other head dimensions: the tile kernels too, but a keep-list call that comes
+  // without a workspace runs on the general kernel, which reads the flags as they are
+  bool tiled = true;
+  if (a.keep_chunks) {
     if (n_blocks != 1) return fail(FEDATTN_EUNSUPPORTED, "a keep-list applies to one block per call");
     const PrefillWs w = prefill_ws_layout(p, total, chunk_tokens);
     const bool have_ws = workspace && workspace_bytes >= w.total;
@@ -241,7 +239,7 @@ fedattn_status run_prefill(const fedattn_params* p, int32_t block_idx0, int32_t 
   if (!tiled)
     e = launch_prefill_generic(a, n_blocks, p->dtype, s);
   else
-    e = mfma ? launch_prefill_mfma(a, n_blocks, s) : launch_prefill_f32(a, n_blocks, s);
+    e = p->dtype == FEDATTN_BF16 ? launch_prefill_mfma(a, n_blocks, s) : launch_prefill_f32(a, n_blocks, s);
   if (e != hipSuccess) return fail(FEDATTN_ELAUNCH, "prefill: %s", hipGetErrorString(e));
   return FEDATTN_OK;
 }

@@ -101,8 +101,10 @@ __device__ inline float sum_over_kgroups(float x) {
   return sum_across_halves(__uint_as_float(a) + __uint_as_float(b));
 }
 
+// Tile rows are D wide in LDS: the head dimension, or a multiple of 32 that it is padded to (the
+// padding re-reads the row's last chunk, so whatever a padded operand multiplies is finite).
 // VSWZ selects the chunk swizzle of V tiles: the transposing reads of the 32x32x16
-// product touch 4 rows x 4 chunks per 32 lanes (VSWZ = 1: f = 4 (row mod 4)), those of the
+// product touch 4 rows x 4 chunks per 32 lanes (VSWZ = 1), those of the
 // 16x16x16 product 8 rows x 2 chunks (VSWZ = 0: f = 2 (row mod 8)).
 // NW = wavefronts that load a tile together (4, or 8 for 8-wave workgroups sharing one tile).
 template <int D, int VSWZ, int NW = 4>
@@ -118,11 +120,20 @@ struct KvTile {
 
   // HBM -> LDS: one load instruction moves 64 x 16 bytes to 1 KB of consecutive LDS
   // (lane l lands at +16 l).  LDS slot (row, cp) receives chunk cp ^ f(row) of the row:
-  // f = row mod CPR for K (conflict-free 16-byte reads down 16 rows), v_swizzle(row) for V
-  // (conflict-free 8-byte transposing reads).
+  // k_swizzle for K (conflict-free 16-byte reads down 8 rows), v_swizzle for V (conflict-free
+  // 8-byte transposing reads).  LDS has 256 bytes of banks: rows of a multiple of 256, of 128 and
+  // of 64 bytes start on the same bank, on two and on four different ones in turn, and the
+  // swizzle spreads what then still coincides.
+  static __device__ __attribute__((always_inline)) int k_swizzle(int row) {
+    if constexpr (D % 128 == 0) return row & 15;
+    if constexpr (D % 64 == 0) return row & 7;
+    return (row >> 2) & 3;
+  }
   static __device__ __attribute__((always_inline)) int v_swizzle(int row) {
-    if (VSWZ == 0) return (2 * (row & 7)) & (CPR - 1);
-    return CPR >= 16 ? 4 * (row & 3) : 4 * ((row >> 1) & 1);
+    if constexpr (VSWZ == 0) return (2 * (row & 7)) & (CPR - 1);
+    if constexpr (D % 128 == 0) return 4 * (row & 3);
+    if constexpr (D % 64 == 0) return 4 * ((row >> 1) & 1);
+    return 0;
   }
   uint32_t dma_koff[IPW];  // byte offset from the tile's first row of what this lane fetches in its
   uint32_t dma_voff[IPW];  // wave's i-th instruction (full tiles; ragged tiles work theirs out on the spot)
@@ -137,17 +148,19 @@ struct KvTile {
   int v_off[DT];
   int wave;
   int row_elems;           // elements between consecutive KV rows in HBM
+  int last_chunk;          // last 16-byte chunk of a row in HBM (CPR - 1 without padding)
 
   // tile row and element offset of the chunk inside the row that this lane fetches in its wave's i-th instruction
   __device__ __attribute__((always_inline)) void dma_slot(int i, bool is_v, int& row, int& col) const {
     const int sidx = (wave * IPW + i) * 64 + lane;
     const int cp = sidx % CPR;
     row = sidx / CPR;
-    col = (cp ^ (is_v ? v_swizzle(row) : (row & (CPR - 1)))) * 8;
+    col = min(cp ^ (is_v ? v_swizzle(row) : k_swizzle(row)), last_chunk) * 8;
   }
 
-  __device__ __attribute__((always_inline)) void init(int lane_, int wave_, int row_elems_) {
+  __device__ __attribute__((always_inline)) void init(int lane_, int wave_, int row_elems_, int last_chunk_ = CPR - 1) {
     const int lane = lane_;
+    last_chunk = last_chunk_;
     this->lane = lane_;
     wave = wave_;
     row_elems = row_elems_;
@@ -161,7 +174,7 @@ struct KvTile {
       dma_voff[i] = (uint32_t)(row * row_elems + vcol) * 2u;
     }
 #pragma unroll
-    for (int st = 0; st < KSTEPS; ++st) k_off[st] = l32 * ROWB + (((2 * st + hf) ^ (l32 & (CPR - 1))) * 16);
+    for (int st = 0; st < KSTEPS; ++st) k_off[st] = l32 * ROWB + (((2 * st + hf) ^ k_swizzle(l32)) * 16);
     const int i16 = lane & 15, e = i16 >> 2, c = i16 & 3, dsel = (lane >> 4) & 1;
     const int vrow = 4 * hf + e;
     const int fv = v_swizzle(vrow);
@@ -255,6 +268,10 @@ struct KvTile {
     }
     __builtin_amdgcn_sched_group_barrier(FEDATTN_SGB_MFMA, kLook, 0);
   }
+
+  // The same with fp32 weights, still on bf16 MFMA: every weight enters as the three bf16 parts
+  // whose sum it is, so products and sums are those of fp32 arithmetic.
+  __device__ __attribute__((always_inline)) void pv_f32(lds_cptr lds0, int vb, const f32x16 (&s)[2], f32x16 (&o)[DT]) const;
 };
 
 // Masks the tile rows a lane's query may not see: rows [lim, 64) of the tile.
@@ -392,6 +409,62 @@ __device__ __attribute__((always_inline)) inline void softmax_step_rel(f32x16 (&
     if (!move) break;
   }
   l_run += ps0 + ps1;
+}
+
+// Part 2 for a second product at full precision: the exponentials stay in s as fp32 weights.
+__device__ __attribute__((always_inline)) inline void softmax_exp_f32(f32x16 (&s)[2], float sc, float m_use, float& l_run) {
+  float ps[2] = {0.f, 0.f};
+#pragma unroll
+  for (int aa = 0; aa < 2; ++aa)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      s[aa][e] = __builtin_amdgcn_exp2f(fmaf(s[aa][e], sc, -m_use));
+      ps[e & 1] += s[aa][e];
+    }
+  l_run += ps[0] + ps[1];
+}
+
+// Eight fp32 weights as a sum of three bf16 operands, exactly: 8 significant bits are cut off at a
+// time, and each remainder is exact in fp32 (24 = 3 x 8 bits).
+__device__ __attribute__((always_inline)) inline void split_weights(const float (&p)[8], bf16x8 (&part)[3]) {
+#pragma unroll
+  for (int i = 0; i < 8; i += 2) {
+    float x = p[i], y = p[i + 1];
+#pragma unroll
+    for (int t = 0; t < 3; ++t) {
+      const uint32_t ux = __float_as_uint(x), uy = __float_as_uint(y);
+      const bf16x2 w = __builtin_bit_cast(bf16x2, __builtin_amdgcn_perm(uy, ux, 0x07060302u));
+      part[t][i] = w[0];
+      part[t][i + 1] = w[1];
+      x -= __uint_as_float(ux & 0xffff0000u);
+      y -= __uint_as_float(uy & 0xffff0000u);
+    }
+  }
+}
+
+template <int D, int VSWZ, int NW>
+__device__ __attribute__((always_inline)) inline void KvTile<D, VSWZ, NW>::pv_f32(lds_cptr lds0, int vb, const f32x16 (&s)[2],
+                                                                                  f32x16 (&o)[DT]) const {
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk) {
+    float p[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) p[e] = s[kk >> 1][8 * (kk & 1) + e];
+    bf16x8 part[3];
+    split_weights(p, part);
+    bf16x8 vf[DT];
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) {
+      const lds_cptr ptr = lds0 + (v_off[dt] + vb) + 16 * kk * ROWB;
+      const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)ptr);
+      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(ptr + 8 * ROWB));
+      vf[dt] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    }
+#pragma unroll
+    for (int t = 2; t >= 0; --t)
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[dt], part[t], o[dt], 0, 0, 0);
+  }
 }
 
 // Both parts back to back.

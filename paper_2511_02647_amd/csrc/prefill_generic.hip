@@ -1,7 +1,7 @@
 // General prefill attention kernel (plain ALU, fp32 arithmetic): one wavefront per
 // (query row, query head).  It reads token-granular keep flags as they are and needs no
-// workspace, so it takes the keep-list calls that come without one, and the bf16 head
-// dimensions other than 64 and 128; everything else runs on the matrix cores.
+// workspace, so it takes the keep-list calls that come without one (fp32, and bf16 with head
+// dimensions other than 64 and 128); everything else runs on the matrix cores.
 //
 // Visibility of key j for query i (Section III-B causal mask; Phase I / Phase II;
 // adaptive KV aggregation): own segment always, remote segments only in a sync

@@ -44,9 +44,15 @@ namespace {
 // score, a quarter of the softmax's (3-4 % of the kernel's time on the large workloads).  Folding
 // the scale rounds q * scale to bf16 once more; the host asks for it only when the scale does not
 // exceed 1/sqrt(D), where that rounding stays well below the rounding of the weights themselves.
-template <int D, int NG, bool FOLD>
-__global__ __launch_bounds__(256 * NG, 2) void prefill_mfma_kernel(PrefillArgs a) {
-  using TL = KvTile<D, 1>;
+// EXACT: the weights keep their fp32 precision in the second product (three bf16 parts each), for
+// the head dimensions other than 64 and 128; DP is the head dimension padded to a multiple of 32.
+// Its matrix work is (1 + 3) / 2 times that of the other kind: 8 x 2000 tokens, 32/8 heads, sync:
+// 590 useful TFLOP/s at head dimension 96 (1160 at 128 without EXACT).  A local and a sync block of
+// 4 x 100..900 tokens, 8/2 heads of 96: 1794 us on the wavefront-per-row kernel, 72 us here.
+template <int DP, int NG, bool FOLD, bool EXACT>
+__global__ __launch_bounds__(256 * NG, DP > 128 ? 1 : 2) void prefill_mfma_kernel(PrefillArgs a) {
+  using TL = KvTile<DP, 1>;
+  const int D = EXACT ? a.D : DP;
   constexpr int KSTEPS = TL::KSTEPS, DT = TL::DT, TILEB = TL::TILEB;
   // Per group: K and V tiles double-buffered; the group's i-th tile lives in stage i&1.
   // Layout per group: K stage 0, K stage 1, V stage 0, V stage 1 (TILEB bytes each).
@@ -140,7 +146,7 @@ __global__ __launch_bounds__(256 * NG, 2) void prefill_mfma_kernel(PrefillArgs a
   const int row_elems = Hkv * D;  // elements between consecutive KV rows in HBM
 
   TL tile_io;
-  tile_io.init(lane, wave, row_elems);
+  tile_io.init(lane, wave, row_elems, EXACT ? D / 8 - 1 : TL::CPR - 1);
 
   struct Walk : KvWalk {
     int row0w;  // first query row of this wavefront
@@ -166,7 +172,8 @@ __global__ __launch_bounds__(256 * NG, 2) void prefill_mfma_kernel(PrefillArgs a
     const uint16_t* qrow = qp + ((int64_t)row_ld * Hq + head) * D + 8 * hf;
 #pragma unroll
     for (int st = 0; st < KSTEPS; ++st)
-      qf[st] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(qrow + 16 * st));
+      qf[st] = __builtin_bit_cast(bf16x8, !EXACT || 16 * st + 8 * hf < D ? *reinterpret_cast<const u32x4*>(qrow + 16 * st)
+                                                                         : u32x4{0u, 0u, 0u, 0u});
   };
 
   // The first walk's Q rows come through LDS instead: loaded as above, an instruction touches
@@ -185,7 +192,8 @@ __global__ __launch_bounds__(256 * NG, 2) void prefill_mfma_kernel(PrefillArgs a
       const int sidx = i * 64 + lane;
       const int row = sidx / TL::CPR, cp = sidx % TL::CPR;
       const int row_ld = min(w.row0w + row, w.seg_hi - 1) - rbase;  // >= 0
-      const uint32_t off = (uint32_t)(row_ld * (Hq * D) + ((cp ^ (row & (TL::CPR - 1))) * 8)) * 2u;
+      const int chunk = min(cp ^ TL::k_swizzle(row), tile_io.last_chunk);
+      const uint32_t off = (uint32_t)(row_ld * (Hq * D) + chunk * 8) * 2u;
       lds_dma_16(qbase, off, lds_base + q_lds + i * 1024);
     }
   };
@@ -194,6 +202,11 @@ __global__ __launch_bounds__(256 * NG, 2) void prefill_mfma_kernel(PrefillArgs a
     for (int st = 0; st < KSTEPS; ++st)
       qf[st] = __builtin_bit_cast(
           bf16x8, *reinterpret_cast<const __attribute__((address_space(3))) u32x4*>(lds0 + (q_lds + tile_io.k_off[st])));
+    if constexpr (EXACT) {   // the padded columns are zero
+#pragma unroll
+      for (int st = 0; st < KSTEPS; ++st)
+        if (16 * st + 8 * hf >= D) qf[st] = __builtin_bit_cast(bf16x8, u32x4{0u, 0u, 0u, 0u});
+    }
   };
 
   // The workgroup's walks run as one pipeline: the stage parity carries on from the
@@ -219,7 +232,7 @@ __global__ __launch_bounds__(256 * NG, 2) void prefill_mfma_kernel(PrefillArgs a
   // rows of the workgroup's own query rows are requested now, one dword per 128-byte line; all
   // workgroups together cover every row, and the walks then find their tiles in L2.
   unsigned warm_k = 0;
-  if (a.warm_kv && grp == 0) {
+  if (!EXACT && a.warm_kv && grp == 0) {
     constexpr int LPR = TL::ROWB / 128;  // 128-byte lines per K/V row
     const int sub = wave % HS;
 #pragma unroll
@@ -287,11 +300,16 @@ __global__ __launch_bounds__(256 * NG, 2) void prefill_mfma_kernel(PrefillArgs a
           mask_scores(s_cur, lim, hf);
         }
 
-        bf16x8 pb[4];
-        if constexpr (FOLD) softmax_step_rel<DT>(s_cur, m_run, l_run, o, neg_ref, pb);
-        else softmax_step<DT>(s_cur, sc, m_run, l_run, o, pb);
-
-        tile_io.pv(lds0, 2 * TILEB + st_cur, pb, o);
+        if constexpr (EXACT) {
+          const float m_use = softmax_max<DT>(s_cur, sc, m_run, l_run, o);
+          softmax_exp_f32(s_cur, sc, m_use, l_run);
+          tile_io.pv_f32(lds0, 2 * TILEB + st_cur, s_cur, o);
+        } else {
+          bf16x8 pb[4];
+          if constexpr (FOLD) softmax_step_rel<DT>(s_cur, m_run, l_run, o, neg_ref, pb);
+          else softmax_step<DT>(s_cur, sc, m_run, l_run, o, pb);
+          tile_io.pv(lds0, 2 * TILEB + st_cur, pb, o);
+        }
       }
 
       wait_vmcnt<0>();
@@ -348,7 +366,7 @@ __global__ __launch_bounds__(256 * NG, 2) void prefill_mfma_kernel(PrefillArgs a
     const float l_tot = sum_across_halves(l_run);
     const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
     if (grp == 0) {
-      constexpr int ROWO = 2 * D, CPR = D / 8, RPI = 64 / CPR;  // row bytes, 16-byte chunks per row, rows per store
+      constexpr int ROWB = TL::ROWB, CPR = TL::CPR;
       const int st_free = ((git - 1) & 1) * TILEB;
       unsigned char* stage = NG == 2 ? kv_lds + (wave >> 1) * 4 * TILEB + (wave & 1) * 2 * TILEB + st_free
                                      : kv_lds + (wave >> 1) * 2 * TILEB + st_free + (wave & 1) * (TILEB / 2);
@@ -360,15 +378,14 @@ __global__ __launch_bounds__(256 * NG, 2) void prefill_mfma_kernel(PrefillArgs a
 #pragma unroll
           for (int e = 0; e < 4; ++e) w[e] = (bf16_t)(o[dt][4 * vq + e] * inv);
           const int c = 4 * dt + vq;
-          *reinterpret_cast<u32x2*>(stage + l32 * ROWO + ((c ^ (l32 & (CPR - 1))) << 4) + 8 * hf) =
+          *reinterpret_cast<u32x2*>(stage + l32 * ROWB + ((c ^ TL::k_swizzle(l32)) << 4) + 8 * hf) =
               __builtin_bit_cast(u32x2, w);
         }
-      const int c = lane % CPR;
 #pragma unroll
-      for (int kk = 0; kk < kWaveRows / RPI; ++kk) {
-        const int r = kk * RPI + lane / CPR;
-        const u32x4 w = *reinterpret_cast<const u32x4*>(stage + r * ROWO + ((c ^ (r & (CPR - 1))) << 4));
-        if (cur.row0w + r < cur.seg_hi)
+      for (int kk = 0; kk < kWaveRows * CPR / 64; ++kk) {
+        const int r = (kk * 64 + lane) / CPR, c = (kk * 64 + lane) % CPR;
+        const u32x4 w = *reinterpret_cast<const u32x4*>(stage + r * ROWB + ((c ^ TL::k_swizzle(r)) << 4));
+        if (cur.row0w + r < cur.seg_hi && (!EXACT || 8 * c < D))
           // streaming store: the rows are not read again in this launch, and written through
           // now they are not left for the write-back at the end of the kernel
           __builtin_nontemporal_store(w, reinterpret_cast<u32x4*>(op + ((int64_t)(cur.row0w + r) * Hq + head) * D + 8 * c));
@@ -521,14 +538,21 @@ hipError_t launch_pack_kept_rows(const PrefillArgs& a, int row_bytes, int32_t* k
   return hipGetLastError();
 }
 
-template <int D, int NG, bool FOLD>
+template <int DP, int NG, bool FOLD, bool EXACT>
 hipError_t launch_prefill_mfma_t(const PrefillArgs& a, dim3 grid, hipStream_t s) {
-  constexpr int smem = NG * 4 * KvTile<D, 1>::TILEB;
+  constexpr int smem = NG * 4 * KvTile<DP, 1>::TILEB;
   static std::atomic<uint64_t> attr_done{0};
-  hipError_t e0 = set_max_dynamic_lds_once(attr_done, reinterpret_cast<const void*>(&prefill_mfma_kernel<D, NG, FOLD>), smem);
+  hipError_t e0 = set_max_dynamic_lds_once(attr_done, reinterpret_cast<const void*>(&prefill_mfma_kernel<DP, NG, FOLD, EXACT>), smem);
   if (e0 != hipSuccess) return e0;
-  hipLaunchKernelGGL((prefill_mfma_kernel<D, NG, FOLD>), grid, dim3(256 * NG), smem, s, a);
+  hipLaunchKernelGGL((prefill_mfma_kernel<DP, NG, FOLD, EXACT>), grid, dim3(256 * NG), smem, s, a);
   return hipGetLastError();
+}
+
+template <int DP>
+hipError_t launch_prefill_exact(const PrefillArgs& a, bool wide, dim3 grid, hipStream_t s) {
+  if constexpr (DP <= 128)
+    if (wide) return launch_prefill_mfma_t<DP, 2, false, true>(a, grid, s);
+  return launch_prefill_mfma_t<DP, 1, false, true>(a, grid, s);
 }
 
 hipError_t launch_prefill_mfma(const PrefillArgs& a_in, int n_blocks, hipStream_t s) {
@@ -547,7 +571,8 @@ hipError_t launch_prefill_mfma(const PrefillArgs& a_in, int n_blocks, hipStream_
   // query tile between two groups keep two wavefronts on every SIMD, at the price of a merge
   // through LDS per query tile and a heavier start.  That pays from about 16 KV tiles per
   // workgroup on (measured at 2048 tokens: 1.06 vs 1.35 us per tile, 14.0 vs 9.6 us fixed).
-  bool wide = (int64_t)grid.x * grid.y < 2 * (int64_t)a.n_cus;
+  // (Two groups' stages of a head dimension beyond 128 do not fit LDS.)
+  bool wide = (int64_t)grid.x * grid.y < 2 * (int64_t)a.n_cus && a.D <= 128;
   if (wide && n_blocks == 1) {
     const bool is_sync = a.sync_override >= 0 ? a.sync_override != 0 : sync_block_rule(a.sync_interval, a.block_idx0);
     const int N = a.seg.n;
@@ -595,14 +620,26 @@ hipError_t launch_prefill_mfma(const PrefillArgs& a_in, int n_blocks, hipStream_
     if (!is_sync) order_segments_by_length(a);
     grid.x = (unsigned)(a.n_q_tiles * per_tile);
   }
+  if (a.D != 64 && a.D != 128) {
+    switch ((a.D + 31) / 32) {
+      case 1: return launch_prefill_exact<32>(a, wide, grid, s);
+      case 2: return launch_prefill_exact<64>(a, wide, grid, s);
+      case 3: return launch_prefill_exact<96>(a, wide, grid, s);
+      case 4: return launch_prefill_exact<128>(a, wide, grid, s);
+      case 5: return launch_prefill_exact<160>(a, wide, grid, s);
+      case 6: return launch_prefill_exact<192>(a, wide, grid, s);
+      case 7: return launch_prefill_exact<224>(a, wide, grid, s);
+      default: return launch_prefill_exact<256>(a, wide, grid, s);
+    }
+  }
   // scale folded into Q only up to the usual 1/sqrt(D): its rounding error grows with the scale
   const bool fold = (double)a.scale * (double)a.scale * a.D <= 1.0 + 1e-6;
   if (a.D == 128) {
-    if (fold) return wide ? launch_prefill_mfma_t<128, 2, true>(a, grid, s) : launch_prefill_mfma_t<128, 1, true>(a, grid, s);
-    return wide ? launch_prefill_mfma_t<128, 2, false>(a, grid, s) : launch_prefill_mfma_t<128, 1, false>(a, grid, s);
+    if (fold) return wide ? launch_prefill_mfma_t<128, 2, true, false>(a, grid, s) : launch_prefill_mfma_t<128, 1, true, false>(a, grid, s);
+    return wide ? launch_prefill_mfma_t<128, 2, false, false>(a, grid, s) : launch_prefill_mfma_t<128, 1, false, false>(a, grid, s);
   }
-  if (fold) return wide ? launch_prefill_mfma_t<64, 2, true>(a, grid, s) : launch_prefill_mfma_t<64, 1, true>(a, grid, s);
-  return wide ? launch_prefill_mfma_t<64, 2, false>(a, grid, s) : launch_prefill_mfma_t<64, 1, false>(a, grid, s);
+  if (fold) return wide ? launch_prefill_mfma_t<64, 2, true, false>(a, grid, s) : launch_prefill_mfma_t<64, 1, true, false>(a, grid, s);
+  return wide ? launch_prefill_mfma_t<64, 2, false, false>(a, grid, s) : launch_prefill_mfma_t<64, 1, false, false>(a, grid, s);
 }
 
 hipError_t launch_build_kept_tiles(const PrefillArgs& a, int2* kept_tiles, int32_t* kept_cum,

@@ -1,6 +1,6 @@
-"""GPU parity of the shapes outside bf16 x head dimension 64 / 128: fp32 prefill on the matrix
-cores, in every split of the work that its launcher chooses, at head dimensions on and between
-the padded sizes."""
+"""GPU parity of the shapes outside bf16 x head dimension 64 / 128: fp32 prefill and bf16 prefill
+with other head dimensions on the matrix cores, in every split of the work that the launchers
+choose, at head dimensions on and between the padded sizes."""
 import numpy as np
 import pytest
 import torch
@@ -36,21 +36,45 @@ def test_f32_prefill(layout, D):
         check(got[rows, heads], ref, F32, what)
 
 
+# ordered tiles, 8-wave workgroups on few long walks, one tile per workgroup heaviest first
+BF16_LAYOUTS = {"ordered": ([70, 0, 63, 1, 258], 4, 1), "wide": ([1100, 0, 1003], 6, 3), "heavy-first": ([3101, 2, 3137], 32, 8)}
+
+
+@pytest.mark.parametrize("layout", sorted(BF16_LAYOUTS))
+@pytest.mark.parametrize("D", [8, 40, 72, 96, 120, 160, 184, 200, 256])
+def test_bf16_prefill_other_head_dims(layout, D):
+    """The weights enter the second product exactly (three bf16 parts), so the error is that of fp32
+    arithmetic plus the rounding of the output to bf16, half a unit in the last place: 2^-9 of the value."""
+    lens, Hq, Hkv = BF16_LAYOUTS[layout]
+    seg = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    total = int(seg[-1])
+    q, k, v = rand_block(43, total, Hq, Hkv, D)
+    rows, heads = fi.sample_rows(seg, Hq, 64, fi.DEFAULT_SEED, salt=D, tile=32, max_boundary_rows=200)
+    for sync, causal in [(0, True), (1, True), (1, False)]:
+        what = "bf16 %s D=%d sync=%d causal=%d" % (layout, D, sync, causal)
+        say(what)
+        got = prefill(q, k, v, seg, Hq=Hq, Hkv=Hkv, D=D, H=0, block=0, dtype=BF16, causal=causal, sync_override=sync)
+        ref = oracle.attend_rows(q, k, v, seg, rows, heads, is_sync=bool(sync), causal=causal)
+        check(got[rows, heads], ref, BF16, what)
+        assert np.all(np.abs(got[rows, heads] - ref) <= 2.0 ** -8 * np.abs(ref) + 1e-5), what   # twice half a unit: values at a binade's edge
+
+
 @pytest.mark.parametrize("chunk", [1, 20, 64])
 @pytest.mark.parametrize("causal", [True, False])
-def test_f32_prefill_keep_lists_with_and_without_workspace(chunk, causal):
+@pytest.mark.parametrize("dtype", [F32, BF16])
+def test_keep_lists_with_and_without_workspace(chunk, causal, dtype):
     seg = np.array([0, 130, 130, 321, 402], dtype=np.int32)
     Hq, Hkv, D = 4, 2, 72
-    q, k, v = rand_block(42, 402, Hq, Hkv, D, bf16=False)
+    q, k, v = rand_block(42, 402, Hq, Hkv, D, bf16=dtype == BF16)
     flags = (np.random.default_rng(7).random(int(fi.chunk_counts(np.diff(seg), chunk).sum())) < 0.4).astype(np.uint8)
     ref = oracle.attend_block(q, k, v, seg, is_sync=True, causal=causal, keep_tok=oracle.expand_keep_chunks(flags, seg, chunk))
-    say("f32 keep-list chunk=%d causal=%d" % (chunk, causal))
-    got = prefill(q, k, v, seg, Hq=Hq, Hkv=Hkv, D=D, H=1, block=0, dtype=F32, causal=causal, keep_chunks=flags, chunk_tokens=chunk)
-    check(got, ref, F32, "f32 keep-list chunk=%d" % chunk)
+    say("keep-list chunk=%d causal=%d" % (chunk, causal))
+    got = prefill(q, k, v, seg, Hq=Hq, Hkv=Hkv, D=D, H=1, block=0, dtype=dtype, causal=causal, keep_chunks=flags, chunk_tokens=chunk)
+    check(got, ref, dtype, "keep-list chunk=%d" % chunk)
     # without a workspace the flags are read by the general kernel
-    p = fa.make_params(4, Hq, Hkv, D, 1, F32, causal=causal)
-    tq = dev(q, F32)
+    p = fa.make_params(4, Hq, Hkv, D, 1, dtype, causal=causal)
+    tq = dev(q, dtype)
     out = torch.full_like(tq, float("nan"))
-    fa.fedattn_prefill(p, 0, tq, dev(k, F32), dev(v, F32), out, seg, keep_chunks=torch.from_numpy(flags).to("cuda"), chunk_tokens=chunk)
+    fa.fedattn_prefill(p, 0, tq, dev(k, dtype), dev(v, dtype), out, seg, keep_chunks=torch.from_numpy(flags).to("cuda"), chunk_tokens=chunk)
     torch.cuda.synchronize()
-    check(host(out), ref, F32, "f32 keep-list chunk=%d, no workspace" % chunk)
+    check(host(out), ref, dtype, "keep-list chunk=%d, no workspace" % chunk)
