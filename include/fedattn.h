@@ -180,6 +180,8 @@ FEDATTN_API fedattn_status fedattn_prefill_blocks(const fedattn_params* params, 
  *   workspace      device, >= fedattn_workspace_bytes(DECODE); holds split-KV partials and
  *                  chunk counters while the call's kernels run.  What it contains on entry
  *                  does not matter; calls that share a workspace must be ordered (same stream).
+ *                  fp32 and bf16 with D other than 64 and 128 also run without one, unsplit and
+ *                  many times slower.
  */
 FEDATTN_API fedattn_status fedattn_decode(const fedattn_params* params, int32_t block_idx, const void* q,
                               const void* k_cache, const void* v_cache, void* out,

@@ -129,7 +129,6 @@ size_t decode_counter_bytes(const fedattn_params* p) {
 }
 
 size_t decode_ws_bytes(const fedattn_params* p, int32_t capacity) {
-  if (!(p->dtype == FEDATTN_BF16 && (p->head_dim == 64 || p->head_dim == 128))) return 16;
   const size_t G = (size_t)(p->n_q_heads / p->n_kv_heads);
   const size_t N = (size_t)p->n_participants;
   // chunks <= sum_n (rows_n / chunk_rows + 1) <= target + N
@@ -392,18 +391,25 @@ static fedattn_status run_decode(bool fused, const fedattn_params* params, int32
   const int N = params->n_participants;
   const int32_t capacity = seg_offsets[N];
 
-  const bool mfma = params->dtype == FEDATTN_BF16 && (params->head_dim == 64 || params->head_dim == 128);
-  const size_t esize = params->dtype == FEDATTN_BF16 ? 2 : 4;
+  // fp32 and bf16 with other head dimensions: split too, but a call that comes without the workspace
+  // runs one wavefront per (participant, head)
+  const bool must_split = use_mfma_prefill(params);
+  bool split = true;
+  const size_t esize = (size_t)elem_bytes(params);
   DecodeArgs args[2];  // [0] local block, [1] sync block: the split differs, the layout does not
   bool built[2] = {false, false};
   int32_t* counters = nullptr;
   int slices = 1;            // blocks in flight at once, each in its own slice of the workspace
   size_t slice_bytes = 0;
-  if (mfma) {
-    const size_t need = decode_ws_bytes(params, capacity);
-    if (!workspace || workspace_bytes < need)
-      return fail(FEDATTN_EWORKSPACE, "decode needs %zu workspace bytes, got %zu", need, workspace_bytes);
-    if (!aligned16(workspace)) return fail(FEDATTN_EINVAL, "workspace must be 16-byte aligned");
+  const size_t need = decode_ws_bytes(params, capacity);
+  if (!workspace || workspace_bytes < need) {
+    if (must_split) return fail(FEDATTN_EWORKSPACE, "decode needs %zu workspace bytes, got %zu", need, workspace_bytes);
+    split = false;
+  } else if (!aligned16(workspace)) {
+    if (must_split) return fail(FEDATTN_EINVAL, "workspace must be 16-byte aligned");
+    split = false;
+  }
+  if (split) {
     slice_bytes = align_up(need, 256);
     if (fused) {
       if (n_blocks > 65535) return fail(FEDATTN_EINVAL, "at most 65535 blocks per fused call");
@@ -415,7 +421,7 @@ static fedattn_status run_decode(bool fused, const fedattn_params* params, int32
     // zero and every launch leaves them at zero for the next one
     counters = reinterpret_cast<int32_t*>(reinterpret_cast<unsigned char*>(workspace) + need - decode_counter_bytes(params));
   }
-  fused = fused && mfma;
+  fused = fused && split;
   const auto block_is_sync = [&](int b) {
     return sync_override >= 0 ? sync_override != 0 : sync_block_rule(params->sync_interval, block_idx0 + b);
   };
@@ -448,20 +454,23 @@ static fedattn_status run_decode(bool fused, const fedattn_params* params, int32
         }
       }
       a.n_chunks = (int32_t)chunks;
-      if (mfma) {
-        const size_t need = decode_ws_bytes(params, capacity) - decode_counter_bytes(params);
+      if (split) {
+        const size_t room = need - decode_counter_bytes(params);
         const size_t rows = (size_t)a.Hkv * (size_t)a.n_chunks * (size_t)a.cols;
         const size_t o_bytes = align_up(rows * (size_t)a.D * 4, 256);
-        if (o_bytes + rows * 8 > need)
+        if (o_bytes + rows * 8 > room)
           return fail(FEDATTN_EWORKSPACE, "decode partials (%zu bytes) exceed the workspace", o_bytes + rows * 8);
         a.part_o = reinterpret_cast<float*>(workspace);
         a.part_ml = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(workspace) + o_bytes);
         a.counters = counters;
-        // fused combine: the workgroups of a segment write its output rows, so every segment
+        // in-kernel merge: the workgroups of a segment write its output rows, so every segment
         // needs one (an empty segment's zero rows come from the separate combine kernel)
-        bool all_have_rows = true;
-        for (int n = 0; n < N; ++n) all_have_rows = all_have_rows && seg_lens[n] > 0;
-        a.fuse_combine = (!sync && a.cols <= 16 && all_have_rows) ? 1 : 0;
+        bool all_have_rows = true, one_chunk = true;
+        for (int n = 0; n < N; ++n) {
+          all_have_rows = all_have_rows && seg_lens[n] > 0;
+          one_chunk = one_chunk && seg_lens[n] <= a.chunk_rows;
+        }
+        a.merge_in_kernel = !sync && all_have_rows && (params->dtype == FEDATTN_F32 ? one_chunk : a.cols <= 16) ? 1 : 0;
       }
       a.q_block_bytes = q_block_stride * (int64_t)esize;
       a.cache_block_bytes = cache_block_stride * (int64_t)esize;
@@ -475,7 +484,7 @@ static fedattn_status run_decode(bool fused, const fedattn_params* params, int32
     st = prepare(block_is_sync(b));
     if (st != FEDATTN_OK) return st;
   }
-  if (mfma) {
+  if (split && params->dtype == FEDATTN_BF16) {
     hipError_t e = launch_decode_zero_counters(counters, params->n_kv_heads * N, slices, (int64_t)slice_bytes,
                                                reinterpret_cast<hipStream_t>(stream));
     if (e != hipSuccess) return fail(FEDATTN_ELAUNCH, "decode (counters): %s", hipGetErrorString(e));
@@ -498,7 +507,7 @@ static fedattn_status run_decode(bool fused, const fedattn_params* params, int32
         first = b;
         if (cnt == 0) continue;
         a.q = q; a.out = out; a.k_cache = k_cache; a.v_cache = v_cache;
-        hipError_t e = launch_decode(a, params->dtype, cnt, reinterpret_cast<hipStream_t>(stream));
+        hipError_t e = launch_decode(a, params->dtype, true, cnt, reinterpret_cast<hipStream_t>(stream));
         if (e != hipSuccess) return fail(FEDATTN_ELAUNCH, "decode (fused, %d blocks): %s", cnt, hipGetErrorString(e));
       }
     }
@@ -513,7 +522,7 @@ static fedattn_status run_decode(bool fused, const fedattn_params* params, int32
     a.out = reinterpret_cast<unsigned char*>(out) + (size_t)b * (size_t)q_block_stride * esize;
     a.k_cache = reinterpret_cast<const unsigned char*>(k_cache) + (size_t)b * (size_t)cache_block_stride * esize;
     a.v_cache = reinterpret_cast<const unsigned char*>(v_cache) + (size_t)b * (size_t)cache_block_stride * esize;
-    hipError_t e = launch_decode(a, params->dtype, 1, reinterpret_cast<hipStream_t>(stream));
+    hipError_t e = launch_decode(a, params->dtype, split, 1, reinterpret_cast<hipStream_t>(stream));
     if (e != hipSuccess) return fail(FEDATTN_ELAUNCH, "decode (block %d): %s", block_idx0 + b, hipGetErrorString(e));
   }
   return FEDATTN_OK;
@@ -586,7 +595,7 @@ fedattn_status fedattn_decode_static(const fedattn_params* params, int32_t block
                                         remote_lens, sync_override);
   if (st != FEDATTN_OK) return st;
   const size_t need = decode_ws_bytes(params, seg_offsets[params->n_participants]);
-  if (need > (size_t)FEDATTN_STATIC_SCRATCH_BYTES)
+  if (need > (size_t)FEDATTN_STATIC_SCRATCH_BYTES && use_mfma_prefill(params))
     return fail(FEDATTN_EWORKSPACE,
                 "fedattn_decode_static: this problem needs %zu bytes of scratch, the built-in array holds %zu; "
                 "use fedattn_decode with a workspace",

@@ -15,6 +15,7 @@
 // at the end and a second small kernel merges the chunks:
 //   o = sum_c O_c 2^(m_c - m) / sum_c l_c 2^(m_c - m).
 #include "common.h"
+#include "decode_walk.h"
 #include "mfma_tile.h"
 
 namespace fedattn {
@@ -25,10 +26,12 @@ namespace {
 // worked on): measured against four stages (three in flight), the deeper ring only lengthens
 // the queue in front of the memory system; a block-step of 16 x 1152 rows takes 17.4 instead
 // of 18.0 us.
-constexpr int kDecodeStages = 3;
+// (Rows of more than 192 elements: two, three do not fit LDS.)
+template <int D>
+constexpr int decode_stages() { return D > 192 ? 2 : 3; }
 
 template <int D>
-constexpr int decode_smem_bytes() { return kDecodeStages * 2 * KvTile<D, 0>::TILEB; }
+constexpr int decode_smem_bytes() { return decode_stages<D>() * 2 * KvTile<D, 0>::TILEB; }
 
 // COLSPLIT = false (at most 16 query columns, e.g. the G heads of one participant in a
 // local block): 4 wavefronts, wavefront w takes tile rows 16w..16w+15; they are merged
@@ -38,16 +41,21 @@ constexpr int decode_smem_bytes() { return kDecodeStages * 2 * KvTile<D, 0>::TIL
 // 16-row sub-tiles fill the 8 k-slots per lane of one v_mfma_f32_16x16x32_bf16 in the second
 // product (slot e < 4: row 4 kg + e of the first sub-tile, e >= 4: of the second), which
 // halves its MFMA count.  The two row halves of a column block are merged through LDS.
-template <int D, bool COLSPLIT>
+// EXACT (head dimensions other than 64 and 128, padded to DP): the weights keep their fp32 precision
+// in the second product, as three bf16 parts each (one participant of 62..207 rows to eight of 1500,
+// bf16: 5 to 14 times faster than one wavefront per participant and head).
+template <int DP, bool COLSPLIT, bool EXACT>
 __global__ __launch_bounds__(COLSPLIT ? 512 : 256, 1) void decode_stream_kernel(DecodeArgs a) {
   constexpr int NW = COLSPLIT ? 8 : 4;
-  using TL = KvTile<D, 0, NW>;
-  constexpr int KS = D / 32;                 // k-steps of S^T (16x16x32)
-  constexpr int DT = D / 16;                 // 16-row tiles of O^T along head_dim
-  constexpr int CPR = TL::CPR, ROWB = TL::ROWB, TILEB = TL::TILEB, IPW = TL::IPW;
+  using TL = KvTile<DP, 0, NW>;
+  constexpr int kDecodeStages = decode_stages<DP>();
+  const int D = EXACT ? a.D : DP;
+  constexpr int KS = DP / 32;                // k-steps of S^T (16x16x32)
+  constexpr int DT = DP / 16;                // 16-row tiles of O^T along head_dim
+  constexpr int ROWB = TL::ROWB, TILEB = TL::TILEB, IPW = TL::IPW;
   constexpr int RSUB = COLSPLIT ? 2 : 1;     // 16-row sub-tiles a wavefront processes per tile
   constexpr int QCOLS = COLSPLIT ? 64 : 16;  // query columns per workgroup
-  constexpr int OPAD = D + 4;                // floats per row of the merge buffer
+  constexpr int OPAD = DP + 4;               // floats per row of the merge buffer
   // stage s: K tile at s*2*TILEB, V tile at s*2*TILEB + TILEB; after the stream the
   // ring is reused as the merge buffer (row split only)
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
@@ -80,31 +88,12 @@ __global__ __launch_bounds__(COLSPLIT ? 512 : 256, 1) void decode_stream_kernel(
   const int rh = COLSPLIT ? wave >> 2 : 0;   // row half of the tile (column split only)
   const int cb = blockIdx.y * QCOLS + (COLSPLIT ? 16 * (wave & 3) : 0);  // first query column of this wavefront
 
-  // The segment tables sit in the kernel-argument buffer; a walk over them would take one
-  // scalar-cache miss after another before the first cache row is requested.  Every lane
-  // fetches the entries of segments `lane` and `lane + 64` at once, the chunk's segment is
-  // found with ballots and its entries are read out of the lanes that hold them.
   const int N = a.N;
-  const int ck_lo = a.chunk_cum[lane + 1], ck_hi = a.chunk_cum[lane + 65];
-  const int sl_lo = a.seg_lens[lane], sl_hi = a.seg_lens[lane + 64];
-  const int rl_lo = a.remote_lens[lane], rl_hi = a.remote_lens[lane + 64];
-  const int so_lo = a.seg_off[lane], so_hi = a.seg_off[lane + 64];
-  int m = __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane < N && gc >= ck_lo));
-  if (N > 64) m += __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane + 64 < N && gc >= ck_hi));
-  auto pick = [&](int lo, int hi, int idx) __attribute__((always_inline)) {
-    return idx < 64 ? __builtin_amdgcn_readlane(lo, idx) : __builtin_amdgcn_readlane(hi, idx - 64);
-  };
-  const int chunk0 = m == 0 ? 0 : pick(ck_lo, ck_hi, m - 1);  // first chunk of segment m
-  const int n_seg_chunks = pick(ck_lo, ck_hi, m) - chunk0;
-  const int c = gc - chunk0;
-  const int own_len = pick(sl_lo, sl_hi, m);
-  const int rem_len = a.has_remote ? pick(rl_lo, rl_hi, m) : own_len;
-  const int seg_row0 = pick(so_lo, so_hi, m);
+  const DecodeChunk ch = find_decode_chunk(a, gc, lane);
+  const int m = ch.m, chunk0 = ch.chunk0, n_seg_chunks = ch.n_seg_chunks;
+  const int own_len = ch.own_len, rem_len = ch.rem_len, seg_row0 = ch.seg_row0;
+  const int r_lo = ch.r_lo, r_hi = ch.r_hi, min_limit = ch.min_limit;
   const bool sync = a.is_sync != 0;
-  const int rows_end = sync ? max(own_len, rem_len) : own_len;
-  const int min_limit = sync ? min(own_len, rem_len) : own_len;
-  const int r_lo = c * a.chunk_rows;
-  const int r_hi = min(r_lo + a.chunk_rows, rows_end);
   const int nt = (r_hi - r_lo + kKvTile - 1) / kKvTile;
   const int row_elems = Hkv * D;
 
@@ -112,7 +101,7 @@ __global__ __launch_bounds__(COLSPLIT ? 512 : 256, 1) void decode_stream_kernel(
   const uint16_t* vbase = reinterpret_cast<const uint16_t*>(v_ptr) + ((int64_t)(seg_row0 + r_lo) * Hkv + g) * D;
 
   TL tile_io;
-  tile_io.init(lane, wave, row_elems);
+  tile_io.init(lane, wave, row_elems, EXACT ? D / 8 - 1 : TL::CPR - 1);
 
   // this lane's query column -> (participant, head); columns past the end are zero
   // rows: local block, column = head inside the KV group; sync block, column =
@@ -127,10 +116,12 @@ __global__ __launch_bounds__(COLSPLIT ? 512 : 256, 1) void decode_stream_kernel(
   const int limit = col_ok ? (col_part == m ? own_len : rem_len) : 0;  // visible rows of this segment
   u32x4 qw[KS];  // B operand of S^T: Q[col][32 st + 8 kg .. +8]
   {
-    const uint16_t* qrow = reinterpret_cast<const uint16_t*>(q_ptr) + ((int64_t)col_part * Hq + col_head) * D + 8 * kg;
+    const uint16_t* qrow = reinterpret_cast<const uint16_t*>(q_ptr) + ((int64_t)col_part * Hq + col_head) * D;
 #pragma unroll
-    for (int st = 0; st < KS; ++st)
-      asm volatile("global_load_dwordx4 %0, %1, off" : "=v"(qw[st]) : "v"(qrow + 32 * st) : "memory");
+    for (int st = 0; st < KS; ++st) {
+      const int d0 = EXACT ? min(32 * st + 8 * kg, D - 8) : 32 * st + 8 * kg;
+      asm volatile("global_load_dwordx4 %0, %1, off" : "=v"(qw[st]) : "v"(qrow + d0) : "memory");
+    }
   }
 
   auto issue = [&](int t) __attribute__((always_inline)) {
@@ -150,7 +141,7 @@ __global__ __launch_bounds__(COLSPLIT ? 512 : 256, 1) void decode_stream_kernel(
   // which leaves the swizzle term unchanged
   int k_off[KS];
 #pragma unroll
-  for (int st = 0; st < KS; ++st) k_off[st] = l16 * ROWB + (((4 * st + kg) ^ (l16 & (CPR - 1))) * 16);
+  for (int st = 0; st < KS; ++st) k_off[st] = l16 * ROWB + (((4 * st + kg) ^ TL::k_swizzle(l16)) * 16);
   // LDS -> A operand of O^T: transposing 8-byte reads; lane i = 4 e + c of a 16-lane group
   // supplies the address of V[sub-tile row 4 kg + e][16 dt + 4 c ..] and receives
   // V[sub-tile rows 4 kg + 0..3][16 dt + i]
@@ -180,7 +171,10 @@ __global__ __launch_bounds__(COLSPLIT ? 512 : 256, 1) void decode_stream_kernel(
       wait_vmcnt<0>();
     __syncthreads();  // tile t is complete in LDS, and everyone is done with tile t-1
 #pragma unroll
-    for (int st = 0; st < KS; ++st) asm volatile("" : "+v"(qw[st]));  // the query loads have landed by now
+    for (int st = 0; st < KS; ++st) {
+      asm volatile("" : "+v"(qw[st]));  // the query loads have landed by now
+      if (EXACT && 32 * st + 8 * kg >= D) qw[st] = u32x4{0u, 0u, 0u, 0u};  // padded columns
+    }
     if (t + kDecodeStages - 1 < nt) issue(t + kDecodeStages - 1);  // into the stage tile t-1 used
     if (COLSPLIT && !wave_has_cols) continue;
 
@@ -223,22 +217,29 @@ __global__ __launch_bounds__(COLSPLIT ? 512 : 256, 1) void decode_stream_kernel(
       for (int dt = 0; dt < DT; ++dt) o[dt] *= alpha;
     }
     const float m_use = (m_run == -INFINITY) ? 0.f : m_run;
-    s16x4 pb[RSUB];
+    constexpr int PARTS = EXACT ? 3 : 1;
+    s16x4 pb[PARTS][RSUB];
 #pragma unroll
     for (int rs = 0; rs < RSUB; ++rs) {
       float p[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) p[e] = __builtin_amdgcn_exp2f(fmaf(s[rs][e], sc, -m_use));
       l_run += (p[0] + p[1]) + (p[2] + p[3]);
-      const bf16x4 pv4 = {(bf16_t)p[0], (bf16_t)p[1], (bf16_t)p[2], (bf16_t)p[3]};
-      pb[rs] = __builtin_bit_cast(s16x4, pv4);
+      if constexpr (EXACT) {
+        bf16x4 part[3];
+        split_weights(p, part);
+#pragma unroll
+        for (int t3 = 0; t3 < 3; ++t3) pb[t3][rs] = __builtin_bit_cast(s16x4, part[t3]);
+      } else {
+        const bf16x4 pv4 = {(bf16_t)p[0], (bf16_t)p[1], (bf16_t)p[2], (bf16_t)p[3]};
+        pb[0][rs] = __builtin_bit_cast(s16x4, pv4);
+      }
     }
 
     // ---- O^T[d][q] += V^T P^T -----------------------------------------------------------------
     if constexpr (COLSPLIT) {
       // both sub-tiles in one 16x16x32 MFMA: k-slot 8 kg + e = row 4 kg + (e mod 4) of sub-tile e / 4
       const int sub = 2 * rh * 16 * ROWB;
-      const s16x8 pp = __builtin_shufflevector(pb[0], pb[1], 0, 1, 2, 3, 4, 5, 6, 7);
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt) {
         const s16x4 v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
@@ -246,8 +247,12 @@ __global__ __launch_bounds__(COLSPLIT ? 512 : 256, 1) void decode_stream_kernel(
         const s16x4 v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
             (__attribute__((address_space(3))) s16x4*)(lds0 + (kb + TILEB + sub + 16 * ROWB + v_off[dt])));
         const s16x8 vv = __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7);
-        o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, vv), __builtin_bit_cast(bf16x8, pp),
-                                                        o[dt], 0, 0, 0);
+#pragma unroll
+        for (int t3 = PARTS - 1; t3 >= 0; --t3) {
+          const s16x8 pp = __builtin_shufflevector(pb[t3][0], pb[t3][1], 0, 1, 2, 3, 4, 5, 6, 7);
+          o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, vv), __builtin_bit_cast(bf16x8, pp),
+                                                          o[dt], 0, 0, 0);
+        }
       }
     } else {
       // k-slot 4 kg + e of the 16x16x16 MFMA = sub-tile row 4 kg + e
@@ -256,7 +261,8 @@ __global__ __launch_bounds__(COLSPLIT ? 512 : 256, 1) void decode_stream_kernel(
       for (int dt = 0; dt < DT; ++dt) {
         const s16x4 vf = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
             (__attribute__((address_space(3))) s16x4*)(lds0 + (kb + TILEB + sub + v_off[dt])));
-        o[dt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vf, pb[0], o[dt], 0, 0, 0);
+#pragma unroll
+        for (int t3 = PARTS - 1; t3 >= 0; --t3) o[dt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vf, pb[t3][0], o[dt], 0, 0, 0);
       }
     }
   }
@@ -288,7 +294,8 @@ __global__ __launch_bounds__(COLSPLIT ? 512 : 256, 1) void decode_stream_kernel(
     if (rh == 0 && col_ok) {
       const int64_t prow = ((int64_t)g * a.n_chunks + gc) * a.cols + col;
 #pragma unroll
-      for (int dt = 0; dt < DT; ++dt) *reinterpret_cast<f32x4*>(part_o + prow * D + 16 * dt + 4 * kg) = o[dt];
+      for (int dt = 0; dt < DT; ++dt)
+        if (!EXACT || 16 * dt + 4 * kg < D) *reinterpret_cast<f32x4*>(part_o + prow * D + 16 * dt + 4 * kg) = o[dt];
       if (kg == 0) {
         part_ml[prow * 2] = m_run;
         part_ml[prow * 2 + 1] = l_run;
@@ -312,7 +319,7 @@ __global__ __launch_bounds__(COLSPLIT ? 512 : 256, 1) void decode_stream_kernel(
     const float* o_all = reinterpret_cast<const float*>(smem);
     // local block with the combine fused in: query column cl is head g G + cl of participant m
     uint16_t* out_rows = reinterpret_cast<uint16_t*>(out_ptr) + ((int64_t)m * Hq + g * G + col0) * D;
-    if (a.fuse_combine && n_seg_chunks == 1) {
+    if (a.merge_in_kernel && n_seg_chunks == 1) {
       // the segment's only chunk: normalise and write the output rows, no partials
       for (int idx = tid; idx < n_cols * (D / 4); idx += 256) {
         const int cl = idx / (D / 4), d4 = idx % (D / 4);
@@ -328,7 +335,7 @@ __global__ __launch_bounds__(COLSPLIT ? 512 : 256, 1) void decode_stream_kernel(
       }
       return;
     }
-    if (!a.fuse_combine) {
+    if (!a.merge_in_kernel) {
       for (int idx = tid; idx < n_cols * (D / 4); idx += 256) {
         const int cl = idx / (D / 4), d4 = idx % (D / 4);
         const float* src = o_all + cl * OPAD + 4 * d4;
@@ -423,7 +430,7 @@ __global__ void decode_zero_counters_kernel(int32_t* counters, int n, int64_t sl
 
 // Merges the chunk partials of one (participant, query head) and writes the output row:
 //   o = sum_c O_c 2^(m_c - m) / sum_c l_c 2^(m_c - m),  m = max_c m_c.
-// D/4 x 4 threads: thread (cg, d4) sums 4 head-dim elements over the chunks c = cg (mod 4),
+// At least D/4 x 4 threads: thread (cg, d4) sums 4 head-dim elements over the chunks c = cg (mod 4),
 // all its loads in flight at once (the kernel is a chain of memory round trips: (m, l) of
 // every chunk, then the partial O rows, then the store); the 4 chunk groups meet in LDS.
 template <typename T>
@@ -443,7 +450,7 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(DecodeArgs a) {
   const int64_t base = (int64_t)g * a.n_chunks;
   const int tid = threadIdx.x;
   const int D = a.D, D4 = D / 4;
-  const int d4 = tid % D4, cg = tid / D4;  // blockDim = D4 * CG
+  const int d4 = tid % D4, cg = tid / D4;  // blockDim: whole wavefronts, at least D4 * CG; the rest (cg >= CG) only helps with (m, l)
   // block of a fused launch
   const int bz = blockIdx.y;
   unsigned char* out_ptr = reinterpret_cast<unsigned char*>(a.out) + (int64_t)a.block_list[bz] * a.q_block_bytes;
@@ -460,7 +467,7 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(DecodeArgs a) {
 #pragma unroll
     for (int u = 0; u < 16; ++u) {
       const int i = cg + CG * u;
-      part[u] = i < nb ? *reinterpret_cast<const f32x4*>(po + i * cstride * D) : f32x4{0.f, 0.f, 0.f, 0.f};
+      part[u] = i < nb && cg < CG ? *reinterpret_cast<const f32x4*>(po + i * cstride * D) : f32x4{0.f, 0.f, 0.f, 0.f};
     }
     float m_i = -INFINITY, l_i = 0.f;
     if (tid < nb) {
@@ -485,7 +492,7 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(DecodeArgs a) {
       const int i = cg + CG * u;
       if (i < nb) acc += part[u] * w_s[i];
     }
-    acc_s[cg][d4] = acc;
+    if (cg < CG) acc_s[cg][d4] = acc;
     if (tid == 0) {
       float den = 0.f;
       for (int i = 0; i < nb; ++i) den = fmaf(l_s[i], w_s[i], den);
@@ -530,11 +537,11 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(DecodeArgs a) {
     __syncthreads();
     const float* po = part_o + ((base + cb) * cstride + col) * D + 4 * d4;
 #pragma unroll 8
-    for (int i = cg; i < nb; i += CG) acc += *reinterpret_cast<const f32x4*>(po + i * cstride * D) * w_s[i];
+    for (int i = cg < CG ? cg : nb; i < nb; i += CG) acc += *reinterpret_cast<const f32x4*>(po + i * cstride * D) * w_s[i];
     if (tid == 0)
       for (int i = 0; i < nb; ++i) den = fmaf(l_s[i], w_s[i], den);
   }
-  acc_s[cg][d4] = acc;
+  if (cg < CG) acc_s[cg][d4] = acc;
   if (tid == 0) m_s[8] = den;
   __syncthreads();
   if (cg == 0) {
@@ -552,7 +559,8 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(DecodeArgs a) {
 }
 
 // General decode kernel (plain ALU, fp32 arithmetic, any head_dim up to 256, fp32 or
-// bf16 storage): one wavefront per (participant, query head), no split.
+// bf16 storage): one wavefront per (participant, query head), no split and no workspace.  It takes
+// the calls that come without one; with one they run 5 to 59 times faster on the split kernels.
 template <typename T>
 __device__ inline float ld(const T* p) {
   if constexpr (sizeof(T) == 2)
@@ -627,30 +635,46 @@ __global__ __launch_bounds__(64) void decode_rows_kernel(DecodeArgs a) {
   }
 }
 
-template <int D, bool COLSPLIT>
+template <int DP, bool COLSPLIT, bool EXACT>
 hipError_t launch_stream_mode(const DecodeArgs& a, int n_z, hipStream_t s) {
   static std::atomic<uint64_t> attr_done{0};
-  hipError_t e0 = set_max_dynamic_lds_once(attr_done, reinterpret_cast<const void*>(&decode_stream_kernel<D, COLSPLIT>),
-                                           decode_smem_bytes<D>());
+  hipError_t e0 = set_max_dynamic_lds_once(attr_done, reinterpret_cast<const void*>(&decode_stream_kernel<DP, COLSPLIT, EXACT>),
+                                           decode_smem_bytes<DP>());
   if (e0 != hipSuccess) return e0;
   const int qcols = COLSPLIT ? 64 : 16;
   dim3 grid((unsigned)(a.n_chunks * a.Hkv), (unsigned)((a.cols + qcols - 1) / qcols), (unsigned)n_z);
-  hipLaunchKernelGGL((decode_stream_kernel<D, COLSPLIT>), grid, dim3(COLSPLIT ? 512 : 256), decode_smem_bytes<D>(), s, a);
+  hipLaunchKernelGGL((decode_stream_kernel<DP, COLSPLIT, EXACT>), grid, dim3(COLSPLIT ? 512 : 256), decode_smem_bytes<DP>(), s, a);
   return hipGetLastError();
 }
 
+// D: 64 or 128
 template <int D>
 hipError_t launch_stream(const DecodeArgs& a, int n_z, hipStream_t s) {
-  return a.cols <= 16 ? launch_stream_mode<D, false>(a, n_z, s) : launch_stream_mode<D, true>(a, n_z, s);
+  return a.cols <= 16 ? launch_stream_mode<D, false, false>(a, n_z, s) : launch_stream_mode<D, true, false>(a, n_z, s);
+}
+
+// other head dimensions, at most DP (8 wavefronts share a tile's loads evenly from multiples of 64 on)
+template <int DP>
+hipError_t launch_stream_exact(const DecodeArgs& a, int n_z, hipStream_t s) {
+  return a.cols <= 16 ? launch_stream_mode<DP, false, true>(a, n_z, s)
+                      : launch_stream_mode<(DP + 63) / 64 * 64, true, true>(a, n_z, s);
 }
 
 }  // namespace
 
-// n_z > 1: the blocks a.block_list[0 .. n_z) in one launch (MFMA path only)
-hipError_t launch_decode(const DecodeArgs& a, int dtype, int n_z, hipStream_t s) {
+hipError_t launch_decode_combine(const DecodeArgs& a, int dtype, int n_z, hipStream_t s) {
+  const dim3 grid((unsigned)(a.N * a.Hq), (unsigned)n_z), block((unsigned)((a.D + 63) / 64 * 64));
+  if (dtype == FEDATTN_F32)
+    hipLaunchKernelGGL(decode_combine_kernel<float>, grid, block, 0, s, a);
+  else
+    hipLaunchKernelGGL(decode_combine_kernel<uint16_t>, grid, block, 0, s, a);
+  return hipGetLastError();
+}
+
+// n_z > 1: the blocks a.block_list[0 .. n_z) in one launch (split kernels only)
+hipError_t launch_decode(const DecodeArgs& a, int dtype, bool split, int n_z, hipStream_t s) {
   if (a.N == 0 || n_z == 0) return hipSuccess;
-  const bool mfma = dtype == FEDATTN_BF16 && (a.D == 64 || a.D == 128);
-  if (!mfma) {
+  if (!split) {
     if (n_z != 1) return hipErrorInvalidValue;
     dim3 grid((unsigned)(a.N * a.Hq));
     if (dtype == FEDATTN_F32)
@@ -660,13 +684,23 @@ hipError_t launch_decode(const DecodeArgs& a, int dtype, int n_z, hipStream_t s)
     return hipGetLastError();
   }
   if (a.n_chunks > 0) {
-    hipError_t e = a.D == 128 ? launch_stream<128>(a, n_z, s) : launch_stream<64>(a, n_z, s);
+    hipError_t e;
+    if (dtype == FEDATTN_F32) e = launch_decode_f32(a, n_z, s);
+    else if (a.D == 128) e = launch_stream<128>(a, n_z, s);
+    else if (a.D == 64) e = launch_stream<64>(a, n_z, s);
+    else switch ((a.D + 31) / 32) {
+      case 1: e = launch_stream_exact<32>(a, n_z, s); break;
+      case 2: e = launch_stream_exact<64>(a, n_z, s); break;
+      case 3: e = launch_stream_exact<96>(a, n_z, s); break;
+      case 4: e = launch_stream_exact<128>(a, n_z, s); break;
+      case 5: e = launch_stream_exact<160>(a, n_z, s); break;
+      case 6: e = launch_stream_exact<192>(a, n_z, s); break;
+      case 7: e = launch_stream_exact<224>(a, n_z, s); break;
+      default: e = launch_stream_exact<256>(a, n_z, s);
+    }
     if (e != hipSuccess) return e;
   }
-  if (a.fuse_combine) return hipSuccess;
-  hipLaunchKernelGGL(decode_combine_kernel<uint16_t>, dim3((unsigned)(a.N * a.Hq), (unsigned)n_z), dim3(a.D), 0,
-                     s, a);
-  return hipGetLastError();
+  return a.merge_in_kernel ? hipSuccess : launch_decode_combine(a, dtype, n_z, s);
 }
 
 hipError_t launch_decode_zero_counters(int32_t* counters, int n, int slices, int64_t slice_bytes, hipStream_t s) {

@@ -105,7 +105,7 @@ __device__ inline float sum_over_kgroups(float x) {
 // padding re-reads the row's last chunk, so whatever a padded operand multiplies is finite).
 // VSWZ selects the chunk swizzle of V tiles: the transposing reads of the 32x32x16
 // product touch 4 rows x 4 chunks per 32 lanes (VSWZ = 1), those of the
-// 16x16x16 product 8 rows x 2 chunks (VSWZ = 0: f = 2 (row mod 8)).
+// 16x16x16 product 8 rows x 2 chunks (VSWZ = 0).
 // NW = wavefronts that load a tile together (4, or 8 for 8-wave workgroups sharing one tile).
 template <int D, int VSWZ, int NW = 4>
 struct KvTile {
@@ -130,10 +130,9 @@ struct KvTile {
     return (row >> 2) & 3;
   }
   static __device__ __attribute__((always_inline)) int v_swizzle(int row) {
-    if constexpr (VSWZ == 0) return (2 * (row & 7)) & (CPR - 1);
-    if constexpr (D % 128 == 0) return 4 * (row & 3);
-    if constexpr (D % 64 == 0) return 4 * ((row >> 1) & 1);
-    return 0;
+    if constexpr (D % 128 == 0) return VSWZ == 0 ? 2 * (row & 7) : 4 * (row & 3);
+    if constexpr (D % 64 == 0) return VSWZ == 0 ? 2 * ((row >> 1) & 3) : 4 * ((row >> 1) & 1);
+    return VSWZ == 0 ? 2 * ((row >> 2) & 1) : 0;
   }
   uint32_t dma_koff[IPW];  // byte offset from the tile's first row of what this lane fetches in its
   uint32_t dma_voff[IPW];  // wave's i-th instruction (full tiles; ragged tiles work theirs out on the spot)
@@ -424,11 +423,12 @@ __device__ __attribute__((always_inline)) inline void softmax_exp_f32(f32x16 (&s
   l_run += ps[0] + ps[1];
 }
 
-// Eight fp32 weights as a sum of three bf16 operands, exactly: 8 significant bits are cut off at a
+// N fp32 weights as a sum of three bf16 operands, exactly: 8 significant bits are cut off at a
 // time, and each remainder is exact in fp32 (24 = 3 x 8 bits).
-__device__ __attribute__((always_inline)) inline void split_weights(const float (&p)[8], bf16x8 (&part)[3]) {
+template <int N, typename BF16xN>
+__device__ __attribute__((always_inline)) inline void split_weights(const float (&p)[N], BF16xN (&part)[3]) {
 #pragma unroll
-  for (int i = 0; i < 8; i += 2) {
+  for (int i = 0; i < N; i += 2) {
     float x = p[i], y = p[i + 1];
 #pragma unroll
     for (int t = 0; t < 3; ++t) {

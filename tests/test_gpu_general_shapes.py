@@ -1,6 +1,6 @@
 """GPU parity of the shapes outside bf16 x head dimension 64 / 128: fp32 prefill and bf16 prefill
 with other head dimensions on the matrix cores, in every split of the work that the launchers
-choose, at head dimensions on and between the padded sizes."""
+choose, at head dimensions on and between the padded sizes; decoding with the same shapes."""
 import numpy as np
 import pytest
 import torch
@@ -8,7 +8,7 @@ import torch
 import fedattn_inputs as fi
 import oracle
 import paper_2511_02647_amd as fa
-from gpu_util import check, dev, host, prefill, say
+from gpu_util import check, decode, dev, host, prefill, say
 from test_gpu_parity import rand_block
 
 pytestmark = pytest.mark.gpu
@@ -78,3 +78,50 @@ def test_keep_lists_with_and_without_workspace(chunk, causal, dtype):
     fa.fedattn_prefill(p, 0, tq, dev(k, dtype), dev(v, dtype), out, seg, keep_chunks=torch.from_numpy(flags).to("cuda"), chunk_tokens=chunk)
     torch.cuda.synchronize()
     check(host(out), ref, dtype, "keep-list chunk=%d, no workspace" % chunk)
+
+
+@pytest.mark.parametrize("dtype,D", [(BF16, d) for d in (8, 40, 80, 96, 120, 160, 200, 256)] + [(F32, d) for d in (8, 64, 72, 128, 136, 256)])
+@pytest.mark.parametrize("lens,Hq,Hkv", [([200, 77, 130], 8, 2), ([64], 3, 1), ([700, 0, 1, 333, 64, 65], 12, 2), ([40, 1500], 40, 2)])
+def test_decode_other_shapes(dtype, D, lens, Hq, Hkv):
+    """One chunk and many per segment, an empty segment, one to 120 query columns; with and without a workspace."""
+    N = len(lens)
+    cap = np.asarray(lens, dtype=np.int32) + 3
+    seg = np.concatenate([[0], np.cumsum(cap)]).astype(np.int32)
+    lens = np.asarray(lens, dtype=np.int32)
+    _, kc, vc = rand_block(50, int(seg[-1]), Hkv, Hkv, D, bf16=dtype == BF16)
+    q, _, _ = rand_block(51, N, Hq, Hkv, D, bf16=dtype == BF16)
+    p = fa.make_params(N, Hq, Hkv, D, 0, dtype)
+    for sync, rl in [(0, None), (1, None), (1, lens // 2)]:
+        what = "decode %s D=%d lens=%s %d/%d sync=%d remote=%s" % (dtype, D, lens.tolist(), Hq, Hkv, sync, rl is not None)
+        say(what)
+        ref = oracle.decode_step(q, kc, vc, seg, lens, is_sync=bool(sync), remote_lens=rl)
+        got = decode(q, kc, vc, seg, lens, Hq=Hq, Hkv=Hkv, D=D, H=0, block=0, dtype=dtype, remote_lens=rl, sync_override=sync)
+        check(got, ref, dtype, what)
+        if dtype == BF16:   # fp32 arithmetic, output rounded to bf16 (see above)
+            assert np.all(np.abs(got - ref) <= 2.0 ** -8 * np.abs(ref) + 1e-5), what
+        tq = dev(q, dtype)
+        out = torch.full_like(tq, float("nan"))
+        fa.fedattn_decode(p, 0, tq, dev(kc, dtype), dev(vc, dtype), out, seg, lens, remote_lens=rl, sync_override=sync)
+        torch.cuda.synchronize()
+        check(host(out), ref, dtype, what + ", no workspace")
+
+
+@pytest.mark.parametrize("dtype,D", [(F32, 64), (BF16, 96)])
+def test_decode_other_shapes_fused_blocks_equal_single_calls(dtype, D):
+    N, Hq, Hkv, M, cap = 3, 8, 2, 5, 300
+    seg = (np.arange(N + 1) * cap).astype(np.int32)
+    lens = np.array([300, 20, 129], dtype=np.int32)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    mk = lambda *s: torch.randn(*s, generator=g, device="cuda", dtype=torch.float32).to(dtype)
+    q, k, v = mk(M, N, Hq, D), mk(M, N * cap, Hkv, D), mk(M, N * cap, Hkv, D)
+    p = fa.make_params(N, Hq, Hkv, D, 2, dtype)
+    one, many = torch.zeros_like(q), torch.zeros_like(q)
+    need = fa.fedattn_workspace_bytes(p, fa.FEDATTN_OP_DECODE, N * cap)
+    ws = torch.full((4 * (need + 256),), 255, dtype=torch.uint8, device="cuda")
+    say("decode %s D=%d fused blocks" % (dtype, D))
+    for b in range(M):
+        fa.fedattn_decode(p, b, q[b], k[b], v[b], one[b], seg, lens, workspace=ws)
+    fa.fedattn_decode_blocks_fused(p, 0, M, q, k, v, many, q[0].numel(), k[0].numel(), seg, lens, workspace=ws)
+    torch.cuda.synchronize()
+    assert torch.equal(one, many)
