@@ -4,7 +4,8 @@ Every function has the name and the meaning of the C entry point it calls
 (include/fedattn.h); all arithmetic runs in the library's gfx950 kernels.
 PyTorch is used for device memory and the stream only.  There is no CPU or
 PyTorch fallback: if libfedattn.so is missing or fails to load, importing a
-function's result fails loudly.
+function's result fails loudly.  The arguments of the calls that enqueue kernels
+are marshalled natively (csrc/binding.cpp); `load()` returns the library itself.
 """
 from __future__ import annotations
 
@@ -45,17 +46,23 @@ class FedAttnError(RuntimeError):
 
 
 _lib = None
+_nat = None  # csrc/binding.cpp, bound to the loaded library
 
 
 def load():
     """Load libfedattn.so (built by paper_2511_02647_amd.build.build)."""
-    global _lib
+    global _lib, _nat
     if _lib is not None:
         return _lib
     if not os.path.exists(LIB_PATH):
         raise RuntimeError("%s not found: build it with `python -m paper_2511_02647_amd.build` "
                            "(there is no fallback path)" % LIB_PATH)
     lib = ctypes.CDLL(LIB_PATH)
+    try:
+        from . import _native
+    except ImportError as e:
+        raise RuntimeError("the native binding is missing or does not load (%s): build it with "
+                           "`python -m paper_2511_02647_amd.build`" % e) from e
     i32, i64, vp, sz = ctypes.c_int32, ctypes.c_int64, ctypes.c_void_p, ctypes.c_size_t
     pp = ctypes.POINTER(fedattn_params)
     lib.fedattn_is_sync_block.argtypes = [i32, i32]
@@ -95,8 +102,16 @@ def load():
     lib.fedattn_probe_mfma.restype = i64
     lib.fedattn_last_error.restype = ctypes.c_char_p
     lib.fedattn_version.restype = ctypes.c_char_p
-    _lib = lib
+    _native.bind({name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in EXPORTS}, _host_i32,
+                 torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice)
+    _lib, _nat = lib, _native
     return lib
+
+
+def _calls():
+    if _nat is None:
+        load()
+    return _nat
 
 
 def make_params(n_participants: int, n_q_heads: int, n_kv_heads: int, head_dim: int,
@@ -155,75 +170,30 @@ def fedattn_prefill(params: fedattn_params, block_idx: int, q: torch.Tensor, k: 
                     v: torch.Tensor, out: torch.Tensor, seg_offsets, keep_chunks: Optional[torch.Tensor] = None,
                     chunk_tokens: int = 0, sync_override: int = -1,
                     workspace: Optional[torch.Tensor] = None, stream=None) -> None:
-    seg = _host_i32(seg_offsets, "seg_offsets")
-    if seg.shape[0] != params.n_participants + 1:
-        raise ValueError("seg_offsets must have n_participants + 1 entries")
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(load().fedattn_prefill(ctypes.byref(params), int(block_idx), _dev(q, "q"), _dev(k, "k"),
-                                  _dev(v, "v"), _dev(out, "out"), seg.ctypes.data_as(ctypes.c_void_p),
-                                  _dev(keep_chunks, "keep_chunks"), int(chunk_tokens), int(sync_override),
-                                  _dev(workspace, "workspace"), ws_bytes, _stream(stream)))
-
-
-def _local_ptrs(local: Sequence[Optional[torch.Tensor]], n: int, name: str):
-    arr = (ctypes.c_void_p * n)()
-    for i in range(n):
-        t = local[i]
-        if t is None or t.numel() == 0:
-            arr[i] = None
-        else:
-            if not (t.is_cuda and t.is_contiguous()):
-                raise TypeError("%s[%d] must be a contiguous device tensor" % (name, i))
-            arr[i] = t.data_ptr()
-    return arr
+    _check(_calls().prefill(params, block_idx, q, k, v, out, seg_offsets, keep_chunks, chunk_tokens, sync_override,
+                             workspace, stream))
 
 
 def fedattn_prefill_sync_local_kv(params: fedattn_params, q: torch.Tensor, k_local: Sequence[Optional[torch.Tensor]],
                                   v_local: Sequence[Optional[torch.Tensor]], out: torch.Tensor, seg_offsets,
                                   keep_chunks: Optional[torch.Tensor] = None, chunk_tokens: int = 0,
                                   workspace: Optional[torch.Tensor] = None, stream=None) -> None:
-    seg = _host_i32(seg_offsets, "seg_offsets")
-    n = params.n_participants
-    if seg.shape[0] != n + 1 or len(k_local) != n or len(v_local) != n:
-        raise ValueError("k_local / v_local / seg_offsets have the wrong length")
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(load().fedattn_prefill_sync_local_kv(ctypes.byref(params), _dev(q, "q"), _local_ptrs(k_local, n, "k_local"),
-                                                _local_ptrs(v_local, n, "v_local"), _dev(out, "out"),
-                                                seg.ctypes.data_as(ctypes.c_void_p), _dev(keep_chunks, "keep_chunks"),
-                                                int(chunk_tokens), _dev(workspace, "workspace"), ws_bytes,
-                                                _stream(stream)))
+    _check(_calls().prefill_sync_local_kv(params, q, k_local, v_local, out, seg_offsets, keep_chunks, chunk_tokens,
+                                           workspace, stream))
 
 
 def fedattn_prefill_blocks(params: fedattn_params, block_idx0: int, n_blocks: int, q: torch.Tensor,
                            k: torch.Tensor, v: torch.Tensor, out: torch.Tensor, q_block_stride: int,
                            kv_block_stride: int, seg_offsets, stream=None) -> None:
-    seg = _host_i32(seg_offsets, "seg_offsets")
-    if seg.shape[0] != params.n_participants + 1:
-        raise ValueError("seg_offsets must have n_participants + 1 entries")
-    _check(load().fedattn_prefill_blocks(ctypes.byref(params), int(block_idx0), int(n_blocks), _dev(q, "q"),
-                                         _dev(k, "k"), _dev(v, "v"), _dev(out, "out"), int(q_block_stride),
-                                         int(kv_block_stride), seg.ctypes.data_as(ctypes.c_void_p),
-                                         _stream(stream)))
+    _check(_calls().prefill_blocks(params, block_idx0, n_blocks, q, k, v, out, q_block_stride, kv_block_stride,
+                                    seg_offsets, stream))
 
 
 def fedattn_decode(params: fedattn_params, block_idx: int, q: torch.Tensor, k_cache: torch.Tensor,
                    v_cache: torch.Tensor, out: torch.Tensor, seg_offsets, seg_lens, remote_lens=None,
                    sync_override: int = -1, workspace: Optional[torch.Tensor] = None, stream=None) -> None:
-    seg = _host_i32(seg_offsets, "seg_offsets")
-    lens = _host_i32(seg_lens, "seg_lens")
-    if seg.shape[0] != params.n_participants + 1 or lens.shape[0] != params.n_participants:
-        raise ValueError("seg_offsets / seg_lens have the wrong length")
-    rl = None
-    if remote_lens is not None:
-        rl = _host_i32(remote_lens, "remote_lens")
-        if rl.shape[0] != params.n_participants:
-            raise ValueError("remote_lens has the wrong length")
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(load().fedattn_decode(ctypes.byref(params), int(block_idx), _dev(q, "q"), _dev(k_cache, "k_cache"),
-                                 _dev(v_cache, "v_cache"), _dev(out, "out"),
-                                 seg.ctypes.data_as(ctypes.c_void_p), lens.ctypes.data_as(ctypes.c_void_p),
-                                 None if rl is None else rl.ctypes.data_as(ctypes.c_void_p),
-                                 int(sync_override), _dev(workspace, "workspace"), ws_bytes, _stream(stream)))
+    _check(_calls().decode_blocks(params, block_idx, 1, q, k_cache, v_cache, out, 0, 0, seg_offsets, seg_lens,
+                                   remote_lens, sync_override, workspace, stream, False))
 
 
 FEDATTN_STATIC_SCRATCH_BYTES = 16 << 20
@@ -233,20 +203,8 @@ def fedattn_decode_static(params: fedattn_params, block_idx: int, q: torch.Tenso
                           v_cache: torch.Tensor, out: torch.Tensor, seg_offsets, seg_lens, remote_lens=None,
                           sync_override: int = -1, stream=None) -> None:
     """fedattn_decode without a workspace (the library's built-in scratch array; allocates nothing)."""
-    seg = _host_i32(seg_offsets, "seg_offsets")
-    lens = _host_i32(seg_lens, "seg_lens")
-    if seg.shape[0] != params.n_participants + 1 or lens.shape[0] != params.n_participants:
-        raise ValueError("seg_offsets / seg_lens have the wrong length")
-    rl = None
-    if remote_lens is not None:
-        rl = _host_i32(remote_lens, "remote_lens")
-        if rl.shape[0] != params.n_participants:
-            raise ValueError("remote_lens has the wrong length")
-    _check(load().fedattn_decode_static(ctypes.byref(params), int(block_idx), _dev(q, "q"), _dev(k_cache, "k_cache"),
-                                        _dev(v_cache, "v_cache"), _dev(out, "out"),
-                                        seg.ctypes.data_as(ctypes.c_void_p), lens.ctypes.data_as(ctypes.c_void_p),
-                                        None if rl is None else rl.ctypes.data_as(ctypes.c_void_p),
-                                        int(sync_override), _stream(stream)))
+    _check(_calls().decode_static(params, block_idx, q, k_cache, v_cache, out, seg_offsets, seg_lens, remote_lens,
+                                   sync_override, stream))
 
 
 def fedattn_decode_blocks(params: fedattn_params, block_idx0: int, n_blocks: int, q: torch.Tensor,
@@ -254,23 +212,9 @@ def fedattn_decode_blocks(params: fedattn_params, block_idx0: int, n_blocks: int
                           cache_block_stride: int, seg_offsets, seg_lens, remote_lens=None, sync_override: int = -1,
                           workspace: Optional[torch.Tensor] = None, stream=None, fused: bool = False) -> None:
     """fused=True calls fedattn_decode_blocks_fused (blocks of one kind share launches)."""
-    seg = _host_i32(seg_offsets, "seg_offsets")
-    lens = _host_i32(seg_lens, "seg_lens")
-    if seg.shape[0] != params.n_participants + 1 or lens.shape[0] != params.n_participants:
-        raise ValueError("seg_offsets / seg_lens have the wrong length")
-    rl = None
-    if remote_lens is not None:
-        rl = _host_i32(remote_lens, "remote_lens")
-        if rl.shape[0] != params.n_participants:
-            raise ValueError("remote_lens has the wrong length")
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    fn = load().fedattn_decode_blocks_fused if fused else load().fedattn_decode_blocks
-    _check(fn(ctypes.byref(params), int(block_idx0), int(n_blocks), _dev(q, "q"),
-              _dev(k_cache, "k_cache"), _dev(v_cache, "v_cache"), _dev(out, "out"),
-              int(q_block_stride), int(cache_block_stride),
-              seg.ctypes.data_as(ctypes.c_void_p), lens.ctypes.data_as(ctypes.c_void_p),
-              None if rl is None else rl.ctypes.data_as(ctypes.c_void_p),
-              int(sync_override), _dev(workspace, "workspace"), ws_bytes, _stream(stream)))
+    _check(_calls().decode_blocks(params, block_idx0, n_blocks, q, k_cache, v_cache, out, q_block_stride,
+                                   cache_block_stride, seg_offsets, seg_lens, remote_lens, sync_override, workspace,
+                                   stream, fused))
 
 
 def fedattn_decode_blocks_fused(*args, **kwargs) -> None:
@@ -281,20 +225,14 @@ def fedattn_decode_blocks_fused(*args, **kwargs) -> None:
 def fedattn_aggregate_kv(params: fedattn_params, k_local: Sequence[Optional[torch.Tensor]],
                          v_local: Sequence[Optional[torch.Tensor]], seg_offsets, k_global: torch.Tensor,
                          v_global: torch.Tensor, stream=None) -> None:
-    seg = _host_i32(seg_offsets, "seg_offsets")
-    n = params.n_participants
-    if seg.shape[0] != n + 1 or len(k_local) != n or len(v_local) != n:
-        raise ValueError("k_local / v_local / seg_offsets have the wrong length")
-    kp, vp = _local_ptrs(k_local, n, "k_local"), _local_ptrs(v_local, n, "v_local")
-    _check(load().fedattn_aggregate_kv(ctypes.byref(params), kp, vp, seg.ctypes.data_as(ctypes.c_void_p),
-                                       _dev(k_global, "k_global"), _dev(v_global, "v_global"), _stream(stream)))
+    _check(_calls().aggregate_kv(params, k_local, v_local, seg_offsets, k_global, v_global, stream))
 
 
 def fedattn_rmsnorm(x: torch.Tensor, out: torch.Tensor, eps: float = 1e-6, stream=None) -> None:
     """x fp32 [rows, d_model] -> out bf16 [rows, d_model]."""
     if x.dtype != torch.float32 or out.dtype != torch.bfloat16 or x.shape != out.shape or x.dim() != 2:
         raise TypeError("rmsnorm: x fp32 [rows, d_model], out bf16 of the same shape")
-    _check(load().fedattn_rmsnorm(_dev(x, "x"), _dev(out, "out"), x.shape[0], x.shape[1], float(eps), _stream(stream)))
+    _check(_calls().rmsnorm(x, None, out, x.shape[0], x.shape[1], eps, stream))
 
 
 def fedattn_rope_split_qkv(qkv: torch.Tensor, pos: Optional[torch.Tensor], q: torch.Tensor, k: torch.Tensor,
@@ -308,8 +246,7 @@ def fedattn_rope_split_qkv(qkv: torch.Tensor, pos: Optional[torch.Tensor], q: to
         raise TypeError("rope: qkv, q, k, v must be bf16")
     if pos is not None and (pos.dtype != torch.int32 or pos.shape != (T,)):
         raise TypeError("rope: pos must be int32 [tokens]")
-    _check(load().fedattn_rope_split_qkv(_dev(qkv, "qkv"), _dev(pos, "pos"), _dev(q, "q"), _dev(k, "k"), _dev(v, "v"),
-                                         T, Hq, Hkv, D, float(theta), _stream(stream)))
+    _check(_calls().rope_split_qkv(qkv, pos, q, k, v, T, Hq, Hkv, D, theta, stream))
 
 
 def fedattn_swiglu(gate_up: torch.Tensor, out: torch.Tensor, stream=None) -> None:
@@ -318,14 +255,14 @@ def fedattn_swiglu(gate_up: torch.Tensor, out: torch.Tensor, stream=None) -> Non
         raise ValueError("swiglu: gate_up [rows, 2 F], out [rows, F]")
     if gate_up.dtype != torch.bfloat16 or out.dtype != torch.bfloat16:
         raise TypeError("swiglu: bf16 tensors")
-    _check(load().fedattn_swiglu(_dev(gate_up, "gate_up"), _dev(out, "out"), out.shape[0], out.shape[1], _stream(stream)))
+    _check(_calls().swiglu(gate_up, out, out.shape[0], out.shape[1], stream))
 
 
 def fedattn_residual_add(x: torch.Tensor, y: torch.Tensor, stream=None) -> None:
     """x fp32 += y bf16, same shape."""
     if x.dtype != torch.float32 or y.dtype != torch.bfloat16 or x.shape != y.shape:
         raise TypeError("residual_add: x fp32, y bf16, same shape")
-    _check(load().fedattn_residual_add(_dev(x, "x"), _dev(y, "y"), x.numel(), _stream(stream)))
+    _check(_calls().residual_add(x, y, x.numel(), stream))
 
 
 def fedattn_residual_add_rmsnorm(x: torch.Tensor, y: torch.Tensor, out: torch.Tensor, eps: float = 1e-6, stream=None) -> None:
@@ -333,8 +270,7 @@ def fedattn_residual_add_rmsnorm(x: torch.Tensor, y: torch.Tensor, out: torch.Te
     if x.dtype != torch.float32 or y.dtype != torch.bfloat16 or out.dtype != torch.bfloat16 or x.dim() != 2 \
             or x.shape != y.shape or x.shape != out.shape:
         raise TypeError("residual_add_rmsnorm: x fp32, y and out bf16, all [rows, d_model]")
-    _check(load().fedattn_residual_add_rmsnorm(_dev(x, "x"), _dev(y, "y"), _dev(out, "out"), x.shape[0], x.shape[1],
-                                               float(eps), _stream(stream)))
+    _check(_calls().rmsnorm(x, y, out, x.shape[0], x.shape[1], eps, stream))
 
 
 def fedattn_probe_stream(src: torch.Tensor, pattern: int, sink: torch.Tensor, stream=None) -> int:

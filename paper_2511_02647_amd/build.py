@@ -1,14 +1,16 @@
-"""Builds libfedattn.so (HIP, gfx950 only) in-tree with hipcc."""
+"""Builds libfedattn.so (HIP, gfx950 only) with hipcc and its Python binding _native.so with g++, in-tree."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libfedattn.so")
+NATIVE = os.path.join(HERE, "_native.so")
 SOURCES = ["api.hip", "prefill_generic.hip", "prefill_mfma.hip", "prefill_f32.hip", "decode.hip", "decode_f32.hip", "aggregate.hip", "block_ops.hip", "probes.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc", "-fvisibility=hidden", "-Wno-inline-asm",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -23,9 +25,9 @@ def hipcc() -> str:
 
 
 def needs_build() -> bool:
-    if not os.path.exists(LIB):
+    if not (os.path.exists(LIB) and os.path.exists(NATIVE)):
         return True
-    t = os.path.getmtime(LIB)
+    t = min(os.path.getmtime(LIB), os.path.getmtime(NATIVE))
     deps = [os.path.join(CSRC, f) for f in os.listdir(CSRC)] + [os.path.join(ROOT, "include", "fedattn.h")]
     return any(os.path.getmtime(d) > t for d in deps)
 
@@ -45,16 +47,22 @@ def build(force: bool = True, verbose: bool = False, extra_flags=()) -> str:
             print(" ".join(cmd), flush=True)
         procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
         objs.append(obj)
+    tmp_native = NATIVE + ".tmp%d" % os.getpid()
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-Wall", "-fPIC", "-shared", "-fvisibility=hidden",
+           "-I" + os.path.join(ROOT, "include"), "-I" + sysconfig.get_paths()["include"],
+           os.path.join(CSRC, "binding.cpp"), "-o", tmp_native]
+    procs.append(("binding.cpp", subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
     for src, p in procs:
         out, _ = p.communicate()
         out = "\n".join(l for l in out.splitlines() if "packed-fp32-ops" not in l)
         if p.returncode != 0:
-            raise RuntimeError("hipcc failed on %s:\n%s" % (src, out))
+            raise RuntimeError("the compiler failed on %s:\n%s" % (src, out))
         if verbose and out.strip():
             print(out)
     tmp = LIB + ".tmp%d" % os.getpid()
     subprocess.check_call([hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs)
     os.replace(tmp, LIB)
+    os.replace(tmp_native, NATIVE)
     return LIB
 
 
