@@ -11,7 +11,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libfedattn.so")
 NATIVE = os.path.join(HERE, "_native.so")
-SOURCES = ["api.hip", "prefill_generic.hip", "prefill_mfma.hip", "prefill_f32.hip", "decode.hip", "decode_f32.hip", "aggregate.hip", "block_ops.hip", "probes.hip"]
+SOURCES = ["api.hip", "prefill_generic.hip", "prefill_mfma.hip", "prefill_split.hip", "prefill_f32.hip", "decode.hip", "decode_f32.hip", "aggregate.hip", "block_ops.hip", "probes.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc", "-fvisibility=hidden", "-Wno-inline-asm",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-I" + os.path.join(ROOT, "include"), "-I" + CSRC]

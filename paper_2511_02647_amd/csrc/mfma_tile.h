@@ -106,14 +106,16 @@ __device__ inline float sum_over_kgroups(float x) {
 // VSWZ selects the chunk swizzle of V tiles: the transposing reads of the 32x32x16
 // product touch 4 rows x 4 chunks per 32 lanes (VSWZ = 1), those of the
 // 16x16x16 product 8 rows x 2 chunks (VSWZ = 0).
-// NW = wavefronts that load a tile together (4, or 8 for 8-wave workgroups sharing one tile).
-template <int D, int VSWZ, int NW = 4>
+// NW = wavefronts that load a tile together (4, 8 for 8-wave workgroups sharing one tile, 1 for a
+// wavefront with tiles of its own), ROWS = KV rows of a tile.
+template <int D, int VSWZ, int NW = 4, int ROWS = kKvTile>
 struct KvTile {
   static constexpr int KSTEPS = D / 16;         // MFMA k-steps of S^T = K Q^T
   static constexpr int DT = D / 32;             // 32-row tiles of O^T along head_dim
   static constexpr int CPR = D / 8;             // 16-byte chunks per K/V row
   static constexpr int ROWB = D * 2;            // LDS bytes per K/V row (unpadded; chunks XOR-swizzled)
-  static constexpr int TILEB = kKvTile * ROWB;  // one K or V stage
+  static constexpr int TILEB = ROWS * ROWB;     // one K or V stage
+  static constexpr int AA = ROWS / 32;          // 32-row halves of a tile's scores
   static constexpr int NINST = TILEB / 1024;    // direct-to-LDS load instructions per tile (1 KB each)
   static constexpr int IPW = NINST / NW;        // per wavefront
   static_assert(NINST % NW == 0, "tile loads must divide evenly among the wavefronts");
@@ -187,7 +189,7 @@ struct KvTile {
   // tile's valid length re-read its last valid row (they are masked out of the scores).
   template <bool IS_V, bool STREAM = false>
   __device__ __attribute__((always_inline)) void dma(const uint16_t* tile_base, uint32_t lds_stage, int len) const {
-    if (len == kKvTile) {
+    if (len == ROWS) {
 #pragma unroll
       for (int i = 0; i < IPW; ++i)
         lds_dma_16<STREAM>(tile_base, IS_V ? dma_voff[i] : dma_koff[i], lds_stage + (wave * IPW + i) * 1024);
@@ -207,58 +209,60 @@ struct KvTile {
   // `init` is what the accumulation starts from: zeros, or minus the reference value of the
   // softmax in every element (the scores then come out relative to it at no cost).
   __device__ __attribute__((always_inline)) void scores(lds_cptr lds0, int kb, const bf16x8 (&qf)[KSTEPS],
-                                                        const f32x16& init, f32x16 (&s)[2]) const {
-    s[0] = init;
-    s[1] = init;
-    bf16x8 kf[KSTEPS][2];
+                                                        const f32x16& init, f32x16 (&s)[AA]) const {
+#pragma unroll
+    for (int aa = 0; aa < AA; ++aa) s[aa] = init;
+    bf16x8 kf[KSTEPS][AA];
 #pragma unroll
     for (int st = 0; st < KSTEPS; ++st) {
       const lds_cptr ptr = lds0 + (k_off[st] + kb);
 #pragma unroll
-      for (int aa = 0; aa < 2; ++aa)
+      for (int aa = 0; aa < AA; ++aa)
         kf[st][aa] = __builtin_bit_cast(
             bf16x8, *reinterpret_cast<const __attribute__((address_space(3))) u32x4*>(ptr + 32 * aa * ROWB));
     }
 #pragma unroll
     for (int st = 0; st < KSTEPS; ++st)
 #pragma unroll
-      for (int aa = 0; aa < 2; ++aa) s[aa] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[st][aa], qf[st], s[aa], 0, 0, 0);
+      for (int aa = 0; aa < AA; ++aa) s[aa] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[st][aa], qf[st], s[aa], 0, 0, 0);
     constexpr int kLook = KSTEPS > 2 ? 2 : KSTEPS - 1;
-    __builtin_amdgcn_sched_group_barrier(FEDATTN_SGB_DS_READ, 2 * kLook, 0);
+    __builtin_amdgcn_sched_group_barrier(FEDATTN_SGB_DS_READ, AA * kLook, 0);
 #pragma unroll
     for (int st = 0; st < KSTEPS - kLook; ++st) {
-      __builtin_amdgcn_sched_group_barrier(FEDATTN_SGB_MFMA, 2, 0);
-      __builtin_amdgcn_sched_group_barrier(FEDATTN_SGB_DS_READ, 2, 0);
+      __builtin_amdgcn_sched_group_barrier(FEDATTN_SGB_MFMA, AA, 0);
+      __builtin_amdgcn_sched_group_barrier(FEDATTN_SGB_DS_READ, AA, 0);
     }
 #pragma unroll
     for (int st = 0; st < kLook; ++st) {
-      __builtin_amdgcn_sched_group_barrier(FEDATTN_SGB_MFMA, 2, 0);
+      __builtin_amdgcn_sched_group_barrier(FEDATTN_SGB_MFMA, AA, 0);
     }
+  }
+
+  // A operand of O^T += V^T P^T for k-step kk and head-dimension slice dt, from the V stage at LDS byte offset vb.
+  __device__ __attribute__((always_inline)) bf16x8 v_operand(lds_cptr lds0, int vb, int kk, int dt) const {
+    const lds_cptr ptr = lds0 + (v_off[dt] + vb) + 16 * kk * ROWB;
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)ptr);
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(ptr + 8 * ROWB));
+    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
   }
 
   // O^T[d][q] += V^T P^T from the V stage at LDS byte offset vb; k-step kk covers tile
   // rows 16 kk + {4hf..4hf+3, 8+4hf..8+4hf+3}, the order in which P^T sits in the
   // lane's registers.  k-step major, so that the first MFMAs need only the first
   // quarter of P.
-  __device__ __attribute__((always_inline)) void pv(lds_cptr lds0, int vb, const bf16x8 (&pb)[4],
+  __device__ __attribute__((always_inline)) void pv(lds_cptr lds0, int vb, const bf16x8 (&pb)[2 * AA],
                                                     f32x16 (&o)[DT]) const {
-    bf16x8 vf[4][DT];
+    bf16x8 vf[2 * AA][DT];
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk)
+    for (int kk = 0; kk < 2 * AA; ++kk)
 #pragma unroll
-      for (int dt = 0; dt < DT; ++dt) {
-        const lds_cptr ptr = lds0 + (v_off[dt] + vb) + 16 * kk * ROWB;
-        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)ptr);
-        const s16x4 hi =
-            __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(ptr + 8 * ROWB));
-        vf[kk][dt] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-      }
+      for (int dt = 0; dt < DT; ++dt) vf[kk][dt] = v_operand(lds0, vb, kk, dt);
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk)
+    for (int kk = 0; kk < 2 * AA; ++kk)
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt) o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[kk][dt], pb[kk], o[dt], 0, 0, 0);
-    constexpr int kLook = 4;    // MFMAs of lookahead
-    constexpr int NM = 4 * DT;  // MFMAs in this product
+        constexpr int NM = 2 * AA * DT;         // MFMAs in this product
+    constexpr int kLook = NM > 4 ? 4 : NM;  // MFMAs of lookahead
     __builtin_amdgcn_sched_group_barrier(FEDATTN_SGB_DS_READ, 2 * kLook, 0);
 #pragma unroll
     for (int i = 0; i < NM - kLook; ++i) {
@@ -270,17 +274,37 @@ struct KvTile {
 
   // The same with fp32 weights, still on bf16 MFMA: every weight enters as the three bf16 parts
   // whose sum it is, so products and sums are those of fp32 arithmetic.
-  __device__ __attribute__((always_inline)) void pv_f32(lds_cptr lds0, int vb, const f32x16 (&s)[2], f32x16 (&o)[DT]) const;
+  __device__ __attribute__((always_inline)) void pv_f32(lds_cptr lds0, int vb, const f32x16 (&s)[AA], f32x16 (&o)[DT]) const;
 };
 
 // Masks the tile rows a lane's query may not see: rows [lim, 64) of the tile.
-__device__ __attribute__((always_inline)) inline void mask_scores(f32x16 (&s)[2], int lim, int hf) {
+template <int AA>
+__device__ __attribute__((always_inline)) inline void mask_scores(f32x16 (&s)[AA], int lim, int hf) {
   const int limh = lim - 4 * hf;
 #pragma unroll
-  for (int aa = 0; aa < 2; ++aa)
+  for (int aa = 0; aa < AA; ++aa)
 #pragma unroll
     for (int e = 0; e < 16; ++e)
       if (32 * aa + 8 * (e >> 2) + (e & 3) >= limh) s[aa][e] = -INFINITY;
+}
+
+// Maximum of a query's scores in this tile (both halves of the wavefront).
+template <int AA>
+__device__ __attribute__((always_inline)) inline float row_max(const f32x16 (&s)[AA]) {
+  float mx0 = s[0][0], mx1 = s[0][1];
+#pragma unroll
+  for (int aa = 1; aa < AA; ++aa) {
+    mx0 = fmaxf(mx0, s[aa][0]);
+    mx1 = fmaxf(mx1, s[aa][1]);
+  }
+#pragma unroll
+  for (int e = 2; e < 16; e += 2)
+#pragma unroll
+    for (int aa = 0; aa < AA; ++aa) {
+      mx0 = fmaxf(mx0, s[aa][e]);
+      mx1 = fmaxf(mx1, s[aa][e + 1]);
+    }
+  return max_across_halves(fmaxf(mx0, mx1));
 }
 
 // Online softmax in the log2 domain on the scores of one tile, in two parts so that
@@ -289,17 +313,10 @@ __device__ __attribute__((always_inline)) inline void mask_scores(f32x16 (&s)[2]
 // rescaled only when some row's maximum has grown by more than the threshold; exact,
 // because numerator and denominator of the final division refer to the same value).
 // Returns the reference value the exponentials of this tile use.
-template <int DT>
-__device__ __attribute__((always_inline)) inline float softmax_max(const f32x16 (&s)[2], float sc, float& m_run,
+template <int DT, int AA>
+__device__ __attribute__((always_inline)) inline float softmax_max(const f32x16 (&s)[AA], float sc, float& m_run,
                                                                    float& l_run, f32x16 (&o)[DT]) {
-  float mx0 = fmaxf(s[0][0], s[1][0]);
-  float mx1 = fmaxf(s[0][1], s[1][1]);
-#pragma unroll
-  for (int e = 2; e < 16; e += 2) {
-    mx0 = fmaxf(fmaxf(mx0, s[0][e]), s[1][e]);
-    mx1 = fmaxf(fmaxf(mx1, s[0][e + 1]), s[1][e + 1]);
-  }
-  const float m_cand = max_across_halves(fmaxf(mx0, mx1)) * sc;
+  const float m_cand = row_max(s) * sc;
   if (__builtin_amdgcn_ballot_w64(m_cand > m_run + kRescaleThreshold) != 0) {
     const float m_new = fmaxf(m_run, m_cand);
     const float m_ref = (m_new == -INFINITY) ? 0.f : m_new;
@@ -316,12 +333,13 @@ __device__ __attribute__((always_inline)) inline float softmax_max(const f32x16 
 // in bf16 in pb.  The row sum is taken over the bf16 weights, the ones the second product
 // uses (numerator and denominator of the softmax then carry the same rounding), two at a
 // time with v_dot2c_f32_bf16 against (1, 1): half the additions of a sum over fp32 weights.
-__device__ __attribute__((always_inline)) inline void softmax_exp(const f32x16 (&s)[2], float sc, float m_use,
-                                                                   float& l_run, bf16x8 (&pb)[4]) {
+template <int AA>
+__device__ __attribute__((always_inline)) inline void softmax_exp(const f32x16 (&s)[AA], float sc, float m_use,
+                                                                   float& l_run, bf16x8 (&pb)[2 * AA]) {
   const bf16x2 ones = {(bf16_t)1.0f, (bf16_t)1.0f};
   float ps0 = 0.f, ps1 = 0.f;
 #pragma unroll
-  for (int aa = 0; aa < 2; ++aa)
+  for (int aa = 0; aa < AA; ++aa)
 #pragma unroll
     for (int e = 0; e < 16; e += 4) {
       const float p0 = __builtin_amdgcn_exp2f(fmaf(s[aa][e], sc, -m_use));
@@ -352,10 +370,19 @@ __device__ __attribute__((always_inline)) inline void softmax_exp(const f32x16 (
 // there, accumulators and row sums rescaled, the scores shifted, neg_ref refilled and the
 // exponentials taken again.  A first tile (no reference yet) starts with the maxima.  With a reference that lags the
 // running maximum by at most the threshold every weight stays <= 2^threshold, as before.
-template <int DT>
-__device__ __attribute__((always_inline)) inline void softmax_step_rel(f32x16 (&s)[2], float& m_run, float& l_run,
-                                                                        f32x16 (&o)[DT], f32x16& neg_ref,
-                                                                        bf16x8 (&pb)[4]) {
+// neg_ref may be a block of 16 equal values, to start the accumulation from as it is, or one value.
+__device__ inline float ref_value(const f32x16& r) { return r[0]; }
+__device__ inline float ref_value(float r) { return r; }
+__device__ __attribute__((always_inline)) inline void set_ref(f32x16& r, float x) {
+#pragma unroll
+  for (int e = 0; e < 16; ++e) r[e] = x;
+}
+__device__ inline void set_ref(float& r, float x) { r = x; }
+
+template <int DT, int AA, typename Ref>
+__device__ __attribute__((always_inline)) inline void softmax_step_rel(f32x16 (&s)[AA], float& m_run, float& l_run,
+                                                                        f32x16 (&o)[DT], Ref& neg_ref,
+                                                                        bf16x8 (&pb)[2 * AA]) {
   const bf16x2 ones = {(bf16_t)1.0f, (bf16_t)1.0f};
   const float limit = __builtin_amdgcn_exp2f(kRescaleThreshold);
   float ps0, ps1;
@@ -363,15 +390,8 @@ __device__ __attribute__((always_inline)) inline void softmax_step_rel(f32x16 (&
   bool move = __builtin_amdgcn_ballot_w64(m_run == -INFINITY) != 0;  // a first tile: straight to the maxima
   while (true) {
     if (move) {
-      float mx0 = fmaxf(s[0][0], s[1][0]);
-      float mx1 = fmaxf(s[0][1], s[1][1]);
-#pragma unroll
-      for (int e = 2; e < 16; e += 2) {
-        mx0 = fmaxf(fmaxf(mx0, s[0][e]), s[1][e]);
-        mx1 = fmaxf(fmaxf(mx1, s[0][e + 1]), s[1][e + 1]);
-      }
-      const float r = max_across_halves(fmaxf(mx0, mx1));  // row maximum relative to the reference
-      const float ref_old = -neg_ref[0];
+      const float r = row_max(s);  // row maximum relative to the reference
+      const float ref_old = -ref_value(neg_ref);
       const float m_new = fmaxf(m_run, r + ref_old);
       const float ref_new = (m_new == -INFINITY) ? 0.f : m_new;
       const float alpha = __builtin_amdgcn_exp2f(m_run - ref_new);  // exp2(-inf) = 0 at the first tile
@@ -381,17 +401,16 @@ __device__ __attribute__((always_inline)) inline void softmax_step_rel(f32x16 (&
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt) o[dt] *= alpha;
 #pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        s[0][e] -= shift;
-        s[1][e] -= shift;
-        neg_ref[e] = -ref_new;
-      }
+      for (int e = 0; e < 16; ++e)
+#pragma unroll
+        for (int aa = 0; aa < AA; ++aa) s[aa][e] -= shift;
+      set_ref(neg_ref, -ref_new);
       moved = true;
     }
     ps0 = 0.f;
     ps1 = 0.f;
 #pragma unroll
-    for (int aa = 0; aa < 2; ++aa)
+    for (int aa = 0; aa < AA; ++aa)
 #pragma unroll
       for (int e = 0; e < 16; e += 4) {
         const bf16x2 q0 = {(bf16_t)__builtin_amdgcn_exp2f(s[aa][e]), (bf16_t)__builtin_amdgcn_exp2f(s[aa][e + 1])};
@@ -411,10 +430,11 @@ __device__ __attribute__((always_inline)) inline void softmax_step_rel(f32x16 (&
 }
 
 // Part 2 for a second product at full precision: the exponentials stay in s as fp32 weights.
-__device__ __attribute__((always_inline)) inline void softmax_exp_f32(f32x16 (&s)[2], float sc, float m_use, float& l_run) {
+template <int AA>
+__device__ __attribute__((always_inline)) inline void softmax_exp_f32(f32x16 (&s)[AA], float sc, float m_use, float& l_run) {
   float ps[2] = {0.f, 0.f};
 #pragma unroll
-  for (int aa = 0; aa < 2; ++aa)
+  for (int aa = 0; aa < AA; ++aa)
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
       s[aa][e] = __builtin_amdgcn_exp2f(fmaf(s[aa][e], sc, -m_use));
@@ -442,11 +462,11 @@ __device__ __attribute__((always_inline)) inline void split_weights(const float 
   }
 }
 
-template <int D, int VSWZ, int NW>
-__device__ __attribute__((always_inline)) inline void KvTile<D, VSWZ, NW>::pv_f32(lds_cptr lds0, int vb, const f32x16 (&s)[2],
-                                                                                  f32x16 (&o)[DT]) const {
+template <int D, int VSWZ, int NW, int ROWS>
+__device__ __attribute__((always_inline)) inline void KvTile<D, VSWZ, NW, ROWS>::pv_f32(lds_cptr lds0, int vb, const f32x16 (&s)[AA],
+                    f32x16 (&o)[DT]) const {
 #pragma unroll
-  for (int kk = 0; kk < 4; ++kk) {
+  for (int kk = 0; kk < 2 * AA; ++kk) {
     float p[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) p[e] = s[kk >> 1][8 * (kk & 1) + e];
@@ -454,12 +474,7 @@ __device__ __attribute__((always_inline)) inline void KvTile<D, VSWZ, NW>::pv_f3
     split_weights(p, part);
     bf16x8 vf[DT];
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt) {
-      const lds_cptr ptr = lds0 + (v_off[dt] + vb) + 16 * kk * ROWB;
-      const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)ptr);
-      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(ptr + 8 * ROWB));
-      vf[dt] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-    }
+    for (int dt = 0; dt < DT; ++dt) vf[dt] = v_operand(lds0, vb, kk, dt);
 #pragma unroll
     for (int t = 2; t >= 0; --t)
 #pragma unroll
@@ -468,10 +483,10 @@ __device__ __attribute__((always_inline)) inline void KvTile<D, VSWZ, NW>::pv_f3
 }
 
 // Both parts back to back.
-template <int DT>
-__device__ __attribute__((always_inline)) inline void softmax_step(const f32x16 (&s)[2], float sc, float& m_run,
-                                                                    float& l_run, f32x16 (&o)[DT], bf16x8 (&pb)[4]) {
-  const float m_use = softmax_max<DT>(s, sc, m_run, l_run, o);
+template <int DT, int AA>
+__device__ __attribute__((always_inline)) inline void softmax_step(const f32x16 (&s)[AA], float sc, float& m_run,
+                                                                    float& l_run, f32x16 (&o)[DT], bf16x8 (&pb)[2 * AA]) {
+  const float m_use = softmax_max(s, sc, m_run, l_run, o);
   softmax_exp(s, sc, m_use, l_run, pb);
 }
 

@@ -20,6 +20,8 @@
 //                 segment up to the diagonal.
 // Tiles entirely above the diagonal or in other participants' segments of a local
 // block are never visited; only diagonal and ragged tiles apply an element mask.
+#include <math.h>
+
 #include <algorithm>
 #include <type_traits>
 
@@ -31,10 +33,12 @@ namespace fedattn {
 
 namespace {
 
-// NG = 1: 4 wavefronts per workgroup (two workgroups share a CU when the grid is large
+// NG = 1: 4 wavefronts per workgroup (two or three workgroups share a CU when the grid is large
 // enough, and one's matrix work overlaps the other's softmax: inside a wavefront the softmax
 // sits between the two products that depend on it, and spreading it under the MFMAs of the
-// neighbouring tiles instead measured slower).  NG = 2, for grids that would
+// neighbouring tiles instead measured slower).  Three wavefronts per SIMD where the registers allow
+// it (head dimension up to 64: 8 x 2000 tokens, 32/8 heads, sync 1132 -> 1032 us against two).
+// NG = 2, for grids that would
 // leave one workgroup per CU: 8 wavefronts = two groups of 4 on the same query rows;
 // group g takes the KV tiles j with j mod 2 == g through its own LDS stages and the two
 // partial results are merged at the end (split-KV inside the workgroup).
@@ -50,7 +54,7 @@ namespace {
 // 590 useful TFLOP/s at head dimension 96 (1160 at 128 without EXACT).  A local and a sync block of
 // 4 x 100..900 tokens, 8/2 heads of 96: 1794 us on the wavefront-per-row kernel, 72 us here.
 template <int DP, int NG, bool FOLD, bool EXACT>
-__global__ __launch_bounds__(256 * NG, DP > 128 ? 1 : 2) void prefill_mfma_kernel(PrefillArgs a) {
+__global__ __launch_bounds__(256 * NG, DP > 128 ? 1 : DP > 64 ? 2 : 3) void prefill_mfma_kernel(PrefillArgs a) {
   using TL = KvTile<DP, 1>;
   const int D = EXACT ? a.D : DP;
   constexpr int KSTEPS = TL::KSTEPS, DT = TL::DT, TILEB = TL::TILEB;
@@ -95,8 +99,8 @@ __global__ __launch_bounds__(256 * NG, DP > 128 ? 1 : 2) void prefill_mfma_kerne
   const bool sparse = is_sync && a.keep_chunks != nullptr;
 
   // Causal work grows along the sequence (sync block) or along each segment (local
-  // block); a workgroup takes a heavy query tile and then its light mirror image so
-  // that all workgroups carry the same load.
+  // block); a workgroup takes one query tile, dispatched in an order that the host lays out or
+  // longest walks first, or a heavy tile and then its light mirror image.
   int tile_a = -1, tile_b = -1;  // heavy tile, then its light partner (or none)
   if (a.n_ordered > 0) {
     // small causal launch: one query tile per workgroup, in the order the host laid out
@@ -109,9 +113,9 @@ __global__ __launch_bounds__(256 * NG, DP > 128 ? 1 : 2) void prefill_mfma_kerne
     if (p >= T) return;
     tile_a = T - 1 - p;
   } else if (a.one_tile_heavy_first) {
-    // A launch of several rounds of workgroups: equal-sized pairs would all finish together and
-    // leave the last round partly empty.  One tile per workgroup instead, dispatched heaviest
-    // first, so that the short walks at the end of the list fill the gaps.  Sync block: work
+    // One tile per workgroup, dispatched heaviest first: in a launch of several rounds of workgroups
+    // the short walks at the end of the list fill the gaps that equal-sized pairs would leave in
+    // the last round, in a launch of one round each walk is half a pair's.  Sync block: work
     // grows with the position in the sequence.  Local block: the participants in order of
     // decreasing length, each one's tiles from its last to its first.
     if (p >= T) return;
@@ -301,13 +305,13 @@ __global__ __launch_bounds__(256 * NG, DP > 128 ? 1 : 2) void prefill_mfma_kerne
         }
 
         if constexpr (EXACT) {
-          const float m_use = softmax_max<DT>(s_cur, sc, m_run, l_run, o);
+          const float m_use = softmax_max(s_cur, sc, m_run, l_run, o);
           softmax_exp_f32(s_cur, sc, m_use, l_run);
           tile_io.pv_f32(lds0, 2 * TILEB + st_cur, s_cur, o);
         } else {
           bf16x8 pb[4];
-          if constexpr (FOLD) softmax_step_rel<DT>(s_cur, m_run, l_run, o, neg_ref, pb);
-          else softmax_step<DT>(s_cur, sc, m_run, l_run, o, pb);
+          if constexpr (FOLD) softmax_step_rel(s_cur, m_run, l_run, o, neg_ref, pb);
+          else softmax_step(s_cur, sc, m_run, l_run, o, pb);
           tile_io.pv(lds0, 2 * TILEB + st_cur, pb, o);
         }
       }
@@ -555,6 +559,105 @@ hipError_t launch_prefill_exact(const PrefillArgs& a, bool wide, dim3 grid, hipS
   return launch_prefill_mfma_t<DP, 1, false, true>(a, grid, s);
 }
 
+namespace {
+
+// ---- which of the launches a block takes ------------------------------------------------------
+// kFour: 4-wavefront workgroups, one query tile each, several per CU.  kEight: 8-wavefront workgroups
+// whose two groups share out the KV tiles of one query tile; kEightPairs: of a heavy tile and then its
+// light mirror image.  kSplit: one head's 32 rows per workgroup, keys shared out among its 8 wavefronts
+// (prefill_split.hip).  From left to right a launch has more and shorter walks for the same work and pays
+// more for each: the right one depends on how far the block fills the chip, so their times are estimated.
+enum Plan { kFour, kEight, kEightPairs, kSplit };
+
+// Measured on one MI355X, microseconds: an iteration of one workgroup alone on its CU and as its share
+// of a full CU, start and end of a walk when the launch waits for it and when the CU's next workgroup
+// does; workgroups resident per CU.  An iteration is 64 keys (kFour), 128 (kEight) or 256 (kSplit).
+// (Bidirectional blocks of 1024, 2048 and 4096 tokens with 1 to 8 heads.)
+struct Pace { float alone, full, ends, turn; int resident; };
+struct Paces { Pace four, eight, split; };
+const Paces& paces(int D) {
+  static const Paces d64 = {{.87f, .53f, 3.2f, 2.0f, 3}, {1.11f, 1.26f, 3.3f, 3.3f, 1}, {.70f, .74f, 2.5f, 4.5f, 2}};
+  static const Paces d128 = {{1.15f, .89f, 3.2f, 2.2f, 2}, {1.73f, 2.04f, 3.5f, 3.5f, 1}, {1.19f, 1.50f, 2.7f, 4.3f, 1}};
+  // weights at full precision (other head dimensions), by padded size
+  static const Paces e64 = {{1.20f, .98f, 3.2f, 1.8f, 3}, {1.95f, 2.30f, 3.3f, 3.3f, 1}, {1.05f, 1.00f, 2.5f, 4.5f, 2}};
+  static const Paces e96 = {{1.53f, 1.36f, 3.2f, 2.0f, 2}, {2.41f, 3.00f, 3.5f, 3.5f, 1}, {1.38f, 1.80f, 2.7f, 3.0f, 1}};
+  static const Paces e128 = {{1.89f, 1.75f, 3.2f, 2.0f, 2}, {2.82f, 3.64f, 3.5f, 3.5f, 1}, {1.64f, 2.35f, 2.8f, 3.5f, 1}};
+  return D == 64 ? d64 : D == 128 ? d128 : D <= 64 ? e64 : D <= 96 ? e96 : e128;
+}
+
+// Workgroups of a launch, iterations of its longest walk and of all walks together.
+struct Walks { double wgs, longest, total; };
+Walks count_walks(const PrefillArgs& a, bool is_sync, int rows, int keys, int wgs_per_tile) {
+  Walks w = {0, 0, 0};
+  for (int n = 0; n < a.seg.n; ++n) {
+    const double off = a.seg.seg_off[n], len = a.seg.seg_off[n + 1] - off;
+    if (len == 0) continue;
+    const double tiles = ceil(len / rows);
+    double most, mean;   // keys that the segment's last rows and its rows on average see
+    if (a.causal) {
+      // remote rows under a keep-list: their number is known to the device only, half are taken to be kept
+      const double before = is_sync ? (a.keep_chunks ? off / 2 : off) : 0;
+      most = before + len;
+      mean = before + (len + fmin(rows, len)) / 2;
+    } else {
+      most = mean = is_sync ? (a.keep_chunks ? (a.total + len) / 2 : a.total) : len;
+    }
+    w.wgs += tiles;
+    w.longest = fmax(w.longest, ceil(most / keys));
+    w.total += tiles * (a.causal ? fmax(1.0, mean / keys + 0.5) : ceil(mean / keys));
+  }
+  w.wgs *= wgs_per_tile;
+  w.total *= wgs_per_tile;
+  return w;
+}
+
+// Microseconds of the launch without what every launch costs: the longer of its longest walk, which
+// shares its CU with average ones, and the work of a CU (bidirectional blocks have walks of one length
+// that fill no gaps: whole workgroups count).
+double estimate(const Pace& p, const Walks& w, bool causal, int cus) {
+  const double on_cu = ceil(w.wgs / cus);   // workgroups that the fullest CU gets
+  const double together = fmin(on_cu, p.resident);
+  const double mean = w.total / w.wgs;
+  // with some, not all places of a CU taken, a workgroup's share is a little worse than full
+  const double shared = together > 1 ? fmax(p.alone, together * p.full * (together < p.resident ? 1.15 : 1.0))
+                                     : w.wgs > 0.45 * cus ? fmax(p.alone, p.full) : p.alone;
+  const double path = p.ends + (w.longest - mean) * p.alone + mean * shared;
+  const double work = causal ? p.turn * w.wgs / (p.resident * cus) + w.total * p.full / cus
+                             : on_cu * (p.turn / p.resident + mean * p.full);
+  return fmax(path, work);
+}
+
+Plan choose_plan(const PrefillArgs& a, bool is_sync) {
+  if (a.D > 128) return kFour;   // the others' tiles do not fit LDS
+  const Paces& p = paces(a.D);
+  const bool causal = a.causal != 0;
+  const int per_tile = a.Hkv * (a.Hq / a.Hkv / a.heads_per_wg);
+  const Walks four = count_walks(a, is_sync, a.q_tile_rows, kKvTile, per_tile);
+  Walks eight = count_walks(a, is_sync, a.q_tile_rows, 2 * kKvTile, per_tile);
+  const Walks split = count_walks(a, is_sync, kWaveRows, 256, a.Hq);
+  Plan best = kFour;
+  double t = estimate(p.four, four, causal, a.n_cus);
+  const auto consider = [&](Plan plan, double x) {
+    if (x < t) {
+      t = x;
+      best = plan;
+    }
+  };
+  consider(kEight, estimate(p.eight, eight, causal, a.n_cus));
+  if (causal) {   // half as many workgroups, each with a heavy and a light walk
+    const double pairs = (double)a.seg.pair_cum[a.seg.n] * per_tile;
+    eight.longest = is_sync ? 2 * eight.total / eight.wgs : eight.longest + 1;
+    eight.wgs = pairs;
+    Pace pp = p.eight;
+    pp.ends *= 1.95f;
+    consider(kEightPairs, estimate(pp, eight, true, a.n_cus));
+  }
+  consider(kSplit, estimate(p.split, split, causal, a.n_cus));
+  return best;
+}
+
+}  // namespace
+
 hipError_t launch_prefill_mfma(const PrefillArgs& a_in, int n_blocks, hipStream_t s) {
   if (a_in.n_q_tiles == 0 || n_blocks == 0) return hipSuccess;
   PrefillArgs a = a_in;
@@ -565,39 +668,26 @@ hipError_t launch_prefill_mfma(const PrefillArgs& a_in, int n_blocks, hipStream_
   const int per_tile = a.Hkv * (G / a.heads_per_wg);  // workgroups per query tile (or pair)
   // causal: query tiles are paired; a local block pairs inside each segment, which
   // needs at least as many workgroups as the sequence-wide pairing of a sync block
-  int wg_tiles = a.causal ? a.seg.pair_cum[a.seg.n] : a.n_q_tiles;
-  dim3 grid((unsigned)(wg_tiles * per_tile), (unsigned)n_blocks, 1);
-  // Fewer than two 4-wave workgroups per CU: 8-wave workgroups that split the KV tiles of a
-  // query tile between two groups keep two wavefronts on every SIMD, at the price of a merge
-  // through LDS per query tile and a heavier start.  That pays from about 16 KV tiles per
-  // workgroup on (measured at 2048 tokens: 1.06 vs 1.35 us per tile, 14.0 vs 9.6 us fixed).
-  // (Two groups' stages of a head dimension beyond 128 do not fit LDS.)
+  dim3 grid((unsigned)((a.causal ? a.seg.pair_cum[a.seg.n] : a.n_q_tiles) * per_tile), (unsigned)n_blocks, 1);
+  // scale folded into Q only up to the usual 1/sqrt(D): its rounding error grows with the scale
+  const bool exact = a.D != 64 && a.D != 128;
+  const bool fold = !exact && (double)a.scale * (double)a.scale * a.D <= 1.0 + 1e-6;
+  // several blocks in one launch (local and sync ones mixed): pairs, in 8-wavefront workgroups where
+  // there would be fewer than two 4-wavefront ones per CU
   bool wide = (int64_t)grid.x * grid.y < 2 * (int64_t)a.n_cus && a.D <= 128;
-  if (wide && n_blocks == 1) {
+  if (n_blocks == 1) {
     const bool is_sync = a.sync_override >= 0 ? a.sync_override != 0 : sync_block_rule(a.sync_interval, a.block_idx0);
-    const int N = a.seg.n;
-    int64_t kv_tiles = 0;  // KV tiles walked by all workgroups of one (KV head, head subgroup)
-    for (int n = 0; n < N; ++n) {
-      const int64_t len = a.seg.seg_off[n + 1] - a.seg.seg_off[n];
-      const int64_t q_tiles = a.seg.tile_cum[n + 1] - a.seg.tile_cum[n];
-      const int64_t span = is_sync ? (a.causal ? a.seg.seg_off[n] + len : (int64_t)a.total) : len;  // keys a late row sees
-      const int64_t first = is_sync && a.causal ? a.seg.seg_off[n] : 0;
-      // causal: a query tile sees the keys up to its own rows, on average half of its segment's span
-      const int64_t mean_keys = a.causal ? first + (span - first + 1) / 2 : span;
-      kv_tiles += q_tiles * ((mean_keys + kKvTile - 1) / kKvTile + (a.causal ? 1 : 0));
-    }
-    wide = kv_tiles >= 16 * (int64_t)wg_tiles;
-    // Not enough tiles per workgroup for the split, and every query tile can have a workgroup of
-    // its own with all of them resident at once (two per CU): drop the pairing.  Two unrelated
-    // 4-wave workgroups on a CU overlap each other's matrix and vector phases, which one
-    // workgroup walking a pair cannot do with itself.  Order: heavy half first, heaviest first;
-    // then the light half, lightest first, so that the workgroups that come to share a CU
-    // (index p and p + half, dispatched in order) carry about the same load together.
-    if (!wide && a.causal && a.n_q_tiles <= kMaxOrderedTiles && (int64_t)a.n_q_tiles * per_tile <= 2 * (int64_t)a.n_cus) {
+    const Plan plan = choose_plan(a, is_sync);
+    if (plan == kSplit) return launch_prefill_split(a_in, fold, 1, s);
+    wide = plan != kFour;
+    if (plan == kFour && a.causal && a.n_q_tiles <= kMaxOrderedTiles && (int64_t)a.n_q_tiles * per_tile <= 2 * (int64_t)a.n_cus) {
+      // All workgroups are resident at once, two per CU.  Order: heavy half first, heaviest first;
+      // then the light half, lightest first, so that the workgroups that come to share a CU
+      // (index p and p + half, dispatched in order) carry about the same load together.
       struct Item { int tile, work; };
       Item items[kMaxOrderedTiles];
       int cnt = 0;
-      for (int n = 0; n < N; ++n) {
+      for (int n = 0; n < a.seg.n; ++n) {
         const int lo = a.seg.seg_off[n], hi = a.seg.seg_off[n + 1];
         for (int t = a.seg.tile_cum[n]; t < a.seg.tile_cum[n + 1]; ++t) {
           const int last = min(lo + (t - a.seg.tile_cum[n] + 1) * a.q_tile_rows, hi);  // one past the tile's last row
@@ -609,18 +699,14 @@ hipError_t launch_prefill_mfma(const PrefillArgs& a_in, int n_blocks, hipStream_
       for (int i = 0; i < half; ++i) a.tile_order[i] = (uint16_t)items[i].tile;
       for (int i = half; i < cnt; ++i) a.tile_order[i] = (uint16_t)items[cnt - 1 - (i - half)].tile;
       a.n_ordered = cnt;
-      wg_tiles = cnt;
-      grid.x = (unsigned)(wg_tiles * per_tile);
+      grid.x = (unsigned)(cnt * per_tile);
+    } else if (plan != kEightPairs && a.causal) {
+      a.one_tile_heavy_first = 1;
+      if (!is_sync) order_segments_by_length(a);
+      grid.x = (unsigned)(a.n_q_tiles * per_tile);
     }
   }
-  // More than one round of 4-wave workgroups (two per CU): one query tile per workgroup, heaviest first.
-  if (!wide && n_blocks == 1 && a.causal && a.n_ordered == 0 && (int64_t)grid.x > 2 * (int64_t)a.n_cus) {
-    const bool is_sync = a.sync_override >= 0 ? a.sync_override != 0 : sync_block_rule(a.sync_interval, a.block_idx0);
-    a.one_tile_heavy_first = 1;
-    if (!is_sync) order_segments_by_length(a);
-    grid.x = (unsigned)(a.n_q_tiles * per_tile);
-  }
-  if (a.D != 64 && a.D != 128) {
+  if (exact) {
     switch ((a.D + 31) / 32) {
       case 1: return launch_prefill_exact<32>(a, wide, grid, s);
       case 2: return launch_prefill_exact<64>(a, wide, grid, s);
@@ -632,8 +718,6 @@ hipError_t launch_prefill_mfma(const PrefillArgs& a_in, int n_blocks, hipStream_
       default: return launch_prefill_exact<256>(a, wide, grid, s);
     }
   }
-  // scale folded into Q only up to the usual 1/sqrt(D): its rounding error grows with the scale
-  const bool fold = (double)a.scale * (double)a.scale * a.D <= 1.0 + 1e-6;
   if (a.D == 128) {
     if (fold) return wide ? launch_prefill_mfma_t<128, 2, true, false>(a, grid, s) : launch_prefill_mfma_t<128, 1, true, false>(a, grid, s);
     return wide ? launch_prefill_mfma_t<128, 2, false, false>(a, grid, s) : launch_prefill_mfma_t<128, 1, false, false>(a, grid, s);

@@ -125,3 +125,25 @@ def test_decode_other_shapes_fused_blocks_equal_single_calls(dtype, D):
     fa.fedattn_decode_blocks_fused(p, 0, M, q, k, v, many, q[0].numel(), k[0].numel(), seg, lens, workspace=ws)
     torch.cuda.synchronize()
     assert torch.equal(one, many)
+
+
+# bf16 with head dimension 64 / 128: ragged layouts that reach every launch of a prefill block - one head
+# per workgroup with split keys, ordered tiles, 8-wave workgroups on single tiles and on pairs, tiles
+# longest first - with empty and one-token segments
+PLAN_LAYOUTS = {"split": ([70, 0, 63, 1, 258], 4, 1), "split-long": ([1, 1999, 33], 2, 1), "ordered": ([100, 1, 0, 301, 33], 64, 16),
+                "eight": ([129, 0, 700, 1, 1203], 16, 4), "pairs": ([513, 1, 450, 600, 500], 32, 8), "longest-first": ([3101, 2, 3137], 32, 8)}
+
+
+@pytest.mark.parametrize("layout", sorted(PLAN_LAYOUTS))
+@pytest.mark.parametrize("D,scale", [(128, 0.0), (64, 0.0), (128, 0.2), (64, 0.3)])
+def test_bf16_prefill_launches(layout, D, scale):
+    lens, Hq, Hkv = PLAN_LAYOUTS[layout]
+    seg = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    q, k, v = rand_block(60, int(seg[-1]), Hq, Hkv, D)
+    rows, heads = fi.sample_rows(seg, Hq, 64, fi.DEFAULT_SEED, salt=D, tile=32, max_boundary_rows=200)
+    for sync, causal in [(0, True), (1, True), (1, False)]:
+        what = "bf16 %s D=%d scale=%.1f sync=%d causal=%d" % (layout, D, scale, sync, causal)
+        say(what)
+        got = prefill(q, k, v, seg, Hq=Hq, Hkv=Hkv, D=D, H=0, block=0, dtype=BF16, causal=causal, sync_override=sync, scale=scale)
+        ref = oracle.attend_rows(q, k, v, seg, rows, heads, is_sync=bool(sync), causal=causal, scale=scale if scale else None)
+        check(got[rows, heads], ref, BF16, what)
