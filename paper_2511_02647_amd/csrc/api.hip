@@ -8,6 +8,7 @@
 #include <string.h>
 
 #include <atomic>
+#include <chrono>
 #include <mutex>
 
 #include "common.h"
@@ -125,7 +126,7 @@ PrefillWs prefill_ws_layout(const fedattn_params* p, int32_t tokens, int32_t chu
 
 // chunk counters of the fused combine, one per (KV head, participant), at the end of the workspace
 size_t decode_counter_bytes(const fedattn_params* p) {
-  return align_up((size_t)p->n_kv_heads * (size_t)p->n_participants * 4, 256);
+  return align_up((size_t)p->n_kv_heads * (size_t)p->n_participants * sizeof(uint64_t), 256);
 }
 
 size_t decode_ws_bytes(const fedattn_params* p, int32_t capacity) {
@@ -136,6 +137,17 @@ size_t decode_ws_bytes(const fedattn_params* p, int32_t capacity) {
   const size_t chunks = (size_t)decode_target_chunks(p->n_kv_heads) + N;
   const size_t rows = (size_t)p->n_kv_heads * chunks * G * N;  // sync blocks: N*G query columns per chunk
   return align_up(rows * (size_t)p->head_dim * 4, 256) + align_up(rows * 8, 256) + decode_counter_bytes(p);
+}
+
+// A number that no other decode call of this process gets: it tells the counters that a call's
+// workgroups have set up from whatever the workspace held before.  48 bits from a start that
+// differs from process to process, so that values left in memory do not meet it by design.
+uint64_t next_ticket() {
+  static std::atomic<uint64_t> next{(uint64_t)std::chrono::steady_clock::now().time_since_epoch().count() * 0x9E3779B97F4A7C15ull};
+  uint64_t t;
+  do t = next.fetch_add(0x9E3779B97F4A7C15ull, std::memory_order_relaxed) >> 16;
+  while (t == 0);
+  return t;
 }
 
 // fedattn_prefill_sync_local_kv, participants' K/V not back to back: room for one aggregated copy each
@@ -398,7 +410,8 @@ static fedattn_status run_decode(bool fused, const fedattn_params* params, int32
   const size_t esize = (size_t)elem_bytes(params);
   DecodeArgs args[2];  // [0] local block, [1] sync block: the split differs, the layout does not
   bool built[2] = {false, false};
-  int32_t* counters = nullptr;
+  uint64_t* counters = nullptr;
+  const uint64_t ticket = next_ticket();
   int slices = 1;            // blocks in flight at once, each in its own slice of the workspace
   size_t slice_bytes = 0;
   const size_t need = decode_ws_bytes(params, capacity);
@@ -417,9 +430,8 @@ static fedattn_status run_decode(bool fused, const fedattn_params* params, int32
       slices = (int)(fit < (size_t)kMaxFusedBlocks ? fit : (size_t)kMaxFusedBlocks);
       if (slices > n_blocks) slices = n_blocks;
     }
-    // local blocks count their chunks in at the end of their slice; the counters start at
-    // zero and every launch leaves them at zero for the next one
-    counters = reinterpret_cast<int32_t*>(reinterpret_cast<unsigned char*>(workspace) + need - decode_counter_bytes(params));
+    // local blocks count their chunks in at the end of their slice
+    counters = reinterpret_cast<uint64_t*>(reinterpret_cast<unsigned char*>(workspace) + need - decode_counter_bytes(params));
   }
   fused = fused && split;
   const auto block_is_sync = [&](int b) {
@@ -463,6 +475,7 @@ static fedattn_status run_decode(bool fused, const fedattn_params* params, int32
         a.part_o = reinterpret_cast<float*>(workspace);
         a.part_ml = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(workspace) + o_bytes);
         a.counters = counters;
+        a.ticket = ticket;
         // in-kernel merge: the workgroups of a segment write its output rows, so every segment
         // needs one (an empty segment's zero rows come from the separate combine kernel)
         bool all_have_rows = true, one_chunk = true;
@@ -483,11 +496,6 @@ static fedattn_status run_decode(bool fused, const fedattn_params* params, int32
   for (int b = 0; b < n_blocks && !(built[0] && built[1]); ++b) {
     st = prepare(block_is_sync(b));
     if (st != FEDATTN_OK) return st;
-  }
-  if (split && params->dtype == FEDATTN_BF16) {
-    hipError_t e = launch_decode_zero_counters(counters, params->n_kv_heads * N, slices, (int64_t)slice_bytes,
-                                               reinterpret_cast<hipStream_t>(stream));
-    if (e != hipSuccess) return fail(FEDATTN_ELAUNCH, "decode (counters): %s", hipGetErrorString(e));
   }
   if (fused) {
     for (int kind = 0; kind < 2; ++kind) {

@@ -71,7 +71,8 @@ struct DecodeArgs {
   void* out;
   float* part_o;            // [Hkv, n_chunks, cols, D] fp32: sum_j p_j v_j with p_j = 2^(s_j - m), unnormalised
   float* part_ml;           // [Hkv, n_chunks, cols, 2] (m in log2 domain, l)
-  int32_t* counters;        // [Hkv, N] chunks counted in per (KV head, segment); zero before and after a launch
+  uint64_t* counters;       // [Hkv, N] chunks counted in per (KV head, segment), zero after a launch
+  uint64_t ticket;          // this call's, 48 bits, not zero: marks the counters as set up
   int32_t merge_in_kernel;  // local block: the split kernel writes the output rows itself (no combine launch), bf16
                             // through the last chunk of a segment, fp32 because every segment is one chunk
   int32_t N, Hq, Hkv, D;
@@ -148,7 +149,6 @@ hipError_t launch_pack_kept_rows(const PrefillArgs& a, int row_bytes, int32_t* k
                                  void* v_packed, int2* kept_tiles, int32_t* kept_cum, hipStream_t s);
 hipError_t launch_decode(const DecodeArgs& a, int dtype, bool split, int n_z, hipStream_t s);
 hipError_t launch_decode_f32(const DecodeArgs& a, int n_z, hipStream_t s);
-hipError_t launch_decode_zero_counters(int32_t* counters, int n, int slices, int64_t slice_bytes, hipStream_t s);
 hipError_t launch_aggregate(const AggregateArgs& a, hipStream_t s);
 hipError_t launch_rmsnorm(const float* x, void* out, int64_t rows, int d_model, float eps, hipStream_t s);
 hipError_t launch_residual_add_rmsnorm(float* x, const void* y, void* out, int64_t rows, int d_model, float eps,

@@ -79,7 +79,7 @@ __global__ __launch_bounds__(COLSPLIT ? 512 : 256, 1) void decode_stream_kernel(
   const unsigned char* v_ptr = reinterpret_cast<const unsigned char*>(a.v_cache) + blk * a.cache_block_bytes;
   float* part_o = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(a.part_o) + bz * a.slice_bytes);
   float* part_ml = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(a.part_ml) + bz * a.slice_bytes);
-  int32_t* counters = reinterpret_cast<int32_t*>(reinterpret_cast<unsigned char*>(a.counters) + bz * a.slice_bytes);
+  uint64_t* counters = reinterpret_cast<uint64_t*>(reinterpret_cast<unsigned char*>(a.counters) + bz * a.slice_bytes);
 
   const int Hq = a.Hq, Hkv = a.Hkv;
   const int G = Hq / Hkv;
@@ -135,6 +135,14 @@ __global__ __launch_bounds__(COLSPLIT ? 512 : 256, 1) void decode_stream_kernel(
 #pragma unroll
   for (int t = 0; t < kDecodeStages - 1; ++t)
     if (t < nt) issue(t);
+  // Chunk counter of the segment (merge below): (ticket of this call) << 16 | chunks counted in.  What it
+  // holds on entry does not matter: the first workgroups of the segment put the ticket there.  The
+  // value is requested here, behind the first tiles (ahead of them it cost 0.4 us of an 18 us launch),
+  // and looked at after the stream.
+  const bool counts = !COLSPLIT && a.merge_in_kernel && n_seg_chunks > 1;
+  uint64_t* cnt = counters + g * N + m;  // at most 16 columns: one workgroup per chunk
+  uint64_t cnt_found = 0;
+  if (counts) asm volatile("global_load_dwordx2 %0, %1, off sc1" : "=v"(cnt_found) : "v"(cnt) : "memory");
 
   // LDS -> A operand of S^T: lane (row l16 of a 16-row sub-tile, k-group kg) reads chunk
   // 4 st + kg; the sub-tile's first row goes in the address as a multiple of 16 rows,
@@ -162,8 +170,11 @@ __global__ __launch_bounds__(COLSPLIT ? 512 : 256, 1) void decode_stream_kernel(
   for (int t = 0; t < nt; ++t) {
     // this wavefront's part of tile t has landed once at most the loads of the tiles
     // issued after it are outstanding (the query loads are older still)
+    // (the counter's load is allowed for where it matters, before the first tile)
     const int after = min(nt, t + kDecodeStages - 1) - (t + 1);
-    if (after >= 2)
+    if (t == 0 && counts && after == 1)
+      wait_vmcnt<2 * IPW + 1>();
+    else if (after >= 2)
       wait_vmcnt<2 * 2 * IPW>();
     else if (after == 1)
       wait_vmcnt<2 * IPW>();
@@ -267,6 +278,15 @@ __global__ __launch_bounds__(COLSPLIT ? 512 : 256, 1) void decode_stream_kernel(
     }
   }
 
+  if (counts) {
+    wait_vmcnt<0>();   // one tile only: the counter's value was requested after it
+    asm volatile("" : "+v"(cnt_found));
+    // Not this call's yet: make it so.  The exchange fails only if another workgroup of the segment came
+    // first, and it has completed (with the partial stores) before this workgroup counts itself in.
+    if (tid == 0 && cnt_found >> 16 != a.ticket)
+      (void)__hip_atomic_compare_exchange_strong(cnt, &cnt_found, a.ticket << 16, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT);
+  }
   l_run = sum_over_kgroups(l_run);
   if constexpr (COLSPLIT) {
     // ---- merge the two row halves of a column block: half 1 hands (m, l, O) to half 0 -------
@@ -358,8 +378,7 @@ __global__ __launch_bounds__(COLSPLIT ? 512 : 256, 1) void decode_stream_kernel(
     // between) rather than with plain accesses plus cache-wide write-back and invalidate
     // fences, which cost far more than the few KB exchanged here.  A workgroup counts itself
     // in only after all its partial stores have completed (vmcnt = 0 in every wavefront,
-    // then the barrier); the workgroup that finds all other chunks counted in merges and
-    // leaves the counter at zero for the next launch.
+    // then the barrier); the workgroup that finds all other chunks counted in merges.
     for (int idx = tid; idx < n_cols * (D / 4); idx += 256) {
       const int cl = idx / (D / 4), d4 = idx % (D / 4);
       const float* src = o_all + cl * OPAD + 4 * d4;
@@ -385,10 +404,10 @@ __global__ __launch_bounds__(COLSPLIT ? 512 : 256, 1) void decode_stream_kernel(
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
     __syncthreads();
     if (tid == 0) {
-      int* cnt = counters + g * N + m;  // at most 16 columns: one workgroup per chunk
-      const int seen = __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      const int last = seen == n_seg_chunks - 1;
-      if (last) __hip_atomic_store(cnt, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const uint64_t seen = __hip_atomic_fetch_add(cnt, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const int last = (int)(seen & 0xffff) == n_seg_chunks - 1;
+      // left at zero: a launch replayed from a graph comes with the same ticket
+      if (last) __hip_atomic_store(cnt, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       last_s = last;
     }
     __syncthreads();
@@ -419,13 +438,6 @@ __global__ __launch_bounds__(COLSPLIT ? 512 : 256, 1) void decode_stream_kernel(
       *reinterpret_cast<u32x2*>(out_rows + cl * D + 4 * d4) = __builtin_bit_cast(u32x2, w4);
     }
   }
-}
-
-// Zeroes the chunk counters of the fused combine (a kernel rather than a memset so that
-// callers may capture the calls in a graph).
-__global__ void decode_zero_counters_kernel(int32_t* counters, int n, int64_t slice_bytes) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;  // grid y: workspace slice
-  if (i < n) reinterpret_cast<int32_t*>(reinterpret_cast<unsigned char*>(counters) + blockIdx.y * slice_bytes)[i] = 0;
 }
 
 // Merges the chunk partials of one (participant, query head) and writes the output row:
@@ -462,12 +474,13 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(DecodeArgs a) {
     // Few chunks (the usual case): one round trip.  Every thread requests its partial O rows
     // and one chunk's (m, l) before anything is known about the weights.
     const int nb = c1 - c0;
+    const int nb_o = cg < CG ? nb : 0;   // chunks whose O rows this thread sums (every CG-th from cg on)
     const float* po = part_o + ((base + c0) * cstride + col) * D + 4 * d4;
     f32x4 part[16];
 #pragma unroll
     for (int u = 0; u < 16; ++u) {
       const int i = cg + CG * u;
-      part[u] = i < nb && cg < CG ? *reinterpret_cast<const f32x4*>(po + i * cstride * D) : f32x4{0.f, 0.f, 0.f, 0.f};
+      part[u] = i < nb_o ? *reinterpret_cast<const f32x4*>(po + i * cstride * D) : f32x4{0.f, 0.f, 0.f, 0.f};
     }
     float m_i = -INFINITY, l_i = 0.f;
     if (tid < nb) {
@@ -490,7 +503,7 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(DecodeArgs a) {
 #pragma unroll
     for (int u = 0; u < 16; ++u) {
       const int i = cg + CG * u;
-      if (i < nb) acc += part[u] * w_s[i];
+      if (i < nb_o) acc += part[u] * w_s[i];
     }
     if (cg < CG) acc_s[cg][d4] = acc;
     if (tid == 0) {
@@ -701,12 +714,6 @@ hipError_t launch_decode(const DecodeArgs& a, int dtype, bool split, int n_z, hi
     if (e != hipSuccess) return e;
   }
   return a.merge_in_kernel ? hipSuccess : launch_decode_combine(a, dtype, n_z, s);
-}
-
-hipError_t launch_decode_zero_counters(int32_t* counters, int n, int slices, int64_t slice_bytes, hipStream_t s) {
-  hipLaunchKernelGGL(decode_zero_counters_kernel, dim3((unsigned)((n + 255) / 256), (unsigned)slices), dim3(256), 0, s,
-                     counters, n, slice_bytes);
-  return hipGetLastError();
 }
 
 }  // namespace fedattn
