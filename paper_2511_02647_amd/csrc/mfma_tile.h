@@ -107,8 +107,8 @@ __device__ inline float sum_over_kgroups(float x) {
 // product touch 4 rows x 4 chunks per 32 lanes (VSWZ = 1), those of the
 // 16x16x16 product 8 rows x 2 chunks (VSWZ = 0).
 // NW = wavefronts that load a tile together (4, 8 for 8-wave workgroups sharing one tile, 1 for a
-// wavefront with tiles of its own), ROWS = KV rows of a tile.
-template <int D, int VSWZ, int NW = 4, int ROWS = kKvTile>
+// wavefront with tiles of its own), ROWS = KV rows of a tile, PAD = rows in HBM may be shorter than D.
+template <int D, int VSWZ, int NW = 4, int ROWS = kKvTile, bool PAD = false>
 struct KvTile {
   static constexpr int KSTEPS = D / 16;         // MFMA k-steps of S^T = K Q^T
   static constexpr int DT = D / 32;             // 32-row tiles of O^T along head_dim
@@ -149,14 +149,15 @@ struct KvTile {
   int v_off[DT];
   int wave;
   int row_elems;           // elements between consecutive KV rows in HBM
-  int last_chunk;          // last 16-byte chunk of a row in HBM (CPR - 1 without padding)
+  int last_chunk;          // last 16-byte chunk of a row in HBM (PAD)
 
+  __device__ __attribute__((always_inline)) int stored_chunk(int c) const { return PAD ? min(c, last_chunk) : c; }
   // tile row and element offset of the chunk inside the row that this lane fetches in its wave's i-th instruction
   __device__ __attribute__((always_inline)) void dma_slot(int i, bool is_v, int& row, int& col) const {
     const int sidx = (wave * IPW + i) * 64 + lane;
     const int cp = sidx % CPR;
     row = sidx / CPR;
-    col = min(cp ^ (is_v ? v_swizzle(row) : k_swizzle(row)), last_chunk) * 8;
+    col = stored_chunk(cp ^ (is_v ? v_swizzle(row) : k_swizzle(row))) * 8;
   }
 
   __device__ __attribute__((always_inline)) void init(int lane_, int wave_, int row_elems_, int last_chunk_ = CPR - 1) {
@@ -462,8 +463,8 @@ __device__ __attribute__((always_inline)) inline void split_weights(const float 
   }
 }
 
-template <int D, int VSWZ, int NW, int ROWS>
-__device__ __attribute__((always_inline)) inline void KvTile<D, VSWZ, NW, ROWS>::pv_f32(lds_cptr lds0, int vb, const f32x16 (&s)[AA],
+template <int D, int VSWZ, int NW, int ROWS, bool PAD>
+__device__ __attribute__((always_inline)) inline void KvTile<D, VSWZ, NW, ROWS, PAD>::pv_f32(lds_cptr lds0, int vb, const f32x16 (&s)[AA],
                     f32x16 (&o)[DT]) const {
 #pragma unroll
   for (int kk = 0; kk < 2 * AA; ++kk) {

@@ -55,7 +55,7 @@ namespace {
 // 4 x 100..900 tokens, 8/2 heads of 96: 1794 us on the wavefront-per-row kernel, 72 us here.
 template <int DP, int NG, bool FOLD, bool EXACT>
 __global__ __launch_bounds__(256 * NG, DP > 128 ? 1 : DP > 64 ? 2 : 3) void prefill_mfma_kernel(PrefillArgs a) {
-  using TL = KvTile<DP, 1>;
+  using TL = KvTile<DP, 1, 4, kKvTile, EXACT>;
   const int D = EXACT ? a.D : DP;
   constexpr int KSTEPS = TL::KSTEPS, DT = TL::DT, TILEB = TL::TILEB;
   // Per group: K and V tiles double-buffered; the group's i-th tile lives in stage i&1.
@@ -150,7 +150,7 @@ __global__ __launch_bounds__(256 * NG, DP > 128 ? 1 : DP > 64 ? 2 : 3) void pref
   const int row_elems = Hkv * D;  // elements between consecutive KV rows in HBM
 
   TL tile_io;
-  tile_io.init(lane, wave, row_elems, EXACT ? D / 8 - 1 : TL::CPR - 1);
+  tile_io.init(lane, wave, row_elems, D / 8 - 1);
 
   struct Walk : KvWalk {
     int row0w;  // first query row of this wavefront
@@ -196,7 +196,7 @@ __global__ __launch_bounds__(256 * NG, DP > 128 ? 1 : DP > 64 ? 2 : 3) void pref
       const int sidx = i * 64 + lane;
       const int row = sidx / TL::CPR, cp = sidx % TL::CPR;
       const int row_ld = min(w.row0w + row, w.seg_hi - 1) - rbase;  // >= 0
-      const int chunk = min(cp ^ TL::k_swizzle(row), tile_io.last_chunk);
+      const int chunk = tile_io.stored_chunk(cp ^ TL::k_swizzle(row));
       const uint32_t off = (uint32_t)(row_ld * (Hq * D) + chunk * 8) * 2u;
       lds_dma_16(qbase, off, lds_base + q_lds + i * 1024);
     }

@@ -37,7 +37,7 @@ __device__ inline void wait_lds_reads() { asm volatile("s_waitcnt lgkmcnt(0)" ::
 template <int DP, bool FOLD, bool EXACT>
 __global__ __launch_bounds__(64 * kSplitWaves, DP > 64 ? 2 : 4) void prefill_split_kernel(PrefillArgs a) {
   constexpr int KS = kSplitWaves;
-  using TL = KvTile<DP, 1, 1, kSplitRows>;
+  using TL = KvTile<DP, 1, 1, kSplitRows, EXACT>;
   constexpr int KSTEPS = TL::KSTEPS, DT = TL::DT, TILEB = TL::TILEB, ROWB = TL::ROWB, CPR = TL::CPR;
   constexpr int WAVEB = 2 * TILEB;           // a wavefront's share: K tile, V tile; in the end its partial result
   constexpr int NT = 64 * KS;
@@ -92,7 +92,7 @@ __global__ __launch_bounds__(64 * kSplitWaves, DP > 64 ? 2 : 4) void prefill_spl
   const float sc = a.scale * kLog2e;
   const int row_elems = Hkv * D;
   TL tile_io;
-  tile_io.init(lane, 0, row_elems, EXACT ? D / 8 - 1 : CPR - 1);
+  tile_io.init(lane, 0, row_elems, D / 8 - 1);
 
   // 32-key tiles of the walk: every listed 64-row tile is two (the second one may be empty), then the dense range
   const int n_list = 2 * w.n_list;
@@ -131,7 +131,7 @@ __global__ __launch_bounds__(64 * kSplitWaves, DP > 64 ? 2 : 4) void prefill_spl
     const int i = i0 + wave;
     if (i < QTILEB / 1024) {
       const int sidx = i * 64 + lane;
-      const int row = sidx / CPR, chunk = min((sidx % CPR) ^ TL::k_swizzle(row), tile_io.last_chunk);
+      const int row = sidx / CPR, chunk = tile_io.stored_chunk((sidx % CPR) ^ TL::k_swizzle(row));
       const int row_ld = min(row0 + row, w.seg_hi - 1);
       lds_dma_16(qp + ((int64_t)row0 * Hq + head) * D, (uint32_t)((row_ld - row0) * (Hq * D) + chunk * 8) * 2u,
                  lds_addr_of(q_lds) + i * 1024);
