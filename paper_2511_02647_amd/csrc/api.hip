@@ -136,7 +136,9 @@ size_t decode_ws_bytes(const fedattn_params* p, int32_t capacity) {
   (void)capacity;
   const size_t chunks = (size_t)decode_target_chunks(p->n_kv_heads) + N;
   const size_t rows = (size_t)p->n_kv_heads * chunks * G * N;  // sync blocks: N*G query columns per chunk
-  return align_up(rows * (size_t)p->head_dim * 4, 256) + align_up(rows * 8, 256) + decode_counter_bytes(p);
+  // Room for the counters: these bytes and the unused partials (there are at most target + N - 1 chunks).
+  const size_t counters = align_up((size_t)p->n_kv_heads * N * sizeof(uint32_t), 256);
+  return align_up(rows * (size_t)p->head_dim * 4, 256) + align_up(rows * 8, 256) + counters;
 }
 
 // A number that no other decode call of this process gets: it tells the counters that a call's
@@ -412,6 +414,7 @@ static fedattn_status run_decode(bool fused, const fedattn_params* params, int32
   bool built[2] = {false, false};
   uint64_t* counters = nullptr;
   const uint64_t ticket = next_ticket();
+  bool counters_ready = false;   // a launch of this call has set them up, and every launch leaves them at zero
   int slices = 1;            // blocks in flight at once, each in its own slice of the workspace
   size_t slice_bytes = 0;
   const size_t need = decode_ws_bytes(params, capacity);
@@ -475,7 +478,6 @@ static fedattn_status run_decode(bool fused, const fedattn_params* params, int32
         a.part_o = reinterpret_cast<float*>(workspace);
         a.part_ml = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(workspace) + o_bytes);
         a.counters = counters;
-        a.ticket = ticket;
         // in-kernel merge: the workgroups of a segment write its output rows, so every segment
         // needs one (an empty segment's zero rows come from the separate combine kernel)
         bool all_have_rows = true, one_chunk = true;
@@ -515,6 +517,8 @@ static fedattn_status run_decode(bool fused, const fedattn_params* params, int32
         first = b;
         if (cnt == 0) continue;
         a.q = q; a.out = out; a.k_cache = k_cache; a.v_cache = v_cache;
+        a.ticket = counters_ready ? 0 : ticket;   // no later launch of this kind has more slices than the first
+        counters_ready = counters_ready || a.merge_in_kernel;
         hipError_t e = launch_decode(a, params->dtype, true, cnt, reinterpret_cast<hipStream_t>(stream));
         if (e != hipSuccess) return fail(FEDATTN_ELAUNCH, "decode (fused, %d blocks): %s", cnt, hipGetErrorString(e));
       }
@@ -530,6 +534,8 @@ static fedattn_status run_decode(bool fused, const fedattn_params* params, int32
     a.out = reinterpret_cast<unsigned char*>(out) + (size_t)b * (size_t)q_block_stride * esize;
     a.k_cache = reinterpret_cast<const unsigned char*>(k_cache) + (size_t)b * (size_t)cache_block_stride * esize;
     a.v_cache = reinterpret_cast<const unsigned char*>(v_cache) + (size_t)b * (size_t)cache_block_stride * esize;
+    a.ticket = counters_ready ? 0 : ticket;
+    counters_ready = counters_ready || a.merge_in_kernel;
     hipError_t e = launch_decode(a, params->dtype, split, 1, reinterpret_cast<hipStream_t>(stream));
     if (e != hipSuccess) return fail(FEDATTN_ELAUNCH, "decode (block %d): %s", block_idx0 + b, hipGetErrorString(e));
   }

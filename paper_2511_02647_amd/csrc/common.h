@@ -72,7 +72,7 @@ struct DecodeArgs {
   float* part_o;            // [Hkv, n_chunks, cols, D] fp32: sum_j p_j v_j with p_j = 2^(s_j - m), unnormalised
   float* part_ml;           // [Hkv, n_chunks, cols, 2] (m in log2 domain, l)
   uint64_t* counters;       // [Hkv, N] chunks counted in per (KV head, segment), zero after a launch
-  uint64_t ticket;          // this call's, 48 bits, not zero: marks the counters as set up
+  uint64_t ticket;          // first launch of a call: the call's number, 48 bits, marks the counters as set up; later ones: 0
   int32_t merge_in_kernel;  // local block: the split kernel writes the output rows itself (no combine launch), bf16
                             // through the last chunk of a segment, fp32 because every segment is one chunk
   int32_t N, Hq, Hkv, D;

@@ -47,7 +47,7 @@ constexpr int decode_smem_bytes() { return decode_stages<D>() * 2 * KvTile<D, 0>
 template <int DP, bool COLSPLIT, bool EXACT>
 __global__ __launch_bounds__(COLSPLIT ? 512 : 256, 1) void decode_stream_kernel(DecodeArgs a) {
   constexpr int NW = COLSPLIT ? 8 : 4;
-  using TL = KvTile<DP, 0, NW>;
+  using TL = KvTile<DP, 0, NW, kKvTile, EXACT>;
   constexpr int kDecodeStages = decode_stages<DP>();
   const int D = EXACT ? a.D : DP;
   constexpr int KS = DP / 32;                // k-steps of S^T (16x16x32)
@@ -101,7 +101,7 @@ __global__ __launch_bounds__(COLSPLIT ? 512 : 256, 1) void decode_stream_kernel(
   const uint16_t* vbase = reinterpret_cast<const uint16_t*>(v_ptr) + ((int64_t)(seg_row0 + r_lo) * Hkv + g) * D;
 
   TL tile_io;
-  tile_io.init(lane, wave, row_elems, EXACT ? D / 8 - 1 : TL::CPR - 1);
+  tile_io.init(lane, wave, row_elems, D / 8 - 1);
 
   // this lane's query column -> (participant, head); columns past the end are zero
   // rows: local block, column = head inside the KV group; sync block, column =
@@ -135,14 +135,14 @@ __global__ __launch_bounds__(COLSPLIT ? 512 : 256, 1) void decode_stream_kernel(
 #pragma unroll
   for (int t = 0; t < kDecodeStages - 1; ++t)
     if (t < nt) issue(t);
-  // Chunk counter of the segment (merge below): (ticket of this call) << 16 | chunks counted in.  What it
-  // holds on entry does not matter: the first workgroups of the segment put the ticket there.  The
-  // value is requested here, behind the first tiles (ahead of them it cost 0.4 us of an 18 us launch),
-  // and looked at after the stream.
-  const bool counts = !COLSPLIT && a.merge_in_kernel && n_seg_chunks > 1;
+  // Chunk counter of the segment (merge below): (ticket of the call) << 16 | chunks counted in.  Every
+  // launch leaves it at zero.  What it holds before a call does not matter: in the call's first launch
+  // (ticket set) the first workgroups of the segment put the ticket there.  The value is requested here,
+  // behind the first tiles (ahead of them it cost 0.4 us of an 18 us launch), and looked at after the stream.
+  const bool set_up = !COLSPLIT && a.merge_in_kernel && n_seg_chunks > 1 && a.ticket != 0;
   uint64_t* cnt = counters + g * N + m;  // at most 16 columns: one workgroup per chunk
   uint64_t cnt_found = 0;
-  if (counts) asm volatile("global_load_dwordx2 %0, %1, off sc1" : "=v"(cnt_found) : "v"(cnt) : "memory");
+  if (set_up) cnt_found = __hip_atomic_load(cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 
   // LDS -> A operand of S^T: lane (row l16 of a 16-row sub-tile, k-group kg) reads chunk
   // 4 st + kg; the sub-tile's first row goes in the address as a multiple of 16 rows,
@@ -172,7 +172,7 @@ __global__ __launch_bounds__(COLSPLIT ? 512 : 256, 1) void decode_stream_kernel(
     // issued after it are outstanding (the query loads are older still)
     // (the counter's load is allowed for where it matters, before the first tile)
     const int after = min(nt, t + kDecodeStages - 1) - (t + 1);
-    if (t == 0 && counts && after == 1)
+    if (t == 0 && set_up && after == 1)
       wait_vmcnt<2 * IPW + 1>();
     else if (after >= 2)
       wait_vmcnt<2 * 2 * IPW>();
@@ -278,15 +278,11 @@ __global__ __launch_bounds__(COLSPLIT ? 512 : 256, 1) void decode_stream_kernel(
     }
   }
 
-  if (counts) {
-    wait_vmcnt<0>();   // one tile only: the counter's value was requested after it
-    asm volatile("" : "+v"(cnt_found));
-    // Not this call's yet: make it so.  The exchange fails only if another workgroup of the segment came
-    // first, and it has completed (with the partial stores) before this workgroup counts itself in.
-    if (tid == 0 && cnt_found >> 16 != a.ticket)
-      (void)__hip_atomic_compare_exchange_strong(cnt, &cnt_found, a.ticket << 16, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                 __HIP_MEMORY_SCOPE_AGENT);
-  }
+  // Not this call's yet: make it so.  The exchange fails only if another workgroup of the segment came
+  // first, and it has completed (with the partial stores) before this workgroup counts itself in.
+  if (set_up && tid == 0 && cnt_found >> 16 != a.ticket)
+    (void)__hip_atomic_compare_exchange_strong(cnt, &cnt_found, a.ticket << 16, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_AGENT);
   l_run = sum_over_kgroups(l_run);
   if constexpr (COLSPLIT) {
     // ---- merge the two row halves of a column block: half 1 hands (m, l, O) to half 0 -------
