@@ -101,23 +101,19 @@ int decode_chunk_rows(int64_t total_rows, int Hkv) {
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 // prefill workspace: [kept_cum: (kMaxP+1) int32, padded][kept_tiles: int2 per 64-row tile]
-// and, for keep chunks finer than a tile where a tile kernel runs:
-// [kept_rows: kMaxP int32][src_index: int32 per token][packed K][packed V]
+// and, for keep chunks finer than a tile where a tile kernel runs: [packed K][packed V]
 constexpr size_t kKeptCumBytes = 1024;
-constexpr size_t kKeptRowsBytes = 512;
 struct PrefillWs {
-  size_t tiles_off, rows_off, index_off, k_off, v_off, total;
+  size_t tiles_off, list_end, k_off, v_off, total;
 };
 PrefillWs prefill_ws_layout(const fedattn_params* p, int32_t tokens, int32_t chunk_tokens) {
   PrefillWs w;
   const size_t max_tiles = (size_t)tokens / kKvTile + (size_t)p->n_participants + 1;
   w.tiles_off = kKeptCumBytes;
-  w.rows_off = w.tiles_off + align_up(max_tiles * sizeof(int2), 256);
-  w.index_off = w.k_off = w.v_off = w.total = w.rows_off;
+  w.list_end = w.tiles_off + align_up(max_tiles * sizeof(int2), 256);
+  w.k_off = w.v_off = w.total = w.list_end;
   if (needs_row_packing(chunk_tokens)) {
     const size_t kv_bytes = (size_t)tokens * (size_t)p->n_kv_heads * (size_t)p->head_dim * (size_t)elem_bytes(p);
-    w.index_off = w.rows_off + kKeptRowsBytes;
-    w.k_off = w.index_off + align_up((size_t)tokens * 4, 256);
     w.v_off = w.k_off + align_up(kv_bytes, 256);
     w.total = w.v_off + align_up(kv_bytes, 256);
   }
@@ -239,9 +235,7 @@ fedattn_status run_prefill(const fedattn_params* p, int32_t block_idx0, int32_t 
       if (needs_row_packing(chunk_tokens)) {
         a.k_list = ws + w.k_off;
         a.v_list = ws + w.v_off;
-        e = launch_pack_kept_rows(a, a.Hkv * a.D * elem_bytes(p), reinterpret_cast<int32_t*>(ws + w.rows_off),
-                                  reinterpret_cast<int32_t*>(ws + w.index_off), ws + w.k_off, ws + w.v_off,
-                                  kept_tiles, kept_cum, s);
+        e = launch_pack_kept_rows(a, a.Hkv * a.D * elem_bytes(p), ws + w.k_off, ws + w.v_off, kept_tiles, kept_cum, s);
       } else {
         e = launch_build_kept_tiles(a, kept_tiles, kept_cum, s);
       }
@@ -327,7 +321,7 @@ fedattn_status fedattn_prefill_sync_local_kv(const fedattn_params* params, const
     if (!aligned16(workspace)) return fail(FEDATTN_EINVAL, "workspace must be 16-byte aligned");
     if (keep_chunks && chunk_tokens > 0) {
       const PrefillWs w = prefill_ws_layout(params, total, chunk_tokens);
-      const size_t need = 2 * copy + (use_mfma_prefill(params) ? w.total : w.rows_off);
+      const size_t need = 2 * copy + (use_mfma_prefill(params) ? w.total : w.list_end);
       if (workspace_bytes < need)
         return fail(FEDATTN_EWORKSPACE, "workspace too small for the aggregated copy and the keep-list (%zu bytes needed)", need);
     }

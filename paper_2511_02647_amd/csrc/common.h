@@ -145,8 +145,8 @@ hipError_t launch_prefill_split(const PrefillArgs& a, bool fold, int n_blocks, h
 hipError_t launch_prefill_f32(const PrefillArgs& a, int n_blocks, hipStream_t s);
 hipError_t launch_build_kept_tiles(const PrefillArgs& a, int2* kept_tiles, int32_t* kept_cum,
                                    hipStream_t s);
-hipError_t launch_pack_kept_rows(const PrefillArgs& a, int row_bytes, int32_t* kept_rows, int32_t* src_index, void* k_packed,
-                                 void* v_packed, int2* kept_tiles, int32_t* kept_cum, hipStream_t s);
+hipError_t launch_pack_kept_rows(const PrefillArgs& a, int row_bytes, void* k_packed, void* v_packed, int2* kept_tiles,
+                                 int32_t* kept_cum, hipStream_t s);
 hipError_t launch_decode(const DecodeArgs& a, int dtype, bool split, int n_z, hipStream_t s);
 hipError_t launch_decode_f32(const DecodeArgs& a, int n_z, hipStream_t s);
 hipError_t launch_aggregate(const AggregateArgs& a, hipStream_t s);

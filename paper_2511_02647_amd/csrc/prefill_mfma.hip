@@ -400,145 +400,186 @@ __global__ __launch_bounds__(256 * NG, DP > 128 ? 1 : DP > 64 ? 2 : 3) void pref
   }
 }
 
-// Compacts the keep flags of a sync block into the list of kept 64-row KV tiles,
-// participant after participant, plus the number of kept tiles before each
-// participant.  One thread per participant (the lists are short).
-__global__ __launch_bounds__(kMaxP) void build_kept_tiles_kernel(PrefillArgs a, int2* kept_tiles,
-                                                                 int32_t* kept_cum) {
-  __shared__ int cnt[kMaxP + 1];
-  const int n = threadIdx.x;
-  const int N = a.seg.n;
-  int my = 0;
-  if (n < N) {
-    const int lo = a.seg.seg_off[n], hi = a.seg.seg_off[n + 1];
-    const uint8_t* keep = a.keep_chunks + a.seg.chunk_cum[n];
-    const int nc = a.seg.chunk_cum[n + 1] - a.seg.chunk_cum[n];
-    for (int c = 0; c < nc; ++c) {
-      if (!keep[c]) continue;
-      const int clen = min(a.chunk_tokens, hi - (lo + c * a.chunk_tokens));
-      my += (clen + kKvTile - 1) / kKvTile;
-    }
-  }
-  cnt[n] = my;
-  __syncthreads();
-  if (n == 0) {
-    int run = 0;
-    for (int i = 0; i < N; ++i) {
-      const int c = cnt[i];
-      cnt[i] = run;
-      kept_cum[i] = run;
-      run += c;
-    }
-    cnt[N] = run;
-    kept_cum[N] = run;
-  }
-  __syncthreads();
-  if (n < N) {
-    const int lo = a.seg.seg_off[n], hi = a.seg.seg_off[n + 1];
-    const uint8_t* keep = a.keep_chunks + a.seg.chunk_cum[n];
-    const int nc = a.seg.chunk_cum[n + 1] - a.seg.chunk_cum[n];
-    int w = cnt[n];
-    for (int c = 0; c < nc; ++c) {
-      if (!keep[c]) continue;
-      const int start = lo + c * a.chunk_tokens;
-      const int clen = min(a.chunk_tokens, hi - start);
-      for (int t = 0; t < clen; t += kKvTile) kept_tiles[w++] = make_int2(start + t, min(kKvTile, clen - t));
-    }
-  }
+// ---- keep-lists of a sync block -----------------------------------------------------------------
+// The attention kernels walk a list of kept 64-row KV tiles, participant after participant, with the
+// number of kept tiles before each participant beside it.  Nothing here moves much data: what counts is
+// the chain of dependent memory accesses, and the launches.
+
+// This lane's share of the flags set in keep[0 .. nc).
+__device__ inline int lane_flags(const uint8_t* keep, int nc, int lane) {
+  int n = 0;
+#pragma unroll 4
+  for (int c = lane; c < nc; c += 64) n += keep[c] != 0 ? 1 : 0;
+  return n;
+}
+__device__ inline int wave_sum_int(int x) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
+  return x;
 }
 
-// ---- keep-lists finer than a tile: the kept rows of every participant are packed ------------
-// A sync block under sparse KV exchange sees, of a remote participant, only the rows the
-// keep-list flags.  When a flag covers whole 64-row tiles the attention kernel visits the kept
-// tiles where they are; for finer lists (down to single tokens) three small kernels first
-// gather each participant's kept rows into the front of its own segment of a packed K, V copy,
-// so that the attention kernel still walks dense tiles.  Among remote rows only membership
-// matters (a remote participant lies entirely before or entirely after the query in the
-// global order), so packing loses nothing.
+// One wavefront: cnt[n] tiles of participant n (zero from N on) -> tiles of the participants before it, cnt[N] = all.
+__device__ inline void sum_before(int (&cnt)[kMaxP + 1], int N, int lane, int32_t* kept_cum) {
+  static_assert(kMaxP == 128, "two participants per lane");
+  const int x0 = cnt[2 * lane], x1 = cnt[2 * lane + 1];
+  int incl = x0 + x1;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int up = __shfl_up(incl, o, 64);
+    if (lane >= o) incl += up;
+  }
+  const int before = incl - x0 - x1;
+  cnt[2 * lane] = before;
+  cnt[2 * lane + 1] = before + x0;
+  if (lane == 63) cnt[kMaxP] = incl;
+  if (2 * lane <= N) kept_cum[2 * lane] = before;
+  if (2 * lane + 1 <= N) kept_cum[2 * lane + 1] = before + x0;
+  if (N == kMaxP && lane == 63) kept_cum[kMaxP] = incl;
+}
 
-// Workgroup m scans participant m's flags: src_index[lo + p] = global row of its p-th kept
-// row (-1 past the last), kept_rows[m] = their number.
-__global__ __launch_bounds__(256) void scan_kept_rows_kernel(PrefillArgs a, int32_t* kept_rows, int32_t* src_index) {
-  __shared__ int wave_cnt[4];
-  const int m = blockIdx.x;
-  const int lo = a.seg.seg_off[m], hi = a.seg.seg_off[m + 1];
-  const uint8_t* keep = a.keep_chunks + a.seg.chunk_cum[m];
+// Keep chunks of whole tiles: the list of the kept tiles where they are, one wavefront per participant
+// (16 participants of 64 chunks: 22 us with one thread each, 5 us now; a launch alone takes 4 in the same trace).
+constexpr int kListWaves = 16;
+__global__ __launch_bounds__(64 * kListWaves) void build_kept_tiles_kernel(PrefillArgs a, int2* kept_tiles, int32_t* kept_cum) {
+  __shared__ int cnt[kMaxP + 1];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  int carry = 0;
-  for (int base = lo; base < hi; base += 256) {
-    const int t = base + tid;
-    const bool flag = t < hi && keep[(t - lo) / a.chunk_tokens] != 0;
-    const unsigned long long bal = __builtin_amdgcn_ballot_w64(flag);
-    const int before = __builtin_popcountll(bal & ((1ull << lane) - 1ull));
-    __syncthreads();  // wave_cnt of the previous round has been read
-    if (lane == 0) wave_cnt[wave] = __builtin_popcountll(bal);
-    __syncthreads();
-    int pos = carry + before;
-    for (int w = 0; w < wave; ++w) pos += wave_cnt[w];
-    if (flag) src_index[lo + pos] = t;
-    carry += wave_cnt[0] + wave_cnt[1] + wave_cnt[2] + wave_cnt[3];
-  }
-  for (int p = lo + carry + tid; p < hi; p += 256) src_index[p] = -1;
-  if (tid == 0) kept_rows[m] = carry;
-}
-
-// The packed rows of participant m occupy [seg_off[m], seg_off[m] + kept_rows[m]): the list
-// of their 64-row tiles (the last one ragged) and the tile count before each participant.
-__global__ __launch_bounds__(kMaxP) void build_packed_tiles_kernel(PrefillArgs a, const int32_t* kept_rows,
-                                                                   int2* kept_tiles, int32_t* kept_cum) {
-  __shared__ int cnt[kMaxP + 1];
-  const int n = threadIdx.x;
   const int N = a.seg.n;
-  const int kc = n < N ? kept_rows[n] : 0;
-  cnt[n] = (kc + kKvTile - 1) / kKvTile;
+  const int tpc = a.chunk_tokens / kKvTile;   // tiles of a chunk; the last one of a participant may have fewer
+  if (tid <= kMaxP) cnt[tid] = 0;
   __syncthreads();
-  if (n == 0) {
-    int run = 0;
-    for (int i = 0; i < N; ++i) {
-      const int c = cnt[i];
-      cnt[i] = run;
-      kept_cum[i] = run;
-      run += c;
+  for (int n = wave; n < N; n += kListWaves) {
+    const uint8_t* keep = a.keep_chunks + a.seg.chunk_cum[n];
+    const int nc = a.seg.chunk_cum[n + 1] - a.seg.chunk_cum[n];
+    int tiles = lane_flags(keep, nc, lane) * tpc;
+    if (nc > 0 && lane == 0 && keep[nc - 1]) {
+      const int len = a.seg.seg_off[n + 1] - a.seg.seg_off[n] - (nc - 1) * a.chunk_tokens;
+      tiles -= tpc - (len + kKvTile - 1) / kKvTile;
     }
-    kept_cum[N] = run;
+    tiles = wave_sum_int(tiles);
+    if (lane == 0) cnt[n] = tiles;
   }
   __syncthreads();
-  if (n < N) {
-    const int lo = a.seg.seg_off[n];
-    int w = cnt[n];
-    for (int t = 0; t < kc; t += kKvTile) kept_tiles[w++] = make_int2(lo + t, min(kKvTile, kc - t));
+  if (wave == 0) sum_before(cnt, N, lane, kept_cum);
+  __syncthreads();
+  for (int n = wave; n < N; n += kListWaves) {
+    const int lo = a.seg.seg_off[n], hi = a.seg.seg_off[n + 1];
+    const uint8_t* keep = a.keep_chunks + a.seg.chunk_cum[n];
+    const int nc = a.seg.chunk_cum[n + 1] - a.seg.chunk_cum[n];
+    int w0 = cnt[n];
+    for (int c0 = 0; c0 < nc; c0 += 64) {
+      const int c = c0 + lane;
+      const bool flag = c < nc && keep[c] != 0;
+      const unsigned long long set = __builtin_amdgcn_ballot_w64(flag);
+      if (flag) {
+        const int start = lo + c * a.chunk_tokens;
+        const int clen = min(a.chunk_tokens, hi - start);
+        int w = w0 + __builtin_popcountll(set & ((1ull << lane) - 1ull)) * tpc;
+        for (int t = 0; t < clen; t += kKvTile) kept_tiles[w++] = make_int2(start + t, min(kKvTile, clen - t));
+      }
+      w0 += __builtin_popcountll(set) * tpc;
+    }
   }
 }
 
-// Packed row p of K and V = row src_index[p] of the block's K and V (row_vecs 16-byte pieces, one per thread).
-__global__ __launch_bounds__(256) void gather_kept_rows_kernel(PrefillArgs a, int row_vecs,
-                                                               const int32_t* src_index, uint4* k_packed,
-                                                               uint4* v_packed) {
-  const int rows_per_wg = max(1, 256 / row_vecs);
-  const uint4* src = reinterpret_cast<const uint4*>(blockIdx.y == 0 ? a.k : a.v);
-  uint4* dst = blockIdx.y == 0 ? k_packed : v_packed;
-  for (int i = threadIdx.x; i < rows_per_wg * row_vecs; i += 256) {
-    const int p = blockIdx.x * rows_per_wg + i / row_vecs;
-    if (p >= a.total) break;
-    const int from = src_index[p];
-    if (from >= 0) dst[(int64_t)p * row_vecs + i % row_vecs] = src[(int64_t)from * row_vecs + i % row_vecs];
+// Keep chunks finer than a tile (down to single tokens): each participant's kept rows are gathered
+// into the front of its own segment of a packed K, V copy, so that the attention kernel still walks
+// dense tiles.  Among remote rows only membership matters (a remote participant lies entirely before or
+// entirely after the query in the global order), so packing loses nothing.
+// Workgroup (x, m, z): rows [x span, (x + 1) span) of participant m, of K (z = 0) or V.  It counts the kept
+// rows before its own by reading the participant's flags over again; span is at least a 64th of the longest
+// segment, so that this stays a few reads per flag.  The workgroups of the last x write the tile list.
+// (8 participants of 300..1500 rows of 1 KB, single tokens: a scan, a list and a gather kernel took
+// 4.8 + 4.8 + 5.2 us under a profiler that shows 4 us for an empty one; now one launch.)
+constexpr int kPackThreads = 512;
+__global__ __launch_bounds__(kPackThreads) void pack_kept_rows_kernel(PrefillArgs a, int row_vecs, int span, uint4* __restrict__ k_packed,
+                                                                      uint4* __restrict__ v_packed, int2* kept_tiles, int32_t* kept_cum) {
+  constexpr int NW = kPackThreads / 64;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int N = a.seg.n;
+  if (blockIdx.x == gridDim.x - 1) {
+    // packed rows of participant n: [seg_off[n], + kept rows), in tiles of 64 of which the last is ragged
+    __shared__ int cnt[kMaxP + 1], rows[kMaxP];
+    if (blockIdx.y != 0 || blockIdx.z != 0) return;
+    if (tid <= kMaxP) cnt[tid] = 0;
+    __syncthreads();
+    for (int n = wave; n < N; n += NW) {
+      const uint8_t* keep = a.keep_chunks + a.seg.chunk_cum[n];
+      const int nc = a.seg.chunk_cum[n + 1] - a.seg.chunk_cum[n];
+      int kept = lane_flags(keep, nc, lane) * a.chunk_tokens;
+      if (nc > 0 && lane == 0 && keep[nc - 1]) kept -= nc * a.chunk_tokens - (a.seg.seg_off[n + 1] - a.seg.seg_off[n]);
+      kept = wave_sum_int(kept);
+      if (lane == 0) {
+        rows[n] = kept;
+        cnt[n] = (kept + kKvTile - 1) / kKvTile;
+      }
+    }
+    __syncthreads();
+    if (wave == 0) sum_before(cnt, N, lane, kept_cum);
+    __syncthreads();
+    for (int n = wave; n < N; n += NW) {
+      const int lo = a.seg.seg_off[n];
+      for (int i = lane; i * kKvTile < rows[n]; i += 64) kept_tiles[cnt[n] + i] = make_int2(lo + i * kKvTile, min(kKvTile, rows[n] - i * kKvTile));
+    }
+    return;
+  }
+
+  __shared__ int wave_cnt[NW];
+  __shared__ int from[kPackThreads];   // kept rows of this round
+  const int m = blockIdx.y;
+  const int lo = a.seg.seg_off[m], hi = a.seg.seg_off[m + 1];
+  const int64_t first64 = lo + (int64_t)blockIdx.x * span;
+  if (first64 >= hi) return;
+  const int first = (int)first64, last = min(first64 + span, (int64_t)hi);
+  const uint8_t* keep = a.keep_chunks + a.seg.chunk_cum[m];
+  const uint4* __restrict__ src = reinterpret_cast<const uint4*>(blockIdx.z == 0 ? a.k : a.v);
+  uint4* __restrict__ dst = blockIdx.z == 0 ? k_packed : v_packed;
+
+  const int c_first = (first - lo) / a.chunk_tokens;   // chunk of the first row; those before it are whole
+  int n = 0;
+  for (int c = tid; c < c_first; c += kPackThreads) n += keep[c] != 0 ? 1 : 0;
+  n = wave_sum_int(n);
+  if (lane == 0) wave_cnt[wave] = n;
+  __syncthreads();
+  n = 0;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) n += wave_cnt[w];
+  int to = lo + n * a.chunk_tokens;   // packed row of the next kept one
+  if (keep[c_first]) to += first - lo - c_first * a.chunk_tokens;
+
+  for (int base = first; base < last; base += kPackThreads) {
+    const int t = base + tid;
+    const bool flag = t < last && keep[(t - lo) / a.chunk_tokens] != 0;
+    const unsigned long long set = __builtin_amdgcn_ballot_w64(flag);
+    __syncthreads();   // wave_cnt and from have been read
+    if (lane == 0) wave_cnt[wave] = __builtin_popcountll(set);
+    __syncthreads();
+    int pos = __builtin_popcountll(set & ((1ull << lane) - 1ull)), kept = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      pos += w < wave ? wave_cnt[w] : 0;
+      kept += wave_cnt[w];
+    }
+    if (flag) from[pos] = t;
+    __syncthreads();
+#pragma unroll 4
+    for (int i = tid; i < kept * row_vecs; i += kPackThreads) {
+      const int r = i / row_vecs, v = i - r * row_vecs;
+      dst[(int64_t)(to + r) * row_vecs + v] = src[(int64_t)from[r] * row_vecs + v];
+    }
+    to += kept;
   }
 }
 
 }  // namespace
 
-hipError_t launch_pack_kept_rows(const PrefillArgs& a, int row_bytes, int32_t* kept_rows, int32_t* src_index, void* k_packed,
-                                 void* v_packed, int2* kept_tiles, int32_t* kept_cum, hipStream_t s) {
-  hipLaunchKernelGGL(scan_kept_rows_kernel, dim3((unsigned)a.seg.n), dim3(256), 0, s, a, kept_rows, src_index);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(build_packed_tiles_kernel, dim3(1), dim3(kMaxP), 0, s, a, kept_rows, kept_tiles, kept_cum);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  const int row_vecs = row_bytes / 16;
-  const int rows_per_wg = row_vecs >= 256 ? 1 : 256 / row_vecs;
-  hipLaunchKernelGGL(gather_kept_rows_kernel, dim3((unsigned)((a.total + rows_per_wg - 1) / rows_per_wg), 2), dim3(256),
-                     0, s, a, row_vecs, src_index, reinterpret_cast<uint4*>(k_packed), reinterpret_cast<uint4*>(v_packed));
+hipError_t launch_pack_kept_rows(const PrefillArgs& a, int row_bytes, void* k_packed, void* v_packed, int2* kept_tiles,
+                                 int32_t* kept_cum, hipStream_t s) {
+  int max_len = 1;
+  for (int n = 0; n < a.seg.n; ++n) max_len = max(max_len, a.seg.seg_off[n + 1] - a.seg.seg_off[n]);
+  const int span = (max_len - 1) / 4096 * 64 + 64;
+  const dim3 grid((unsigned)((max_len - 1) / span + 2), (unsigned)a.seg.n, 2);
+  hipLaunchKernelGGL(pack_kept_rows_kernel, grid, dim3(kPackThreads), 0, s, a, row_bytes / 16, span,
+                     reinterpret_cast<uint4*>(k_packed), reinterpret_cast<uint4*>(v_packed), kept_tiles, kept_cum);
   return hipGetLastError();
 }
 
@@ -728,7 +769,7 @@ hipError_t launch_prefill_mfma(const PrefillArgs& a_in, int n_blocks, hipStream_
 
 hipError_t launch_build_kept_tiles(const PrefillArgs& a, int2* kept_tiles, int32_t* kept_cum,
                                    hipStream_t s) {
-  hipLaunchKernelGGL(build_kept_tiles_kernel, dim3(1), dim3(kMaxP), 0, s, a, kept_tiles, kept_cum);
+  hipLaunchKernelGGL(build_kept_tiles_kernel, dim3(1), dim3(64 * kListWaves), 0, s, a, kept_tiles, kept_cum);
   return hipGetLastError();
 }
 

@@ -147,3 +147,27 @@ def test_bf16_prefill_launches(layout, D, scale):
         got = prefill(q, k, v, seg, Hq=Hq, Hkv=Hkv, D=D, H=0, block=0, dtype=BF16, causal=causal, sync_override=sync, scale=scale)
         ref = oracle.attend_rows(q, k, v, seg, rows, heads, is_sync=bool(sync), causal=causal, scale=scale if scale else None)
         check(got[rows, heads], ref, BF16, what)
+
+
+# more chunks than a wavefront has lanes, rows past the 4096 where a workgroup's share grows, chunks longer than
+# a segment, kept last chunks that end inside a tile; as many participants as there can be
+COMPACTION = {"long": [4500, 0, 1, 70, 511, 512, 513, 4096], "many": [1 + 5 * (i % 7) for i in range(fa.FEDATTN_MAX_PARTICIPANTS)]}
+
+
+@pytest.mark.parametrize("layout", sorted(COMPACTION))
+@pytest.mark.parametrize("chunk", [1, 3, 513, 64, 128, 8192])
+def test_keep_list_compaction(layout, chunk):
+    seg = np.concatenate([[0], np.cumsum(COMPACTION[layout])]).astype(np.int32)
+    Hq, Hkv, D = 2, 1, 64
+    q, k, v = rand_block(44, int(seg[-1]), Hq, Hkv, D)
+    rows, heads = fi.sample_rows(seg, Hq, 64, fi.DEFAULT_SEED, salt=chunk, tile=64, max_boundary_rows=200)
+    n_flags = int(fi.chunk_counts(np.diff(seg), chunk).sum())
+    for share in (0.4, 1.0):
+        flags = (np.random.default_rng(8).random(n_flags) < share).astype(np.uint8)
+        kt = oracle.expand_keep_chunks(flags, seg, chunk)
+        for causal in (True, False):
+            what = "compaction %s chunk=%d share=%.1f causal=%d" % (layout, chunk, share, causal)
+            say(what)
+            got = prefill(q, k, v, seg, Hq=Hq, Hkv=Hkv, D=D, H=1, block=0, dtype=BF16, causal=causal, keep_chunks=flags, chunk_tokens=chunk)
+            ref = oracle.attend_rows(q, k, v, seg, rows, heads, is_sync=True, causal=causal, keep_tok=kt)
+            check(got[rows, heads], ref, BF16, what)
