@@ -33,6 +33,17 @@ constexpr int decode_stages() { return D > 192 ? 2 : 3; }
 template <int D>
 constexpr int decode_smem_bytes() { return decode_stages<D>() * 2 * KvTile<D, 0>::TILEB; }
 
+// Chunks whose partials the merge inside the kernel has in flight at once.
+constexpr int kMergeBatch = 8;
+
+// Two floats at an 8-byte aligned address, coherent at the device.
+__device__ inline void store_pair_agent(float* p, float x, float y) {
+  __hip_atomic_store(reinterpret_cast<uint64_t*>(p), __builtin_bit_cast(uint64_t, f32x2{x, y}), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline f32x2 load_pair_agent(const float* p) {
+  return __builtin_bit_cast(f32x2, __hip_atomic_load(reinterpret_cast<const uint64_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
+
 // COLSPLIT = false (at most 16 query columns, e.g. the G heads of one participant in a
 // local block): 4 wavefronts, wavefront w takes tile rows 16w..16w+15; they are merged
 // through LDS at the end.  COLSPLIT = true (up to 64 query columns, sync blocks): 8
@@ -278,6 +289,7 @@ __global__ __launch_bounds__(COLSPLIT ? 512 : 256, 1) void decode_stream_kernel(
     }
   }
 
+  asm volatile("" : "+v"(cnt_found));   // its wait belongs here: behind the exchange it would wait for that, too
   // Not this call's yet: make it so.  The exchange fails only if another workgroup of the segment came
   // first, and it has completed (with the partial stores) before this workgroup counts itself in.
   if (set_up && tid == 0 && cnt_found >> 16 != a.ticket)
@@ -329,8 +341,8 @@ __global__ __launch_bounds__(COLSPLIT ? 512 : 256, 1) void decode_stream_kernel(
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt) *reinterpret_cast<f32x4*>(o_s + l16 * OPAD + 16 * dt + 4 * kg) = o[dt] * f;
     __syncthreads();
-    const int n_cols = min(QCOLS, a.cols - blockIdx.y * QCOLS);
-    const int col0 = blockIdx.y * QCOLS;
+    const int col0 = (int)blockIdx.y * QCOLS;
+    const int n_cols = min(QCOLS, a.cols - col0);
     const int64_t prow0 = ((int64_t)g * a.n_chunks + gc) * a.cols + col0;
     const float* o_all = reinterpret_cast<const float*>(smem);
     // local block with the combine fused in: query column cl is head g G + cl of participant m
@@ -384,16 +396,12 @@ __global__ __launch_bounds__(COLSPLIT ? 512 : 256, 1) void decode_stream_kernel(
       const f32x4 v3 = *reinterpret_cast<const f32x4*>(src + 48 * OPAD);
       const f32x4 sum = (v0 + v1) + (v2 + v3);
       float* dst = part_o + (prow0 + cl) * D + 4 * d4;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) __hip_atomic_store(dst + e, sum[e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      store_pair_agent(dst, sum[0], sum[1]);
+      store_pair_agent(dst + 2, sum[2], sum[3]);
     }
-    if (tid < n_cols) {
-      __hip_atomic_store(part_ml + (prow0 + tid) * 2,
-                         fmaxf(fmaxf(m_s[0][tid], m_s[1][tid]), fmaxf(m_s[2][tid], m_s[3][tid])), __ATOMIC_RELAXED,
-                         __HIP_MEMORY_SCOPE_AGENT);
-      __hip_atomic_store(part_ml + (prow0 + tid) * 2 + 1, l_s[0][tid] + l_s[1][tid] + l_s[2][tid] + l_s[3][tid],
-                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    if (tid < n_cols)
+      store_pair_agent(part_ml + (prow0 + tid) * 2, fmaxf(fmaxf(m_s[0][tid], m_s[1][tid]), fmaxf(m_s[2][tid], m_s[3][tid])),
+                       l_s[0][tid] + l_s[1][tid] + l_s[2][tid] + l_s[3][tid]);
     __shared__ int last_s;
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
     wait_vmcnt<0>();
@@ -408,26 +416,47 @@ __global__ __launch_bounds__(COLSPLIT ? 512 : 256, 1) void decode_stream_kernel(
     }
     __syncthreads();
     if (!last_s) return;
+    // All partials of kMergeBatch chunks are requested before the first is looked at: one round trip to
+    // memory for them together (one chunk at a time, for the maximum and again for the sum, it was two per
+    // chunk: a third of the time of a call on short caches).
     const int64_t crow0 = ((int64_t)g * a.n_chunks + chunk0) * a.cols + col0;  // chunk 0 of the segment, column 0
     const int64_t cstride = a.cols;                                            // partial rows between chunks
     for (int idx = tid; idx < n_cols * (D / 4); idx += 256) {
       const int cl = idx / (D / 4), d4 = idx % (D / 4);
       const float* ml = part_ml + (crow0 + cl) * 2;
-      float mm = -INFINITY;
-      for (int cc = 0; cc < n_seg_chunks; ++cc)
-        mm = fmaxf(mm, __hip_atomic_load(ml + cc * cstride * 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-      const float mu = (mm == -INFINITY) ? 0.f : mm;
-      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-      float den = 0.f;
       const float* po = part_o + (crow0 + cl) * D + 4 * d4;
-      for (int cc = 0; cc < n_seg_chunks; ++cc) {
-        const float mc = __hip_atomic_load(ml + cc * cstride * 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const float lc = __hip_atomic_load(ml + cc * cstride * 2 + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const float w = __builtin_amdgcn_exp2f(mc - mu);
-        den = fmaf(lc, w, den);
+      float mm = -INFINITY, den = 0.f;
+      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+      for (int c0 = 0; c0 < n_seg_chunks; c0 += kMergeBatch) {
+        const int nb = min(kMergeBatch, n_seg_chunks - c0);
+        f32x2 mls[kMergeBatch], lo[kMergeBatch], hi[kMergeBatch];
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-          acc[e] = fmaf(__hip_atomic_load(po + cc * cstride * D + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), w, acc[e]);
+        for (int u = 0; u < kMergeBatch; ++u) {
+          mls[u] = f32x2{-INFINITY, 0.f};
+          lo[u] = hi[u] = f32x2{0.f, 0.f};
+          if (u < nb) {
+            mls[u] = load_pair_agent(ml + (c0 + u) * cstride * 2);
+            lo[u] = load_pair_agent(po + (c0 + u) * cstride * D);
+            hi[u] = load_pair_agent(po + (c0 + u) * cstride * D + 2);
+          }
+        }
+        float m_new = mm;
+#pragma unroll
+        for (int u = 0; u < kMergeBatch; ++u) m_new = fmaxf(m_new, mls[u][0]);
+        const float mu = (m_new == -INFINITY) ? 0.f : m_new;
+        const float before = __builtin_amdgcn_exp2f(mm - mu);
+        mm = m_new;
+        den *= before;
+        acc *= before;
+#pragma unroll
+        for (int u = 0; u < kMergeBatch; ++u) {
+          const float w = __builtin_amdgcn_exp2f(mls[u][0] - mu);
+          den = fmaf(mls[u][1], w, den);
+          acc[0] = fmaf(lo[u][0], w, acc[0]);
+          acc[1] = fmaf(lo[u][1], w, acc[1]);
+          acc[2] = fmaf(hi[u][0], w, acc[2]);
+          acc[3] = fmaf(hi[u][1], w, acc[3]);
+        }
       }
       const f32x4 val = acc * (den > 0.f ? 1.f / den : 0.f);
       const bf16x4 w4 = {(bf16_t)val[0], (bf16_t)val[1], (bf16_t)val[2], (bf16_t)val[3]};
