@@ -98,6 +98,8 @@ int decode_chunk_rows(int64_t total_rows, int Hkv) {
   return (int)(rows < kKvTile ? kKvTile : rows);
 }
 
+constexpr int64_t kMaxMergeTrips = 4;
+
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 // prefill workspace: [kept_cum: (kMaxP+1) int32, padded][kept_tiles: int2 per 64-row tile]
@@ -408,7 +410,7 @@ static fedattn_status run_decode(bool fused, const fedattn_params* params, int32
   bool built[2] = {false, false};
   uint64_t* counters = nullptr;
   const uint64_t ticket = next_ticket();
-  bool counters_ready = false;   // a launch of this call has set them up, and every launch leaves them at zero
+  bool counters_ready[2] = {false, false};   // a launch of this call and kind has set its counters up, and every launch leaves them at zero
   int slices = 1;            // blocks in flight at once, each in its own slice of the workspace
   size_t slice_bytes = 0;
   const size_t need = decode_ws_bytes(params, capacity);
@@ -427,7 +429,7 @@ static fedattn_status run_decode(bool fused, const fedattn_params* params, int32
       slices = (int)(fit < (size_t)kMaxFusedBlocks ? fit : (size_t)kMaxFusedBlocks);
       if (slices > n_blocks) slices = n_blocks;
     }
-    // local blocks count their chunks in at the end of their slice
+    // blocks count their chunks in at the end of their slice
     counters = reinterpret_cast<uint64_t*>(reinterpret_cast<unsigned char*>(workspace) + need - decode_counter_bytes(params));
   }
   fused = fused && split;
@@ -472,14 +474,26 @@ static fedattn_status run_decode(bool fused, const fedattn_params* params, int32
         a.part_o = reinterpret_cast<float*>(workspace);
         a.part_ml = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(workspace) + o_bytes);
         a.counters = counters;
-        // in-kernel merge: the workgroups of a segment write its output rows, so every segment
-        // needs one (an empty segment's zero rows come from the separate combine kernel)
-        bool all_have_rows = true, one_chunk = true;
+        // Merge inside the split kernel, by the workgroup that finishes last: up to 16 query columns
+        // share a workgroup per chunk, and every output row needs a chunk to come from (an empty
+        // segment's zero rows come from the separate combine kernel).  It makes a round trip to memory
+        // per kMergeBatch chunks and 256 x 4 elements, about 0.9 us, where the combine kernel costs
+        // 3.5 us for its launch (bf16 calls of one block, combined apart and inside: 1 x 2048 rows, 8/2 heads
+        // of 128, 4 trips 10.8 and 9.3 us; 1 x 4096 rows, 8 trips 11.1 and 13.7; sync blocks of 1 x 64 rows
+        // 12.0 and 8.3, of 3 x 64..400 rows 11.0 and 9.9, of 4 x 1000 rows, 16 trips 11.5 and 22.3).
+        bool all_have_rows = true;
+        int64_t most = 0;   // chunks merged into one row
         for (int n = 0; n < N; ++n) {
           all_have_rows = all_have_rows && seg_lens[n] > 0;
-          one_chunk = one_chunk && seg_lens[n] <= a.chunk_rows;
+          const int64_t c = ((int64_t)seg_lens[n] + a.chunk_rows - 1) / a.chunk_rows;
+          most = c > most ? c : most;
         }
-        a.merge_in_kernel = !sync && all_have_rows && (params->dtype == FEDATTN_F32 ? one_chunk : a.cols <= 16) ? 1 : 0;
+        if (sync) {
+          all_have_rows = chunks > 0;
+          most = chunks;
+        }
+        const int64_t trips = ((int64_t)a.cols * (a.D / 4) + 255) / 256 * ((most + kMergeBatch - 1) / kMergeBatch);
+        a.merge_in_kernel = all_have_rows && a.cols <= 16 && (most == 1 || trips <= kMaxMergeTrips) ? 1 : 0;
       }
       a.q_block_bytes = q_block_stride * (int64_t)esize;
       a.cache_block_bytes = cache_block_stride * (int64_t)esize;
@@ -511,8 +525,8 @@ static fedattn_status run_decode(bool fused, const fedattn_params* params, int32
         first = b;
         if (cnt == 0) continue;
         a.q = q; a.out = out; a.k_cache = k_cache; a.v_cache = v_cache;
-        a.ticket = counters_ready ? 0 : ticket;   // no later launch of this kind has more slices than the first
-        counters_ready = counters_ready || a.merge_in_kernel;
+        a.ticket = counters_ready[kind] ? 0 : ticket;   // no later launch of this kind has more slices than the first
+        counters_ready[kind] = true;
         hipError_t e = launch_decode(a, params->dtype, true, cnt, reinterpret_cast<hipStream_t>(stream));
         if (e != hipSuccess) return fail(FEDATTN_ELAUNCH, "decode (fused, %d blocks): %s", cnt, hipGetErrorString(e));
       }
@@ -528,8 +542,8 @@ static fedattn_status run_decode(bool fused, const fedattn_params* params, int32
     a.out = reinterpret_cast<unsigned char*>(out) + (size_t)b * (size_t)q_block_stride * esize;
     a.k_cache = reinterpret_cast<const unsigned char*>(k_cache) + (size_t)b * (size_t)cache_block_stride * esize;
     a.v_cache = reinterpret_cast<const unsigned char*>(v_cache) + (size_t)b * (size_t)cache_block_stride * esize;
-    a.ticket = counters_ready ? 0 : ticket;
-    counters_ready = counters_ready || a.merge_in_kernel;
+    a.ticket = counters_ready[sync ? 1 : 0] ? 0 : ticket;
+    counters_ready[sync ? 1 : 0] = true;
     hipError_t e = launch_decode(a, params->dtype, split, 1, reinterpret_cast<hipStream_t>(stream));
     if (e != hipSuccess) return fail(FEDATTN_ELAUNCH, "decode (block %d): %s", block_idx0 + b, hipGetErrorString(e));
   }

@@ -15,8 +15,9 @@ namespace fedattn {
 constexpr int kMaxP = FEDATTN_MAX_PARTICIPANTS;
 constexpr int kKvTile = 64;    // KV rows per MFMA prefill tile; also the keep-list tile
 constexpr int kWaveRows = 32;  // query rows per wave in the MFMA prefill kernel
-constexpr int kMaxOrderedTiles = 512;
-constexpr int kMaxFusedBlocks = 64;    // blocks of one fused decode launch  // query tiles of a launch that assigns them through an explicit order
+constexpr int kMaxOrderedTiles = 512;  // query tiles of a launch that assigns them through an explicit order
+constexpr int kMaxFusedBlocks = 64;    // blocks of one fused decode launch
+constexpr int kMergeBatch = 8;         // chunks whose partials a decode merge has in flight at once
 
 // Segment layout of the global sequence, passed by value in the kernel arguments
 // (read with scalar loads; no device copy of host arrays is needed).
@@ -71,10 +72,9 @@ struct DecodeArgs {
   void* out;
   float* part_o;            // [Hkv, n_chunks, cols, D] fp32: sum_j p_j v_j with p_j = 2^(s_j - m), unnormalised
   float* part_ml;           // [Hkv, n_chunks, cols, 2] (m in log2 domain, l)
-  uint64_t* counters;       // [Hkv, N] chunks counted in per (KV head, segment), zero after a launch
+  uint64_t* counters;       // [Hkv, N] chunks counted in per (KV head, segment), sync block: [Hkv, 0]; zero after a launch
   uint64_t ticket;          // first launch of a call: the call's number, 48 bits, marks the counters as set up; later ones: 0
-  int32_t merge_in_kernel;  // local block: the split kernel writes the output rows itself (no combine launch), bf16
-                            // through the last chunk of a segment, fp32 because every segment is one chunk
+  int32_t merge_in_kernel;  // the split kernel writes the output rows itself (no combine launch)
   int32_t N, Hq, Hkv, D;
   int32_t is_sync;
   int32_t chunk_rows;       // cache rows per workgroup

@@ -12,7 +12,8 @@
 // v_mfma_f32_16x16x16_bf16, whose k-slots are exactly the 4 rows per lane that the
 // first product leaves in a lane, with V^T operands from transposing LDS reads.  Each
 // wavefront keeps its own online softmax per query column; the wavefronts are merged
-// at the end and a second small kernel merges the chunks:
+// at the end, and the chunks by the workgroup that finishes last (few columns and chunks) or
+// by a second small kernel:
 //   o = sum_c O_c 2^(m_c - m) / sum_c l_c 2^(m_c - m).
 #include "common.h"
 #include "decode_walk.h"
@@ -32,17 +33,6 @@ constexpr int decode_stages() { return D > 192 ? 2 : 3; }
 
 template <int D>
 constexpr int decode_smem_bytes() { return decode_stages<D>() * 2 * KvTile<D, 0>::TILEB; }
-
-// Chunks whose partials the merge inside the kernel has in flight at once.
-constexpr int kMergeBatch = 8;
-
-// Two floats at an 8-byte aligned address, coherent at the device.
-__device__ inline void store_pair_agent(float* p, float x, float y) {
-  __hip_atomic_store(reinterpret_cast<uint64_t*>(p), __builtin_bit_cast(uint64_t, f32x2{x, y}), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ inline f32x2 load_pair_agent(const float* p) {
-  return __builtin_bit_cast(f32x2, __hip_atomic_load(reinterpret_cast<const uint64_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-}
 
 // COLSPLIT = false (at most 16 query columns, e.g. the G heads of one participant in a
 // local block): 4 wavefronts, wavefront w takes tile rows 16w..16w+15; they are merged
@@ -99,9 +89,8 @@ __global__ __launch_bounds__(COLSPLIT ? 512 : 256, 1) void decode_stream_kernel(
   const int rh = COLSPLIT ? wave >> 2 : 0;   // row half of the tile (column split only)
   const int cb = blockIdx.y * QCOLS + (COLSPLIT ? 16 * (wave & 3) : 0);  // first query column of this wavefront
 
-  const int N = a.N;
   const DecodeChunk ch = find_decode_chunk(a, gc, lane);
-  const int m = ch.m, chunk0 = ch.chunk0, n_seg_chunks = ch.n_seg_chunks;
+  const int m = ch.m;
   const int own_len = ch.own_len, rem_len = ch.rem_len, seg_row0 = ch.seg_row0;
   const int r_lo = ch.r_lo, r_hi = ch.r_hi, min_limit = ch.min_limit;
   const bool sync = a.is_sync != 0;
@@ -146,14 +135,12 @@ __global__ __launch_bounds__(COLSPLIT ? 512 : 256, 1) void decode_stream_kernel(
 #pragma unroll
   for (int t = 0; t < kDecodeStages - 1; ++t)
     if (t < nt) issue(t);
-  // Chunk counter of the segment (merge below): (ticket of the call) << 16 | chunks counted in.  Every
-  // launch leaves it at zero.  What it holds before a call does not matter: in the call's first launch
-  // (ticket set) the first workgroups of the segment put the ticket there.  The value is requested here,
-  // behind the first tiles (ahead of them it cost 0.4 us of an 18 us launch), and looked at after the stream.
-  const bool set_up = !COLSPLIT && a.merge_in_kernel && n_seg_chunks > 1 && a.ticket != 0;
-  uint64_t* cnt = counters + g * N + m;  // at most 16 columns: one workgroup per chunk
+  // The chunk counter is requested here, behind the first tiles (ahead of them it cost 0.4 us of an 18 us
+  // launch), and looked at after the stream.
+  const MergeSet ms = merge_set(a, ch, g, counters);
+  const bool set_up = !COLSPLIT && a.merge_in_kernel && ms.count > 1 && a.ticket != 0;
   uint64_t cnt_found = 0;
-  if (set_up) cnt_found = __hip_atomic_load(cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (set_up) cnt_found = __hip_atomic_load(ms.cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 
   // LDS -> A operand of S^T: lane (row l16 of a 16-row sub-tile, k-group kg) reads chunk
   // 4 st + kg; the sub-tile's first row goes in the address as a multiple of 16 rows,
@@ -290,11 +277,7 @@ __global__ __launch_bounds__(COLSPLIT ? 512 : 256, 1) void decode_stream_kernel(
   }
 
   asm volatile("" : "+v"(cnt_found));   // its wait belongs here: behind the exchange it would wait for that, too
-  // Not this call's yet: make it so.  The exchange fails only if another workgroup of the segment came
-  // first, and it has completed (with the partial stores) before this workgroup counts itself in.
-  if (set_up && tid == 0 && cnt_found >> 16 != a.ticket)
-    (void)__hip_atomic_compare_exchange_strong(cnt, &cnt_found, a.ticket << 16, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                               __HIP_MEMORY_SCOPE_AGENT);
+  if (set_up) claim_counter(ms, cnt_found, a.ticket);
   l_run = sum_over_kgroups(l_run);
   if constexpr (COLSPLIT) {
     // ---- merge the two row halves of a column block: half 1 hands (m, l, O) to half 0 -------
@@ -341,53 +324,11 @@ __global__ __launch_bounds__(COLSPLIT ? 512 : 256, 1) void decode_stream_kernel(
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt) *reinterpret_cast<f32x4*>(o_s + l16 * OPAD + 16 * dt + 4 * kg) = o[dt] * f;
     __syncthreads();
-    const int col0 = (int)blockIdx.y * QCOLS;
-    const int n_cols = min(QCOLS, a.cols - col0);
-    const int64_t prow0 = ((int64_t)g * a.n_chunks + gc) * a.cols + col0;
+    const int64_t prow0 = ((int64_t)g * a.n_chunks + gc) * a.cols;   // at most 16 columns: one workgroup per chunk
     const float* o_all = reinterpret_cast<const float*>(smem);
-    // local block with the combine fused in: query column cl is head g G + cl of participant m
-    uint16_t* out_rows = reinterpret_cast<uint16_t*>(out_ptr) + ((int64_t)m * Hq + g * G + col0) * D;
-    if (a.merge_in_kernel && n_seg_chunks == 1) {
-      // the segment's only chunk: normalise and write the output rows, no partials
-      for (int idx = tid; idx < n_cols * (D / 4); idx += 256) {
-        const int cl = idx / (D / 4), d4 = idx % (D / 4);
-        const float* src = o_all + cl * OPAD + 4 * d4;
-        const f32x4 v0 = *reinterpret_cast<const f32x4*>(src);
-        const f32x4 v1 = *reinterpret_cast<const f32x4*>(src + 16 * OPAD);
-        const f32x4 v2 = *reinterpret_cast<const f32x4*>(src + 32 * OPAD);
-        const f32x4 v3 = *reinterpret_cast<const f32x4*>(src + 48 * OPAD);
-        const float den = l_s[0][cl] + l_s[1][cl] + l_s[2][cl] + l_s[3][cl];
-        const f32x4 val = ((v0 + v1) + (v2 + v3)) * (den > 0.f ? 1.f / den : 0.f);
-        const bf16x4 w = {(bf16_t)val[0], (bf16_t)val[1], (bf16_t)val[2], (bf16_t)val[3]};
-        *reinterpret_cast<u32x2*>(out_rows + cl * D + 4 * d4) = __builtin_bit_cast(u32x2, w);
-      }
-      return;
-    }
-    if (!a.merge_in_kernel) {
-      for (int idx = tid; idx < n_cols * (D / 4); idx += 256) {
-        const int cl = idx / (D / 4), d4 = idx % (D / 4);
-        const float* src = o_all + cl * OPAD + 4 * d4;
-        const f32x4 v0 = *reinterpret_cast<const f32x4*>(src);
-        const f32x4 v1 = *reinterpret_cast<const f32x4*>(src + 16 * OPAD);
-        const f32x4 v2 = *reinterpret_cast<const f32x4*>(src + 32 * OPAD);
-        const f32x4 v3 = *reinterpret_cast<const f32x4*>(src + 48 * OPAD);
-        *reinterpret_cast<f32x4*>(part_o + (prow0 + cl) * D + 4 * d4) = (v0 + v1) + (v2 + v3);
-      }
-      if (tid < n_cols) {
-        part_ml[(prow0 + tid) * 2] = fmaxf(fmaxf(m_s[0][tid], m_s[1][tid]), fmaxf(m_s[2][tid], m_s[3][tid]));
-        part_ml[(prow0 + tid) * 2 + 1] = l_s[0][tid] + l_s[1][tid] + l_s[2][tid] + l_s[3][tid];
-      }
-      return;
-    }
-
-    // ---- fused combine: the workgroup that finishes a segment's last chunk merges them ------
-    // The partials travel between workgroups inside one launch, so they are written and read
-    // with device-scope atomic accesses (coherent at the device whatever caches sit in
-    // between) rather than with plain accesses plus cache-wide write-back and invalidate
-    // fences, which cost far more than the few KB exchanged here.  A workgroup counts itself
-    // in only after all its partial stores have completed (vmcnt = 0 in every wavefront,
-    // then the barrier); the workgroup that finds all other chunks counted in merges.
-    for (int idx = tid; idx < n_cols * (D / 4); idx += 256) {
+    uint16_t* out = reinterpret_cast<uint16_t*>(out_ptr);
+    const bool only = a.merge_in_kernel && ms.count == 1;   // nothing to merge: normalise and write the output rows
+    for (int idx = tid; idx < a.cols * (D / 4); idx += 256) {
       const int cl = idx / (D / 4), d4 = idx % (D / 4);
       const float* src = o_all + cl * OPAD + 4 * d4;
       const f32x4 v0 = *reinterpret_cast<const f32x4*>(src);
@@ -395,73 +336,20 @@ __global__ __launch_bounds__(COLSPLIT ? 512 : 256, 1) void decode_stream_kernel(
       const f32x4 v2 = *reinterpret_cast<const f32x4*>(src + 32 * OPAD);
       const f32x4 v3 = *reinterpret_cast<const f32x4*>(src + 48 * OPAD);
       const f32x4 sum = (v0 + v1) + (v2 + v3);
-      float* dst = part_o + (prow0 + cl) * D + 4 * d4;
-      store_pair_agent(dst, sum[0], sum[1]);
-      store_pair_agent(dst + 2, sum[2], sum[3]);
+      if (only) {
+        const float den = l_s[0][cl] + l_s[1][cl] + l_s[2][cl] + l_s[3][cl];
+        store_out4(out + decode_out_row(a, g, m, cl) * D + 4 * d4, sum * (den > 0.f ? 1.f / den : 0.f));
+      } else {
+        float* dst = part_o + (prow0 + cl) * D + 4 * d4;
+        store_pair_agent(dst, sum[0], sum[1]);
+        store_pair_agent(dst + 2, sum[2], sum[3]);
+      }
     }
-    if (tid < n_cols)
+    if (only) return;
+    if (tid < a.cols)
       store_pair_agent(part_ml + (prow0 + tid) * 2, fmaxf(fmaxf(m_s[0][tid], m_s[1][tid]), fmaxf(m_s[2][tid], m_s[3][tid])),
                        l_s[0][tid] + l_s[1][tid] + l_s[2][tid] + l_s[3][tid]);
-    __shared__ int last_s;
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-    wait_vmcnt<0>();
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-    __syncthreads();
-    if (tid == 0) {
-      const uint64_t seen = __hip_atomic_fetch_add(cnt, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      const int last = (int)(seen & 0xffff) == n_seg_chunks - 1;
-      // left at zero: a launch replayed from a graph comes with the same ticket
-      if (last) __hip_atomic_store(cnt, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      last_s = last;
-    }
-    __syncthreads();
-    if (!last_s) return;
-    // All partials of kMergeBatch chunks are requested before the first is looked at: one round trip to
-    // memory for them together (one chunk at a time, for the maximum and again for the sum, it was two per
-    // chunk: a third of the time of a call on short caches).
-    const int64_t crow0 = ((int64_t)g * a.n_chunks + chunk0) * a.cols + col0;  // chunk 0 of the segment, column 0
-    const int64_t cstride = a.cols;                                            // partial rows between chunks
-    for (int idx = tid; idx < n_cols * (D / 4); idx += 256) {
-      const int cl = idx / (D / 4), d4 = idx % (D / 4);
-      const float* ml = part_ml + (crow0 + cl) * 2;
-      const float* po = part_o + (crow0 + cl) * D + 4 * d4;
-      float mm = -INFINITY, den = 0.f;
-      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-      for (int c0 = 0; c0 < n_seg_chunks; c0 += kMergeBatch) {
-        const int nb = min(kMergeBatch, n_seg_chunks - c0);
-        f32x2 mls[kMergeBatch], lo[kMergeBatch], hi[kMergeBatch];
-#pragma unroll
-        for (int u = 0; u < kMergeBatch; ++u) {
-          mls[u] = f32x2{-INFINITY, 0.f};
-          lo[u] = hi[u] = f32x2{0.f, 0.f};
-          if (u < nb) {
-            mls[u] = load_pair_agent(ml + (c0 + u) * cstride * 2);
-            lo[u] = load_pair_agent(po + (c0 + u) * cstride * D);
-            hi[u] = load_pair_agent(po + (c0 + u) * cstride * D + 2);
-          }
-        }
-        float m_new = mm;
-#pragma unroll
-        for (int u = 0; u < kMergeBatch; ++u) m_new = fmaxf(m_new, mls[u][0]);
-        const float mu = (m_new == -INFINITY) ? 0.f : m_new;
-        const float before = __builtin_amdgcn_exp2f(mm - mu);
-        mm = m_new;
-        den *= before;
-        acc *= before;
-#pragma unroll
-        for (int u = 0; u < kMergeBatch; ++u) {
-          const float w = __builtin_amdgcn_exp2f(mls[u][0] - mu);
-          den = fmaf(mls[u][1], w, den);
-          acc[0] = fmaf(lo[u][0], w, acc[0]);
-          acc[1] = fmaf(lo[u][1], w, acc[1]);
-          acc[2] = fmaf(hi[u][0], w, acc[2]);
-          acc[3] = fmaf(hi[u][1], w, acc[3]);
-        }
-      }
-      const f32x4 val = acc * (den > 0.f ? 1.f / den : 0.f);
-      const bf16x4 w4 = {(bf16_t)val[0], (bf16_t)val[1], (bf16_t)val[2], (bf16_t)val[3]};
-      *reinterpret_cast<u32x2*>(out_rows + cl * D + 4 * d4) = __builtin_bit_cast(u32x2, w4);
-    }
+    if (a.merge_in_kernel) merge_if_last(a, ms, g, m, D, part_o, part_ml, out);
   }
 }
 
@@ -542,12 +430,7 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(DecodeArgs a) {
       const f32x4 sum = (acc_s[0][d4] + acc_s[1][d4]) + (acc_s[2][d4] + acc_s[3][d4]);
       const f32x4 val = sum * (dn > 0.f ? 1.f / dn : 0.f);
       T* out = reinterpret_cast<T*>(out_ptr) + ((int64_t)n * a.Hq + h) * D + 4 * d4;
-      if constexpr (sizeof(T) == 2) {
-        const bf16x4 w4 = {(bf16_t)val[0], (bf16_t)val[1], (bf16_t)val[2], (bf16_t)val[3]};
-        *reinterpret_cast<u32x2*>(out) = __builtin_bit_cast(u32x2, w4);
-      } else {
-        *reinterpret_cast<f32x4*>(out) = val;
-      }
+      store_out4(out, val);
     }
     return;
   }
@@ -587,12 +470,7 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(DecodeArgs a) {
     const f32x4 sum = (acc_s[0][d4] + acc_s[1][d4]) + (acc_s[2][d4] + acc_s[3][d4]);
     const f32x4 val = sum * (dn > 0.f ? 1.f / dn : 0.f);
     T* out = reinterpret_cast<T*>(out_ptr) + ((int64_t)n * a.Hq + h) * D + 4 * d4;
-    if constexpr (sizeof(T) == 2) {
-      const bf16x4 w4 = {(bf16_t)val[0], (bf16_t)val[1], (bf16_t)val[2], (bf16_t)val[3]};
-      *reinterpret_cast<u32x2*>(out) = __builtin_bit_cast(u32x2, w4);
-    } else {
-      *reinterpret_cast<f32x4*>(out) = val;
-    }
+    store_out4(out, val);
   }
 }
 

@@ -6,8 +6,8 @@
 // group, where they are the B operand of O^T += V^T P^T as they stand (layouts as in prefill_f32.hip).
 // A 64-row tile costs a CU 16 D NQ matrix cycles and 512 D bytes of loads, so up to 64 columns the
 // chip is bound by memory, and short caches by the launches: 5 participants with 200..1500 rows,
-// 8/2 heads of 64, one local and one sync block (6 MB): 26 us with the two combine launches, where one
-// wavefront per (participant, head) took 1525 us.
+// 8/2 heads of 64, one local and one sync block (6 MB): 21 us, where one wavefront per (participant, head)
+// took 1525 us.
 #include "common.h"
 #include "decode_walk.h"
 #include "mfma_tile.h"
@@ -47,6 +47,7 @@ __global__ __launch_bounds__(256, 1) void decode_f32_kernel(DecodeArgs a) {
   float* out_ptr = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(a.out) + blk * a.q_block_bytes);
   float* part_o = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(a.part_o) + bz * a.slice_bytes);
   float* part_ml = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(a.part_ml) + bz * a.slice_bytes);
+  uint64_t* counters = reinterpret_cast<uint64_t*>(reinterpret_cast<unsigned char*>(a.counters) + bz * a.slice_bytes);
 
   const int Hq = a.Hq, Hkv = a.Hkv, D = a.D;
   const int G = Hq / Hkv;
@@ -93,6 +94,10 @@ __global__ __launch_bounds__(256, 1) void decode_f32_kernel(DecodeArgs a) {
       q[iq][s] = 16 * s + 4 * kg < D ? *reinterpret_cast<const f32x4*>(qrow + 16 * s) : f32x4{0.f, 0.f, 0.f, 0.f};
   }
   issue(0);
+  const MergeSet ms = merge_set(a, ch, g, counters);
+  const bool set_up = NQ == 1 && a.merge_in_kernel && ms.count > 1 && a.ticket != 0;
+  uint64_t cnt_found = 0;
+  if (set_up) cnt_found = __hip_atomic_load(ms.cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 
   const int k_addr = (16 * wave + l16) * ROWB;
   const int k_swz = l16 & 7;
@@ -169,6 +174,7 @@ __global__ __launch_bounds__(256, 1) void decode_f32_kernel(DecodeArgs a) {
       }
   }
 
+  if (set_up) claim_counter(ms, cnt_found, a.ticket);
   // merge the 4 wavefronts through LDS, each taking every fourth slice of the head dimension
   __syncthreads();
   f32x4* xo = reinterpret_cast<f32x4*>(smem) + lane;
@@ -197,20 +203,25 @@ __global__ __launch_bounds__(256, 1) void decode_f32_kernel(DecodeArgs a) {
       den = fmaf(ml_s[k][iq][1][l16], f[k], den);
     }
     const int64_t prow = ((int64_t)g * a.n_chunks + gc) * a.cols + col;
-    // the segment's only chunk of a local block writes the output row, others their partial
-    const float norm = a.merge_in_kernel ? (den > 0.f ? 1.f / den : 0.f) : 1.f;
-    float* dst = a.merge_in_kernel ? out_ptr + ((int64_t)m * Hq + g * G + col) * D : part_o + prow * D;
+    const bool only = a.merge_in_kernel && ms.count == 1;   // nothing to merge: the output row itself
+    const float norm = only ? (den > 0.f ? 1.f / den : 0.f) : 1.f;
+    float* dst = only ? out_ptr + decode_out_row(a, g, m, col) * D : part_o + prow * D;
     for (int dt = wave; dt < DS; dt += 4) {
       f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int k = 0; k < 4; ++k) acc += xo[((k * NQ + iq) * DS + dt) * 64] * f[k];
-      if (16 * dt + 4 * kg < D) *reinterpret_cast<f32x4*>(dst + 16 * dt + 4 * kg) = acc * norm;
+      acc *= norm;
+      if (16 * dt + 4 * kg >= D) continue;
+      if (NQ > 1 || only) {
+        *reinterpret_cast<f32x4*>(dst + 16 * dt + 4 * kg) = acc;
+      } else {
+        store_pair_agent(dst + 16 * dt + 4 * kg, acc[0], acc[1]);
+        store_pair_agent(dst + 16 * dt + 4 * kg + 2, acc[2], acc[3]);
+      }
     }
-    if (!a.merge_in_kernel && wave == 0 && kg == 0) {
-      part_ml[prow * 2] = mm;
-      part_ml[prow * 2 + 1] = den;
-    }
+    if (!only && wave == 0 && kg == 0) store_pair_agent(part_ml + prow * 2, mm, den);
   }
+  if (NQ == 1 && a.merge_in_kernel && ms.count > 1) merge_if_last(a, ms, g, m, D, part_o, part_ml, out_ptr);
 }
 
 template <int DP, int NQ>

@@ -171,3 +171,27 @@ def test_keep_list_compaction(layout, chunk):
             got = prefill(q, k, v, seg, Hq=Hq, Hkv=Hkv, D=D, H=1, block=0, dtype=BF16, causal=causal, keep_chunks=flags, chunk_tokens=chunk)
             ref = oracle.attend_rows(q, k, v, seg, rows, heads, is_sync=True, causal=causal, keep_tok=kt)
             check(got[rows, heads], ref, BF16, what)
+
+
+@pytest.mark.parametrize("dtype,D", [(BF16, 128), (BF16, 64), (BF16, 72), (F32, 64)])
+@pytest.mark.parametrize("lens", [[64], [512], [576], [2048], [2112], [9000], [1, 0, 130], [65, 300, 7], [700, 1, 64, 65]])
+def test_decode_merge_inside_the_launch(dtype, D, lens):
+    """Chunk counts on both sides of the merge's batches of eight and of its limit, local and sync blocks in turn over one
+    workspace full of ones; a second call finds the first one's partials and counters, a third another order of blocks."""
+    N, Hq, Hkv, M = len(lens), 8, 2, 4
+    lens = np.asarray(lens, dtype=np.int32)
+    seg = np.concatenate([[0], np.cumsum(lens + 2)]).astype(np.int32)
+    p = fa.make_params(N, Hq, Hkv, D, 2, dtype)
+    q = np.stack([rand_block(70 + b, N, Hq, Hkv, D, bf16=dtype == BF16)[0] for b in range(M)])
+    kv = [rand_block(80 + b, int(seg[-1]), Hkv, Hkv, D, bf16=dtype == BF16)[1:] for b in range(M)]
+    tq, tk, tv = dev(q, dtype), dev(np.stack([k for k, _ in kv]), dtype), dev(np.stack([v for _, v in kv]), dtype)
+    ws = torch.full((fa.fedattn_workspace_bytes(p, fa.FEDATTN_OP_DECODE, int(seg[-1])),), 255, dtype=torch.uint8, device="cuda")
+    for first in (0, 0, 1):
+        what = "decode merge %s D=%d lens=%s first=%d" % (dtype, D, lens.tolist(), first)
+        say(what)
+        out = torch.full_like(tq, float("nan"))
+        fa.fedattn_decode_blocks(p, first, M, tq, tk, tv, out, tq[0].numel(), tk[0].numel(), seg, lens, workspace=ws)
+        torch.cuda.synchronize()
+        for b in range(M):
+            ref = oracle.decode_step(q[b], kv[b][0], kv[b][1], seg, lens, is_sync=oracle.is_sync_block(2, first + b))
+            check(host(out[b]), ref, dtype, what)
