@@ -383,7 +383,8 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(DecodeArgs a) {
   const float* part_ml = reinterpret_cast<const float*>(reinterpret_cast<const unsigned char*>(a.part_ml) + bz * a.slice_bytes);
   const int64_t cstride = a.cols;          // partial rows between consecutive chunks
 
-  if (c1 - c0 <= 16 * CG) {
+  static_assert(kCombineAtOnce == 16 * CG, "16 partial rows per thread");
+  if (c1 - c0 <= kCombineAtOnce) {
     // Few chunks (the usual case): one round trip.  Every thread requests its partial O rows
     // and one chunk's (m, l) before anything is known about the weights.
     const int nb = c1 - c0;
