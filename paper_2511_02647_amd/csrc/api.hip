@@ -485,6 +485,7 @@ static fedattn_status run_decode(bool fused, const fedattn_params* params, int32
     if (!built[sync ? 1 : 0]) {
       memset(&a, 0, sizeof(a));
       a.N = N; a.Hq = params->n_q_heads; a.Hkv = params->n_kv_heads; a.D = params->head_dim;
+      a.n_cus = device_cus();
       a.is_sync = sync ? 1 : 0;
       a.has_remote = (sync && remote_lens) ? 1 : 0;
       a.scale = resolve_scale(params);

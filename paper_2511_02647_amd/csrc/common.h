@@ -77,6 +77,7 @@ struct DecodeArgs {
   uint64_t ticket;          // first launch of a call: the call's number, 48 bits, marks the counters as set up; later ones: 0
   int32_t merge_in_kernel;  // the split kernel writes the output rows itself (no combine launch)
   int32_t N, Hq, Hkv, D;
+  int32_t n_cus;            // compute units of the device (launch shape heuristics)
   int32_t is_sync;
   int32_t chunk_rows;       // cache rows per workgroup
   int32_t n_chunks;         // total chunks over all segments

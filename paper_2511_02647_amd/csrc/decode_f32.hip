@@ -8,6 +8,8 @@
 // chip is bound by memory, and short caches by the launches: 5 participants with 200..1500 rows,
 // 8/2 heads of 64, one local and one sync block (6 MB): 21 us, where one wavefront per (participant, head)
 // took 1525 us.
+#include <math.h>
+
 #include "common.h"
 #include "decode_walk.h"
 #include "mfma_tile.h"
@@ -234,10 +236,31 @@ hipError_t launch_decode_f32_t(const DecodeArgs& a, int n_z, hipStream_t s) {
   return hipGetLastError();
 }
 
-// More than 16 query columns: 64 (32 beyond 128 elements) per workgroup, so that a tile is staged once for them
+// Query columns per workgroup, 16 NQ: a tile costs a workgroup NQ times the matrix work, and the more columns
+// it takes the fewer workgroups share that work out.  Microseconds: 4 for a workgroup's start and end, 0.85 for
+// 64 rows x 16 columns at head dimension 128; as many workgroups on a CU as tiles fit LDS.  Sync block with 64
+// (32 beyond 128 elements) columns throughout and with this rule: 5 x 200..1500 rows, 8/2 heads of 64 13.8 -> 10.9 us,
+// 2 x 1500 rows, 24/1 heads of 128 19.0 -> 11.6 (NQ = 1); 8 x 1000..4000 rows, 8/2 heads of 128 31.2 -> 23.3 (NQ = 2,
+// 26.4 with 1); 32 x 500..1500 rows, 8/1 heads of 128 112 (NQ = 4, 116 with 2, 140 with 1).
 template <int DP>
 hipError_t launch_decode_f32_d(const DecodeArgs& a, int n_z, hipStream_t s) {
-  return a.cols <= 16 ? launch_decode_f32_t<DP, 1>(a, n_z, s) : launch_decode_f32_t<DP, (DP > 128 ? 2 : 4)>(a, n_z, s);
+  constexpr int kMost = DP > 128 ? 2 : 4;
+  constexpr int kResident = 160 * 1024 / f32_smem_bytes<DP>() > 2 ? 2 : 160 * 1024 / f32_smem_bytes<DP>();
+  const double tiles = (a.chunk_rows + kKvTile - 1) / kKvTile, u = 0.85 * DP / 128;
+  int nq = 1;
+  double best = 1e30;
+  for (int x = a.cols <= 16 ? 1 : kMost; x >= 1; x /= 2) {
+    const double wgs = (double)a.n_chunks * a.Hkv * ((a.cols + 16 * x - 1) / (16 * x)) * n_z;
+    const double places = wgs / ((double)a.n_cus * kResident);
+    const double us = 4 * (places > 1 ? places : 1) + ceil(wgs / a.n_cus) * tiles * x * u;
+    if (us < best) {
+      best = us;
+      nq = x;
+    }
+  }
+  if (nq == 1) return launch_decode_f32_t<DP, 1>(a, n_z, s);
+  if (nq == 2) return launch_decode_f32_t<DP, 2>(a, n_z, s);
+  return launch_decode_f32_t<DP, kMost>(a, n_z, s);
 }
 
 }  // namespace

@@ -195,3 +195,20 @@ def test_decode_merge_inside_the_launch(dtype, D, lens):
         for b in range(M):
             ref = oracle.decode_step(q[b], kv[b][0], kv[b][1], seg, lens, is_sync=oracle.is_sync_block(2, first + b))
             check(host(out[b]), ref, dtype, what)
+
+
+@pytest.mark.parametrize("D,Hq", [(64, 16), (128, 32), (128, 64), (256, 32), (72, 64)])
+@pytest.mark.parametrize("dtype", [F32, BF16])
+def test_decode_sync_blocks_that_fill_the_chip(dtype, D, Hq):
+    """Enough (chunk, KV head) pairs that the launches take more columns per workgroup (fp32: 16, 32 or 64) and
+    longer chunks (bf16); ragged, empty and one-row segments, rows that only their own participant sees."""
+    lens = np.array([900, 700, 1, 1300, 650, 1000, 0, 777], dtype=np.int32)
+    N, Hkv = len(lens), 8
+    seg = np.concatenate([[0], np.cumsum(lens + 1)]).astype(np.int32)
+    q, _, _ = rand_block(90, N, Hq, Hkv, D, bf16=dtype == BF16)
+    _, kc, vc = rand_block(91, int(seg[-1]), Hkv, Hkv, D, bf16=dtype == BF16)
+    for rl in (None, lens - lens // 3):
+        say("decode sync %s D=%d Hq=%d remote=%s" % (dtype, D, Hq, rl is not None))
+        got = decode(q, kc, vc, seg, lens, Hq=Hq, Hkv=Hkv, D=D, H=1, block=0, dtype=dtype, remote_lens=rl)
+        ref = oracle.decode_step(q, kc, vc, seg, lens, is_sync=True, remote_lens=rl)
+        check(got, ref, dtype, "decode sync D=%d Hq=%d" % (D, Hq))
