@@ -355,15 +355,17 @@ __global__ __launch_bounds__(COLSPLIT ? 512 : 256, 1) void decode_stream_kernel(
 
 // Merges the chunk partials of one (participant, query head) and writes the output row:
 //   o = sum_c O_c 2^(m_c - m) / sum_c l_c 2^(m_c - m),  m = max_c m_c.
-// At least D/4 x 4 threads: thread (cg, d4) sums 4 head-dim elements over the chunks c = cg (mod 4),
-// all its loads in flight at once (the kernel is a chain of memory round trips: (m, l) of
-// every chunk, then the partial O rows, then the store); the 4 chunk groups meet in LDS.
+// A chain of memory round trips: per kCombineAtOnce chunks one, in which every thread requests its partial O
+// rows and the first wavefront the chunks' (m, l) before anything is known about the weights.  At least
+// D/4 x 4 threads: thread (cg, d4) sums 4 head-dim elements over the chunks c = cg (mod 4); the 4 chunk groups
+// meet in LDS.  (With a serial sum of the l, three barriers and, beyond 64 chunks, two passes over them, a sync
+// block of 16 x 300..1000 rows, 8/4 heads of 64 took 12.4 instead of 11.2 us, of 1 x 8192 rows, 8/2 heads 11.9 instead of 11.3.)
 template <typename T>
 __global__ __launch_bounds__(256) void decode_combine_kernel(DecodeArgs a) {
   constexpr int CG = 4;
-  __shared__ float m_s[256];
-  __shared__ float w_s[256];
-  __shared__ float l_s[256];
+  static_assert(kCombineAtOnce == 64 && kCombineAtOnce == 16 * CG, "one chunk per lane, 16 partial rows per thread");
+  __shared__ float w_s[2][64];
+  __shared__ float alpha_s[2], den_s;
   __shared__ f32x4 acc_s[CG][64];
   const int n = blockIdx.x / a.Hq;
   const int h = blockIdx.x % a.Hq;
@@ -375,7 +377,7 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(DecodeArgs a) {
   const int64_t base = (int64_t)g * a.n_chunks;
   const int tid = threadIdx.x;
   const int D = a.D, D4 = D / 4;
-  const int d4 = tid % D4, cg = tid / D4;  // blockDim: whole wavefronts, at least D4 * CG; the rest (cg >= CG) only helps with (m, l)
+  const int d4 = tid % D4, cg = tid / D4;  // blockDim: whole wavefronts, at least D4 * CG
   // block of a fused launch
   const int bz = blockIdx.y;
   unsigned char* out_ptr = reinterpret_cast<unsigned char*>(a.out) + (int64_t)a.block_list[bz] * a.q_block_bytes;
@@ -383,95 +385,47 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(DecodeArgs a) {
   const float* part_ml = reinterpret_cast<const float*>(reinterpret_cast<const unsigned char*>(a.part_ml) + bz * a.slice_bytes);
   const int64_t cstride = a.cols;          // partial rows between consecutive chunks
 
-  static_assert(kCombineAtOnce == 16 * CG, "16 partial rows per thread");
-  if (c1 - c0 <= kCombineAtOnce) {
-    // Few chunks (the usual case): one round trip.  Every thread requests its partial O rows
-    // and one chunk's (m, l) before anything is known about the weights.
-    const int nb = c1 - c0;
-    const int nb_o = cg < CG ? nb : 0;   // chunks whose O rows this thread sums (every CG-th from cg on)
-    const float* po = part_o + ((base + c0) * cstride + col) * D + 4 * d4;
+  float m_run = -INFINITY, den = 0.f;      // first wavefront
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  int buf = 0;                             // the batch after the next one writes only when everyone is past the next barrier
+  for (int cb = c0; cb < c1; cb += kCombineAtOnce, buf ^= 1) {
+    const int nb = min(kCombineAtOnce, c1 - cb);
+    const int nb_o = cg < CG ? nb : 0;     // chunks whose O rows this thread sums (every CG-th from cg on)
+    const float* po = part_o + ((base + cb) * cstride + col) * D + 4 * d4;
     f32x4 part[16];
 #pragma unroll
     for (int u = 0; u < 16; ++u) {
       const int i = cg + CG * u;
       part[u] = i < nb_o ? *reinterpret_cast<const f32x4*>(po + i * cstride * D) : f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    float m_i = -INFINITY, l_i = 0.f;
-    if (tid < nb) {
-      const f32x2 ml = *reinterpret_cast<const f32x2*>(part_ml + ((base + c0 + tid) * cstride + col) * 2);
-      m_i = ml[0];
-      l_i = ml[1];
-    }
-    float mm = wave_max(m_i);
-    if ((tid & 63) == 0) m_s[tid >> 6] = mm;
-    __syncthreads();
-    mm = -INFINITY;
-    for (int w = 0; w < (int)((blockDim.x + 63) >> 6); ++w) mm = fmaxf(mm, m_s[w]);
-    const float mu = (mm == -INFINITY) ? 0.f : mm;
-    if (tid < nb) {
-      w_s[tid] = __builtin_amdgcn_exp2f(m_i - mu);
-      l_s[tid] = l_i;
+    if (tid < 64) {
+      f32x2 ml = {-INFINITY, 0.f};
+      if (tid < nb) ml = *reinterpret_cast<const f32x2*>(part_ml + ((base + cb + tid) * cstride + col) * 2);
+      const float m_new = fmaxf(m_run, wave_max(ml[0]));
+      const float mu = (m_new == -INFINITY) ? 0.f : m_new;
+      const float w = __builtin_amdgcn_exp2f(ml[0] - mu);
+      const float alpha = __builtin_amdgcn_exp2f(m_run - mu);
+      w_s[buf][tid] = w;
+      if (tid == 0) alpha_s[buf] = alpha;
+      den = den * alpha + wave_sum(ml[1] * w);
+      if (tid == 0) den_s = den;
+      m_run = m_new;
     }
     __syncthreads();
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    acc *= alpha_s[buf];
 #pragma unroll
     for (int u = 0; u < 16; ++u) {
       const int i = cg + CG * u;
-      if (i < nb_o) acc += part[u] * w_s[i];
+      if (i < nb_o) acc += part[u] * w_s[buf][i];
     }
-    if (cg < CG) acc_s[cg][d4] = acc;
-    if (tid == 0) {
-      float den = 0.f;
-      for (int i = 0; i < nb; ++i) den = fmaf(l_s[i], w_s[i], den);
-      m_s[8] = den;
-    }
-    __syncthreads();
-    if (cg == 0) {
-      const float dn = m_s[8];
-      const f32x4 sum = (acc_s[0][d4] + acc_s[1][d4]) + (acc_s[2][d4] + acc_s[3][d4]);
-      const f32x4 val = sum * (dn > 0.f ? 1.f / dn : 0.f);
-      T* out = reinterpret_cast<T*>(out_ptr) + ((int64_t)n * a.Hq + h) * D + 4 * d4;
-      store_out4(out, val);
-    }
-    return;
-  }
-
-  // row maximum over all chunks
-  float mm = -INFINITY;
-  for (int cc = c0 + tid; cc < c1; cc += blockDim.x) mm = fmaxf(mm, part_ml[((base + cc) * cstride + col) * 2]);
-  mm = wave_max(mm);
-  if ((tid & 63) == 0) m_s[tid >> 6] = mm;
-  __syncthreads();
-  mm = -INFINITY;
-  for (int w = 0; w < (int)((blockDim.x + 63) >> 6); ++w) mm = fmaxf(mm, m_s[w]);
-  const float mu = (mm == -INFINITY) ? 0.f : mm;
-
-  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  float den = 0.f;
-  for (int cb = c0; cb < c1; cb += 256) {
-    const int nb = min(256, c1 - cb);
-    __syncthreads();
-    for (int i = tid; i < nb; i += blockDim.x) {
-      const float* ml = part_ml + ((base + cb + i) * cstride + col) * 2;
-      w_s[i] = __builtin_amdgcn_exp2f(ml[0] - mu);
-      l_s[i] = ml[1];
-    }
-    __syncthreads();
-    const float* po = part_o + ((base + cb) * cstride + col) * D + 4 * d4;
-#pragma unroll 8
-    for (int i = cg < CG ? cg : nb; i < nb; i += CG) acc += *reinterpret_cast<const f32x4*>(po + i * cstride * D) * w_s[i];
-    if (tid == 0)
-      for (int i = 0; i < nb; ++i) den = fmaf(l_s[i], w_s[i], den);
   }
   if (cg < CG) acc_s[cg][d4] = acc;
-  if (tid == 0) m_s[8] = den;
   __syncthreads();
   if (cg == 0) {
-    const float dn = m_s[8];
+    const float dn = c1 > c0 ? den_s : 0.f;
     const f32x4 sum = (acc_s[0][d4] + acc_s[1][d4]) + (acc_s[2][d4] + acc_s[3][d4]);
-    const f32x4 val = sum * (dn > 0.f ? 1.f / dn : 0.f);
     T* out = reinterpret_cast<T*>(out_ptr) + ((int64_t)n * a.Hq + h) * D + 4 * d4;
-    store_out4(out, val);
+    store_out4(out, sum * (dn > 0.f ? 1.f / dn : 0.f));
   }
 }
 
