@@ -98,6 +98,10 @@ FEDATTN_API size_t fedattn_workspace_bytes(const fedattn_params* params, int32_t
  *   bf16), otherwise applied to the fp32 scores.  Other bf16 shapes: fp32 arithmetic on the
  *   bf16 values (on bf16 MFMA: the products of bf16 values are exact in fp32, and a weight enters
  *   the second product as the three bf16 values that it is the exact sum of).
+ *   Non-finite elements of K and V make the rows that see them non-finite; a masked row meets them
+ *   with weight zero, so those of V also reach rows of the same query tile (at most 128 rows of
+ *   one segment) that come before them.  The calls that run on the general kernel (fp32, or bf16 with
+ *   another D, with a keep-list and no workspace) have no such tile.
  *
  *   block_idx      0-based block index; with sync_override = -1 the block is a sync
  *                  block iff fedattn_is_sync_block(params->sync_interval, block_idx).
