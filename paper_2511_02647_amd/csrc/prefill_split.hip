@@ -15,6 +15,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "half_tile.h"
 #include "mfma_tile.h"
 #include "prefill_walk.h"
 
@@ -22,7 +23,6 @@ namespace fedattn {
 
 namespace {
 
-constexpr int kSplitRows = 32;   // keys of a wavefront's tile
 constexpr int kSplitWaves = 8;
 
 // Waits that also keep the compiler from moving LDS accesses across them: a wavefront's buffers are its
@@ -98,31 +98,31 @@ __global__ __launch_bounds__(64 * kSplitWaves, DP > 64 ? 2 : 4) void prefill_spl
   const int n_list = 2 * w.n_list;
   const int nt = n_list + (w.dhi - w.dlo + kSplitRows - 1) / kSplitRows;
   struct Tile {
-    const uint16_t *k, *v;
-    int kv0, len;
+    const uint16_t *k, *v;   // first row to load
+    int kv0, len, load_len;
     bool causal_tile;
   };
   auto tile_at = [&](int it) __attribute__((always_inline)) {
     Tile t;
+    int first;
     if (it < n_list) {
       const int i2 = it >> 1;
       const int2 e = a.kept_tiles[i2 < w.la_n ? i2 : w.lb0 + (i2 - w.la_n)];
-      const int half = (it & 1) * kSplitRows;
-      t.kv0 = __builtin_amdgcn_readfirstlane(e.x) + half;
-      t.len = min(__builtin_amdgcn_readfirstlane(e.y) - half, kSplitRows);
+      const HalfTile h = half_of_tile(__builtin_amdgcn_readfirstlane(e.x), __builtin_amdgcn_readfirstlane(e.y), it & 1);
+      t.kv0 = h.kv0;
+      t.len = h.len;
+      t.load_len = h.load_len;
+      first = h.load0;
       t.causal_tile = false;
     } else {
-      t.kv0 = w.dlo + kSplitRows * (it - n_list);
-      t.len = min(w.dhi - t.kv0, kSplitRows);
+      t.kv0 = first = w.dlo + kSplitRows * (it - n_list);
+      t.len = t.load_len = min(w.dhi - t.kv0, kSplitRows);
       t.causal_tile = causal;
     }
-    // an empty half loads the row before it and is masked out
-    const int64_t first = (int64_t)(t.len > 0 ? t.kv0 : t.kv0 - 1) * row_elems;
-    t.k = (it < n_list ? kp_list : kp) + first;
-    t.v = (it < n_list ? vp_list : vp) + first;
+    t.k = (it < n_list ? kp_list : kp) + (int64_t)first * row_elems;
+    t.v = (it < n_list ? vp_list : vp) + (int64_t)first * row_elems;
     return t;
   };
-  auto load_len = [](const Tile& t) __attribute__((always_inline)) { return max(t.len, 1); };
 
   // Q tile (whole rows, K's swizzled layout): the wavefronts share the loads out among them
   constexpr int QTILEB = kWaveRows * ROWB;
@@ -139,8 +139,8 @@ __global__ __launch_bounds__(64 * kSplitWaves, DP > 64 ? 2 : 4) void prefill_spl
   }
   Tile cur = tile_at(min(wave, nt - 1));
   if (wave < nt) {
-    tile_io.template dma<false>(cur.k, lds_base, load_len(cur));
-    tile_io.template dma<true>(cur.v, lds_base + TILEB, load_len(cur));
+    tile_io.template dma<false>(cur.k, lds_base, cur.load_len);
+    tile_io.template dma<true>(cur.v, lds_base + TILEB, cur.load_len);
     wait_loads<2 * TL::IPW>();
   } else {
     wait_loads<0>();
@@ -182,7 +182,7 @@ __global__ __launch_bounds__(64 * kSplitWaves, DP > 64 ? 2 : 4) void prefill_spl
     for (int st = 0; st < KSTEPS; ++st) s[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[st], qf[st], s[0], 0, 0, 0);
     if constexpr (MORE) {
       wait_lds_reads();
-      tile_io.template dma<false>(nx.k, lds_base, load_len(nx));
+      tile_io.template dma<false>(nx.k, lds_base, nx.load_len);
     }
     if (t.len < kSplitRows || (t.causal_tile && t.kv0 + kSplitRows - 1 > row0)) {
       int lim = t.len;
@@ -226,7 +226,7 @@ __global__ __launch_bounds__(64 * kSplitWaves, DP > 64 ? 2 : 4) void prefill_spl
     }
     if constexpr (MORE) {
       wait_lds_reads();
-      tile_io.template dma<true>(nx.v, lds_base + TILEB, load_len(nx));
+      tile_io.template dma<true>(nx.v, lds_base + TILEB, nx.load_len);
     }
   };
   if (wave < nt) {

@@ -174,6 +174,37 @@ def test_keep_list_compaction(layout, chunk):
 
 
 @pytest.mark.parametrize("dtype,D", [(BF16, 128), (BF16, 64), (BF16, 72), (F32, 64)])
+@pytest.mark.parametrize("chunk", [1, 20, 64])
+@pytest.mark.parametrize("tail", [1, 31, 32, 33])
+def test_kept_tiles_load_only_kept_rows(dtype, D, chunk, tail):
+    """Listed tiles with 1 to 33 valid rows, last in their participant's list: what follows them in memory (rows of a
+    participant that shares nothing, unwritten workspace, the end of K and V) is NaN and must not reach anybody."""
+    lens = [64 + tail, 45, 70, 64 + tail]
+    Hq, Hkv = 8, 2
+    seg = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    q, k, v = rand_block(46, int(seg[-1]), Hq, Hkv, D, bf16=dtype == BF16)
+    first = np.concatenate([[0], np.cumsum(fi.chunk_counts(np.diff(seg), chunk))])
+    flags = np.ones(int(first[-1]), dtype=np.uint8)
+    flags[first[1]:first[2]] = 0              # participant 1 shares nothing
+    if chunk == 1:                            # `tail` rows of the others, from anywhere
+        for n in (0, 2, 3):
+            flags[first[n]:first[n + 1]] = 0
+            flags[first[n] + np.random.default_rng(n).choice(lens[n], min(tail, lens[n]), replace=False)] = 1
+    kt = oracle.expand_keep_chunks(flags, seg, chunk)
+    kn, vn = k.copy(), v.copy()
+    kn[seg[1]:seg[2]] = vn[seg[1]:seg[2]] = np.nan
+    others = np.r_[seg[0]:seg[1], seg[2]:seg[4]]
+    for causal in (True, False):
+        what = "kept tiles %s D=%d chunk=%d tail=%d causal=%d" % (dtype, D, chunk, tail, causal)
+        ref = oracle.attend_block(q, k, v, seg, is_sync=True, causal=causal, keep_tok=kt)
+        say(what)
+        got = prefill(q, k, v, seg, Hq=Hq, Hkv=Hkv, D=D, H=1, block=0, dtype=dtype, causal=causal, keep_chunks=flags, chunk_tokens=chunk)
+        check(got, ref, dtype, what)
+        got = prefill(q, kn, vn, seg, Hq=Hq, Hkv=Hkv, D=D, H=1, block=0, dtype=dtype, causal=causal, keep_chunks=flags, chunk_tokens=chunk)
+        check(got[others], ref[others], dtype, what + ", participant 1 NaN")
+
+
+@pytest.mark.parametrize("dtype,D", [(BF16, 128), (BF16, 64), (BF16, 72), (F32, 64)])
 @pytest.mark.parametrize("lens", [[64], [512], [576], [2048], [2112], [9000], [1, 0, 130], [65, 300, 7], [700, 1, 64, 65]])
 def test_decode_merge_inside_the_launch(dtype, D, lens):
     """Chunk counts on both sides of the merge's batches of eight and of its limit, local and sync blocks in turn over one
