@@ -102,7 +102,7 @@ def load():
     lib.fedattn_probe_mfma.restype = i64
     lib.fedattn_last_error.restype = ctypes.c_char_p
     lib.fedattn_version.restype = ctypes.c_char_p
-    _native.bind({name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in EXPORTS}, _host_i32,
+    _native.bind({name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in EXPORTS}, fedattn_params, _host_i32,
                  torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice)
     _lib, _nat = lib, _native
     return lib

@@ -17,7 +17,7 @@
 namespace {
 
 PyObject *s_is_cuda, *s_is_contiguous, *s_data_ptr, *s_nbytes, *s_numel, *s_cuda_stream;
-PyObject *g_as_i32, *g_raw_stream, *g_get_device;   // set by bind()
+PyObject *g_params_type, *g_as_i32, *g_raw_stream, *g_get_device;   // set by bind()
 
 decltype(&fedattn_prefill) f_prefill;
 decltype(&fedattn_prefill_sync_local_kv) f_prefill_sync_local_kv;
@@ -63,7 +63,7 @@ struct Args {
     PyObject* o = next();
     if (!ok) return 0;
     PyObject* idx = PyNumber_Long(o);
-    const long long x = idx ? PyLong_AsLongLong(idx) : -1;
+    const int64_t x = idx ? (int64_t)PyLong_AsUnsignedLongLongMask(idx) : -1;   // what does not fit is cut off
     Py_XDECREF(idx);
     if (x == -1 && PyErr_Occurred()) ok = false;
     return x;
@@ -71,7 +71,9 @@ struct Args {
   double real() {
     PyObject* o = next();
     if (!ok) return 0.0;
-    const double x = PyFloat_AsDouble(o);
+    PyObject* num = PyNumber_Float(o);
+    const double x = num ? PyFloat_AsDouble(num) : -1.0;
+    Py_XDECREF(num);
     if (x == -1.0 && PyErr_Occurred()) ok = false;
     return x;
   }
@@ -91,8 +93,10 @@ struct Args {
   const fedattn_params* params() {
     PyObject* o = next();
     if (!ok) return nullptr;
-    Py_buffer* b = hold(o, nullptr);
-    if (b && b->len != (Py_ssize_t)sizeof(fedattn_params)) {
+    Py_buffer* b = nullptr;
+    if (PyObject_TypeCheck(o, (PyTypeObject*)g_params_type)) {
+      b = hold(o, nullptr);
+    } else {
       PyErr_SetString(PyExc_TypeError, "params must be a fedattn_params");
       ok = false;
     }
@@ -140,9 +144,10 @@ struct Args {
     if (PyErr_Occurred()) ok = false;
     return x;
   }
-  void* tensor(const char* name, bool optional = false, size_t* bytes = nullptr) {
+  // a device tensor's address; None is NULL, which the library accepts or rejects by its own rules
+  void* tensor(const char* name, size_t* bytes = nullptr) {
     PyObject* o = next();
-    if (!ok || (optional && o == Py_None)) return nullptr;
+    if (!ok || o == Py_None) return nullptr;
     if (!truthy(PyObject_GetAttr(o, s_is_cuda))) {
       if (!PyErr_Occurred()) PyErr_Format(PyExc_TypeError, "%s must be a device tensor", name);
       ok = false;
@@ -166,7 +171,7 @@ struct Args {
   }
   void* workspace(size_t* bytes) {
     *bytes = 0;
-    return tensor("workspace", true, bytes);
+    return tensor("workspace", bytes);
   }
   // device pointers of the participants' matrices; absent and empty ones are NULL
   void locals(const char* name, int n_part, const void** out) {
@@ -246,7 +251,7 @@ PyObject* py_prefill(PyObject*, PyObject* const* v, Py_ssize_t n) {
   void* out = a.tensor("out");
   const int32_t* seg = a.vec("seg_offsets", &ns);
   if (a.ok && ns != p->n_participants + 1) a.fail("seg_offsets must have n_participants + 1 entries");
-  const uint8_t* keep = (const uint8_t*)a.tensor("keep_chunks", true);
+  const uint8_t* keep = (const uint8_t*)a.tensor("keep_chunks");
   const int32_t chunk = (int32_t)a.integer(), over = (int32_t)a.integer();
   void* ws = a.workspace(&wsb);
   void* st = a.stream();
@@ -272,7 +277,7 @@ PyObject* py_prefill_sync_local_kv(PyObject*, PyObject* const* v, Py_ssize_t n) 
   a.locals("v_local", n_ptrs, vl);
   void* out = a.tensor("out");
   a.at = 6;
-  const uint8_t* keep = (const uint8_t*)a.tensor("keep_chunks", true);
+  const uint8_t* keep = (const uint8_t*)a.tensor("keep_chunks");
   const int32_t chunk = (int32_t)a.integer();
   void* ws = a.workspace(&wsb);
   void* st = a.stream();
@@ -365,7 +370,7 @@ PyObject* py_rmsnorm(PyObject*, PyObject* const* v, Py_ssize_t n) {
   if (!a.ok) return nullptr;
   float* x = (float*)a.tensor("x");
   const bool add = v[1] != Py_None;
-  const void* y = a.tensor("y", true);
+  const void* y = a.tensor("y");
   void* out = a.tensor("out");
   const int64_t rows = a.integer();
   const int32_t d = (int32_t)a.integer();
@@ -378,7 +383,7 @@ PyObject* py_rope_split_qkv(PyObject*, PyObject* const* v, Py_ssize_t n) {
   Args a(v, n, 11);
   if (!a.ok) return nullptr;
   const void* qkv = a.tensor("qkv");
-  const int32_t* pos = (const int32_t*)a.tensor("pos", true);
+  const int32_t* pos = (const int32_t*)a.tensor("pos");
   void *q = a.tensor("q"), *k = a.tensor("k"), *vv = a.tensor("v");
   const int64_t t = a.integer();
   const int32_t hq = (int32_t)a.integer(), hkv = (int32_t)a.integer(), d = (int32_t)a.integer();
@@ -408,10 +413,10 @@ PyObject* py_residual_add(PyObject*, PyObject* const* v, Py_ssize_t n) {
   return finish(a, [&] { return f_residual_add(x, y, cnt, st); });
 }
 
-// bind(addresses: dict name -> int, as_i32, raw_stream, get_device)
+// bind(addresses: dict name -> int, params_type: the ctypes structure, as_i32, raw_stream, get_device)
 PyObject* py_bind(PyObject*, PyObject* args) {
-  PyObject *dict, *as_i32, *raw, *dev;
-  if (!PyArg_ParseTuple(args, "O!OOO", &PyDict_Type, &dict, &as_i32, &raw, &dev)) return nullptr;
+  PyObject *dict, *type, *as_i32, *raw, *dev;
+  if (!PyArg_ParseTuple(args, "O!O!OOO", &PyDict_Type, &dict, &PyType_Type, &type, &as_i32, &raw, &dev)) return nullptr;
 #define BIND(name)                                                             \
   {                                                                            \
     PyObject* x = PyDict_GetItemString(dict, "fedattn_" #name);                \
@@ -423,6 +428,7 @@ PyObject* py_bind(PyObject*, PyObject* args) {
   BIND(decode_static) BIND(aggregate_kv) BIND(rmsnorm) BIND(rope_split_qkv) BIND(swiglu) BIND(residual_add)
   BIND(residual_add_rmsnorm)
 #undef BIND
+  Py_INCREF(type); Py_XSETREF(g_params_type, type);
   Py_INCREF(as_i32); Py_XSETREF(g_as_i32, as_i32);
   Py_INCREF(raw); Py_XSETREF(g_raw_stream, raw);
   Py_INCREF(dev); Py_XSETREF(g_get_device, dev);

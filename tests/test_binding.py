@@ -92,3 +92,32 @@ def test_every_other_entry_point_reports_the_librarys_reason():
             (lambda: fa.fedattn_aggregate_kv(P, [None, None], [T, T], (0, 4, 8), T, T, stream=Stream), "is NULL")):
         with pytest.raises(fa.FedAttnError, match=reason):
             call()
+
+
+def test_none_is_null_and_the_library_decides():
+    fa.fedattn_prefill(P, 0, None, None, None, None, (0, 0, 0), stream=Stream)          # no tokens: nothing to read
+    fa.fedattn_prefill_sync_local_kv(P, None, [None, None], [None, None], None, (0, 0, 0), stream=Stream)
+    fa.fedattn_prefill_blocks(P, 0, 0, None, None, None, None, 0, 0, (0, 4, 8), stream=Stream)
+    fa.fedattn_decode_blocks(P, 0, 0, None, None, None, None, 0, 0, (0, 4, 8), (1, 1), stream=Stream)
+    fa.fedattn_aggregate_kv(P, [None, None], [None, None], (0, 0, 0), None, None, stream=Stream)
+    for call in (lambda: fa.fedattn_prefill(P, 0, None, T, T, T, (0, 4, 8), stream=Stream),
+                 lambda: fa.fedattn_prefill_blocks(P, 0, 2, T, T, T, None, 8, 8, (0, 4, 8), stream=Stream),
+                 lambda: fa.fedattn_decode(P, 0, None, T, T, T, (0, 4, 8), (1, 1), stream=Stream),
+                 lambda: fa.fedattn_decode_static(P, 0, T, T, T, None, (0, 4, 8), (1, 1), stream=Stream),
+                 lambda: fa.fedattn_aggregate_kv(P, [T, T], [T, T], (0, 4, 8), None, T, stream=Stream)):
+        with pytest.raises(fa.FedAttnError) as e:
+            call()
+        assert e.value.status == fa.FEDATTN_EINVAL and "NULL" in str(e.value)
+    with pytest.raises(fa.FedAttnError) as e:      # a cache without capacity needs no address: only the workspace is missing
+        fa.fedattn_decode(P, 0, T, None, None, T, (0, 0, 0), (0, 0), stream=Stream)
+    assert e.value.status == fa.FEDATTN_EWORKSPACE
+
+
+def test_params_and_numbers_as_before():
+    for bad in (None, bytes(32), np.zeros(8, np.int32), 3):
+        with pytest.raises((TypeError, AttributeError)):
+            fa.fedattn_prefill(bad, 0, None, None, None, None, (0, 0, 0), stream=Stream)
+    for block in (np.int64(0), 0.0, "0", torch.tensor(0), 1 << 70):   # anything int() takes; what does not fit is cut off
+        fa.fedattn_prefill(P, block, None, None, None, None, (0, 0, 0), stream=Stream)
+    with pytest.raises(TypeError):
+        fa.fedattn_prefill(P, None, None, None, None, None, (0, 0, 0), stream=Stream)
