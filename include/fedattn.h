@@ -74,7 +74,8 @@ FEDATTN_API int fedattn_is_sync_block(int32_t sync_interval, int32_t block_idx);
 /* Bytes of device workspace the given op needs (16-byte aligned start).
  *   FEDATTN_OP_PREFILL: `tokens` = total tokens; needed only when a keep-list is
  *     passed (chunk_tokens > 0); 0 otherwise.
- *   FEDATTN_OP_DECODE:  `tokens` = total cache capacity; chunk_tokens ignored.
+ *   FEDATTN_OP_DECODE:  `tokens` = total cache capacity; chunk_tokens ignored.  fp32, and bf16 with
+ *     D other than 64 and 128: at most FEDATTN_STATIC_SCRATCH_BYTES (larger blocks run in pieces).
  *   FEDATTN_OP_PREFILL_SYNC_LOCAL_KV: `tokens` = total tokens; room for one aggregated copy of K
  *     and V (used only when the participants' matrices do not lie back to back) plus the
  *     keep-list's share (chunk_tokens > 0).
@@ -235,7 +236,7 @@ FEDATTN_API fedattn_status fedattn_decode_blocks_fused(const fedattn_params* par
  * counters live in an array of FEDATTN_STATIC_SCRATCH_BYTES that is part of the library's
  * device code (every GPU the library runs on holds its own copy until the process ends).  The
  * call allocates and frees nothing.  Problems whose fedattn_workspace_bytes(DECODE) exceeds
- * the array are rejected with FEDATTN_EWORKSPACE.  All calls on one GPU share that GPU's array:
+ * the array (bf16 with D = 64 or 128 only) are rejected with FEDATTN_EWORKSPACE.  All calls on one GPU share that GPU's array:
  * calls that may overlap (different streams, different threads) race and must be ordered by the
  * caller; what a previous call left in the array does not matter.  The array's address is
  * looked up at the first call on each device: make that call outside a graph capture.

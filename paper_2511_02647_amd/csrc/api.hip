@@ -171,6 +171,14 @@ size_t decode_counter_bytes(const fedattn_params* p) {
   return align_up((size_t)p->n_kv_heads * (size_t)p->n_participants * sizeof(uint64_t), 256);
 }
 
+// The partials of fp32 blocks and of bf16 blocks with head dimensions other than 64 and 128 never take more
+// than the built-in array holds: larger blocks are worked off in pieces (below).  So these shapes ask for
+// little memory however many participants there are, and a call with a workspace takes the route of
+// fedattn_decode_static.  It costs a launch pair per piece: fp32 sync blocks, 32 x 300..900 rows, 32/8 heads of 128
+// 209 us (188 with the 34 MB of the whole block's partials), 128 x 64..200 rows 1276 us (813 with 341 MB); one
+// wavefront per participant and head takes 14.8 and 23.9 ms.
+constexpr size_t kMostPieceBytes = FEDATTN_STATIC_SCRATCH_BYTES;
+
 size_t decode_ws_bytes(const fedattn_params* p, int32_t capacity) {
   const size_t G = (size_t)(p->n_q_heads / p->n_kv_heads);
   const size_t N = (size_t)p->n_participants;
@@ -180,7 +188,8 @@ size_t decode_ws_bytes(const fedattn_params* p, int32_t capacity) {
   const size_t rows = (size_t)p->n_kv_heads * chunks * G * N;  // sync blocks: N*G query columns per chunk
   // Room for the counters: these bytes and the unused partials (there are at most target + N - 1 chunks).
   const size_t counters = align_up((size_t)p->n_kv_heads * N * sizeof(uint32_t), 256);
-  return align_up(rows * (size_t)p->head_dim * 4, 256) + align_up(rows * 8, 256) + counters;
+  const size_t whole = align_up(rows * (size_t)p->head_dim * 4, 256) + align_up(rows * 8, 256) + counters;
+  return use_mfma_prefill(p) || whole < kMostPieceBytes ? whole : kMostPieceBytes;
 }
 
 // A number that no other decode call of this process gets: it tells the counters that a call's
@@ -514,10 +523,26 @@ static fedattn_status run_decode(bool fused, const fedattn_params* params, int32
       a.n_chunks = (int32_t)chunks;
       if (split) {
         const size_t room = need - decode_counter_bytes(params);
-        const size_t rows = (size_t)a.Hkv * (size_t)a.n_chunks * (size_t)a.cols;
-        const size_t o_bytes = align_up(rows * (size_t)a.D * 4, 256);
-        if (o_bytes + rows * 8 > room)
-          return fail(FEDATTN_EWORKSPACE, "decode partials (%zu bytes) exceed the workspace", o_bytes + rows * 8);
+        const auto o_bytes_of = [&](int n_g, int n_cols) {
+          return align_up((size_t)n_g * (size_t)a.n_chunks * (size_t)n_cols * (size_t)a.D * 4, 256);
+        };
+        const auto bytes_of = [&](int n_g, int n_cols) {
+          return o_bytes_of(n_g, n_cols) + (size_t)n_g * (size_t)a.n_chunks * (size_t)n_cols * 8;
+        };
+        a.n_g = a.Hkv;
+        a.n_cols = a.cols;
+        const bool whole = bytes_of(a.Hkv, a.cols) <= room;
+        if (!whole) {
+          if (must_split)
+            return fail(FEDATTN_EWORKSPACE, "decode partials (%zu bytes) exceed the workspace", bytes_of(a.Hkv, a.cols));
+          // as many KV heads as fit, or one head's columns in whole workgroups' (64) or wavefronts' (16) shares
+          const size_t fit = (room - 256) / ((size_t)a.n_chunks * ((size_t)a.D * 4 + 8));   // (KV head, column) pairs
+          a.n_g = fit >= (size_t)a.cols ? (int)(fit / (size_t)a.cols) : 1;
+          if (a.n_g == 1 && fit < (size_t)a.cols) a.n_cols = (int)(fit >= 64 ? fit / 64 * 64 : fit / 16 * 16);
+          if (a.n_cols == 0)
+            return fail(FEDATTN_EWORKSPACE, "decode partials of 16 query columns (%zu bytes) exceed the workspace", bytes_of(1, 16));
+        }
+        const size_t o_bytes = o_bytes_of(a.n_g, a.n_cols);
         a.part_o = reinterpret_cast<float*>(workspace);
         a.part_ml = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(workspace) + o_bytes);
         a.counters = counters;
@@ -540,7 +565,7 @@ static fedattn_status run_decode(bool fused, const fedattn_params* params, int32
           most = chunks;
         }
         const int64_t trips = ((int64_t)a.cols * (a.D / 4) + 255) / 256 * ((most + kMergeBatch - 1) / kMergeBatch);
-        a.merge_in_kernel = all_have_rows && a.cols <= 16 && (most == 1 || trips <= kMaxMergeTrips) ? 1 : 0;
+        a.merge_in_kernel = whole && all_have_rows && a.cols <= 16 && (most == 1 || trips <= kMaxMergeTrips) ? 1 : 0;
       }
       a.q_block_bytes = q_block_stride * (int64_t)esize;
       a.cache_block_bytes = cache_block_stride * (int64_t)esize;
@@ -548,6 +573,21 @@ static fedattn_status run_decode(bool fused, const fedattn_params* params, int32
       built[sync ? 1 : 0] = true;
     }
     return FEDATTN_OK;
+  };
+  // n_z blocks of one kind: one launch (and its combine), or one per piece in stream order, all pieces through the same partials
+  const auto launch = [&](const DecodeArgs& kind, int n_z) -> hipError_t {
+    if (!split || (kind.n_g == kind.Hkv && kind.n_cols == kind.cols))
+      return launch_decode(kind, params->dtype, split, n_z, reinterpret_cast<hipStream_t>(stream));
+    DecodeArgs a = kind;
+    for (a.g0 = 0; a.g0 < a.Hkv; a.g0 += kind.n_g) {
+      a.n_g = kind.n_g < a.Hkv - a.g0 ? kind.n_g : a.Hkv - a.g0;
+      for (a.col0 = 0; a.col0 < a.cols; a.col0 += kind.n_cols) {
+        a.n_cols = kind.n_cols < a.cols - a.col0 ? kind.n_cols : a.cols - a.col0;
+        const hipError_t e = launch_decode(a, params->dtype, split, n_z, reinterpret_cast<hipStream_t>(stream));
+        if (e != hipSuccess) return e;
+      }
+    }
+    return hipSuccess;
   };
   // everything that can fail validation is decided before the first launch
   for (int b = 0; b < n_blocks && !(built[0] && built[1]); ++b) {
@@ -574,7 +614,7 @@ static fedattn_status run_decode(bool fused, const fedattn_params* params, int32
         a.q = q; a.out = out; a.k_cache = k_cache; a.v_cache = v_cache;
         a.ticket = counters_ready[kind] ? 0 : ticket;   // no later launch of this kind has more slices than the first
         counters_ready[kind] = true;
-        hipError_t e = launch_decode(a, params->dtype, true, cnt, reinterpret_cast<hipStream_t>(stream));
+        hipError_t e = launch(a, cnt);
         if (e != hipSuccess) return fail(FEDATTN_ELAUNCH, "decode (fused, %d blocks): %s", cnt, hipGetErrorString(e));
       }
     }
@@ -591,7 +631,7 @@ static fedattn_status run_decode(bool fused, const fedattn_params* params, int32
     a.v_cache = reinterpret_cast<const unsigned char*>(v_cache) + (size_t)b * (size_t)cache_block_stride * esize;
     a.ticket = counters_ready[sync ? 1 : 0] ? 0 : ticket;
     counters_ready[sync ? 1 : 0] = true;
-    hipError_t e = launch_decode(a, params->dtype, split, 1, reinterpret_cast<hipStream_t>(stream));
+    hipError_t e = launch(a, 1);
     if (e != hipSuccess) return fail(FEDATTN_ELAUNCH, "decode (block %d): %s", block_idx0 + b, hipGetErrorString(e));
   }
   return FEDATTN_OK;
@@ -664,7 +704,7 @@ fedattn_status fedattn_decode_static(const fedattn_params* params, int32_t block
                                         remote_lens, sync_override);
   if (st != FEDATTN_OK) return st;
   const size_t need = decode_ws_bytes(params, seg_offsets[params->n_participants]);
-  if (need > (size_t)FEDATTN_STATIC_SCRATCH_BYTES && use_mfma_prefill(params))
+  if (need > (size_t)FEDATTN_STATIC_SCRATCH_BYTES)
     return fail(FEDATTN_EWORKSPACE,
                 "fedattn_decode_static: this problem needs %zu bytes of scratch, the built-in array holds %zu; "
                 "use fedattn_decode with a workspace",

@@ -81,7 +81,7 @@ struct DecodeArgs {
   int32_t is_sync;
   int32_t chunk_rows;       // cache rows per workgroup
   int32_t n_chunks;         // total chunks over all segments
-  int32_t cols;             // query columns per partial row block: G (local) or N*G (sync)
+  int32_t cols;             // query columns per KV head: G (local) or N*G (sync)
   int32_t has_remote;       // remote_lens given
   float scale;
   // several blocks in one launch (grid z, or y for the combine): block z is block_list[z]
@@ -95,6 +95,10 @@ struct DecodeArgs {
   int32_t seg_lens[kMaxP];
   int32_t remote_lens[kMaxP];
   int32_t chunk_cum[kMaxP + 1];
+  // A block whose partials do not fit the workspace runs in pieces (launches with PIECES): KV heads
+  // [g0, g0 + n_g) and query columns [col0, col0 + n_cols), which then take the place of Hkv and cols in the partials.
+  // (At the end: next to `cols`, and read by every launch, they cost calls of a few hundred rows 0.7 us.)
+  int32_t g0, n_g, col0, n_cols;
 };
 
 struct AggregateArgs {
@@ -150,7 +154,7 @@ hipError_t launch_build_kept_tiles(const PrefillArgs& a, int2* kept_tiles, int32
 hipError_t launch_pack_kept_rows(const PrefillArgs& a, int row_bytes, void* k_packed, void* v_packed, int2* kept_tiles,
                                  int32_t* kept_cum, hipStream_t s);
 hipError_t launch_decode(const DecodeArgs& a, int dtype, bool split, int n_z, hipStream_t s);
-hipError_t launch_decode_f32(const DecodeArgs& a, int n_z, hipStream_t s);
+hipError_t launch_decode_f32(const DecodeArgs& a, bool pieces, int n_z, hipStream_t s);
 hipError_t launch_aggregate(const AggregateArgs& a, hipStream_t s);
 hipError_t launch_rmsnorm(const float* x, void* out, int64_t rows, int d_model, float eps, hipStream_t s);
 hipError_t launch_residual_add_rmsnorm(float* x, const void* y, void* out, int64_t rows, int d_model, float eps,

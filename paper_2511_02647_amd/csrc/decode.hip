@@ -45,7 +45,7 @@ constexpr int decode_smem_bytes() { return decode_stages<D>() * 2 * KvTile<D, 0>
 // EXACT (head dimensions other than 64 and 128, padded to DP): the weights keep their fp32 precision
 // in the second product, as three bf16 parts each (one participant of 62..207 rows to eight of 1500,
 // bf16: 5 to 14 times faster than one wavefront per participant and head).
-template <int DP, bool COLSPLIT, bool EXACT>
+template <int DP, bool COLSPLIT, bool EXACT, bool PIECES>
 __global__ __launch_bounds__(COLSPLIT ? 512 : 256, 1) void decode_stream_kernel(DecodeArgs a) {
   constexpr int NW = COLSPLIT ? 8 : 4;
   using TL = KvTile<DP, 0, NW, kKvTile, EXACT>;
@@ -84,10 +84,12 @@ __global__ __launch_bounds__(COLSPLIT ? 512 : 256, 1) void decode_stream_kernel(
 
   const int Hq = a.Hq, Hkv = a.Hkv;
   const int G = Hq / Hkv;
-  const int g = blockIdx.x % Hkv;
-  const int gc = blockIdx.x / Hkv;  // chunk index over all segments
+  const DecodePiece pc = decode_piece<PIECES>(a);
+  const int g = pc.g0 + blockIdx.x % pc.n_g;
+  const int gc = blockIdx.x / pc.n_g;  // chunk index over all segments
   const int rh = COLSPLIT ? wave >> 2 : 0;   // row half of the tile (column split only)
-  const int cb = blockIdx.y * QCOLS + (COLSPLIT ? 16 * (wave & 3) : 0);  // first query column of this wavefront
+  const int cb = pc.col0 + blockIdx.y * QCOLS + (COLSPLIT ? 16 * (wave & 3) : 0);  // first query column of this wavefront
+  const int col_end = pc.col0 + pc.n_cols;
 
   const DecodeChunk ch = find_decode_chunk(a, gc, lane);
   const int m = ch.m;
@@ -109,8 +111,8 @@ __global__ __launch_bounds__(COLSPLIT ? 512 : 256, 1) void decode_stream_kernel(
   // loads) so that the compiler's own wait for them does not drain the tile ring; they
   // are issued before any tile load, so the first tile wait below covers them.
   const int col = cb + l16;
-  const bool col_ok = col < a.cols;
-  const bool wave_has_cols = cb < a.cols;  // wave-uniform
+  const bool col_ok = col < col_end;
+  const bool wave_has_cols = cb < col_end;  // wave-uniform
   const int col_part = col_ok ? (sync ? col / G : m) : 0;
   const int col_head = col_ok ? g * G + (sync ? col % G : col) : 0;
   const int limit = col_ok ? (col_part == m ? own_len : rem_len) : 0;  // visible rows of this segment
@@ -303,7 +305,7 @@ __global__ __launch_bounds__(COLSPLIT ? 512 : 256, 1) void decode_stream_kernel(
     }
     // half 0 owns the merged 16 columns: write the partial straight from registers
     if (rh == 0 && col_ok) {
-      const int64_t prow = ((int64_t)g * a.n_chunks + gc) * a.cols + col;
+      const int64_t prow = partial_row(a, pc, g, gc, col);
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt)
         if (!EXACT || 16 * dt + 4 * kg < D) *reinterpret_cast<f32x4*>(part_o + prow * D + 16 * dt + 4 * kg) = o[dt];
@@ -324,7 +326,7 @@ __global__ __launch_bounds__(COLSPLIT ? 512 : 256, 1) void decode_stream_kernel(
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt) *reinterpret_cast<f32x4*>(o_s + l16 * OPAD + 16 * dt + 4 * kg) = o[dt] * f;
     __syncthreads();
-    const int64_t prow0 = ((int64_t)g * a.n_chunks + gc) * a.cols;   // at most 16 columns: one workgroup per chunk
+    const int64_t prow0 = partial_row(a, pc, g, gc, 0);   // at most 16 columns: one workgroup per chunk
     const float* o_all = reinterpret_cast<const float*>(smem);
     uint16_t* out = reinterpret_cast<uint16_t*>(out_ptr);
     const bool only = a.merge_in_kernel && ms.count == 1;   // nothing to merge: normalise and write the output rows
@@ -353,28 +355,26 @@ __global__ __launch_bounds__(COLSPLIT ? 512 : 256, 1) void decode_stream_kernel(
   }
 }
 
-// Merges the chunk partials of one (participant, query head) and writes the output row:
+// Merges the chunk partials of one query column (of one participant) and KV head and writes the output row:
 //   o = sum_c O_c 2^(m_c - m) / sum_c l_c 2^(m_c - m),  m = max_c m_c.
 // A chain of memory round trips: per kCombineAtOnce chunks one, in which every thread requests its partial O
 // rows and the first wavefront the chunks' (m, l) before anything is known about the weights.  At least
 // D/4 x 4 threads: thread (cg, d4) sums 4 head-dim elements over the chunks c = cg (mod 4); the 4 chunk groups
 // meet in LDS.  (With a serial sum of the l, three barriers and, beyond 64 chunks, two passes over them, a sync
 // block of 16 x 300..1000 rows, 8/4 heads of 64 took 12.4 instead of 11.2 us, of 1 x 8192 rows, 8/2 heads 11.9 instead of 11.3.)
-template <typename T>
+template <typename T, bool PIECES>
 __global__ __launch_bounds__(256) void decode_combine_kernel(DecodeArgs a) {
   constexpr int CG = 4;
   static_assert(kCombineAtOnce == 64 && kCombineAtOnce == 16 * CG, "one chunk per lane, 16 partial rows per thread");
   __shared__ float w_s[2][64];
   __shared__ float alpha_s[2], den_s;
   __shared__ f32x4 acc_s[CG][64];
-  const int n = blockIdx.x / a.Hq;
-  const int h = blockIdx.x % a.Hq;
-  const int G = a.Hq / a.Hkv;
-  const int g = h / G, hh = h % G;
-  const int c0 = a.is_sync ? 0 : a.chunk_cum[n];
-  const int c1 = a.is_sync ? a.n_chunks : a.chunk_cum[n + 1];
-  const int col = a.is_sync ? n * G + hh : hh;
-  const int64_t base = (int64_t)g * a.n_chunks;
+  const DecodePiece pc = decode_piece<PIECES>(a);
+  const int m = blockIdx.x / (pc.n_g * pc.n_cols);   // participant of a local block (0 in a sync block)
+  const int r = blockIdx.x % (pc.n_g * pc.n_cols);
+  const int g = pc.g0 + r / pc.n_cols, col = pc.col0 + r % pc.n_cols;
+  const int c0 = a.is_sync ? 0 : a.chunk_cum[m];
+  const int c1 = a.is_sync ? a.n_chunks : a.chunk_cum[m + 1];
   const int tid = threadIdx.x;
   const int D = a.D, D4 = D / 4;
   const int d4 = tid % D4, cg = tid / D4;  // blockDim: whole wavefronts, at least D4 * CG
@@ -383,7 +383,8 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(DecodeArgs a) {
   unsigned char* out_ptr = reinterpret_cast<unsigned char*>(a.out) + (int64_t)a.block_list[bz] * a.q_block_bytes;
   const float* part_o = reinterpret_cast<const float*>(reinterpret_cast<const unsigned char*>(a.part_o) + bz * a.slice_bytes);
   const float* part_ml = reinterpret_cast<const float*>(reinterpret_cast<const unsigned char*>(a.part_ml) + bz * a.slice_bytes);
-  const int64_t cstride = a.cols;          // partial rows between consecutive chunks
+  const int64_t row0 = partial_row(a, pc, g, 0, col);
+  const int64_t cstride = pc.n_cols;       // partial rows between consecutive chunks
 
   float m_run = -INFINITY, den = 0.f;      // first wavefront
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
@@ -391,7 +392,7 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(DecodeArgs a) {
   for (int cb = c0; cb < c1; cb += kCombineAtOnce, buf ^= 1) {
     const int nb = min(kCombineAtOnce, c1 - cb);
     const int nb_o = cg < CG ? nb : 0;     // chunks whose O rows this thread sums (every CG-th from cg on)
-    const float* po = part_o + ((base + cb) * cstride + col) * D + 4 * d4;
+    const float* po = part_o + (row0 + cb * cstride) * D + 4 * d4;
     f32x4 part[16];
 #pragma unroll
     for (int u = 0; u < 16; ++u) {
@@ -400,7 +401,7 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(DecodeArgs a) {
     }
     if (tid < 64) {
       f32x2 ml = {-INFINITY, 0.f};
-      if (tid < nb) ml = *reinterpret_cast<const f32x2*>(part_ml + ((base + cb + tid) * cstride + col) * 2);
+      if (tid < nb) ml = *reinterpret_cast<const f32x2*>(part_ml + (row0 + (cb + tid) * cstride) * 2);
       const float m_new = fmaxf(m_run, wave_max(ml[0]));
       const float mu = (m_new == -INFINITY) ? 0.f : m_new;
       const float w = __builtin_amdgcn_exp2f(ml[0] - mu);
@@ -424,7 +425,7 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(DecodeArgs a) {
   if (cg == 0) {
     const float dn = c1 > c0 ? den_s : 0.f;
     const f32x4 sum = (acc_s[0][d4] + acc_s[1][d4]) + (acc_s[2][d4] + acc_s[3][d4]);
-    T* out = reinterpret_cast<T*>(out_ptr) + ((int64_t)n * a.Hq + h) * D + 4 * d4;
+    T* out = reinterpret_cast<T*>(out_ptr) + decode_out_row(a, g, m, col) * D + 4 * d4;
     store_out4(out, sum * (dn > 0.f ? 1.f / dn : 0.f));
   }
 }
@@ -506,15 +507,19 @@ __global__ __launch_bounds__(64) void decode_rows_kernel(DecodeArgs a) {
   }
 }
 
-template <int DP, bool COLSPLIT, bool EXACT>
+// Query columns of a launch's KV heads, and those heads.
+int launch_cols(const DecodeArgs& a, bool pieces) { return pieces ? a.n_cols : a.cols; }
+int launch_heads(const DecodeArgs& a, bool pieces) { return pieces ? a.n_g : a.Hkv; }
+
+template <int DP, bool COLSPLIT, bool EXACT, bool PIECES = false>
 hipError_t launch_stream_mode(const DecodeArgs& a, int n_z, hipStream_t s) {
   static std::atomic<uint64_t> attr_done{0};
-  hipError_t e0 = set_max_dynamic_lds_once(attr_done, reinterpret_cast<const void*>(&decode_stream_kernel<DP, COLSPLIT, EXACT>),
-                                           decode_smem_bytes<DP>());
+  const auto kernel = &decode_stream_kernel<DP, COLSPLIT, EXACT, PIECES>;
+  hipError_t e0 = set_max_dynamic_lds_once(attr_done, reinterpret_cast<const void*>(kernel), decode_smem_bytes<DP>());
   if (e0 != hipSuccess) return e0;
   const int qcols = COLSPLIT ? 64 : 16;
-  dim3 grid((unsigned)(a.n_chunks * a.Hkv), (unsigned)((a.cols + qcols - 1) / qcols), (unsigned)n_z);
-  hipLaunchKernelGGL((decode_stream_kernel<DP, COLSPLIT, EXACT>), grid, dim3(COLSPLIT ? 512 : 256), decode_smem_bytes<DP>(), s, a);
+  dim3 grid((unsigned)(a.n_chunks * launch_heads(a, PIECES)), (unsigned)((launch_cols(a, PIECES) + qcols - 1) / qcols), (unsigned)n_z);
+  hipLaunchKernelGGL(kernel, grid, dim3(COLSPLIT ? 512 : 256), decode_smem_bytes<DP>(), s, a);
   return hipGetLastError();
 }
 
@@ -526,21 +531,24 @@ hipError_t launch_stream(const DecodeArgs& a, int n_z, hipStream_t s) {
 
 // other head dimensions, at most DP (8 wavefronts share a tile's loads evenly from multiples of 64 on)
 template <int DP>
-hipError_t launch_stream_exact(const DecodeArgs& a, int n_z, hipStream_t s) {
-  return a.cols <= 16 ? launch_stream_mode<DP, false, true>(a, n_z, s)
-                      : launch_stream_mode<(DP + 63) / 64 * 64, true, true>(a, n_z, s);
+hipError_t launch_stream_exact(const DecodeArgs& a, bool pieces, int n_z, hipStream_t s) {
+  constexpr int DW = (DP + 63) / 64 * 64;
+  if (pieces) return launch_stream_mode<DW, true, true, true>(a, n_z, s);
+  return a.cols <= 16 ? launch_stream_mode<DP, false, true>(a, n_z, s) : launch_stream_mode<DW, true, true>(a, n_z, s);
+}
+
+template <typename T>
+hipError_t launch_decode_combine(const DecodeArgs& a, bool pieces, int n_z, hipStream_t s) {
+  const dim3 grid((unsigned)((a.is_sync ? 1 : a.N) * launch_heads(a, pieces) * launch_cols(a, pieces)), (unsigned)n_z);
+  const dim3 block((unsigned)((a.D + 63) / 64 * 64));
+  if (pieces)
+    hipLaunchKernelGGL((decode_combine_kernel<T, true>), grid, block, 0, s, a);
+  else
+    hipLaunchKernelGGL((decode_combine_kernel<T, false>), grid, block, 0, s, a);
+  return hipGetLastError();
 }
 
 }  // namespace
-
-hipError_t launch_decode_combine(const DecodeArgs& a, int dtype, int n_z, hipStream_t s) {
-  const dim3 grid((unsigned)(a.N * a.Hq), (unsigned)n_z), block((unsigned)((a.D + 63) / 64 * 64));
-  if (dtype == FEDATTN_F32)
-    hipLaunchKernelGGL(decode_combine_kernel<float>, grid, block, 0, s, a);
-  else
-    hipLaunchKernelGGL(decode_combine_kernel<uint16_t>, grid, block, 0, s, a);
-  return hipGetLastError();
-}
 
 // n_z > 1: the blocks a.block_list[0 .. n_z) in one launch (split kernels only)
 hipError_t launch_decode(const DecodeArgs& a, int dtype, bool split, int n_z, hipStream_t s) {
@@ -554,24 +562,26 @@ hipError_t launch_decode(const DecodeArgs& a, int dtype, bool split, int n_z, hi
       hipLaunchKernelGGL(decode_rows_kernel<uint16_t>, grid, dim3(64), 0, s, a);
     return hipGetLastError();
   }
+  const bool pieces = a.n_g < a.Hkv || a.n_cols < a.cols;
   if (a.n_chunks > 0) {
     hipError_t e;
-    if (dtype == FEDATTN_F32) e = launch_decode_f32(a, n_z, s);
+    if (dtype == FEDATTN_F32) e = launch_decode_f32(a, pieces, n_z, s);
     else if (a.D == 128) e = launch_stream<128>(a, n_z, s);
     else if (a.D == 64) e = launch_stream<64>(a, n_z, s);
     else switch ((a.D + 31) / 32) {
-      case 1: e = launch_stream_exact<32>(a, n_z, s); break;
-      case 2: e = launch_stream_exact<64>(a, n_z, s); break;
-      case 3: e = launch_stream_exact<96>(a, n_z, s); break;
-      case 4: e = launch_stream_exact<128>(a, n_z, s); break;
-      case 5: e = launch_stream_exact<160>(a, n_z, s); break;
-      case 6: e = launch_stream_exact<192>(a, n_z, s); break;
-      case 7: e = launch_stream_exact<224>(a, n_z, s); break;
-      default: e = launch_stream_exact<256>(a, n_z, s);
+      case 1: e = launch_stream_exact<32>(a, pieces, n_z, s); break;
+      case 2: e = launch_stream_exact<64>(a, pieces, n_z, s); break;
+      case 3: e = launch_stream_exact<96>(a, pieces, n_z, s); break;
+      case 4: e = launch_stream_exact<128>(a, pieces, n_z, s); break;
+      case 5: e = launch_stream_exact<160>(a, pieces, n_z, s); break;
+      case 6: e = launch_stream_exact<192>(a, pieces, n_z, s); break;
+      case 7: e = launch_stream_exact<224>(a, pieces, n_z, s); break;
+      default: e = launch_stream_exact<256>(a, pieces, n_z, s);
     }
     if (e != hipSuccess) return e;
   }
-  return a.merge_in_kernel ? hipSuccess : launch_decode_combine(a, dtype, n_z, s);
+  if (a.merge_in_kernel) return hipSuccess;
+  return dtype == FEDATTN_F32 ? launch_decode_combine<float>(a, pieces, n_z, s) : launch_decode_combine<uint16_t>(a, pieces, n_z, s);
 }
 
 }  // namespace fedattn

@@ -25,7 +25,7 @@ constexpr int f32_stages() { return DP > 128 ? 1 : 2; }
 template <int DP>
 constexpr int f32_smem_bytes() { return f32_stages<DP>() * 2 * kKvTile * DP * 4; }
 
-template <int DP, int NQ>
+template <int DP, int NQ, bool PIECES>
 __global__ __launch_bounds__(256, 1) void decode_f32_kernel(DecodeArgs a) {
   constexpr int CH = DP / 4;               // 16-byte chunks per row
   constexpr int ROWB = DP * 4;
@@ -53,9 +53,10 @@ __global__ __launch_bounds__(256, 1) void decode_f32_kernel(DecodeArgs a) {
 
   const int Hq = a.Hq, Hkv = a.Hkv, D = a.D;
   const int G = Hq / Hkv;
-  const int g = blockIdx.x % Hkv;
-  const int gc = blockIdx.x / Hkv;
-  const int col0 = blockIdx.y * 16 * NQ;
+  const DecodePiece pc = decode_piece<PIECES>(a);
+  const int g = pc.g0 + blockIdx.x % pc.n_g;
+  const int gc = blockIdx.x / pc.n_g;
+  const int col0 = pc.col0 + blockIdx.y * 16 * NQ, col_end = pc.col0 + pc.n_cols;
   const DecodeChunk ch = find_decode_chunk(a, gc, lane);
   const int m = ch.m;
   const int nt = (ch.r_hi - ch.r_lo + kKvTile - 1) / kKvTile;
@@ -86,7 +87,7 @@ __global__ __launch_bounds__(256, 1) void decode_f32_kernel(DecodeArgs a) {
 #pragma unroll
   for (int iq = 0; iq < NQ; ++iq) {
     const int col = col0 + 16 * iq + l16;
-    const bool ok = col < a.cols;
+    const bool ok = col < col_end;
     const int part = ok ? (a.is_sync ? col / G : m) : 0;
     const int head = ok ? g * G + (a.is_sync ? col % G : col) : 0;
     limit[iq] = ok ? (part == m ? ch.own_len : ch.rem_len) : 0;
@@ -194,7 +195,7 @@ __global__ __launch_bounds__(256, 1) void decode_f32_kernel(DecodeArgs a) {
 #pragma unroll
   for (int iq = 0; iq < NQ; ++iq) {
     const int col = col0 + 16 * iq + l16;
-    if (col >= a.cols) continue;
+    if (col >= col_end) continue;
     float mm = -INFINITY, den = 0.f, f[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) mm = fmaxf(mm, ml_s[k][iq][0][l16]);
@@ -204,7 +205,7 @@ __global__ __launch_bounds__(256, 1) void decode_f32_kernel(DecodeArgs a) {
       f[k] = __builtin_amdgcn_exp2f(ml_s[k][iq][0][l16] - mu);
       den = fmaf(ml_s[k][iq][1][l16], f[k], den);
     }
-    const int64_t prow = ((int64_t)g * a.n_chunks + gc) * a.cols + col;
+    const int64_t prow = partial_row(a, pc, g, gc, col);
     const bool only = a.merge_in_kernel && ms.count == 1;   // nothing to merge: the output row itself
     const float norm = only ? (den > 0.f ? 1.f / den : 0.f) : 1.f;
     float* dst = only ? out_ptr + decode_out_row(a, g, m, col) * D : part_o + prow * D;
@@ -226,13 +227,15 @@ __global__ __launch_bounds__(256, 1) void decode_f32_kernel(DecodeArgs a) {
   if (NQ == 1 && a.merge_in_kernel && ms.count > 1) merge_if_last(a, ms, g, m, D, part_o, part_ml, out_ptr);
 }
 
-template <int DP, int NQ>
+template <int DP, int NQ, bool PIECES = false>
 hipError_t launch_decode_f32_t(const DecodeArgs& a, int n_z, hipStream_t s) {
   static std::atomic<uint64_t> attr_done{0};
-  hipError_t e = set_max_dynamic_lds_once(attr_done, reinterpret_cast<const void*>(&decode_f32_kernel<DP, NQ>), f32_smem_bytes<DP>());
+  const auto kernel = &decode_f32_kernel<DP, NQ, PIECES>;
+  hipError_t e = set_max_dynamic_lds_once(attr_done, reinterpret_cast<const void*>(kernel), f32_smem_bytes<DP>());
   if (e != hipSuccess) return e;
-  dim3 grid((unsigned)(a.n_chunks * a.Hkv), (unsigned)((a.cols + 16 * NQ - 1) / (16 * NQ)), (unsigned)n_z);
-  hipLaunchKernelGGL((decode_f32_kernel<DP, NQ>), grid, dim3(256), f32_smem_bytes<DP>(), s, a);
+  const int heads = PIECES ? a.n_g : a.Hkv, cols = PIECES ? a.n_cols : a.cols;
+  dim3 grid((unsigned)(a.n_chunks * heads), (unsigned)((cols + 16 * NQ - 1) / (16 * NQ)), (unsigned)n_z);
+  hipLaunchKernelGGL(kernel, grid, dim3(256), f32_smem_bytes<DP>(), s, a);
   return hipGetLastError();
 }
 
@@ -243,8 +246,9 @@ hipError_t launch_decode_f32_t(const DecodeArgs& a, int n_z, hipStream_t s) {
 // 2 x 1500 rows, 24/1 heads of 128 19.0 -> 11.6 (NQ = 1); 8 x 1000..4000 rows, 8/2 heads of 128 31.2 -> 23.3 (NQ = 2,
 // 26.4 with 1); 32 x 500..1500 rows, 8/1 heads of 128 112 (NQ = 4, 116 with 2, 140 with 1).
 template <int DP>
-hipError_t launch_decode_f32_d(const DecodeArgs& a, int n_z, hipStream_t s) {
+hipError_t launch_decode_f32_d(const DecodeArgs& a, bool pieces, int n_z, hipStream_t s) {
   constexpr int kMost = DP > 128 ? 2 : 4;
+  if (pieces) return launch_decode_f32_t<DP, kMost, true>(a, n_z, s);   // hundreds of columns
   constexpr int kResident = 160 * 1024 / f32_smem_bytes<DP>() > 2 ? 2 : 160 * 1024 / f32_smem_bytes<DP>();
   const double tiles = (a.chunk_rows + kKvTile - 1) / kKvTile, u = 0.85 * DP / 128;
   int nq = 1;
@@ -265,13 +269,13 @@ hipError_t launch_decode_f32_d(const DecodeArgs& a, int n_z, hipStream_t s) {
 
 }  // namespace
 
-hipError_t launch_decode_f32(const DecodeArgs& a, int n_z, hipStream_t s) {
-  if (a.D <= 32) return launch_decode_f32_d<32>(a, n_z, s);
-  if (a.D <= 64) return launch_decode_f32_d<64>(a, n_z, s);
-  if (a.D <= 96) return launch_decode_f32_d<96>(a, n_z, s);
-  if (a.D <= 128) return launch_decode_f32_d<128>(a, n_z, s);
-  if (a.D <= 192) return launch_decode_f32_d<192>(a, n_z, s);
-  return launch_decode_f32_d<256>(a, n_z, s);
+hipError_t launch_decode_f32(const DecodeArgs& a, bool pieces, int n_z, hipStream_t s) {
+  if (a.D <= 32) return launch_decode_f32_d<32>(a, pieces, n_z, s);
+  if (a.D <= 64) return launch_decode_f32_d<64>(a, pieces, n_z, s);
+  if (a.D <= 96) return launch_decode_f32_d<96>(a, pieces, n_z, s);
+  if (a.D <= 128) return launch_decode_f32_d<128>(a, pieces, n_z, s);
+  if (a.D <= 192) return launch_decode_f32_d<192>(a, pieces, n_z, s);
+  return launch_decode_f32_d<256>(a, pieces, n_z, s);
 }
 
 }  // namespace fedattn

@@ -70,6 +70,19 @@ __device__ __attribute__((always_inline)) inline void claim_counter(const MergeS
     (void)__hip_atomic_compare_exchange_strong(s.cnt, &found, ticket << 16, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// What a launch works on: all KV heads and query columns, or a piece of them.
+struct DecodePiece {
+  int g0, n_g, col0, n_cols;
+};
+template <bool PIECES>
+__device__ __attribute__((always_inline)) inline DecodePiece decode_piece(const DecodeArgs& a) {
+  return PIECES ? DecodePiece{a.g0, a.n_g, a.col0, a.n_cols} : DecodePiece{0, a.Hkv, 0, a.cols};
+}
+// Row of the partials that chunk gc leaves for query column col of KV head g.
+__device__ __attribute__((always_inline)) inline int64_t partial_row(const DecodeArgs& a, const DecodePiece& p, int g, int gc, int col) {
+  return ((int64_t)(g - p.g0) * a.n_chunks + gc) * p.n_cols + (col - p.col0);
+}
+
 // Output row of query column col: local block, head col of participant m's KV group; sync block, head
 // col mod G of participant col / G.
 __device__ __attribute__((always_inline)) inline int64_t decode_out_row(const DecodeArgs& a, int g, int m, int col) {

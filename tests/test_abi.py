@@ -82,3 +82,16 @@ def test_decode_validation_returns_codes_without_touching_the_gpu(lib):
     assert lib.fedattn_decode_blocks_fused(ctypes.byref(ok), 0, 70000, fake, fake, fake, fake, 1024, 32768, seg, lens, null,
                                            -1, fake, big, null) == fa.FEDATTN_EINVAL
     assert b"65535" in lib.fedattn_last_error()
+
+
+def test_decode_workspace_of_other_shapes_is_bounded(lib):
+    """fp32, and bf16 with head dimensions other than 64 and 128: never more than the built-in array of
+    fedattn_decode_static, which therefore takes every such block."""
+    for n, hq, hkv, d, dtype in ((128, 32, 8, 256, torch.float32), (128, 32, 8, 128, torch.float32), (32, 32, 8, 128, torch.float32),
+                                 (128, 64, 8, 256, torch.bfloat16), (128, 32, 1, 96, torch.bfloat16)):
+        p = fa.make_params(n, hq, hkv, d, 2, dtype)
+        assert fa.fedattn_workspace_bytes(p, fa.FEDATTN_OP_DECODE, 1 << 20) == fa.FEDATTN_STATIC_SCRATCH_BYTES
+    small = fa.make_params(4, 8, 2, 64, 2, torch.float32)
+    assert 0 < fa.fedattn_workspace_bytes(small, fa.FEDATTN_OP_DECODE, 4096) < fa.FEDATTN_STATIC_SCRATCH_BYTES
+    big = fa.make_params(128, 64, 8, 128, 2, torch.bfloat16)
+    assert fa.fedattn_workspace_bytes(big, fa.FEDATTN_OP_DECODE, 4096) > fa.FEDATTN_STATIC_SCRATCH_BYTES

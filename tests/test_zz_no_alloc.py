@@ -62,3 +62,41 @@ def test_decode_static_rejects_problems_beyond_its_array():
         fa.fedattn_decode_static(p, 0, t, kv, kv, torch.empty_like(t), seg, np.full(N, 64, np.int32))
     assert e.value.status == fa.FEDATTN_EWORKSPACE and "scratch" in str(e.value)
     torch.cuda.synchronize()
+
+
+# (segment lengths, Hq, Hkv, D): partials of all KV heads beyond the built-in array; those of one head's columns beyond
+# it (pieces of 64 columns, of 48); local blocks beyond it
+PIECES = {"heads": ([65, 0, 1, 130] * 8, 32, 8, 128), "columns": ([70 + n % 60 for n in range(127)] + [0], 16, 4, 256),
+          "few-columns": ([64 + n % 65 for n in range(128)], 4, 1, 256), "local": ([20 + n for n in range(128)], 64, 8, 256)}
+
+
+@pytest.mark.parametrize("shape", sorted(PIECES))
+@pytest.mark.parametrize("dtype", [torch.float32, BF16])
+def test_decode_in_pieces(shape, dtype):
+    """fp32 and bf16 with other head dimensions: blocks whose partials exceed the built-in array run in pieces, with a
+    workspace (never larger than the array) and without one alike."""
+    lens, Hq, Hkv, D = PIECES[shape]
+    D = D if dtype == torch.float32 else D - 24
+    N, lens = len(lens), np.asarray(lens, dtype=np.int32)
+    seg = np.concatenate([[0], np.cumsum(lens + 1)]).astype(np.int32)
+    g = np.random.default_rng(903)
+    mk = lambda *s: (fi.round_to_bf16 if dtype == BF16 else (lambda x: x))(g.standard_normal(s).astype(np.float32))
+    q, kc, vc = mk(N, Hq, D), mk(int(seg[-1]), Hkv, D), mk(int(seg[-1]), Hkv, D)
+    p = fa.make_params(N, Hq, Hkv, D, 2, dtype)
+    need = fa.fedattn_workspace_bytes(p, fa.FEDATTN_OP_DECODE, int(seg[-1]))
+    assert need == fa.FEDATTN_STATIC_SCRATCH_BYTES      # the whole block would take more
+    tq, tk, tv = dev(q, dtype), dev(kc, dtype), dev(vc, dtype)
+    ws = torch.full((2 * need,), 255, dtype=torch.uint8, device="cuda")
+    for block, rl in [(0, None), (1, None), (1, lens // 2)]:
+        what = "decode pieces %s %s block %d remote=%s" % (shape, dtype, block, rl is not None)
+        say(what)
+        ref = oracle.decode_step(q, kc, vc, seg, lens, is_sync=oracle.is_sync_block(2, block), remote_lens=rl)
+        outs = [torch.full_like(tq, float("nan")) for _ in range(4)]
+        fa.fedattn_decode(p, block, tq, tk, tv, outs[0], seg, lens, remote_lens=rl, workspace=ws[:need])
+        fa.fedattn_decode(p, block, tq, tk, tv, outs[1], seg, lens, remote_lens=rl, workspace=ws)
+        fa.fedattn_decode_blocks_fused(p, block, 1, tq, tk, tv, outs[2], tq.numel(), tk.numel(), seg, lens, remote_lens=rl, workspace=ws)
+        fa.fedattn_decode_static(p, block, tq, tk, tv, outs[3], seg, lens, remote_lens=rl)
+        torch.cuda.synchronize()
+        check(host(outs[0]), ref, dtype, what)
+        for o in outs[1:]:
+            assert torch.equal(o, outs[0]), what
