@@ -99,10 +99,10 @@ FEDATTN_API size_t fedattn_workspace_bytes(const fedattn_params* params, int32_t
  *   bf16), otherwise applied to the fp32 scores.  Other bf16 shapes: fp32 arithmetic on the
  *   bf16 values (on bf16 MFMA: the products of bf16 values are exact in fp32, and a weight enters
  *   the second product as the three bf16 values that it is the exact sum of).
- *   Non-finite elements of K and V make the rows that see them non-finite; a masked row meets them
- *   with weight zero, so those of V also reach rows of the same query tile (at most 128 rows of
- *   one segment) that come before them.  The calls that run on the general kernel (fp32, or bf16 with
- *   another D, with a keep-list and no workspace) have no such tile.
+ *   Non-finite elements of K and V make the rows that see them non-finite (a score of minus
+ *   infinity is a weight of zero).  They do not reach other rows, except with bf16 and D = 64 or
+ *   128, where a masked row of V is met with weight zero: there those of V also reach rows of the
+ *   same query tile (at most 128 rows of one segment) that come before them.
  *
  *   block_idx      0-based block index; with sync_override = -1 the block is a sync
  *                  block iff fedattn_is_sync_block(params->sync_interval, block_idx).
@@ -181,7 +181,8 @@ FEDATTN_API fedattn_status fedattn_prefill_blocks(const fedattn_params* params, 
  *   seg_lens       host int32[N]: valid rows of each segment, <= its capacity.
  *   remote_lens    host int32[N] or NULL (= seg_lens): rows of segment m that the
  *                  other participants see in a sync block (e.g. the prompt length
- *                  when generated tokens are not exchanged).
+ *                  when generated tokens are not exchanged).  Non-finite elements of the other
+ *                  rows reach nobody else, except with bf16 and D = 64 or 128 those of V.
  *   workspace      device, >= fedattn_workspace_bytes(DECODE); holds split-KV partials and
  *                  chunk counters while the call's kernels run.  What it contains on entry
  *                  does not matter; calls that share a workspace must be ordered (same stream).

@@ -18,6 +18,7 @@
 #include "common.h"
 #include "decode_walk.h"
 #include "mfma_tile.h"
+#include "row_walk.h"
 
 namespace fedattn {
 
@@ -316,6 +317,8 @@ __global__ __launch_bounds__(COLSPLIT ? 512 : 256, 1) void decode_stream_kernel(
     }
   } else {
     // ---- merge the 4 wavefronts (each saw a quarter of the rows) ----------------------------
+    __shared__ uint32_t odd_s;   // EXACT: output columns that came out not finite
+    if (EXACT && tid == 0) odd_s = 0;
     if (kg == 0) m_s[wave][l16] = m_run;
     __syncthreads();  // also: every wavefront is done with the tile ring
     const float mm = fmaxf(fmaxf(m_s[0][l16], m_s[1][l16]), fmaxf(m_s[2][l16], m_s[3][l16]));
@@ -340,18 +343,26 @@ __global__ __launch_bounds__(COLSPLIT ? 512 : 256, 1) void decode_stream_kernel(
       const f32x4 sum = (v0 + v1) + (v2 + v3);
       if (only) {
         const float den = l_s[0][cl] + l_s[1][cl] + l_s[2][cl] + l_s[3][cl];
-        store_out4(out + decode_out_row(a, g, m, cl) * D + 4 * d4, sum * (den > 0.f ? 1.f / den : 0.f));
+        const f32x4 res = sum * (den > 0.f ? 1.f / den : 0.f);
+        store_out4(out + decode_out_row(a, g, m, cl) * D + 4 * d4, res);
+        if constexpr (EXACT) note_nonfinite(res, cl, &odd_s);
       } else {
         float* dst = part_o + (prow0 + cl) * D + 4 * d4;
         store_pair_agent(dst, sum[0], sum[1]);
         store_pair_agent(dst + 2, sum[2], sum[3]);
       }
     }
-    if (only) return;
+    if (only) {
+      if constexpr (EXACT) {
+        lds_barrier();
+        if (__builtin_expect(odd_s != 0, 0)) redo_decode_columns<uint16_t, 4>(q_ptr, k_ptr, v_ptr, out_ptr, g, m, 0, odd_s);
+      }
+      return;
+    }
     if (tid < a.cols)
       store_pair_agent(part_ml + (prow0 + tid) * 2, fmaxf(fmaxf(m_s[0][tid], m_s[1][tid]), fmaxf(m_s[2][tid], m_s[3][tid])),
                        l_s[0][tid] + l_s[1][tid] + l_s[2][tid] + l_s[3][tid]);
-    if (a.merge_in_kernel) merge_if_last(a, ms, g, m, D, part_o, part_ml, out);
+    if (a.merge_in_kernel) merge_if_last<uint16_t, EXACT>(a, ms, g, m, D, part_o, part_ml, out, q_ptr, k_ptr, v_ptr);
   }
 }
 
@@ -422,11 +433,23 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(DecodeArgs a) {
   }
   if (cg < CG) acc_s[cg][d4] = acc;
   __syncthreads();
+  bool odd = false;
   if (cg == 0) {
     const float dn = c1 > c0 ? den_s : 0.f;
     const f32x4 sum = (acc_s[0][d4] + acc_s[1][d4]) + (acc_s[2][d4] + acc_s[3][d4]);
     T* out = reinterpret_cast<T*>(out_ptr) + decode_out_row(a, g, m, col) * D + 4 * d4;
-    store_out4(out, sum * (dn > 0.f ? 1.f / dn : 0.f));
+    const f32x4 res = sum * (dn > 0.f ? 1.f / dn : 0.f);
+    store_out4(out, res);
+    // second look (row_walk.h); these threads are lanes of the first wavefront
+    FiniteCheck fin;
+    fin.add4(res);
+    odd = fin.failed() && (sizeof(T) == 4 || (D != 64 && D != 128));
+  }
+  if (__builtin_expect(tid < 64 && __builtin_amdgcn_ballot_w64(odd) != 0, 0)) {
+    const int64_t blk = a.block_list[bz];
+    redo_decode_columns<T, 1>(reinterpret_cast<const unsigned char*>(a.q) + blk * a.q_block_bytes,
+                              reinterpret_cast<const unsigned char*>(a.k_cache) + blk * a.cache_block_bytes,
+                              reinterpret_cast<const unsigned char*>(a.v_cache) + blk * a.cache_block_bytes, out_ptr, g, m, col, 1u);
   }
 }
 
@@ -434,77 +457,14 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(DecodeArgs a) {
 // bf16 storage): one wavefront per (participant, query head), no split and no workspace.  It takes
 // the calls that come without one; with one they run 5 to 59 times faster on the split kernels.
 template <typename T>
-__device__ inline float ld(const T* p) {
-  if constexpr (sizeof(T) == 2)
-    return bf16_bits_to_f32(*p);
-  else
-    return *p;
-}
-
-template <typename T>
 __global__ __launch_bounds__(64) void decode_rows_kernel(DecodeArgs a) {
   __shared__ float qs[256];
-  __shared__ float ps[64];
-  const int lane = threadIdx.x;
   const int n = blockIdx.x / a.Hq, h = blockIdx.x % a.Hq;
-  const int g = h / (a.Hq / a.Hkv);
-  const int D = a.D;
-  const T* q = reinterpret_cast<const T*>(a.q) + ((int64_t)n * a.Hq + h) * D;
-  const T* kc = reinterpret_cast<const T*>(a.k_cache);
-  const T* vc = reinterpret_cast<const T*>(a.v_cache);
-  for (int d = lane; d < D; d += 64) qs[d] = ld(q + d);
+  const T* q = reinterpret_cast<const T*>(a.q) + ((int64_t)n * a.Hq + h) * a.D;
+  for (int d = threadIdx.x; d < a.D; d += 64) qs[d] = RowLoad<T>::at(q + d);
   __syncthreads();
-
-  float m_run = -INFINITY, l_run = 0.f;
-  float acc[4] = {0.f, 0.f, 0.f, 0.f};
-  for (int m = 0; m < a.N; ++m) {
-    int len;
-    if (m == n) len = a.seg_lens[m];
-    else if (!a.is_sync) len = 0;
-    else len = a.has_remote ? a.remote_lens[m] : a.seg_lens[m];
-    for (int base = 0; base < len; base += 64) {
-      const int r = base + lane;
-      float s = -INFINITY;
-      if (r < len) {
-        const T* krow = kc + ((int64_t)(a.seg_off[m] + r) * a.Hkv + g) * D;
-        float dot = 0.f;
-        for (int d = 0; d < D; ++d) dot = fmaf(qs[d], ld(krow + d), dot);
-        s = a.scale * dot;
-      }
-      const float m_new = fmaxf(m_run, wave_max(s));
-      const float alpha = expf(m_run - m_new);
-      const float p = expf(s - m_new);
-      ps[lane] = p;
-      l_run = l_run * alpha + wave_sum(p);
-      m_run = m_new;
-#pragma unroll
-      for (int dd = 0; dd < 4; ++dd) acc[dd] *= alpha;
-      __syncthreads();
-      const int cnt = min(64, len - base);
-      for (int jj = 0; jj < cnt; ++jj) {
-        const float pj = ps[jj];
-        const T* vrow = vc + ((int64_t)(a.seg_off[m] + base + jj) * a.Hkv + g) * D;
-#pragma unroll
-        for (int dd = 0; dd < 4; ++dd) {
-          const int d = lane + 64 * dd;
-          if (d < D) acc[dd] = fmaf(pj, ld(vrow + d), acc[dd]);
-        }
-      }
-      __syncthreads();
-    }
-  }
-  const float inv = l_run > 0.f ? 1.f / l_run : 0.f;
-  T* out = reinterpret_cast<T*>(a.out) + ((int64_t)n * a.Hq + h) * D;
-#pragma unroll
-  for (int dd = 0; dd < 4; ++dd) {
-    const int d = lane + 64 * dd;
-    if (d < D) {
-      if constexpr (sizeof(T) == 2)
-        out[d] = f32_to_bf16_bits(acc[dd] * inv);
-      else
-        out[d] = acc[dd] * inv;
-    }
-  }
+  decode_row(a, reinterpret_cast<const T*>(a.k_cache), reinterpret_cast<const T*>(a.v_cache), reinterpret_cast<T*>(a.out), n, h,
+             [&](int d) { return qs[d]; });
 }
 
 // Query columns of a launch's KV heads, and those heads.

@@ -62,8 +62,9 @@ __global__ __launch_bounds__(256, 1) void decode_f32_kernel(DecodeArgs a) {
   const int nt = (ch.r_hi - ch.r_lo + kKvTile - 1) / kKvTile;
   const int row_elems = Hkv * D;
   const int64_t first = ((int64_t)(ch.seg_row0 + ch.r_lo) * Hkv + g) * D;
-  const float* kbase = reinterpret_cast<const float*>(reinterpret_cast<const unsigned char*>(a.k_cache) + blk * a.cache_block_bytes) + first;
-  const float* vbase = reinterpret_cast<const float*>(reinterpret_cast<const unsigned char*>(a.v_cache) + blk * a.cache_block_bytes) + first;
+  const float* k_ptr = reinterpret_cast<const float*>(reinterpret_cast<const unsigned char*>(a.k_cache) + blk * a.cache_block_bytes);
+  const float* v_ptr = reinterpret_cast<const float*>(reinterpret_cast<const unsigned char*>(a.v_cache) + blk * a.cache_block_bytes);
+  const float *kbase = k_ptr + first, *vbase = v_ptr + first;
 
   // slot (row, cp) of a tile receives chunk cp ^ (row mod 8)
   auto issue = [&](int t) __attribute__((always_inline)) {
@@ -179,6 +180,8 @@ __global__ __launch_bounds__(256, 1) void decode_f32_kernel(DecodeArgs a) {
 
   if (set_up) claim_counter(ms, cnt_found, a.ticket);
   // merge the 4 wavefronts through LDS, each taking every fourth slice of the head dimension
+  __shared__ uint32_t odd_s;   // output columns that came out not finite
+  if (tid == 0) odd_s = 0;
   __syncthreads();
   f32x4* xo = reinterpret_cast<f32x4*>(smem) + lane;
 #pragma unroll
@@ -217,6 +220,7 @@ __global__ __launch_bounds__(256, 1) void decode_f32_kernel(DecodeArgs a) {
       if (16 * dt + 4 * kg >= D) continue;
       if (NQ > 1 || only) {
         *reinterpret_cast<f32x4*>(dst + 16 * dt + 4 * kg) = acc;
+        if (NQ == 1) note_nonfinite(acc, l16, &odd_s);
       } else {
         store_pair_agent(dst + 16 * dt + 4 * kg, acc[0], acc[1]);
         store_pair_agent(dst + 16 * dt + 4 * kg + 2, acc[2], acc[3]);
@@ -224,7 +228,14 @@ __global__ __launch_bounds__(256, 1) void decode_f32_kernel(DecodeArgs a) {
     }
     if (!only && wave == 0 && kg == 0) store_pair_agent(part_ml + prow * 2, mm, den);
   }
-  if (NQ == 1 && a.merge_in_kernel && ms.count > 1) merge_if_last(a, ms, g, m, D, part_o, part_ml, out_ptr);
+  if (NQ == 1 && a.merge_in_kernel) {
+    if (ms.count > 1) {
+      merge_if_last<float, true>(a, ms, g, m, D, part_o, part_ml, out_ptr, q_ptr, k_ptr, v_ptr);
+    } else {
+      lds_barrier();
+      if (__builtin_expect(odd_s != 0, 0)) redo_decode_columns<float, 4>(q_ptr, k_ptr, v_ptr, out_ptr, g, m, 0, odd_s);
+    }
+  }
 }
 
 template <int DP, int NQ, bool PIECES = false>

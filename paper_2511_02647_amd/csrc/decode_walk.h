@@ -4,6 +4,7 @@
 
 #include "common.h"
 #include "mfma_tile.h"
+#include "row_walk.h"
 
 namespace fedattn {
 
@@ -100,6 +101,13 @@ __device__ __attribute__((always_inline)) inline void store_out4(T* p, const f32
   }
 }
 
+// Sets bit cl of *odd if one of the four values is not finite.
+__device__ __attribute__((always_inline)) inline void note_nonfinite(const f32x4& v, int cl, uint32_t* odd) {
+  FiniteCheck fin;
+  fin.add4(v);
+  if (fin.failed()) atomicOr(odd, 1u << cl);
+}
+
 // Two floats at an 8-byte aligned address, coherent at the device.
 __device__ inline void store_pair_agent(float* p, float x, float y) {
   __hip_atomic_store(reinterpret_cast<uint64_t*>(p), __builtin_bit_cast(uint64_t, f32x2{x, y}), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -116,10 +124,13 @@ __device__ inline f32x2 load_pair_agent(const float* p) {
 // stores have completed (vmcnt = 0 in every wavefront, then the barrier).
 // All partials of kMergeBatch chunks are requested before the first is looked at: one round trip to memory
 // for them together (one chunk at a time, for the maximum and again for the sum, it was two per chunk).
-template <typename T>
+// REDO: with a second look at columns that come out not finite (row_walk.h); q, k, v: the block's own.
+template <typename T, bool REDO>
 __device__ __attribute__((always_inline)) inline void merge_if_last(const DecodeArgs& a, const MergeSet& s, int g, int m, int D,
-                                                                    const float* part_o, const float* part_ml, T* out) {
+                                                                    const float* part_o, const float* part_ml, T* out, const void* q,
+                                                                    const void* k, const void* v) {
   __shared__ int last_s;
+  __shared__ uint32_t odd_s;
   const int tid = threadIdx.x;
   __atomic_signal_fence(__ATOMIC_SEQ_CST);
   wait_vmcnt<0>();
@@ -131,6 +142,7 @@ __device__ __attribute__((always_inline)) inline void merge_if_last(const Decode
     // left at zero: a launch replayed from a graph comes with the same ticket, and the call's later ones without
     if (last) __hip_atomic_store(s.cnt, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     last_s = last;
+    odd_s = 0;
   }
   __syncthreads();
   if (!last_s) return;
@@ -173,7 +185,13 @@ __device__ __attribute__((always_inline)) inline void merge_if_last(const Decode
         acc[3] = fmaf(hi[u][1], w, acc[3]);
       }
     }
-    store_out4(out + decode_out_row(a, g, m, cl) * D + 4 * d4, acc * (den > 0.f ? 1.f / den : 0.f));
+    acc *= den > 0.f ? 1.f / den : 0.f;
+    store_out4(out + decode_out_row(a, g, m, cl) * D + 4 * d4, acc);
+    if constexpr (REDO) note_nonfinite(acc, cl, &odd_s);
+  }
+  if constexpr (REDO) {
+    lds_barrier();
+    if (__builtin_expect(odd_s != 0, 0)) redo_decode_columns<T, 4>(q, k, v, out, g, m, 0, odd_s);
   }
 }
 

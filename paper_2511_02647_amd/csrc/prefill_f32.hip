@@ -14,6 +14,7 @@
 #include "common.h"
 #include "mfma_tile.h"
 #include "prefill_walk.h"
+#include "row_walk.h"
 
 namespace fedattn {
 
@@ -227,16 +228,29 @@ __global__ __launch_bounds__(256, DP > 128 ? 1 : 2) void prefill_f32_kernel(Pref
 
 #pragma unroll
   for (int iq = 0; iq < NQ; ++iq) l_run[iq] = sum_over_kgroups(l_run[iq]);
+  uint32_t odd = 0;   // rows that came out not finite: bit 16 iq + l16
+  auto look = [&](int iq, bool nan) __attribute__((always_inline)) {
+    const uint64_t lanes = __builtin_amdgcn_ballot_w64(nan);
+    const uint32_t both = (uint32_t)lanes | (uint32_t)(lanes >> 32);
+    odd |= ((both | both >> 16) & 0xffffu) << (16 * iq);
+  };
   if constexpr (KS == 1) {
 #pragma unroll
     for (int iq = 0; iq < NQ; ++iq) {
       const int row = row0 + 16 * iq + l16;
       const float inv = l_run[iq] > 0.f ? 1.f / l_run[iq] : 0.f;
-      if (row >= w.seg_hi) continue;
+      FiniteCheck fin;
       float* orow = op + ((int64_t)row * Hq + head) * D + 4 * kg;
+      const bool mine = row < w.seg_hi;
 #pragma unroll
-      for (int dt = 0; dt < DS; ++dt)
-        if (16 * dt + 4 * kg < D) __builtin_nontemporal_store(o[iq][dt] * inv, reinterpret_cast<f32x4*>(orow + 16 * dt));
+      for (int dt = 0; dt < DS; ++dt) {
+        const f32x4 x = o[iq][dt] * inv;
+        if (16 * dt + 4 * kg < D) {
+          fin.add4(x);
+          if (mine) __builtin_nontemporal_store(x, reinterpret_cast<f32x4*>(orow + 16 * dt));
+        }
+      }
+      look(iq, mine && fin.failed());
     }
   } else {
     // merge the KS wavefronts of a query group through LDS, each taking every KS-th slice of the head dimension
@@ -267,15 +281,23 @@ __global__ __launch_bounds__(256, DP > 128 ? 1 : 2) void prefill_f32_kernel(Pref
       const int row = row0 + 16 * iq + l16;
       const float inv = den > 0.f ? 1.f / den : 0.f;
       float* orow = op + ((int64_t)row * Hq + head) * D + 4 * kg;
+      const bool mine = row < w.seg_hi;
+      FiniteCheck fin;
       for (int dt = ks; dt < DS; dt += KS) {
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int k = 0; k < KS; ++k) acc += xo[(((qg * KS + k) * NQ + iq) * DS + dt) * 64] * f[k];
-        if (row < w.seg_hi && 16 * dt + 4 * kg < D)
-          __builtin_nontemporal_store(acc * inv, reinterpret_cast<f32x4*>(orow + 16 * dt));
+        acc *= inv;
+        if (16 * dt + 4 * kg < D) {
+          fin.add4(acc);
+          if (mine) __builtin_nontemporal_store(acc, reinterpret_cast<f32x4*>(orow + 16 * dt));
+        }
       }
+      look(iq, mine && fin.failed());
     }
   }
+  if (__builtin_expect(odd != 0, 0))   // a wavefront wrote the slices ks, ks + KS, ... of its rows
+    redo_prefill_rows<float, 1>(row0, odd, head, [&](int d) { return KS == 1 || (d >> 4) % KS == ks; });
 }
 
 template <int DP, int NQ, int KS>

@@ -28,6 +28,7 @@
 #include "common.h"
 #include "mfma_tile.h"
 #include "prefill_walk.h"
+#include "row_walk.h"
 
 namespace fedattn {
 
@@ -249,6 +250,10 @@ __global__ __launch_bounds__(256 * NG, DP > 128 ? 1 : DP > 64 ? 2 : 3) void pref
     }
   }
   int git = 0;  // iterations this workgroup has run: stage of an iteration = git & 1
+  // EXACT: the wavefront's rows that came out not finite, per walk (in LDS: its registers are all in use)
+  struct OddRows { uint32_t odd; int row0; };
+  __shared__ OddRows odd_s[4][2];
+  if (EXACT && grp == 0) odd_s[wave][0].odd = odd_s[wave][1].odd = 0;
 
   for (int part = 0;; ++part) {
     const bool more = part == 0 && two;
@@ -385,18 +390,42 @@ __global__ __launch_bounds__(256 * NG, DP > 128 ? 1 : DP > 64 ? 2 : 3) void pref
           *reinterpret_cast<u32x2*>(stage + l32 * ROWB + ((c ^ TL::k_swizzle(l32)) << 4) + 8 * hf) =
               __builtin_bit_cast(u32x2, w);
         }
+      FiniteCheckBf16 fin;
 #pragma unroll
       for (int kk = 0; kk < kWaveRows * CPR / 64; ++kk) {
         const int r = (kk * 64 + lane) / CPR, c = (kk * 64 + lane) % CPR;
         const u32x4 w = *reinterpret_cast<const u32x4*>(stage + r * ROWB + ((c ^ TL::k_swizzle(r)) << 4));
+        if constexpr (EXACT) fin.add8(w);
         if (cur.row0w + r < cur.seg_hi && (!EXACT || 8 * c < D))
           // streaming store: the rows are not read again in this launch, and written through
           // now they are not left for the write-back at the end of the kernel
           __builtin_nontemporal_store(w, reinterpret_cast<u32x4*>(op + ((int64_t)(cur.row0w + r) * Hq + head) * D + 8 * c));
       }
+      if constexpr (EXACT) {
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(fin.failed()) != 0, 0)) {   // which rows
+          if (lane == 0) odd_s[wave][part].row0 = cur.row0w;
+#pragma unroll 1
+          for (int kk = 0; kk < kWaveRows * CPR / 64; ++kk) {
+            const int r = (kk * 64 + lane) / CPR, c = (kk * 64 + lane) % CPR;
+            FiniteCheckBf16 piece;
+            piece.add8(*reinterpret_cast<const u32x4*>(stage + r * ROWB + ((c ^ TL::k_swizzle(r)) << 4)));
+            if (cur.row0w + r < cur.seg_hi && 8 * c < D && piece.failed()) atomicOr(&odd_s[wave][part].odd, 1u << r);
+          }
+        }
+      }
     }
     if (!more) break;
     cur = nxt;
+  }
+  if constexpr (EXACT) {
+    if (grp == 0) {
+#pragma unroll 1
+      for (int part = 0; part < 2; ++part) {
+        const uint32_t odd = __builtin_amdgcn_readfirstlane(odd_s[wave][part].odd);
+        if (__builtin_expect(odd != 0, 0))
+          redo_prefill_rows<uint16_t, 1>(__builtin_amdgcn_readfirstlane(odd_s[wave][part].row0), odd, head, [](int) { return true; });
+      }
+    }
   }
 }
 

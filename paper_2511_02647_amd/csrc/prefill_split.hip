@@ -18,6 +18,7 @@
 #include "half_tile.h"
 #include "mfma_tile.h"
 #include "prefill_walk.h"
+#include "row_walk.h"
 
 namespace fedattn {
 
@@ -43,6 +44,7 @@ __global__ __launch_bounds__(64 * kSplitWaves, DP > 64 ? 2 : 4) void prefill_spl
   constexpr int NT = 64 * KS;
   extern __shared__ __attribute__((aligned(1024))) unsigned char kv_lds[];  // the shares, then the Q tile (in the end the output)
   __shared__ float ml_s[KS][2][64];
+  __shared__ uint32_t odd_s;   // EXACT: rows that came out not finite
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -242,6 +244,7 @@ __global__ __launch_bounds__(64 * kSplitWaves, DP > 64 ? 2 : 4) void prefill_spl
   // quarter of a 32-column slice of the output ------------------------------------------------------
   static_assert(DT * 4096 <= WAVEB, "the merge reuses the tiles");
   f32x4* xo = reinterpret_cast<f32x4*>(own) + lane;
+  if (EXACT && tid == 0) odd_s = 0;
   ml_s[wave][0][lane] = m_run;
   ml_s[wave][1][lane] = sum_across_halves(l_run);
 #pragma unroll
@@ -260,13 +263,19 @@ __global__ __launch_bounds__(64 * kSplitWaves, DP > 64 ? 2 : 4) void prefill_spl
     den = fmaf(ml_s[k][1][lane], f[k], den);
   }
   const float inv = den > 0.f ? 1.f / den : 0.f;
+  FiniteCheck fin;
 #pragma unroll
   for (int c = wave; c < 4 * DT; c += KS) {
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int k = 0; k < KS; ++k) acc += *(reinterpret_cast<const f32x4*>(kv_lds + k * WAVEB) + lane + c * 64) * f[k];
+    if (EXACT && 8 * c < D) fin.add4(acc * inv);
     const bf16x4 b = {(bf16_t)(acc[0] * inv), (bf16_t)(acc[1] * inv), (bf16_t)(acc[2] * inv), (bf16_t)(acc[3] * inv)};
     *reinterpret_cast<u32x2*>(q_lds + l32 * ROWB + ((c ^ TL::k_swizzle(l32)) << 4) + 8 * hf) = __builtin_bit_cast(u32x2, b);
+  }
+  if constexpr (EXACT) {
+    const uint64_t lanes = __builtin_amdgcn_ballot_w64(fin.failed() && row0 + l32 < w.seg_hi);
+    if (lanes != 0 && lane == 0) atomicOr(&odd_s, (uint32_t)lanes | (uint32_t)(lanes >> 32));
   }
   __syncthreads();
 #pragma unroll
@@ -276,6 +285,10 @@ __global__ __launch_bounds__(64 * kSplitWaves, DP > 64 ? 2 : 4) void prefill_spl
     if (r < kWaveRows && row0 + r < w.seg_hi && (!EXACT || 8 * c < D))
       __builtin_nontemporal_store(*reinterpret_cast<const u32x4*>(q_lds + r * ROWB + ((c ^ TL::k_swizzle(r)) << 4)),
                                   reinterpret_cast<u32x4*>(op + ((int64_t)(row0 + r) * Hq + head) * D + 8 * c));
+  }
+  if constexpr (EXACT) {
+    const uint32_t odd = __builtin_amdgcn_readfirstlane(odd_s);
+    if (__builtin_expect(odd != 0, 0)) redo_prefill_rows<uint16_t, KS>(row0, odd, head, [](int) { return true; });
   }
 }
 

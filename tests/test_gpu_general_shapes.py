@@ -243,3 +243,80 @@ def test_decode_sync_blocks_that_fill_the_chip(dtype, D, Hq):
         got = decode(q, kc, vc, seg, lens, Hq=Hq, Hkv=Hkv, D=D, H=1, block=0, dtype=dtype, remote_lens=rl)
         ref = oracle.decode_step(q, kc, vc, seg, lens, is_sync=True, remote_lens=rl)
         check(got, ref, dtype, "decode sync D=%d Hq=%d" % (D, Hq))
+
+
+# what a masked key holds must not reach the rows that do not see it: layouts for every tile kernel of the shapes outside
+# bf16 x 64 / 128 (16-row, key-split and shared fp32 tiles; split, 8-wave and 4-wave bf16 launches)
+HIDDEN = [("narrow", F32, 64), ("narrow", F32, 40), ("split", F32, 128), ("split", F32, 256), ("shared", F32, 32), ("ordered", BF16, 72),
+          ("ordered", BF16, 96), ("eight", BF16, 72), ("wide", BF16, 160), ("heavy-first", BF16, 40), ("heavy-first", BF16, 256)]
+HIDDEN_LAYOUTS = dict(LAYOUTS, **BF16_LAYOUTS, eight=([130, 0, 191, 81], 32, 8))
+
+
+@pytest.mark.parametrize("layout,dtype,D", HIDDEN)
+@pytest.mark.parametrize("bad", [float("nan"), float("inf"), float("-inf")])
+def test_values_of_masked_keys_do_not_reach_other_rows(layout, dtype, D, bad):
+    lens, Hq, Hkv = HIDDEN_LAYOUTS[layout]
+    seg = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    q, k, v = rand_block(47, int(seg[-1]), Hq, Hkv, D, bf16=dtype == BF16)
+    t = int(seg[2]) + lens[2] // 2                       # a token inside participant 2's segment
+    vn = v.copy()
+    vn[t, 0, D // 2 + 1] = bad                           # seen through KV head 0 only
+    rows, heads = fi.sample_rows(seg, Hq, 64, fi.DEFAULT_SEED, salt=D, tile=32, max_boundary_rows=100)
+    near = np.arange(max(0, t - 130), min(int(seg[-1]), t + 40))     # every row of the query tiles around it, first and last head
+    rows = np.concatenate([rows, near, near])
+    heads = np.concatenate([heads, np.zeros_like(near), np.full_like(near, Hq - 1)])
+    for sync in (0, 1):
+        what = "hidden value %s D=%d %s sync=%d bad=%s" % (layout, D, dtype, sync, bad)
+        say(what)
+        got = prefill(q, k, vn, seg, Hq=Hq, Hkv=Hkv, D=D, H=0, block=0, dtype=dtype, sync_override=sync)[rows, heads]
+        sees = (rows >= t) & (heads < Hq // Hkv) & ((sync == 1) | (rows < seg[3]))
+        ref = oracle.attend_rows(q, k, v, seg, rows, heads, is_sync=bool(sync))
+        check(got[~sees], ref[~sees], dtype, what)
+        assert sees.any() and not np.isfinite(got[sees][:, D // 2 + 1]).any(), what
+
+
+@pytest.mark.parametrize("layout,dtype,D", [("narrow", F32, 40), ("split", F32, 88), ("ordered", BF16, 72), ("eight", BF16, 72), ("wide", BF16, 168)])
+def test_an_infinite_key_element_beside_the_padding(layout, dtype, D):
+    """A score of minus infinity is a weight of zero, also where the tile pads the head dimension."""
+    lens, Hq, Hkv = HIDDEN_LAYOUTS[layout]
+    seg = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    q, k, v = rand_block(48, int(seg[-1]), Hq, Hkv, D, bf16=dtype == BF16)
+    q[:, :, D - 1] = -1.0
+    t = int(seg[2]) + 5
+    kn, kf = k.copy(), k.copy()
+    kn[t, :, D - 1], kf[t, :, D - 1] = np.inf, 2.0 ** 100
+    rows, heads = fi.sample_rows(seg, Hq, 64, fi.DEFAULT_SEED, salt=D, tile=32, max_boundary_rows=100)
+    for sync, causal in [(0, True), (1, True), (1, False)]:
+        what = "infinite key %s D=%d %s sync=%d causal=%d" % (layout, D, dtype, sync, causal)
+        say(what)
+        got = prefill(q, kn, v, seg, Hq=Hq, Hkv=Hkv, D=D, H=0, block=0, dtype=dtype, causal=causal, sync_override=sync)
+        check(got[rows, heads], oracle.attend_rows(q, kf, v, seg, rows, heads, is_sync=bool(sync), causal=causal), dtype, what)
+
+
+@pytest.mark.parametrize("dtype,D", [(F32, 64), (F32, 40), (F32, 256), (BF16, 72), (BF16, 96), (BF16, 200)])
+@pytest.mark.parametrize("lens,Hq,Hkv", [([60, 40, 50], 4, 2), ([200, 77, 130], 8, 2), ([700, 90, 1, 333, 64, 65], 12, 2), ([40, 1500, 9], 40, 2)])
+def test_decode_private_rows_stay_private(dtype, D, lens, Hq, Hkv):
+    """Merged in the launch (one chunk, several) and by the combine kernel; participant 1's private rows are NaN, or a
+    key of its segment has an infinite element that gives every query a score of minus infinity."""
+    N, lens = len(lens), np.asarray(lens, dtype=np.int32)
+    seg = np.concatenate([[0], np.cumsum(lens + 3)]).astype(np.int32)
+    _, kc, vc = rand_block(52, int(seg[-1]), Hkv, Hkv, D, bf16=dtype == BF16)
+    q, _, _ = rand_block(53, N, Hq, Hkv, D, bf16=dtype == BF16)
+    rl = np.maximum(lens - 7, 0).astype(np.int32)
+    q[:, :, D - 1] = -1.0
+    others = np.arange(N) != 1
+    for what, poison in (("V", np.nan), ("V", np.inf), ("K", np.inf)):
+        kn, vn, kf = kc.copy(), vc.copy(), kc.copy()
+        if what == "V":
+            vn[seg[1] + rl[1]:seg[1] + lens[1]] = poison
+        else:
+            kn[seg[1] + 3, :, D - 1], kf[seg[1] + 3, :, D - 1] = np.inf, 2.0 ** 100
+        for sync in (0, 1):
+            name = "private rows %s D=%d lens=%s %d/%d %s=%s sync=%d" % (dtype, D, lens.tolist(), Hq, Hkv, what, poison, sync)
+            say(name)
+            got = decode(q, kn, vn, seg, lens, Hq=Hq, Hkv=Hkv, D=D, H=0, block=0, dtype=dtype, remote_lens=rl, sync_override=sync)
+            ref = oracle.decode_step(q, kf, vc, seg, lens, is_sync=bool(sync), remote_lens=rl)
+            sane = others if what == "V" else np.ones(N, dtype=bool)
+            check(got[sane], ref[sane], dtype, name)
+            if what == "V":
+                assert not np.isfinite(got[1]).any(), name
