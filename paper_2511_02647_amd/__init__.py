@@ -46,23 +46,18 @@ class FedAttnError(RuntimeError):
 
 
 _lib = None
-_nat = None  # csrc/binding.cpp, bound to the loaded library
+_nat = None  # csrc/binding.cpp, bound to the loaded library by the first call that enqueues kernels
 
 
 def load():
     """Load libfedattn.so (built by paper_2511_02647_amd.build.build)."""
-    global _lib, _nat
+    global _lib
     if _lib is not None:
         return _lib
     if not os.path.exists(LIB_PATH):
         raise RuntimeError("%s not found: build it with `python -m paper_2511_02647_amd.build` "
                            "(there is no fallback path)" % LIB_PATH)
     lib = ctypes.CDLL(LIB_PATH)
-    try:
-        from . import _native
-    except ImportError as e:
-        raise RuntimeError("the native binding is missing or does not load (%s): build it with "
-                           "`python -m paper_2511_02647_amd.build`" % e) from e
     i32, i64, vp, sz = ctypes.c_int32, ctypes.c_int64, ctypes.c_void_p, ctypes.c_size_t
     pp = ctypes.POINTER(fedattn_params)
     lib.fedattn_is_sync_block.argtypes = [i32, i32]
@@ -102,15 +97,26 @@ def load():
     lib.fedattn_probe_mfma.restype = i64
     lib.fedattn_last_error.restype = ctypes.c_char_p
     lib.fedattn_version.restype = ctypes.c_char_p
-    _native.bind({name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in EXPORTS}, fedattn_params, _host_i32,
-                 torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice)
-    _lib, _nat = lib, _native
+    _lib = lib
     return lib
 
 
 def _calls():
+    global _nat
     if _nat is None:
-        load()
+        lib = load()
+        try:
+            from . import _native
+        except ImportError as e:
+            raise RuntimeError("the native binding is missing or does not load (%s): build it with "
+                               "`python -m paper_2511_02647_amd.build`" % e) from e
+        # torch's own shortcuts to the current stream's handle, which are private, where it has them
+        raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+        if raw is None or device is None:
+            raw, device = (lambda d: torch.cuda.current_stream(d).cuda_stream), torch.cuda.current_device
+        _native.bind({name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in EXPORTS}, fedattn_params,
+                     _host_i32, raw, device)
+        _nat = _native
     return _nat
 
 

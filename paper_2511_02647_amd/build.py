@@ -1,4 +1,4 @@
-"""Builds libfedattn.so (HIP, gfx950 only) with hipcc and its Python binding _native.so with g++, in-tree."""
+"""Builds libfedattn.so (HIP, gfx950 only) with hipcc and its Python binding _native with g++, in-tree."""
 from __future__ import annotations
 
 import os
@@ -10,7 +10,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libfedattn.so")
-NATIVE = os.path.join(HERE, "_native.so")
+NATIVE = os.path.join(HERE, "_native" + sysconfig.get_config_var("EXT_SUFFIX"))   # loads into the Python it was built for only
 SOURCES = ["api.hip", "prefill_generic.hip", "prefill_mfma.hip", "prefill_split.hip", "prefill_f32.hip", "decode.hip", "decode_f32.hip", "aggregate.hip", "block_ops.hip", "probes.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc", "-fvisibility=hidden", "-Wno-inline-asm",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

@@ -1,5 +1,10 @@
 """The native argument marshalling of the Python entry points, on the CPU: every call below is rejected
 before anything would be enqueued, so the device addresses are never used."""
+import os
+import subprocess
+import sys
+import sysconfig
+
 import numpy as np
 import pytest
 import torch
@@ -121,3 +126,35 @@ def test_params_and_numbers_as_before():
         fa.fedattn_prefill(P, block, None, None, None, None, (0, 0, 0), stream=Stream)
     with pytest.raises(TypeError):
         fa.fedattn_prefill(P, None, None, None, None, None, (0, 0, 0), stream=Stream)
+
+
+def run_python(code):
+    return subprocess.run([sys.executable, "-c", code], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=120,
+                          cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
+
+
+def test_the_library_loads_without_the_binding():
+    p = run_python("import sys; sys.modules['paper_2511_02647_amd._native'] = None\n"
+                   "import paper_2511_02647_amd as fa\n"
+                   "assert fa.fedattn_is_sync_block(2, 1) and fa.fedattn_version()\n"
+                   "try: fa.fedattn_prefill(None, 0, None, None, None, None, (0, 0))\n"
+                   "except RuntimeError as e: print('loud:', e)")
+    assert p.returncode == 0 and "loud: the native binding is missing" in p.stdout, p.stdout
+
+
+def test_the_current_stream_without_torchs_shortcuts():
+    p = run_python("import torch\n"
+                   "for n in ('_cuda_getCurrentRawStream', '_cuda_getDevice'):\n"
+                   "    if hasattr(torch._C, n): delattr(torch._C, n)\n"
+                   "asked = []\n"
+                   "class S: cuda_stream = 0\n"
+                   "torch.cuda.current_device = lambda: 3\n"
+                   "torch.cuda.current_stream = lambda d=None: asked.append(d) or S\n"
+                   "import paper_2511_02647_amd as fa\n"
+                   "fa.fedattn_prefill(fa.make_params(1, 1, 1, 64, 1, torch.float32), 0, None, None, None, None, (0, 0))\n"
+                   "print('asked', asked)")
+    assert p.returncode == 0 and "asked [3]" in p.stdout, p.stdout
+
+
+def test_the_binding_is_named_after_its_python():
+    assert os.path.basename(fabuild.NATIVE) == "_native" + sysconfig.get_config_var("EXT_SUFFIX") and os.path.exists(fabuild.NATIVE)
