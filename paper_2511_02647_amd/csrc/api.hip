@@ -250,7 +250,7 @@ fedattn_status run_prefill(const fedattn_params* p, int32_t block_idx0, int32_t 
   a.k_list = k;
   a.v_list = v;
   const int G = a.Hq / a.Hkv;
-  a.heads_per_wg = (G % 4 == 0) ? 4 : ((G % 2 == 0) ? 2 : 1);
+  a.heads_per_wg = heads_in_common(a.Hq / a.Hkv);
   int64_t chunks = 0;
   for (int n = 0; n <= N; ++n) {
     a.seg.seg_off[n] = seg[n];

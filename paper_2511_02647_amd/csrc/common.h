@@ -9,13 +9,11 @@
 #include <atomic>
 
 #include "fedattn.h"
+#include "launch_choice.h"
 
 namespace fedattn {
 
 constexpr int kMaxP = FEDATTN_MAX_PARTICIPANTS;
-constexpr int kKvTile = 64;    // KV rows per MFMA prefill tile; also the keep-list tile
-constexpr int kWaveRows = 32;  // query rows per wave in the MFMA prefill kernel
-constexpr int kMaxOrderedTiles = 512;  // query tiles of a launch that assigns them through an explicit order
 constexpr int kMaxFusedBlocks = 64;    // blocks of one fused decode launch
 constexpr int kCombineAtOnce = 64;     // chunks up to which the decode combine kernel makes one round trip
 constexpr int kMergeBatch = 8;         // chunks whose partials a decode merge has in flight at once

@@ -1,0 +1,158 @@
+// The rules by which a launcher chooses among its kernels and splits, in plain C++ without device code, so that a host
+// program can say which launch a shape takes (the GPU tests name their layouts by it).
+#pragma once
+
+#include <math.h>
+#include <stdint.h>
+
+namespace fedattn {
+
+constexpr int kKvTile = 64;            // KV rows per tile; also the keep-list tile
+constexpr int kWaveRows = 32;          // query rows per wavefront in the bf16 prefill kernels
+constexpr int kMaxOrderedTiles = 512;  // query tiles of a launch that assigns them through an explicit order
+
+// ---- which of the launches a block takes ------------------------------------------------------
+// kFour: 4-wavefront workgroups, one query tile each, several per CU; kFourOrdered: the same, causal and
+// all resident at once, in an order that the host lays out.  kEight: 8-wavefront workgroups whose two
+// groups share out the KV tiles of one query tile; kEightPairs: of a heavy tile and then its light mirror
+// image.  kSplit: one head's 32 rows per workgroup, keys shared out among its 8 wavefronts (prefill_split.hip).  From left to right a launch has more and shorter walks for the same work and pays
+// more for each: the right one depends on how far the block fills the chip, so their times are estimated.
+enum PrefillLaunch { kFour, kFourOrdered, kEight, kEightPairs, kSplit };
+
+// Measured on one MI355X, microseconds: an iteration of one workgroup alone on its CU and as its share
+// of a full CU, start and end of a walk when the launch waits for it and when the CU's next workgroup
+// does; workgroups resident per CU.  An iteration is 64 keys (kFour), 128 (kEight) or 256 (kSplit).
+// (Bidirectional blocks of 1024, 2048 and 4096 tokens with 1 to 8 heads.)
+struct Pace { float alone, full, ends, turn; int resident; };
+struct Paces { Pace four, eight, split; };
+inline const Paces& paces(int D) {
+  static const Paces d64 = {{.87f, .53f, 3.2f, 2.0f, 3}, {1.11f, 1.26f, 3.3f, 3.3f, 1}, {.70f, .74f, 2.5f, 4.5f, 2}};
+  static const Paces d128 = {{1.15f, .89f, 3.2f, 2.2f, 2}, {1.73f, 2.04f, 3.5f, 3.5f, 1}, {1.19f, 1.50f, 2.7f, 4.3f, 1}};
+  // weights at full precision (other head dimensions), by padded size
+  static const Paces e64 = {{1.20f, .98f, 3.2f, 1.8f, 3}, {1.95f, 2.30f, 3.3f, 3.3f, 1}, {1.05f, 1.00f, 2.5f, 4.5f, 2}};
+  static const Paces e96 = {{1.53f, 1.36f, 3.2f, 2.0f, 2}, {2.41f, 3.00f, 3.5f, 3.5f, 1}, {1.38f, 1.80f, 2.7f, 3.0f, 1}};
+  static const Paces e128 = {{1.89f, 1.75f, 3.2f, 2.0f, 2}, {2.82f, 3.64f, 3.5f, 3.5f, 1}, {1.64f, 2.35f, 2.8f, 3.5f, 1}};
+  return D == 64 ? d64 : D == 128 ? d128 : D <= 64 ? e64 : D <= 96 ? e96 : e128;
+}
+
+struct PrefillShape {
+  const int32_t* seg_off;   // [n + 1]
+  int n;
+  int Hq, Hkv, D;
+  bool causal, keep;        // keep: a keep-list
+  int heads_per_wg, q_tile_rows;
+  int n_cus;
+};
+
+// Query tiles of `rows` rows (none crosses a segment's end), and pairs of them inside each segment.
+struct QueryTiles { int64_t tiles, pairs; };
+inline QueryTiles count_query_tiles(const int32_t* seg_off, int n_seg, int rows) {
+  QueryTiles q = {0, 0};
+  for (int n = 0; n < n_seg; ++n) {
+    const int64_t t = ((int64_t)seg_off[n + 1] - seg_off[n] + rows - 1) / rows;
+    q.tiles += t;
+    q.pairs += (t + 1) / 2;
+  }
+  return q;
+}
+
+// Workgroups of a launch, iterations of its longest walk and of all walks together.
+struct Walks { double wgs, longest, total; };
+inline Walks count_walks(const PrefillShape& a, bool is_sync, int rows, int keys, int wgs_per_tile) {
+  Walks w = {0, 0, 0};
+  const double total = a.seg_off[a.n];
+  for (int n = 0; n < a.n; ++n) {
+    const double off = a.seg_off[n], len = a.seg_off[n + 1] - off;
+    if (len == 0) continue;
+    const double tiles = ceil(len / rows);
+    double most, mean;   // keys that the segment's last rows and its rows on average see
+    if (a.causal) {
+      // remote rows under a keep-list: their number is known to the device only, half are taken to be kept
+      const double before = is_sync ? (a.keep ? off / 2 : off) : 0;
+      most = before + len;
+      mean = before + (len + fmin(rows, len)) / 2;
+    } else {
+      most = mean = is_sync ? (a.keep ? (total + len) / 2 : total) : len;
+    }
+    w.wgs += tiles;
+    w.longest = fmax(w.longest, ceil(most / keys));
+    w.total += tiles * (a.causal ? fmax(1.0, mean / keys + 0.5) : ceil(mean / keys));
+  }
+  w.wgs *= wgs_per_tile;
+  w.total *= wgs_per_tile;
+  return w;
+}
+
+// Microseconds of the launch without what every launch costs: the longer of its longest walk, which
+// shares its CU with average ones, and the work of a CU (bidirectional blocks have walks of one length
+// that fill no gaps: whole workgroups count).
+inline double estimate(const Pace& p, const Walks& w, bool causal, int cus) {
+  const double on_cu = ceil(w.wgs / cus);   // workgroups that the fullest CU gets
+  const double together = fmin(on_cu, p.resident);
+  const double mean = w.total / w.wgs;
+  // with some, not all places of a CU taken, a workgroup's share is a little worse than full
+  const double shared = together > 1 ? fmax(p.alone, together * p.full * (together < p.resident ? 1.15 : 1.0))
+                                     : w.wgs > 0.45 * cus ? fmax(p.alone, p.full) : p.alone;
+  const double path = p.ends + (w.longest - mean) * p.alone + mean * shared;
+  const double work = causal ? p.turn * w.wgs / (p.resident * cus) + w.total * p.full / cus
+                             : on_cu * (p.turn / p.resident + mean * p.full);
+  return fmax(path, work);
+}
+
+inline PrefillLaunch choose_prefill_launch(const PrefillShape& a, bool is_sync) {
+  const bool causal = a.causal;
+  const int per_tile = a.Hkv * (a.Hq / a.Hkv / a.heads_per_wg);
+  const QueryTiles q = count_query_tiles(a.seg_off, a.n, a.q_tile_rows);
+  const PrefillLaunch four = causal && q.tiles <= kMaxOrderedTiles && q.tiles * per_tile <= 2 * (int64_t)a.n_cus ? kFourOrdered : kFour;
+  if (a.D > 128) return four;   // the others' tiles do not fit LDS
+  const Paces& p = paces(a.D);
+  const Walks four_walks = count_walks(a, is_sync, a.q_tile_rows, kKvTile, per_tile);
+  Walks eight = count_walks(a, is_sync, a.q_tile_rows, 2 * kKvTile, per_tile);
+  const Walks split = count_walks(a, is_sync, kWaveRows, 256, a.Hq);
+  PrefillLaunch best = four;
+  double t = estimate(p.four, four_walks, causal, a.n_cus);
+  const auto consider = [&](PrefillLaunch plan, double x) {
+    if (x < t) {
+      t = x;
+      best = plan;
+    }
+  };
+  consider(kEight, estimate(p.eight, eight, causal, a.n_cus));
+  if (causal) {   // half as many workgroups, each with a heavy and a light walk
+    const double pairs = (double)(q.pairs * per_tile);
+    eight.longest = is_sync ? 2 * eight.total / eight.wgs : eight.longest + 1;
+    eight.wgs = pairs;
+    Pace pp = p.eight;
+    pp.ends *= 1.95f;
+    consider(kEightPairs, estimate(pp, eight, true, a.n_cus));
+  }
+  consider(kSplit, estimate(p.split, split, causal, a.n_cus));
+  return best;
+}
+
+// ---- fp32 prefill ----------------------------------------------------------------------------
+// (TFLOP/s measured at 8 x 1000 to 8 x 2000 tokens unless stated):
+//  - kF32KeySplit: keys of a tile shared out among the 4 wavefronts of one 32-row query tile and head
+//    (KS = 4 of the kernel): four times as many workgroups as with KS = 1, and walks four times shorter
+//    (8/2 heads of 128, sync: 112 against 91);
+//  - kF32Shared, at least 6 workgroups per CU even with KS = 1: the wavefronts take different heads, each K and V
+//    tile is staged once for all of them (32/8 heads of 128, sync: 137 against 119; at 4 workgroups per
+//    CU still 4 % faster in a sync block, but 8 % slower in a local one);
+//  - kF32Narrow, fewer than 2 workgroups per CU with KS = 4: 16-row query tiles, twice as many workgroups
+//    (4 x 448 tokens, 8/2 heads: 80 against 63).  If even those are all resident at once, the short
+//    half is dispatched shortest first, so that workgroups that come to share a CU carry about the
+//    same load together (1000 tokens, 8 heads: 59 against 51; with more workgroups than fit, longest
+//    first is better: 80 against 73).
+enum F32Launch { kF32Shared, kF32KeySplit, kF32Narrow };
+// Query heads of a KV group that a workgroup of 4 wavefronts takes.
+inline int heads_in_common(int group) { return group % 4 == 0 ? 4 : (group % 2 == 0 ? 2 : 1); }
+inline F32Launch choose_f32_launch(const int32_t* seg_off, int n_seg, int Hq, int Hkv, int D, int n_blocks, int n_cus) {
+  const int nq = D > 128 ? 1 : 2;   // 16-row sub-tiles per wavefront
+  const int group = Hq / Hkv, common = heads_in_common(group);
+  const int64_t shared = count_query_tiles(seg_off, n_seg, 16 * nq * (4 / common)).tiles * Hkv * (group / common) * n_blocks;
+  if (shared >= 6 * (int64_t)n_cus) return kF32Shared;
+  const int64_t split = count_query_tiles(seg_off, n_seg, 16 * nq).tiles * Hq * n_blocks;
+  return nq > 1 && split < 2 * (int64_t)n_cus ? kF32Narrow : kF32KeySplit;
+}
+
+}  // namespace fedattn

@@ -311,39 +311,18 @@ hipError_t launch_prefill_f32_t(const PrefillArgs& a, int n_blocks, hipStream_t 
   return hipGetLastError();
 }
 
-// Which split of the work (TFLOP/s measured at 8 x 1000 to 8 x 2000 tokens unless stated):
-//  - keys of a tile shared out among the 4 wavefronts of one 32-row query tile and head (KS = 4): four
-//    times as many workgroups as with KS = 1, and walks four times shorter (8/2 heads of 128, sync:
-//    112 against 91);
-//  - at least 6 workgroups per CU even with KS = 1: the wavefronts take different heads, each K and V
-//    tile is staged once for all of them (32/8 heads of 128, sync: 137 against 119; at 4 workgroups per
-//    CU still 4 % faster in a sync block, but 8 % slower in a local one);
-//  - fewer than 2 workgroups per CU with KS = 4: 16-row query tiles, twice as many workgroups
-//    (4 x 448 tokens, 8/2 heads: 80 against 63).  If even those are all resident at once, the short
-//    half is dispatched shortest first, so that workgroups that come to share a CU carry about the
-//    same load together (1000 tokens, 8 heads: 59 against 51; with more workgroups than fit, longest
-//    first is better: 80 against 73).
 template <int DP>
 hipError_t launch_prefill_f32_d(PrefillArgs& a, int n_blocks, hipStream_t s) {
   constexpr int NQ = DP > 128 ? 1 : 2;
-  const int G = a.Hq / a.Hkv;
-  const int64_t cus = a.n_cus;
-  const auto wgs = [&] { return (int64_t)a.n_q_tiles * a.Hkv * (G / a.heads_per_wg) * n_blocks; };
-  a.heads_per_wg = G % 4 == 0 ? 4 : (G % 2 == 0 ? 2 : 1);
-  lay_out_query_tiles(a, 16 * NQ * (4 / a.heads_per_wg));
-  const bool shared = wgs() >= 6 * cus;
-  bool narrow = false;
-  if (!shared) {
-    a.heads_per_wg = 1;
-    lay_out_query_tiles(a, 16 * NQ);
-    narrow = wgs() < 2 * cus;
-    if (narrow && NQ > 1) lay_out_query_tiles(a, 16);
-  }
-  if (wgs() / n_blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-  a.short_half_ascending = wgs() <= 2 * cus ? 1 : 0;
+  const F32Launch plan = choose_f32_launch(a.seg.seg_off, a.seg.n, a.Hq, a.Hkv, a.D, n_blocks, a.n_cus);
+  a.heads_per_wg = plan == kF32Shared ? heads_in_common(a.Hq / a.Hkv) : 1;
+  lay_out_query_tiles(a, plan == kF32Narrow ? 16 : 16 * NQ * (4 / (plan == kF32Shared ? a.heads_per_wg : 4)));
+  const int64_t wgs = (int64_t)a.n_q_tiles * a.Hkv * (a.Hq / a.Hkv / a.heads_per_wg) * n_blocks;
+  if (wgs / n_blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+  a.short_half_ascending = wgs <= 2 * (int64_t)a.n_cus ? 1 : 0;
   order_segments_by_length(a);
-  if (shared) return launch_prefill_f32_t<DP, NQ, 1>(a, n_blocks, s);
-  return narrow ? launch_prefill_f32_t<DP, 1, 4>(a, n_blocks, s) : launch_prefill_f32_t<DP, NQ, 4>(a, n_blocks, s);
+  if (plan == kF32Shared) return launch_prefill_f32_t<DP, NQ, 1>(a, n_blocks, s);
+  return plan == kF32Narrow ? launch_prefill_f32_t<DP, 1, 4>(a, n_blocks, s) : launch_prefill_f32_t<DP, NQ, 4>(a, n_blocks, s);
 }
 
 }  // namespace

@@ -629,105 +629,6 @@ hipError_t launch_prefill_exact(const PrefillArgs& a, bool wide, dim3 grid, hipS
   return launch_prefill_mfma_t<DP, 1, false, true>(a, grid, s);
 }
 
-namespace {
-
-// ---- which of the launches a block takes ------------------------------------------------------
-// kFour: 4-wavefront workgroups, one query tile each, several per CU.  kEight: 8-wavefront workgroups
-// whose two groups share out the KV tiles of one query tile; kEightPairs: of a heavy tile and then its
-// light mirror image.  kSplit: one head's 32 rows per workgroup, keys shared out among its 8 wavefronts
-// (prefill_split.hip).  From left to right a launch has more and shorter walks for the same work and pays
-// more for each: the right one depends on how far the block fills the chip, so their times are estimated.
-enum Plan { kFour, kEight, kEightPairs, kSplit };
-
-// Measured on one MI355X, microseconds: an iteration of one workgroup alone on its CU and as its share
-// of a full CU, start and end of a walk when the launch waits for it and when the CU's next workgroup
-// does; workgroups resident per CU.  An iteration is 64 keys (kFour), 128 (kEight) or 256 (kSplit).
-// (Bidirectional blocks of 1024, 2048 and 4096 tokens with 1 to 8 heads.)
-struct Pace { float alone, full, ends, turn; int resident; };
-struct Paces { Pace four, eight, split; };
-const Paces& paces(int D) {
-  static const Paces d64 = {{.87f, .53f, 3.2f, 2.0f, 3}, {1.11f, 1.26f, 3.3f, 3.3f, 1}, {.70f, .74f, 2.5f, 4.5f, 2}};
-  static const Paces d128 = {{1.15f, .89f, 3.2f, 2.2f, 2}, {1.73f, 2.04f, 3.5f, 3.5f, 1}, {1.19f, 1.50f, 2.7f, 4.3f, 1}};
-  // weights at full precision (other head dimensions), by padded size
-  static const Paces e64 = {{1.20f, .98f, 3.2f, 1.8f, 3}, {1.95f, 2.30f, 3.3f, 3.3f, 1}, {1.05f, 1.00f, 2.5f, 4.5f, 2}};
-  static const Paces e96 = {{1.53f, 1.36f, 3.2f, 2.0f, 2}, {2.41f, 3.00f, 3.5f, 3.5f, 1}, {1.38f, 1.80f, 2.7f, 3.0f, 1}};
-  static const Paces e128 = {{1.89f, 1.75f, 3.2f, 2.0f, 2}, {2.82f, 3.64f, 3.5f, 3.5f, 1}, {1.64f, 2.35f, 2.8f, 3.5f, 1}};
-  return D == 64 ? d64 : D == 128 ? d128 : D <= 64 ? e64 : D <= 96 ? e96 : e128;
-}
-
-// Workgroups of a launch, iterations of its longest walk and of all walks together.
-struct Walks { double wgs, longest, total; };
-Walks count_walks(const PrefillArgs& a, bool is_sync, int rows, int keys, int wgs_per_tile) {
-  Walks w = {0, 0, 0};
-  for (int n = 0; n < a.seg.n; ++n) {
-    const double off = a.seg.seg_off[n], len = a.seg.seg_off[n + 1] - off;
-    if (len == 0) continue;
-    const double tiles = ceil(len / rows);
-    double most, mean;   // keys that the segment's last rows and its rows on average see
-    if (a.causal) {
-      // remote rows under a keep-list: their number is known to the device only, half are taken to be kept
-      const double before = is_sync ? (a.keep_chunks ? off / 2 : off) : 0;
-      most = before + len;
-      mean = before + (len + fmin(rows, len)) / 2;
-    } else {
-      most = mean = is_sync ? (a.keep_chunks ? (a.total + len) / 2 : a.total) : len;
-    }
-    w.wgs += tiles;
-    w.longest = fmax(w.longest, ceil(most / keys));
-    w.total += tiles * (a.causal ? fmax(1.0, mean / keys + 0.5) : ceil(mean / keys));
-  }
-  w.wgs *= wgs_per_tile;
-  w.total *= wgs_per_tile;
-  return w;
-}
-
-// Microseconds of the launch without what every launch costs: the longer of its longest walk, which
-// shares its CU with average ones, and the work of a CU (bidirectional blocks have walks of one length
-// that fill no gaps: whole workgroups count).
-double estimate(const Pace& p, const Walks& w, bool causal, int cus) {
-  const double on_cu = ceil(w.wgs / cus);   // workgroups that the fullest CU gets
-  const double together = fmin(on_cu, p.resident);
-  const double mean = w.total / w.wgs;
-  // with some, not all places of a CU taken, a workgroup's share is a little worse than full
-  const double shared = together > 1 ? fmax(p.alone, together * p.full * (together < p.resident ? 1.15 : 1.0))
-                                     : w.wgs > 0.45 * cus ? fmax(p.alone, p.full) : p.alone;
-  const double path = p.ends + (w.longest - mean) * p.alone + mean * shared;
-  const double work = causal ? p.turn * w.wgs / (p.resident * cus) + w.total * p.full / cus
-                             : on_cu * (p.turn / p.resident + mean * p.full);
-  return fmax(path, work);
-}
-
-Plan choose_plan(const PrefillArgs& a, bool is_sync) {
-  if (a.D > 128) return kFour;   // the others' tiles do not fit LDS
-  const Paces& p = paces(a.D);
-  const bool causal = a.causal != 0;
-  const int per_tile = a.Hkv * (a.Hq / a.Hkv / a.heads_per_wg);
-  const Walks four = count_walks(a, is_sync, a.q_tile_rows, kKvTile, per_tile);
-  Walks eight = count_walks(a, is_sync, a.q_tile_rows, 2 * kKvTile, per_tile);
-  const Walks split = count_walks(a, is_sync, kWaveRows, 256, a.Hq);
-  Plan best = kFour;
-  double t = estimate(p.four, four, causal, a.n_cus);
-  const auto consider = [&](Plan plan, double x) {
-    if (x < t) {
-      t = x;
-      best = plan;
-    }
-  };
-  consider(kEight, estimate(p.eight, eight, causal, a.n_cus));
-  if (causal) {   // half as many workgroups, each with a heavy and a light walk
-    const double pairs = (double)a.seg.pair_cum[a.seg.n] * per_tile;
-    eight.longest = is_sync ? 2 * eight.total / eight.wgs : eight.longest + 1;
-    eight.wgs = pairs;
-    Pace pp = p.eight;
-    pp.ends *= 1.95f;
-    consider(kEightPairs, estimate(pp, eight, true, a.n_cus));
-  }
-  consider(kSplit, estimate(p.split, split, causal, a.n_cus));
-  return best;
-}
-
-}  // namespace
-
 hipError_t launch_prefill_mfma(const PrefillArgs& a_in, int n_blocks, hipStream_t s) {
   if (a_in.n_q_tiles == 0 || n_blocks == 0) return hipSuccess;
   PrefillArgs a = a_in;
@@ -747,10 +648,11 @@ hipError_t launch_prefill_mfma(const PrefillArgs& a_in, int n_blocks, hipStream_
   bool wide = (int64_t)grid.x * grid.y < 2 * (int64_t)a.n_cus && a.D <= 128;
   if (n_blocks == 1) {
     const bool is_sync = a.sync_override >= 0 ? a.sync_override != 0 : sync_block_rule(a.sync_interval, a.block_idx0);
-    const Plan plan = choose_plan(a, is_sync);
+    const PrefillLaunch plan = choose_prefill_launch(PrefillShape{a.seg.seg_off, a.seg.n, a.Hq, a.Hkv, a.D, a.causal != 0, a.keep_chunks != nullptr,
+                                                                  a.heads_per_wg, a.q_tile_rows, a.n_cus}, is_sync);
     if (plan == kSplit) return launch_prefill_split(a_in, fold, 1, s);
-    wide = plan != kFour;
-    if (plan == kFour && a.causal && a.n_q_tiles <= kMaxOrderedTiles && (int64_t)a.n_q_tiles * per_tile <= 2 * (int64_t)a.n_cus) {
+    wide = plan == kEight || plan == kEightPairs;
+    if (plan == kFourOrdered) {
       // All workgroups are resident at once, two per CU.  Order: heavy half first, heaviest first;
       // then the light half, lightest first, so that the workgroups that come to share a CU
       // (index p and p + half, dispatched in order) carry about the same load together.

@@ -14,7 +14,8 @@ from test_gpu_parity import rand_block
 pytestmark = pytest.mark.gpu
 BF16, F32 = torch.bfloat16, torch.float32
 
-# (lengths, Hq, Hkv): 16-row tiles; 32-row tiles with the keys split over a workgroup (at least 512
+# Which launch a layout takes on 256 CUs is checked by tests/test_host_rules.py: those called by a launch's name take it.
+# (lengths, Hq, Hkv): 16-row tiles (head dimensions up to 128); 32-row tiles with the keys split over a workgroup (at least 512
 # of them on 256 CUs); heads sharing a workgroup (at least 1536 of them).  Ragged ends, an empty and
 # a one-token segment, groups of 1, 2 and 4 heads per KV head.
 LAYOUTS = {"narrow": ([70, 0, 63, 1, 258], 4, 1), "split": ([500, 33, 484], 16, 8), "shared": ([3101, 2, 3137], 32, 8)}
@@ -36,8 +37,9 @@ def test_f32_prefill(layout, D):
         check(got[rows, heads], ref, F32, what)
 
 
-# ordered tiles, 8-wave workgroups on few long walks, one tile per workgroup heaviest first
-BF16_LAYOUTS = {"ordered": ([70, 0, 63, 1, 258], 4, 1), "wide": ([1100, 0, 1003], 6, 3), "heavy-first": ([3101, 2, 3137], 32, 8)}
+# one head per workgroup with split keys, on short and long walks (head dimensions beyond 128: 4-wave workgroups, in an
+# order if causal); 4-wave workgroups, one tile each, heaviest first (the other launches: test_bf16_prefill_every_launch)
+BF16_LAYOUTS = {"short": ([70, 0, 63, 1, 258], 4, 1), "long": ([1100, 0, 1003], 6, 3), "four": ([3101, 2, 3137], 32, 8)}
 
 
 @pytest.mark.parametrize("layout", sorted(BF16_LAYOUTS))
@@ -127,11 +129,10 @@ def test_decode_other_shapes_fused_blocks_equal_single_calls(dtype, D):
     assert torch.equal(one, many)
 
 
-# bf16 with head dimension 64 / 128: ragged layouts that reach every launch of a prefill block - one head
-# per workgroup with split keys, ordered tiles, 8-wave workgroups on single tiles and on pairs, tiles
-# longest first - with empty and one-token segments
-PLAN_LAYOUTS = {"split": ([70, 0, 63, 1, 258], 4, 1), "split-long": ([1, 1999, 33], 2, 1), "ordered": ([100, 1, 0, 301, 33], 64, 16),
-                "eight": ([129, 0, 700, 1, 1203], 16, 4), "pairs": ([513, 1, 450, 600, 500], 32, 8), "longest-first": ([3101, 2, 3137], 32, 8)}
+# bf16 with head dimension 64 / 128: ragged layouts, named after the launch of their causal sync block, with empty and
+# one-token segments
+PLAN_LAYOUTS = {"split": ([70, 0, 63, 1, 258], 4, 1), "split-long": ([1, 1999, 33], 2, 1), "eight-short": ([100, 1, 0, 301, 33], 64, 16),
+                "eight": ([129, 0, 700, 1, 1203], 16, 4), "eight-pairs": ([513, 1, 450, 600, 500], 32, 8), "four": ([3101, 2, 3137], 32, 8)}
 
 
 @pytest.mark.parametrize("layout", sorted(PLAN_LAYOUTS))
@@ -147,6 +148,55 @@ def test_bf16_prefill_launches(layout, D, scale):
         got = prefill(q, k, v, seg, Hq=Hq, Hkv=Hkv, D=D, H=0, block=0, dtype=BF16, causal=causal, sync_override=sync, scale=scale)
         ref = oracle.attend_rows(q, k, v, seg, rows, heads, is_sync=bool(sync), causal=causal, scale=scale if scale else None)
         check(got[rows, heads], ref, BF16, what)
+
+
+# (launch, sync, causal, lengths, Hq, Hkv, head dimensions): every launch of a bf16 prefill block in every mode that reaches
+# it, at every padded head dimension that has it
+ALL_D = (32, 40, 64, 72, 120, 128)
+LAUNCHES = [("eight", 1, False, [1, 0, 160, 181, 168, 199], 32, 8, ALL_D), ("eight", 0, True, [67, 36, 0, 82, 99, 1], 32, 8, ALL_D),
+            ("eight", 1, True, [214, 1, 259, 0, 262, 263], 32, 8, ALL_D), ("eight-pairs", 0, True, [724, 0, 1, 856, 843], 24, 8, ALL_D),
+            ("eight-pairs", 1, True, [542, 1, 0, 528, 834, 394], 24, 8, ALL_D), ("four", 1, False, [378, 340, 392, 1, 0, 363], 32, 8, ALL_D + (160, 224)),
+            ("four", 0, True, [967, 965, 1, 0, 1050, 955], 24, 8, ALL_D + (192,)), ("four", 1, True, [1101, 1062, 1075, 1192, 0, 1], 24, 8, ALL_D + (256,)),
+            ("four-ordered", 0, True, [34, 60, 50, 48, 0, 1], 32, 8, (32, 40, 72, 120, 160, 184)),
+            ("four-ordered", 0, True, [450, 1, 574, 569, 541, 0], 24, 8, (64, 128)), ("four-ordered", 1, True, [47, 48, 48, 0, 44, 1], 32, 8, (128, 208, 256)),
+            ("split", 1, False, [676, 1, 0, 784, 1894, 645], 1, 1, ALL_D), ("split", 0, True, [139, 72, 94, 0, 1, 194], 8, 2, ALL_D),
+            ("split", 1, True, [134, 119, 117, 129, 1, 0], 8, 8, ALL_D)]
+
+
+@pytest.mark.parametrize("launch,sync,causal,lens,Hq,Hkv,D", [x[:6] + (d,) for x in LAUNCHES for d in x[6]])
+def test_bf16_prefill_every_launch(launch, sync, causal, lens, Hq, Hkv, D):
+    seg = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    q, k, v = rand_block(61, int(seg[-1]), Hq, Hkv, D)
+    rows, heads = fi.sample_rows(seg, Hq, 64, fi.DEFAULT_SEED, salt=D, tile=32, max_boundary_rows=200)
+    for scale in (0.0, 0.2) if D in (64, 128) else (0.0,):     # folded into the query operand or not
+        what = "bf16 launch %s D=%d sync=%d causal=%d scale=%.1f" % (launch, D, sync, causal, scale)
+        say(what)
+        got = prefill(q, k, v, seg, Hq=Hq, Hkv=Hkv, D=D, H=0, block=0, dtype=BF16, causal=causal, sync_override=sync, scale=scale)
+        ref = oracle.attend_rows(q, k, v, seg, rows, heads, is_sync=bool(sync), causal=causal, scale=scale if scale else None)
+        check(got[rows, heads], ref, BF16, what)
+        if D not in (64, 128):
+            assert np.all(np.abs(got[rows, heads] - ref) <= 2.0 ** -8 * np.abs(ref) + 1e-5), what   # as above
+
+
+# several blocks in one launch: pairs of tiles, in 8-wave workgroups (few) and 4-wave ones (at least two per CU)
+@pytest.mark.parametrize("lens,Hq,Hkv", [([130, 0, 70, 133], 8, 2), ([700, 1, 350, 333], 32, 8)])
+@pytest.mark.parametrize("dtype,D", [(BF16, 72), (BF16, 120), (BF16, 200), (F32, 40), (F32, 128)])
+def test_prefill_blocks_other_shapes(lens, Hq, Hkv, dtype, D):
+    M, H = 4, 2
+    seg = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    blocks = [rand_block(62 + b, int(seg[-1]), Hq, Hkv, D, bf16=dtype == BF16) for b in range(M)]
+    rows, heads = fi.sample_rows(seg, Hq, 64, fi.DEFAULT_SEED, salt=D, tile=32, max_boundary_rows=100)
+    for causal in (True, False):
+        p = fa.make_params(len(lens), Hq, Hkv, D, H, dtype, causal=causal)
+        tq, tk, tv = (torch.stack([dev(b[i], dtype) for b in blocks]) for i in range(3))
+        out = torch.full_like(tq, float("nan"))
+        what = "prefill_blocks %s D=%d %d/%d causal=%d" % (dtype, D, Hq, Hkv, causal)
+        say(what)
+        fa.fedattn_prefill_blocks(p, 0, M, tq, tk, tv, out, tq[0].numel(), tk[0].numel(), seg)
+        torch.cuda.synchronize()
+        for b in range(M):
+            ref = oracle.attend_rows(*blocks[b], seg, rows, heads, is_sync=oracle.is_sync_block(H, b), causal=causal)
+            check(host(out[b])[rows, heads], ref, dtype, what)
 
 
 # more chunks than a wavefront has lanes, rows past the 4096 where a workgroup's share grows, chunks longer than
@@ -247,9 +297,9 @@ def test_decode_sync_blocks_that_fill_the_chip(dtype, D, Hq):
 
 # what a masked key holds must not reach the rows that do not see it: layouts for every tile kernel of the shapes outside
 # bf16 x 64 / 128 (16-row, key-split and shared fp32 tiles; split, 8-wave and 4-wave bf16 launches)
-HIDDEN = [("narrow", F32, 64), ("narrow", F32, 40), ("split", F32, 128), ("split", F32, 256), ("shared", F32, 32), ("ordered", BF16, 72),
-          ("ordered", BF16, 96), ("eight", BF16, 72), ("wide", BF16, 160), ("heavy-first", BF16, 40), ("heavy-first", BF16, 256)]
-HIDDEN_LAYOUTS = dict(LAYOUTS, **BF16_LAYOUTS, eight=([130, 0, 191, 81], 32, 8))
+HIDDEN = [("narrow", F32, 64), ("narrow", F32, 40), ("split", F32, 128), ("split", F32, 256), ("shared", F32, 32), ("short", BF16, 72),
+          ("short", BF16, 96), ("eight", BF16, 72), ("eight-pairs", BF16, 72), ("long", BF16, 160), ("four", BF16, 40), ("four", BF16, 256)]
+HIDDEN_LAYOUTS = dict(LAYOUTS, **BF16_LAYOUTS, **{"eight": ([214, 1, 259, 0, 262, 263], 32, 8), "eight-pairs": ([542, 1, 528, 0, 834, 394], 24, 8)})
 
 
 @pytest.mark.parametrize("layout,dtype,D", HIDDEN)
@@ -275,7 +325,7 @@ def test_values_of_masked_keys_do_not_reach_other_rows(layout, dtype, D, bad):
         assert sees.any() and not np.isfinite(got[sees][:, D // 2 + 1]).any(), what
 
 
-@pytest.mark.parametrize("layout,dtype,D", [("narrow", F32, 40), ("split", F32, 88), ("ordered", BF16, 72), ("eight", BF16, 72), ("wide", BF16, 168)])
+@pytest.mark.parametrize("layout,dtype,D", [("narrow", F32, 40), ("split", F32, 88), ("short", BF16, 72), ("eight", BF16, 72), ("long", BF16, 168)])
 def test_an_infinite_key_element_beside_the_padding(layout, dtype, D):
     """A score of minus infinity is a weight of zero, also where the tile pads the head dimension."""
     lens, Hq, Hkv = HIDDEN_LAYOUTS[layout]

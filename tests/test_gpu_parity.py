@@ -165,10 +165,9 @@ def test_mfma_prefill_scores_that_keep_outgrowing_the_reference(D, scale, trend)
 @pytest.mark.parametrize("D,Hkv", [(64, 1), (64, 2), (128, 1), (128, 2)])
 @pytest.mark.parametrize("scale", [0.0, 0.4])
 def test_mfma_prefill_few_long_walks(D, Hkv, scale):
-    """A grid of few workgroups whose walks are long (4 x 512 tokens, one or two KV heads, sync block): the
-    launch that splits every walk's KV tiles between the two halves of an 8-wave workgroup and merges the
-    halves at the end, at both head dimensions, with the folded scale and without; the local block of
-    the same layout (short walks, one tile per 4-wave workgroup) beside it.  Every row is checked."""
+    """A grid of few workgroups whose walks are long (4 x 512 tokens, one or two KV heads, sync block), which takes the
+    launch that shares every walk's keys out among the wavefronts of a workgroup, at both head dimensions,
+    with the folded scale and without; the local block of the same layout beside it.  Every row is checked."""
     Hq = 4 * Hkv
     seg = np.array([0, 512, 1024, 1536, 2048], dtype=np.int32)
     q, k, v = rand_block(17, 2048, Hq, Hkv, D, sigma=0.7)

@@ -8,13 +8,49 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2511_02647_amd", "csrc")
 
 
-def run(tmp_path, name):
+def run(tmp_path, name, stdin=""):
     exe = str(tmp_path / name)
     subprocess.check_call(["g++", "-O1", "-std=c++17", "-Wall", "-Werror", "-I" + CSRC, "-o", exe, os.path.join(ROOT, "tests", "host", name + ".cpp")])
-    p = subprocess.run([exe], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=60)
+    p = subprocess.run([exe], input=stdin, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=60)
     assert p.returncode == 0, p.stdout
     return p.stdout
 
 
 def test_halves_of_a_listed_tile_stay_inside_it(tmp_path):
     assert "clean" in run(tmp_path, "half_tile")
+
+
+def test_the_layouts_of_the_gpu_tests_take_the_launches_they_name(tmp_path):
+    """On the 256 CUs of the device the tests run on; every launch at every padded head dimension that has it is among them."""
+    import test_gpu_general_shapes as g
+    want, shapes = [], []
+
+    def add(what, dtype, D, Hq, Hkv, causal, sync, lens):
+        want.append(what)
+        shapes.append("%s %d %d %d %d %d 0 256 %s" % (dtype, D, Hq, Hkv, causal, sync, " ".join(map(str, lens))))
+
+    for launch, sync, causal, lens, Hq, Hkv, dims in g.LAUNCHES:
+        for D in dims:
+            add(launch, "bf16", D, Hq, Hkv, causal, sync, lens)
+    for name, (lens, Hq, Hkv) in g.PLAN_LAYOUTS.items():
+        for D in (64, 128):
+            add({"eight-short": "eight", "split-long": "split"}.get(name, name), "bf16", D, Hq, Hkv, 1, 1, lens)
+    for D in (8, 40, 72, 96, 120, 160, 256):
+        for sync in (0, 1):
+            for name in ("short", "long"):
+                add("split" if D <= 128 else "four-ordered", "bf16", D, *g.BF16_LAYOUTS[name][1:], 1, sync, g.BF16_LAYOUTS[name][0])
+            add("four", "bf16", D, *g.BF16_LAYOUTS["four"][1:], 1, sync, g.BF16_LAYOUTS["four"][0])
+    for D in (8, 40, 64, 88, 128, 136, 256):
+        for name, (lens, Hq, Hkv) in g.LAYOUTS.items():
+            add("split" if name == "narrow" and D > 128 else name, "f32", D, Hq, Hkv, 1, 1, lens)
+    for name in ("eight", "eight-pairs"):
+        lens, Hq, Hkv = g.HIDDEN_LAYOUTS[name]
+        add(name, "bf16", 72, Hq, Hkv, 1, 1, lens)
+    got = run(tmp_path, "launch_choice", "\n".join(shapes)).split()
+    assert len(got) == len(want)
+    assert not [(s, w, x) for s, w, x in zip(shapes, want, got) if w != x]
+    padded = lambda D: D if D in (64, 128) else -(-D // 32) * 32 + 1000    # 1000: weights at full precision
+    reached = {(launch, padded(D)) for launch, _, _, _, _, _, dims in g.LAUNCHES for D in dims}
+    assert reached >= {(l, d) for l in ("four", "eight", "eight-pairs", "split") for d in (64, 128, 1032, 1064, 1096, 1128)}
+    assert reached >= {("four-ordered", d) for d in (64, 128, 1032, 1064, 1096, 1128, 1160, 1192, 1224, 1256)}
+    assert reached >= {("four", d) for d in (1160, 1192, 1224, 1256)}
