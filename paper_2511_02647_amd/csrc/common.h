@@ -145,7 +145,7 @@ inline void order_segments_by_length(PrefillArgs& a) {
 // Host-side launchers (one per kernel family); each returns the hipError_t of the launch.
 hipError_t launch_prefill_generic(const PrefillArgs& a, int n_blocks, int dtype, hipStream_t s);
 hipError_t launch_prefill_mfma(const PrefillArgs& a, int n_blocks, hipStream_t s);
-hipError_t launch_prefill_split(const PrefillArgs& a, bool fold, int n_blocks, hipStream_t s);
+hipError_t launch_prefill_split(const PrefillArgs& a, bool fold, hipStream_t s);
 hipError_t launch_prefill_f32(const PrefillArgs& a, int n_blocks, hipStream_t s);
 hipError_t launch_build_kept_tiles(const PrefillArgs& a, int2* kept_tiles, int32_t* kept_cum,
                                    hipStream_t s);

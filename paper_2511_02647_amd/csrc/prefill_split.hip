@@ -68,9 +68,7 @@ __global__ __launch_bounds__(64 * kSplitWaves, DP > 64 ? 2 : 4) void prefill_spl
   const int rest = blockIdx.x / Hkv;
   const int head = g * G + rest % G;
   const int p = rest / G;
-  const int block = blockIdx.y;
-  const bool is_sync = a.sync_override >= 0 ? (a.sync_override != 0)
-                                            : sync_block_rule(a.sync_interval, a.block_idx0 + block);
+  const bool is_sync = a.sync_override >= 0 ? (a.sync_override != 0) : sync_block_rule(a.sync_interval, a.block_idx0);
   const bool causal = a.causal != 0;
   const bool sparse = is_sync && a.keep_chunks != nullptr;
   const int rank = a.short_half_ascending && p >= (T + 1) / 2 ? T - 1 - (p - (T + 1) / 2) : p;  // 0: longest walk
@@ -85,12 +83,12 @@ __global__ __launch_bounds__(64 * kSplitWaves, DP > 64 ? 2 : 4) void prefill_spl
   const KvWalk w = make_kv_walk(a, seg_tab, tile_tab, tile, is_sync, sparse);
   const int row0 = w.q0;
 
-  const uint16_t* qp = reinterpret_cast<const uint16_t*>(a.q) + (int64_t)block * a.q_block_stride;
-  const uint16_t* kp = reinterpret_cast<const uint16_t*>(a.k) + (int64_t)block * a.kv_block_stride + g * D;
-  const uint16_t* vp = reinterpret_cast<const uint16_t*>(a.v) + (int64_t)block * a.kv_block_stride + g * D;
+  const uint16_t* qp = reinterpret_cast<const uint16_t*>(a.q);
+  const uint16_t* kp = reinterpret_cast<const uint16_t*>(a.k) + g * D;
+  const uint16_t* vp = reinterpret_cast<const uint16_t*>(a.v) + g * D;
   const uint16_t* kp_list = reinterpret_cast<const uint16_t*>(a.k_list) + g * D;
   const uint16_t* vp_list = reinterpret_cast<const uint16_t*>(a.v_list) + g * D;
-  uint16_t* op = reinterpret_cast<uint16_t*>(a.out) + (int64_t)block * a.q_block_stride;
+  uint16_t* op = reinterpret_cast<uint16_t*>(a.out);
   const float sc = a.scale * kLog2e;
   const int row_elems = Hkv * D;
   TL tile_io;
@@ -293,30 +291,30 @@ __global__ __launch_bounds__(64 * kSplitWaves, DP > 64 ? 2 : 4) void prefill_spl
 }
 
 template <int DP, bool FOLD, bool EXACT>
-hipError_t launch_split_t(const PrefillArgs& a, int n_blocks, hipStream_t s) {
+hipError_t launch_split_t(const PrefillArgs& a, hipStream_t s) {
   constexpr int smem = (2 * kSplitWaves + 1) * KvTile<DP, 1, 1, kSplitRows>::TILEB;
   static std::atomic<uint64_t> attr_done{0};
   hipError_t e = set_max_dynamic_lds_once(attr_done, reinterpret_cast<const void*>(&prefill_split_kernel<DP, FOLD, EXACT>), smem);
   if (e != hipSuccess) return e;
-  dim3 grid((unsigned)(a.n_q_tiles * a.Hq), (unsigned)n_blocks);
+  dim3 grid((unsigned)(a.n_q_tiles * a.Hq));
   hipLaunchKernelGGL((prefill_split_kernel<DP, FOLD, EXACT>), grid, dim3(64 * kSplitWaves), smem, s, a);
   return hipGetLastError();
 }
 
 }  // namespace
 
-// head dimension at most 128
-hipError_t launch_prefill_split(const PrefillArgs& a_in, bool fold, int n_blocks, hipStream_t s) {
+// one block; head dimension at most 128
+hipError_t launch_prefill_split(const PrefillArgs& a_in, bool fold, hipStream_t s) {
   PrefillArgs a = a_in;
   lay_out_query_tiles(a, kWaveRows);
   order_segments_by_length(a);
-  a.short_half_ascending = (int64_t)a.n_q_tiles * a.Hq * n_blocks <= 2 * (int64_t)a.n_cus ? 1 : 0;
-  if (a.D == 128) return fold ? launch_split_t<128, true, false>(a, n_blocks, s) : launch_split_t<128, false, false>(a, n_blocks, s);
-  if (a.D == 64) return fold ? launch_split_t<64, true, false>(a, n_blocks, s) : launch_split_t<64, false, false>(a, n_blocks, s);
-  if (a.D <= 32) return launch_split_t<32, false, true>(a, n_blocks, s);
-  if (a.D <= 64) return launch_split_t<64, false, true>(a, n_blocks, s);
-  if (a.D <= 96) return launch_split_t<96, false, true>(a, n_blocks, s);
-  return launch_split_t<128, false, true>(a, n_blocks, s);
+  a.short_half_ascending = (int64_t)a.n_q_tiles * a.Hq <= 2 * (int64_t)a.n_cus ? 1 : 0;
+  if (a.D == 128) return fold ? launch_split_t<128, true, false>(a, s) : launch_split_t<128, false, false>(a, s);
+  if (a.D == 64) return fold ? launch_split_t<64, true, false>(a, s) : launch_split_t<64, false, false>(a, s);
+  if (a.D <= 32) return launch_split_t<32, false, true>(a, s);
+  if (a.D <= 64) return launch_split_t<64, false, true>(a, s);
+  if (a.D <= 96) return launch_split_t<96, false, true>(a, s);
+  return launch_split_t<128, false, true>(a, s);
 }
 
 }  // namespace fedattn
