@@ -98,50 +98,6 @@ int decode_chunk_rows(int64_t total_rows, int Hkv) {
   return (int)(rows < kKvTile ? kKvTile : rows);
 }
 
-// Sync blocks of more than 16 query columns (bf16): a chunk costs a workgroup per KV head and 64 columns,
-// and partials of all columns that are written and read back, so the split that gives every CU one
-// workgroup per KV head is too fine when the columns or the segments are many.  Microseconds, measured on
-// one MI355X (8 to 32 participants with 64 to 4000 rows each, 24 to 256 columns): a workgroup's start and
-// end 5, a 64-row tile 0.9 (head dimension 128), 0.5 (64), 1.05 (weights at full precision); workgroups
-// beyond one per CU wait; the caches stream at 6.5 MB/us, partials pass at 2.5; the combine kernel takes 2
-// more beyond its one-round-trip case.  Sync block before and after, us:
-//   32 x 2000 rows, 8/1 heads 47.6 -> 25.4       32 x 300..800 rows, 16/4 heads 34.4 -> 21.7
-//   24 x 1000..2000 rows, 32/4 heads 62.5 -> 52     16 x 200..500 rows, 32/8 heads 21.6 -> 17.1
-//   20 x 500..1500 rows, 8/2 heads of 64 17.1 -> 14.3   8 x 300..1000 rows, 16/2 heads 14.9 -> 13.0
-int wide_chunk_rows(const int32_t* rows, int N, int finest, int Hkv, int D, int cols) {
-  const double tile_us = D == 128 ? 0.9 : D == 64 ? 0.5 : 1.05;
-  const int cus = device_cus();
-  const int64_t wgs_per_chunk = (int64_t)Hkv * ((cols + 63) / 64);
-  int64_t total = 0;
-  int longest = 1;
-  for (int n = 0; n < N; ++n) {
-    total += rows[n];
-    longest = rows[n] > longest ? rows[n] : longest;
-  }
-  const double stream_us = (double)total * Hkv * D * 4 / 6.5e6;
-  int best = finest;
-  double best_us = 1e30;
-  // from the finest split to one chunk per segment in 24 steps, and the longest segment in up to 8 equal parts
-  for (int i = 0; i < 33; ++i) {
-    int64_t cr = i < 25 ? finest + (int64_t)(longest - finest) * i / 24 : ((int64_t)longest + (i - 25)) / (i - 24);
-    cr = (cr + kKvTile - 1) / kKvTile * kKvTile;
-    if (cr < finest) continue;
-    const double per = 1.0 / (double)cr;
-    int64_t chunks = 0;   // an estimate's worth: rounding may be off by one where rows divide evenly
-    for (int n = 0; n < N; ++n) chunks += (int)((double)(rows[n] + (cr - 1)) * per);
-    const int64_t tiles = ((cr < longest ? cr : longest) + kKvTile - 1) / kKvTile;
-    const int64_t rounds = (chunks * wgs_per_chunk + cus - 1) / cus;
-    const double walk_us = (double)rounds * (5 + (double)tiles * tile_us);
-    const double us = (walk_us > 5 + stream_us ? walk_us : 5 + stream_us) + (double)chunks * Hkv * cols * (4 * D + 8) / 2.5e6 +
-                      (chunks > kCombineAtOnce ? 2 : 0);
-    if (us < best_us) {
-      best_us = us;
-      best = (int)cr;
-    }
-  }
-  return best;
-}
-
 constexpr int64_t kMaxMergeTrips = 4;
 
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
@@ -509,7 +465,7 @@ static fedattn_status run_decode(bool fused, const fedattn_params* params, int32
       }
       a.chunk_rows = decode_chunk_rows(total_rows, a.Hkv);
       if (split && a.cols > 16 && params->dtype == FEDATTN_BF16)
-        a.chunk_rows = wide_chunk_rows(rows_of, N, a.chunk_rows, a.Hkv, a.D, a.cols);
+        a.chunk_rows = wide_chunk_rows(rows_of, N, a.chunk_rows, a.Hkv, a.D, a.cols, a.n_cus);
       int64_t chunks = 0;
       for (int n = 0; n <= N; ++n) {
         a.seg_off[n] = seg_offsets[n];

@@ -14,8 +14,8 @@
 namespace fedattn {
 
 constexpr int kMaxP = FEDATTN_MAX_PARTICIPANTS;
+static_assert(kMaxP == kMaxSegments, "the launch rules hold one entry per participant");
 constexpr int kMaxFusedBlocks = 64;    // blocks of one fused decode launch
-constexpr int kCombineAtOnce = 64;     // chunks up to which the decode combine kernel makes one round trip
 constexpr int kMergeBatch = 8;         // chunks whose partials a decode merge has in flight at once
 
 // Segment layout of the global sequence, passed by value in the kernel arguments

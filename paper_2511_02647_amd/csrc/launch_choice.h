@@ -10,6 +10,8 @@ namespace fedattn {
 constexpr int kKvTile = 64;            // KV rows per tile; also the keep-list tile
 constexpr int kWaveRows = 32;          // query rows per wavefront in the bf16 prefill kernels
 constexpr int kMaxOrderedTiles = 512;  // query tiles of a launch that assigns them through an explicit order
+constexpr int kCombineAtOnce = 64;     // chunks up to which the decode combine kernel makes one round trip
+constexpr int kMaxSegments = 128;      // participants at most
 
 // ---- which of the launches a block takes ------------------------------------------------------
 // kFour: 4-wavefront workgroups, one query tile each, several per CU; kFourOrdered: the same, causal and
@@ -153,6 +155,59 @@ inline F32Launch choose_f32_launch(const int32_t* seg_off, int n_seg, int Hq, in
   if (shared >= 6 * (int64_t)n_cus) return kF32Shared;
   const int64_t split = count_query_tiles(seg_off, n_seg, 16 * nq).tiles * Hq * n_blocks;
   return nq > 1 && split < 2 * (int64_t)n_cus ? kF32Narrow : kF32KeySplit;
+}
+
+// ---- decode ----------------------------------------------------------------------------------
+// Sync blocks of more than 16 query columns (bf16): a chunk costs a workgroup per KV head and 64 columns,
+// and partials of all columns that are written and read back, so the split that gives every CU one
+// workgroup per KV head is too fine when the columns or the segments are many.  Microseconds, measured on
+// one MI355X (8 to 32 participants with 64 to 4000 rows each, 24 to 256 columns): a workgroup's start and
+// end 5, a 64-row tile 0.9 (head dimension 128), 0.5 (64), 1.05 (weights at full precision); workgroups
+// beyond one per CU wait; the caches stream at 6.5 MB/us, partials pass at 2.5; the combine kernel takes 2
+// more beyond its one-round-trip case.  Sync block before and after, us:
+//   32 x 2000 rows, 8/1 heads 47.6 -> 26.0       32 x 300..800 rows, 16/4 heads 34.4 -> 21.7
+//   24 x 1000..2000 rows, 32/4 heads 62.5 -> 52     16 x 200..500 rows, 32/8 heads 21.6 -> 17.1
+//   20 x 500..1500 rows, 8/2 heads of 64 17.1 -> 14.1   8 x 300..1000 rows, 16/2 heads 14.9 -> 13.0
+// The estimate itself takes 0.3 us at 16 participants and 1.6 at 128 (0.8 and 4.7 when every step was evaluated in full).
+inline int wide_chunk_rows(const int32_t* rows, int N, int finest, int Hkv, int D, int cols, int cus) {
+  const double tile_us = D == 128 ? 0.9 : D == 64 ? 0.5 : 1.05;
+  const int64_t wgs_per_chunk = (int64_t)Hkv * ((cols + 63) / 64);
+  int64_t total = 0;
+  int longest = 1;
+  double rows_d[kMaxSegments];
+  for (int n = 0; n < N; ++n) {
+    total += rows[n];
+    longest = rows[n] > longest ? rows[n] : longest;
+    rows_d[n] = rows[n];
+  }
+  const double stream_us = (double)total * Hkv * D * 4 / 6.5e6;
+  const double partials_us = (double)Hkv * cols * (4 * D + 8) / 2.5e6;   // per chunk
+  int best = finest;
+  double best_us = 1e30;
+  int64_t last = 0;
+  // from the finest split to one chunk per segment in 24 steps, and the longest segment in up to 8 equal parts
+  for (int i = 0; i < 33; ++i) {
+    int64_t cr = i < 25 ? finest + (int64_t)(longest - finest) * i / 24 : ((int64_t)longest + (i - 25)) / (i - 24);
+    cr = (cr + kKvTile - 1) / kKvTile * kKvTile;
+    if (cr < finest || cr == last) continue;
+    last = cr;
+    const double per = 1.0 / (double)cr;
+    const int64_t tiles = ((cr < longest ? cr : longest) + kKvTile - 1) / kKvTile;
+    const auto us_of = [&](int64_t chunks) {
+      const int64_t rounds = (chunks * wgs_per_chunk + cus - 1) / cus;
+      const double walk_us = (double)rounds * (5 + (double)tiles * tile_us);
+      return (walk_us > 5 + stream_us ? walk_us : 5 + stream_us) + (double)chunks * partials_us + (chunks > kCombineAtOnce ? 2 : 0);
+    };
+    if (us_of((int64_t)((double)total * per)) >= best_us) continue;   // with no segment rounded up
+    int chunks = 0;   // an estimate's worth: rounding may be off by one where rows divide evenly
+    for (int n = 0; n < N; ++n) chunks += (int)((rows_d[n] + (double)(cr - 1)) * per);
+    const double us = us_of(chunks);
+    if (us < best_us) {
+      best_us = us;
+      best = (int)cr;
+    }
+  }
+  return best;
 }
 
 }  // namespace fedattn

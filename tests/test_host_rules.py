@@ -54,3 +54,7 @@ def test_the_layouts_of_the_gpu_tests_take_the_launches_they_name(tmp_path):
     assert reached >= {(l, d) for l in ("four", "eight", "eight-pairs", "split") for d in (64, 128, 1032, 1064, 1096, 1128)}
     assert reached >= {("four-ordered", d) for d in (64, 128, 1032, 1064, 1096, 1128, 1160, 1192, 1224, 1256)}
     assert reached >= {("four", d) for d in (1160, 1192, 1224, 1256)}
+
+
+def test_chunk_length_of_wide_sync_blocks_is_that_of_the_full_search(tmp_path):
+    assert "clean" in run(tmp_path, "wide_chunks")
