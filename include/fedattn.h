@@ -59,7 +59,7 @@ typedef struct fedattn_params {
   int32_t n_participants; /* N, 1..FEDATTN_MAX_PARTICIPANTS */
   int32_t n_q_heads;      /* Hq */
   int32_t n_kv_heads;     /* Hkv, divides Hq */
-  int32_t head_dim;       /* D: multiple of 8, at most 256 (bf16 with D = 64 or 128 runs on MFMA) */
+  int32_t head_dim;       /* D: multiple of 8, at most 256 */
   int32_t sync_interval;  /* H of Algorithm 1; <= 0: no block ever synchronises */
   int32_t causal;         /* 1: decoder (a token sees itself and earlier tokens); 0: encoder */
   int32_t dtype;          /* fedattn_dtype of q, k, v, out */
@@ -115,14 +115,15 @@ FEDATTN_API size_t fedattn_workspace_bytes(const fedattn_params* params, int32_t
  *                  seg_offsets[n] + c*chunk_tokens ... (clipped to the segment);
  *                  flags are stored participant after participant.  Read only in
  *                  sync blocks.  chunk_tokens must be positive when keep_chunks is
- *                  given (1 = token-granular exchange).  On the MFMA path (bf16,
- *                  D = 64 or 128) chunks that are multiples of 64 are visited where
- *                  they are; finer chunks have their kept rows packed into the
- *                  workspace first (a K,V-sized copy).  One block per call.
+ *                  given (1 = token-granular exchange).  Chunks that are multiples of 64
+ *                  are visited where they are; finer chunks have their kept rows packed into
+ *                  the workspace first (a K,V-sized copy).  One block per call.
  *   sync_override  -1: rule above; 0: force local; 1: force sync (variable sync
  *                  schedules H_t).
  *   workspace      device, >= fedattn_workspace_bytes(PREFILL); may be NULL when
- *                  keep_chunks is NULL.
+ *                  keep_chunks is NULL.  fp32, and bf16 with D other than 64 and 128: a keep-list
+ *                  call with less (or none, or one that is not 16-byte aligned) runs too, one
+ *                  wavefront per (row, head) and many times slower.
  */
 FEDATTN_API fedattn_status fedattn_prefill(const fedattn_params* params, int32_t block_idx, const void* q,
                                const void* k, const void* v, void* out,
@@ -146,7 +147,9 @@ FEDATTN_API fedattn_status fedattn_prefill(const fedattn_params* params, int32_t
  *   keep_chunks, chunk_tokens  as in fedattn_prefill (sparse KV exchange).
  *   workspace      device, >= fedattn_workspace_bytes(PREFILL_SYNC_LOCAL_KV); when the matrices
  *                  lie back to back only the keep-list's share is used (the copy's share may
- *                  be left out, and the workspace may be NULL without a keep-list).
+ *                  be left out, and the workspace may be NULL without a keep-list).  fp32, and
+ *                  bf16 with D other than 64 and 128: as in fedattn_prefill, a keep-list's share
+ *                  without the packed rows takes the slow kernel.
  */
 FEDATTN_API fedattn_status fedattn_prefill_sync_local_kv(const fedattn_params* params, const void* q,
                                              const void* const* k_local, const void* const* v_local, void* out,

@@ -331,6 +331,8 @@ fedattn_status fedattn_prefill_sync_local_kv(const fedattn_params* params, const
                   2 * copy, workspace_bytes);
     if (!aligned16(workspace)) return fail(FEDATTN_EINVAL, "workspace must be 16-byte aligned");
     if (keep_chunks && chunk_tokens > 0) {
+      // fp32 and other head dimensions: with less than the whole the general kernel runs, as in fedattn_prefill;
+      // room for the list is asked for all the same, as it was before these shapes packed rows
       const PrefillWs w = prefill_ws_layout(params, total, chunk_tokens);
       const size_t need = 2 * copy + (use_mfma_prefill(params) ? w.total : w.list_end);
       if (workspace_bytes < need)

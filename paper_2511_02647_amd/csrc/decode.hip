@@ -455,7 +455,8 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(DecodeArgs a) {
 
 // General decode kernel (plain ALU, fp32 arithmetic, any head_dim up to 256, fp32 or
 // bf16 storage): one wavefront per (participant, query head), no split and no workspace.  It takes
-// the calls that come without one; with one they run 5 to 59 times faster on the split kernels.
+// the calls that come without one; with one the split kernels are up to 70 times faster (fp32 sync
+// block of 32 x 300..900 rows, 32/8 heads of 128: 14.8 ms here, 0.21 ms split).
 template <typename T>
 __global__ __launch_bounds__(64) void decode_rows_kernel(DecodeArgs a) {
   __shared__ float qs[256];

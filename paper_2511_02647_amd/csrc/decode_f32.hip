@@ -6,7 +6,7 @@
 // group, where they are the B operand of O^T += V^T P^T as they stand (layouts as in prefill_f32.hip).
 // A 64-row tile costs a CU 16 D NQ matrix cycles and 512 D bytes of loads, so up to 64 columns the
 // chip is bound by memory, and short caches by the launches: 5 participants with 200..1500 rows,
-// 8/2 heads of 64, one local and one sync block (6 MB): 21 us, where one wavefront per (participant, head)
+// 8/2 heads of 64, one local and one sync block (6 MB): 17.7 us, where one wavefront per (participant, head)
 // took 1525 us.
 #include <math.h>
 

@@ -69,7 +69,12 @@ inline Walks count_walks(const PrefillShape& a, bool is_sync, int rows, int keys
     const double tiles = ceil(len / rows);
     double most, mean;   // keys that the segment's last rows and its rows on average see
     if (a.causal) {
-      // remote rows under a keep-list: their number is known to the device only, half are taken to be kept
+      // Remote rows under a keep-list: their number is known to the device only, half are taken to be kept.
+      // Every launch forced on 8 layouts (4 to 16 participants of 100..2000 tokens, 2 to 32 heads of 64, 96 and 128)
+      // at shares of 0.1, 0.25, 0.5 and 1: kFour, kEight and kSplit were taken where they are the fastest, or within
+      // 4 % of it at a quarter and a half, 11 % at 0.1, 13 % at 1.  kEightPairs, whose two walks are taken to
+      // add up to the same, is overrated under a keep-list: taken in two of the layouts and slower at every share
+      // (at 0.1, 8 x 454..823 tokens, 16/8 heads of 64: 51 us, kFour 31; 16 x 207..786, 8/2 heads of 96: 105, kEight 76).
       const double before = is_sync ? (a.keep ? off / 2 : off) : 0;
       most = before + len;
       mean = before + (len + fmin(rows, len)) / 2;

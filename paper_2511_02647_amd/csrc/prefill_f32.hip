@@ -10,7 +10,7 @@
 // 154 here): a 64-key tile costs a CU 16 000 cycles of matrix work against 64 KB of tile loads, so one
 // stage of K and one of V suffice and two 4-wavefront workgroups per CU cover each other's softmax.
 // 4 participants of 100..900 tokens, 8/2 heads of 128, a local and a sync block: 2057 us on the
-// wavefront-per-row kernel, 122 us here; 8 x 2000 tokens, 32/8 heads, sync: 137 TFLOP/s.
+// wavefront-per-row kernel, 120 us here; 8 x 2000 tokens, 32/8 heads, sync: 137 TFLOP/s.
 #include "common.h"
 #include "mfma_tile.h"
 #include "prefill_walk.h"

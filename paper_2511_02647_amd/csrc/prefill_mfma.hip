@@ -53,7 +53,7 @@ namespace {
 // the head dimensions other than 64 and 128; DP is the head dimension padded to a multiple of 32.
 // Its matrix work is (1 + 3) / 2 times that of the other kind: 8 x 2000 tokens, 32/8 heads, sync:
 // 590 useful TFLOP/s at head dimension 96 (1160 at 128 without EXACT).  A local and a sync block of
-// 4 x 100..900 tokens, 8/2 heads of 96: 1794 us on the wavefront-per-row kernel, 72 us here.
+// 4 x 1000..2500 tokens, 8/2 heads of 96: 190 us.
 template <int DP, int NG, bool FOLD, bool EXACT>
 __global__ __launch_bounds__(256 * NG, DP > 128 ? 1 : DP > 64 ? 2 : 3) void prefill_mfma_kernel(PrefillArgs a) {
   using TL = KvTile<DP, 1, 4, kKvTile, EXACT>;
