@@ -432,6 +432,11 @@ static fedattn_status run_decode(bool fused, const fedattn_params* params, int32
     if (must_split) return fail(FEDATTN_EINVAL, "workspace must be 16-byte aligned");
     split = false;
   }
+  // tens of thousands of KV heads: the counters alone take the piece's room
+  if (split && !must_split && need == kMostPieceBytes) {
+    const size_t chunks = (size_t)decode_target_chunks(params->n_kv_heads) + (size_t)N;
+    if (decode_counter_bytes(params) + 512 + chunks * 16 * ((size_t)params->head_dim * 4 + 8) > need) split = false;
+  }
   if (split) {
     slice_bytes = align_up(need, 256);
     if (fused) {

@@ -100,3 +100,34 @@ def test_decode_in_pieces(shape, dtype):
         check(host(outs[0]), ref, dtype, what)
         for o in outs[1:]:
             assert torch.equal(o, outs[0]), what
+
+
+def test_decode_pieces_of_several_blocks_and_more_heads_than_pieces_have_room_for():
+    lens, Hq, Hkv, D = PIECES["heads"]
+    N, M, lens = len(lens), 3, np.asarray(lens, dtype=np.int32)
+    seg = np.concatenate([[0], np.cumsum(lens + 1)]).astype(np.int32)
+    p = fa.make_params(N, Hq, Hkv, D, 2, torch.float32)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(6)
+    mk = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    q, k, v = mk(M, N, Hq, D), mk(M, int(seg[-1]), Hkv, D), mk(M, int(seg[-1]), Hkv, D)
+    ws = torch.full((2 * fa.FEDATTN_STATIC_SCRATCH_BYTES,), 255, dtype=torch.uint8, device="cuda")   # two blocks in flight
+    one, many = torch.zeros_like(q), torch.zeros_like(q)
+    say("decode pieces, fused blocks")
+    for b in range(M):
+        fa.fedattn_decode_static(p, 1, q[b], k[b], v[b], one[b], seg, lens)
+    fa.fedattn_decode_blocks_fused(p, 1, M, q, k, v, many, q[0].numel(), k[0].numel(), seg, lens, sync_override=1, workspace=ws)
+    torch.cuda.synchronize()
+    assert torch.equal(one, many)
+    # 17000 KV heads: no room for chunk counters beside the partials; one row per participant, so the output is V
+    N, H = 128, 17000
+    p = fa.make_params(N, H, H, 8, 0, torch.float32)
+    seg = np.arange(N + 1, dtype=np.int32)
+    q, k, v = mk(N, H, 8), mk(N, H, 8), mk(N, H, 8)
+    say("decode, 17000 KV heads")
+    for call in (lambda o: fa.fedattn_decode(p, 0, q, k, v, o, seg, np.ones(N, np.int32), workspace=ws),
+                 lambda o: fa.fedattn_decode_static(p, 0, q, k, v, o, seg, np.ones(N, np.int32))):
+        out = torch.full_like(q, float("nan"))
+        call(out)
+        torch.cuda.synchronize()
+        assert torch.allclose(out, v, rtol=1e-6, atol=0)
