@@ -3,7 +3,7 @@
 // of host time per attention call for this (10.6 of 14.9 us at the smallest sizes, where the
 // kernels are shorter than that); here it is about one.
 //
-// bind(call, address) hands over the entry points of the loaded library; every other function takes
+// bind(addresses, ...) hands over the entry points of the loaded library; every other function takes
 // its arguments by position (the Python wrappers hold names and defaults) and returns the status
 // code.  Tensors are asked for is_cuda, is_contiguous() and data_ptr(), host arrays come through the
 // buffer protocol; `as_i32` (Python) converts what is not an int32 vector already.
