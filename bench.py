@@ -281,7 +281,7 @@ def prefill_leg(pb: PrefillBench, H: int, ms_step: np.ndarray, pmc_key: str | No
 
 class DecodeBench:
     """cfg4: N participants, one query each per step, all M blocks of a step through
-    fedattn_decode_blocks (one host call per step, every block with its own launches)."""
+    fedattn_decode_blocks (one host call per step, blocks of one kind share launches)."""
 
     def __init__(self, name: str = "cfg4_decode"):
         self.w = fi.workload(name)
@@ -359,7 +359,7 @@ def decode_leg(iterations: int, n_steps: int | None = None) -> dict:
     pmc = PMC["decode"]
     return {"workload": "%s: N = %d, prompt %d, %d decoding steps x %d blocks, H = %d" % (
                 w.name, w.n_participants, db.prompt, w.decode_steps, db.M, w.sync_interval),
-            "launch": "fedattn_decode_blocks: one host call per decoding step, every block with its own launches; each "
+            "launch": "fedattn_decode_blocks: one host call per decoding step, blocks of a kind share launches; each "
                       "step replayed from its own HIP graph, all %d steps in order per iteration" % len(all_steps),
             "steps_timed": len(all_steps), "blocks": db.M, "iterations": iterations,
             "gbytes_per_run": total_bytes / 1e9, "ms_per_run": med, "ms_per_run_wall": wall * 1e3,

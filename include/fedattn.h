@@ -202,10 +202,11 @@ FEDATTN_API fedattn_status fedattn_decode(const fedattn_params* params, int32_t 
  * The same for n_blocks consecutive blocks block_idx0 .. block_idx0+n_blocks-1 of one
  * decoding step in one host call: block b reads q + b*q_block_stride and the caches
  * + b*cache_block_stride (strides in elements, multiples of 8) and writes
- * out + b*q_block_stride; all blocks share the segment layout and lengths.  The
- * blocks are enqueued one after the other (each with its own launches, as the blocks
- * of a model depend on each other); results equal n_blocks calls of fedattn_decode.
- * The workspace is reused from block to block in stream order.
+ * out + b*q_block_stride; all blocks share the segment layout and lengths.  Results
+ * equal n_blocks calls of fedattn_decode in block order, bit for bit.  Where no block's out
+ * overlaps q, the caches or another block's out (as address ranges over all blocks), blocks of one kind
+ * (local / sync) share launches, as many as the workspace has room for; otherwise
+ * the blocks are enqueued one after the other.
  */
 FEDATTN_API fedattn_status fedattn_decode_blocks(const fedattn_params* params, int32_t block_idx0, int32_t n_blocks,
                                      const void* q, const void* k_cache, const void* v_cache, void* out,
@@ -215,13 +216,10 @@ FEDATTN_API fedattn_status fedattn_decode_blocks(const fedattn_params* params, i
                                      size_t workspace_bytes, void* stream);
 
 /*
- * fedattn_decode_blocks for callers that hold the queries of all n_blocks blocks before the
- * first one runs (the blocks of a model do not: the query of block m + 1 comes out of block
- * m; this entry point serves measurements of the kernels without launch effects and callers
- * with independent layers): same arguments and results, but the blocks of one kind (local /
- * sync, Algorithm 1) share launches.  Every block in flight works in its own slice of the
- * workspace: a launch takes as many blocks as the workspace has slices of
- * fedattn_workspace_bytes(DECODE) rounded up to 256 bytes (at least one, at most 64).
+ * fedattn_decode_blocks for callers who know that the blocks are independent (the blocks of a model are
+ * not: the query of block m + 1 comes out of block m): same arguments and results, and blocks of
+ * one kind (local / sync, Algorithm 1) share launches without a look at their addresses.  A launch takes as many
+ * blocks as the workspace holds partials for, at least one per fedattn_workspace_bytes(DECODE) rounded up to 256 bytes, at most 64.
  * No order is kept between the blocks; q, the caches and out of different blocks must not
  * overlap.
  */

@@ -397,8 +397,28 @@ static fedattn_status check_decode_args(const fedattn_params* params, int32_t bl
   return FEDATTN_OK;
 }
 
-// fused: blocks of one kind (local / sync) share launches, as many per launch as the workspace
-// has slices for; otherwise one launch (pair) per block in block order
+// Whether n_blocks blocks can run in any order, or at the same time: no block writes what it or another one reads or writes.
+static bool blocks_apart(const fedattn_params* p, int32_t n_blocks, const void* q, const void* k_cache, const void* v_cache,
+                         const void* out, int64_t q_block_stride, int64_t cache_block_stride, int32_t capacity) {
+  const int64_t q_elems = (int64_t)p->n_participants * p->n_q_heads * p->head_dim;
+  const int64_t kv_elems = (int64_t)capacity * p->n_kv_heads * p->head_dim;
+  const int64_t esize = elem_bytes(p);
+  if (q_block_stride < q_elems) return false;   // output blocks overlap one another
+  const auto end = [&](const void* base, int64_t stride, int64_t elems) {
+    return reinterpret_cast<uintptr_t>(base) + (uintptr_t)(((n_blocks - 1) * stride + elems) * esize);
+  };
+  const uintptr_t out_lo = reinterpret_cast<uintptr_t>(out), out_hi = end(out, q_block_stride, q_elems);
+  const auto hits = [&](const void* base, int64_t stride, int64_t elems) {
+    return reinterpret_cast<uintptr_t>(base) < out_hi && out_lo < end(base, stride, elems);
+  };
+  return !hits(q, q_block_stride, q_elems) && !hits(k_cache, cache_block_stride, kv_elems) && !hits(v_cache, cache_block_stride, kv_elems);
+}
+
+// Blocks of one kind (local / sync) share launches, as many per launch as the workspace has room for, when the caller
+// says that they may (`fused`) or their memory shows it; otherwise one launch (pair) per block in block order.
+// A launch of one block leaves the chip idle at its start and end, about half its time at 16 x 1152 rows.  Calls one
+// launch per block and shared, us: 6 local and 2 sync blocks of 16 x 1152 rows, 32/8 heads of 128 152 -> 130 (4.65 TB/s);
+// 8 sync blocks of 1 x 312..1041 rows, 8/1 heads of 64 44 -> 12; 2 of 3 x 76, 32/4 heads of 64 17.3 -> 9.0; none slower.
 static fedattn_status run_decode(bool fused, const fedattn_params* params, int32_t block_idx0, int32_t n_blocks,
                                  const void* q, const void* k_cache, const void* v_cache, void* out,
                                  int64_t q_block_stride, int64_t cache_block_stride,
@@ -422,8 +442,6 @@ static fedattn_status run_decode(bool fused, const fedattn_params* params, int32
   uint64_t* counters = nullptr;
   const uint64_t ticket = next_ticket();
   bool counters_ready[2] = {false, false};   // a launch of this call and kind has set its counters up, and every launch leaves them at zero
-  int slices = 1;            // blocks in flight at once, each in its own slice of the workspace
-  size_t slice_bytes = 0;
   const size_t need = decode_ws_bytes(params, capacity);
   if (!workspace || workspace_bytes < need) {
     if (must_split) return fail(FEDATTN_EWORKSPACE, "decode needs %zu workspace bytes, got %zu", need, workspace_bytes);
@@ -437,18 +455,12 @@ static fedattn_status run_decode(bool fused, const fedattn_params* params, int32
     const size_t chunks = (size_t)decode_target_chunks(params->n_kv_heads) + (size_t)N;
     if (decode_counter_bytes(params) + 512 + chunks * 16 * ((size_t)params->head_dim * 4 + 8) > need) split = false;
   }
-  if (split) {
-    slice_bytes = align_up(need, 256);
-    if (fused) {
-      if (n_blocks > 65535) return fail(FEDATTN_EINVAL, "at most 65535 blocks per fused call");
-      const size_t fit = 1 + (workspace_bytes - need) / slice_bytes;
-      slices = (int)(fit < (size_t)kMaxFusedBlocks ? fit : (size_t)kMaxFusedBlocks);
-      if (slices > n_blocks) slices = n_blocks;
-    }
-    // blocks count their chunks in at the end of their slice
-    counters = reinterpret_cast<uint64_t*>(reinterpret_cast<unsigned char*>(workspace) + need - decode_counter_bytes(params));
-  }
-  fused = fused && split;
+  if (fused && split && n_blocks > 65535) return fail(FEDATTN_EINVAL, "at most 65535 blocks per fused call");
+  const bool shared = split && n_blocks > 1 && n_blocks <= 65535 &&
+                      (fused || blocks_apart(params, n_blocks, q, k_cache, v_cache, out, q_block_stride, cache_block_stride, capacity));
+  int slices[2] = {1, 1};   // blocks of a kind in flight at once, each with partials and counters of its own in the workspace
+  // blocks one after the other count their chunks in at the end of the workspace
+  if (split) counters = reinterpret_cast<uint64_t*>(reinterpret_cast<unsigned char*>(workspace) + need - decode_counter_bytes(params));
   const auto block_is_sync = [&](int b) {
     return sync_override >= 0 ? sync_override != 0 : sync_block_rule(params->sync_interval, block_idx0 + b);
   };
@@ -509,6 +521,13 @@ static fedattn_status run_decode(bool fused, const fedattn_params* params, int32
         a.part_o = reinterpret_cast<float*>(workspace);
         a.part_ml = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(workspace) + o_bytes);
         a.counters = counters;
+        if (shared) {
+          const size_t slice = whole ? align_up(bytes_of(a.Hkv, a.cols), 256) + decode_counter_bytes(params) : align_up(need, 256);
+          if (whole) a.counters = reinterpret_cast<uint64_t*>(reinterpret_cast<unsigned char*>(workspace) + slice - decode_counter_bytes(params));
+          const size_t fit = 1 + (workspace_bytes - (whole ? slice : need)) / slice;
+          slices[sync ? 1 : 0] = (int)(fit < (size_t)kMaxFusedBlocks ? fit : (size_t)kMaxFusedBlocks);
+          a.slice_bytes = (int64_t)slice;
+        }
         // Merge inside the split kernel, by the workgroup that finishes last: up to 16 query columns
         // share a workgroup per chunk, and every output row needs a chunk to come from (an empty
         // segment's zero rows come from the separate combine kernel).  It makes a round trip to memory
@@ -532,7 +551,6 @@ static fedattn_status run_decode(bool fused, const fedattn_params* params, int32
       }
       a.q_block_bytes = q_block_stride * (int64_t)esize;
       a.cache_block_bytes = cache_block_stride * (int64_t)esize;
-      a.slice_bytes = (int64_t)slice_bytes;
       built[sync ? 1 : 0] = true;
     }
     return FEDATTN_OK;
@@ -557,28 +575,23 @@ static fedattn_status run_decode(bool fused, const fedattn_params* params, int32
     st = prepare(block_is_sync(b));
     if (st != FEDATTN_OK) return st;
   }
-  if (fused) {
+  if (shared) {
     for (int kind = 0; kind < 2; ++kind) {
       int first = 0;
       while (first < n_blocks) {
         int cnt = 0;
         DecodeArgs& a = args[kind];
         int b = first;
-        for (; b < n_blocks && cnt < slices; ++b) {
+        for (; b < n_blocks && cnt < slices[kind]; ++b) {
           if ((block_is_sync(b) ? 1 : 0) != kind) continue;
-          if (cnt == 0) {
-            st = prepare(kind == 1);
-            if (st != FEDATTN_OK) return st;
-          }
           a.block_list[cnt++] = (uint16_t)b;
         }
         first = b;
         if (cnt == 0) continue;
         a.q = q; a.out = out; a.k_cache = k_cache; a.v_cache = v_cache;
-        a.ticket = counters_ready[kind] ? 0 : ticket;   // no later launch of this kind has more slices than the first
-        counters_ready[kind] = true;
+        a.ticket = ticket;   // the other kind's launches lay the workspace out differently
         hipError_t e = launch(a, cnt);
-        if (e != hipSuccess) return fail(FEDATTN_ELAUNCH, "decode (fused, %d blocks): %s", cnt, hipGetErrorString(e));
+        if (e != hipSuccess) return fail(FEDATTN_ELAUNCH, "decode (%d blocks at once): %s", cnt, hipGetErrorString(e));
       }
     }
     return FEDATTN_OK;

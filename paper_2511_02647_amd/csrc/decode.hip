@@ -32,8 +32,8 @@ namespace {
 template <int D>
 constexpr int decode_stages() { return D > 192 ? 2 : 3; }
 
-template <int D>
-constexpr int decode_smem_bytes() { return decode_stages<D>() * 2 * KvTile<D, 0>::TILEB; }
+template <int D, int STAGES>
+constexpr int decode_smem_bytes() { return STAGES * 2 * KvTile<D, 0>::TILEB; }
 
 // COLSPLIT = false (at most 16 query columns, e.g. the G heads of one participant in a
 // local block): 4 wavefronts, wavefront w takes tile rows 16w..16w+15; they are merged
@@ -46,11 +46,10 @@ constexpr int decode_smem_bytes() { return decode_stages<D>() * 2 * KvTile<D, 0>
 // EXACT (head dimensions other than 64 and 128, padded to DP): the weights keep their fp32 precision
 // in the second product, as three bf16 parts each (one participant of 62..207 rows to eight of 1500,
 // bf16: 5 to 14 times faster than one wavefront per participant and head).
-template <int DP, bool COLSPLIT, bool EXACT, bool PIECES>
+template <int DP, bool COLSPLIT, bool EXACT, bool PIECES, int STAGES>
 __global__ __launch_bounds__(COLSPLIT ? 512 : 256, 1) void decode_stream_kernel(DecodeArgs a) {
   constexpr int NW = COLSPLIT ? 8 : 4;
   using TL = KvTile<DP, 0, NW, kKvTile, EXACT>;
-  constexpr int kDecodeStages = decode_stages<DP>();
   const int D = EXACT ? a.D : DP;
   constexpr int KS = DP / 32;                // k-steps of S^T (16x16x32)
   constexpr int DT = DP / 16;                // 16-row tiles of O^T along head_dim
@@ -129,14 +128,14 @@ __global__ __launch_bounds__(COLSPLIT ? 512 : 256, 1) void decode_stream_kernel(
 
   auto issue = [&](int t) __attribute__((always_inline)) {
     const int len = min(kKvTile, r_hi - r_lo - kKvTile * t);
-    const uint32_t stage = lds_base + (t % kDecodeStages) * 2 * TILEB;
+    const uint32_t stage = lds_base + (t % STAGES) * 2 * TILEB;
     // every cache row is read once: the local-block kernel streams them past the caches (19.2
     // against 20.7 us per block-step at 16 x 1152 rows; no gain in the column-split kernel)
     tile_io.template dma<false, !COLSPLIT>(kbase + (int64_t)t * kKvTile * row_elems, stage, len);
     tile_io.template dma<true, !COLSPLIT>(vbase + (int64_t)t * kKvTile * row_elems, stage + TILEB, len);
   };
 #pragma unroll
-  for (int t = 0; t < kDecodeStages - 1; ++t)
+  for (int t = 0; t < STAGES - 1; ++t)
     if (t < nt) issue(t);
   // The chunk counter is requested here, behind the first tiles (ahead of them it cost 0.4 us of an 18 us
   // launch), and looked at after the stream.
@@ -172,7 +171,7 @@ __global__ __launch_bounds__(COLSPLIT ? 512 : 256, 1) void decode_stream_kernel(
     // this wavefront's part of tile t has landed once at most the loads of the tiles
     // issued after it are outstanding (the query loads are older still)
     // (the counter's load is allowed for where it matters, before the first tile)
-    const int after = min(nt, t + kDecodeStages - 1) - (t + 1);
+    const int after = min(nt, t + STAGES - 1) - (t + 1);
     if (t == 0 && set_up && after == 1)
       wait_vmcnt<2 * IPW + 1>();
     else if (after >= 2)
@@ -187,10 +186,10 @@ __global__ __launch_bounds__(COLSPLIT ? 512 : 256, 1) void decode_stream_kernel(
       asm volatile("" : "+v"(qw[st]));  // the query loads have landed by now
       if (EXACT && 32 * st + 8 * kg >= D) qw[st] = u32x4{0u, 0u, 0u, 0u};  // padded columns
     }
-    if (t + kDecodeStages - 1 < nt) issue(t + kDecodeStages - 1);  // into the stage tile t-1 used
+    if (t + STAGES - 1 < nt) issue(t + STAGES - 1);  // into the stage tile t-1 used
     if (COLSPLIT && !wave_has_cols) continue;
 
-    const int kb = (t % kDecodeStages) * 2 * TILEB;
+    const int kb = (t % STAGES) * 2 * TILEB;
     // ---- S^T: element e of s[rs] = sub-tile row 4 kg + e, query column l16 --------------------
     f32x4 s[RSUB];
 #pragma unroll
@@ -472,16 +471,27 @@ __global__ __launch_bounds__(64) void decode_rows_kernel(DecodeArgs a) {
 int launch_cols(const DecodeArgs& a, bool pieces) { return pieces ? a.n_cols : a.cols; }
 int launch_heads(const DecodeArgs& a, bool pieces) { return pieces ? a.n_g : a.Hkv; }
 
+template <int DP, bool COLSPLIT, bool EXACT, bool PIECES, int STAGES>
+hipError_t launch_stream_stages(const DecodeArgs& a, dim3 grid, hipStream_t s) {
+  static std::atomic<uint64_t> attr_done{0};
+  constexpr int smem = decode_smem_bytes<DP, STAGES>();
+  const auto kernel = &decode_stream_kernel<DP, COLSPLIT, EXACT, PIECES, STAGES>;
+  hipError_t e0 = set_max_dynamic_lds_once(attr_done, reinterpret_cast<const void*>(kernel), smem);
+  if (e0 != hipSuccess) return e0;
+  hipLaunchKernelGGL(kernel, grid, dim3(COLSPLIT ? 512 : 256), smem, s, a);
+  return hipGetLastError();
+}
+
 template <int DP, bool COLSPLIT, bool EXACT, bool PIECES = false>
 hipError_t launch_stream_mode(const DecodeArgs& a, int n_z, hipStream_t s) {
-  static std::atomic<uint64_t> attr_done{0};
-  const auto kernel = &decode_stream_kernel<DP, COLSPLIT, EXACT, PIECES>;
-  hipError_t e0 = set_max_dynamic_lds_once(attr_done, reinterpret_cast<const void*>(kernel), decode_smem_bytes<DP>());
-  if (e0 != hipSuccess) return e0;
   const int qcols = COLSPLIT ? 64 : 16;
   dim3 grid((unsigned)(a.n_chunks * launch_heads(a, PIECES)), (unsigned)((launch_cols(a, PIECES) + qcols - 1) / qcols), (unsigned)n_z);
-  hipLaunchKernelGGL(kernel, grid, dim3(COLSPLIT ? 512 : 256), decode_smem_bytes<DP>(), s, a);
-  return hipGetLastError();
+  // More than one workgroup per CU: a third stage would keep the second one off the CU until the first has ended, and with
+  // two resident one streams while the other starts or merges (6 blocks of 16 x 1152 rows, 32/8 heads, in one
+  // launch: 92 us with three stages, 84 with two).
+  if constexpr (DP == 128)
+    if ((int64_t)grid.x * grid.y * grid.z > a.n_cus) return launch_stream_stages<DP, COLSPLIT, EXACT, PIECES, 2>(a, grid, s);
+  return launch_stream_stages<DP, COLSPLIT, EXACT, PIECES, decode_stages<DP>()>(a, grid, s);
 }
 
 // D: 64 or 128

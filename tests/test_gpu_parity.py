@@ -727,6 +727,37 @@ def test_decode_blocks_equals_per_block_calls():
         check(host(out[b]), ref, BF16, "decode_blocks block %d" % b)
 
 
+@pytest.mark.parametrize("N,Hq,Hkv,D,n_lens,H", [(4, 8, 2, 128, 90, 2),      # local and sync blocks, each kind in one launch
+                                                 (16, 32, 8, 128, 300, 4),   # partials of one sync block fill the workspace
+                                                 (5, 16, 8, 128, 1500, 1),   # more workgroups than CUs: two ring stages
+                                                 (3, 4, 2, 64, 130, 3), (3, 4, 2, 96, 130, 2)])
+def test_decode_blocks_share_launches(N, Hq, Hkv, D, n_lens, H):
+    """Blocks whose memory is apart share launches inside a workspace of the size for one; bit-equal to a call per block,
+    and nothing is written behind the workspace.  With out of block b as query of block b + 1 they run in block order."""
+    M, cap = 6, n_lens + 40
+    seg = (np.arange(N + 1) * cap).astype(np.int32)
+    lens = np.array([max(0, n_lens - 29 * n) for n in range(N)], dtype=np.int32)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(23)
+    x = torch.randn(M + 1, N, Hq, D, generator=g, device="cuda", dtype=BF16)
+    k, v = (torch.randn(M, N * cap, Hkv, D, generator=g, device="cuda", dtype=BF16) for _ in range(2))
+    p = fa.make_params(N, Hq, Hkv, D, H, BF16)
+    need = fa.fedattn_workspace_bytes(p, fa.FEDATTN_OP_DECODE, N * cap)
+    buf = torch.full((need + 4096,), 0xFF, dtype=torch.uint8, device="cuda")
+    for chained in (False, True):
+        say("decode_blocks N=%d D=%d, %s" % (N, D, "chained" if chained else "apart"))
+        ref, here = x.clone(), x.clone()
+        outs = [(t[1:] if chained else torch.full_like(t[1:], float("nan"))) for t in (ref, here)]
+        for b in range(M):
+            fa.fedattn_decode(p, b, ref[b], k[b], v[b], outs[0][b], seg, lens, workspace=buf[:need])
+        torch.cuda.synchronize()
+        buf.fill_(0xFF)
+        fa.fedattn_decode_blocks(p, 0, M, here[:M], k, v, outs[1], x[0].numel(), k[0].numel(), seg, lens, workspace=buf[:need])
+        torch.cuda.synchronize()
+        assert torch.equal(outs[0], outs[1])
+        assert int(buf[need:].min()) == 0xFF
+
+
 @pytest.mark.parametrize("lens", [[200, 150, 1, 77], [130, 0, 64, 200]])
 def test_decode_blocks_fused_equals_decode_blocks(lens):
     """Blocks of one kind sharing launches (every block in flight in its own workspace slice):
