@@ -139,17 +139,14 @@ inline PrefillLaunch choose_prefill_launch(const PrefillShape& a, bool is_sync) 
 
 // ---- fp32 prefill ----------------------------------------------------------------------------
 // (TFLOP/s measured at 8 x 1000 to 8 x 2000 tokens unless stated):
-//  - kF32KeySplit: keys of a tile shared out among the 4 wavefronts of one 32-row query tile and head
-//    (KS = 4 of the kernel): four times as many workgroups as with KS = 1, and walks four times shorter
-//    (8/2 heads of 128, sync: 112 against 91);
-//  - kF32Shared, at least 6 workgroups per CU even with KS = 1: the wavefronts take different heads, each K and V
-//    tile is staged once for all of them (32/8 heads of 128, sync: 137 against 119; at 4 workgroups per
-//    CU still 4 % faster in a sync block, but 8 % slower in a local one);
-//  - kF32Narrow, fewer than 2 workgroups per CU with KS = 4: 16-row query tiles, twice as many workgroups
-//    (4 x 448 tokens, 8/2 heads: 80 against 63).  If even those are all resident at once, the short
-//    half is dispatched shortest first, so that workgroups that come to share a CU carry about the
-//    same load together (1000 tokens, 8 heads: 59 against 51; with more workgroups than fit, longest
-//    first is better: 80 against 73).
+//  - kF32Shared, at least 6 workgroups per CU: the wavefronts take different heads, each K and V
+//    tile is staged once for all of them (32/8 heads of 128, sync: 137; with the keys shared out among the wavefronts 119, 4 % slower
+//    in a sync block already at 4 workgroups per CU, but 8 % faster in a local one);
+//  - kF32KeySplit: the keys shared out among the 4 wavefronts of 16 query rows of one head, more workgroups and walks four
+//    times shorter (8/2 heads of 128, sync: 112 against 91); kF32Narrow: the same kernel, where 32-row tiles would make fewer
+//    than 2 workgroups per CU.  If all workgroups are resident at once, the short half is dispatched shortest first, so that workgroups
+//    that come to share a CU carry about the same load together (1000 tokens, 8 heads: 59 against 51; with
+//    more workgroups than fit, longest first is better: 80 against 73).
 enum F32Launch { kF32Shared, kF32KeySplit, kF32Narrow };
 // Query heads of a KV group that a workgroup of 4 wavefronts takes.
 inline int heads_in_common(int group) { return group % 4 == 0 ? 4 : (group % 2 == 0 ? 2 : 1); }

@@ -9,8 +9,13 @@
 // Bound by the fp32 matrix rate (256 FLOP per cycle and CU, 157 TFLOP/s; a library fp32 GEMM reaches
 // 154 here): a 64-key tile costs a CU 16 000 cycles of matrix work against 64 KB of tile loads, so one
 // stage of K and one of V suffice and two 4-wavefront workgroups per CU cover each other's softmax.
-// 4 participants of 100..900 tokens, 8/2 heads of 128, a local and a sync block: 2057 us on the
-// wavefront-per-row kernel, 120 us here; 8 x 2000 tokens, 32/8 heads, sync: 137 TFLOP/s.
+// 8 x 2000 tokens, 32/8 heads, sync: 137 TFLOP/s.
+// This kernel takes blocks that fill the chip with workgroups whose wavefronts share K and V tiles (KS = 1), and, with
+// KS = 4, head dimensions above 128; the others run prefill_f32_keys_kernel below.
+#include <type_traits>
+
+#include <type_traits>
+
 #include "common.h"
 #include "mfma_tile.h"
 #include "prefill_walk.h"
@@ -19,6 +24,12 @@
 namespace fedattn {
 
 namespace {
+
+// Waits that also keep the compiler from moving memory accesses across them.
+template <int N>
+__device__ inline void wait_loads() {
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
 
 // DP: head dimension padded to the instantiated size (Q is zero there, K and V re-read a valid
 //     chunk, so a padded product is 0 * finite).
@@ -300,6 +311,303 @@ __global__ __launch_bounds__(256, DP > 128 ? 1 : 2) void prefill_f32_kernel(Pref
     redo_prefill_rows<float, 1>(row0, odd, head, [&](int d) { return KS == 1 || (d >> 4) % KS == ks; });
 }
 
+// Tiles whose keys the 4 wavefronts share out (head dimensions up to 128): 16 query rows of one head; wavefront w walks the 16-key
+// slices w, w + 4, ...  No K or V element is used by two wavefronts: V comes straight into the registers that feed the
+// MFMAs, K, whose operand layout would take 16 bytes from each of 16 rows per quarter of a load, passes through LDS buffers that
+// are the wavefront's own, so no barrier stands in the walk.  K of the next slice is in flight while one is worked on.
+// V arrives in 16-byte pieces: lane l16 holds elements 64 c + 4 l16 + j of a row (and 64 C4 + 2 l16 + j of the last 32 where the
+// padded head dimension is an odd multiple of 32), so O^T tile (c, j) has element 64 c + 4 i + j as its row i.
+//
+// Bound by the SIMDs: next to an fp32 MFMA the vector ALU runs, for the same wavefront, hardly at all (a loop of one MFMA and n v_fma_f32
+// takes 32 + 5.3 n cycles) and for two that share a SIMD about half the time.  So what counts beside the 64 MFMAs of a slice is the
+// number of vector instructions: 130 with the loads' addresses worked out per slice, about 40 with those of full slices kept.
+// Bidirectional, 1024 tokens, 8 heads of 128 (2 workgroups per CU), us: keys of a 64-row tile staged for all four wavefronts,
+// as in prefill_f32_kernel, 47.2; K and V into registers 48.1 (K's loads at a quarter of their rate); K through LDS 45.7; addresses kept 41.8.
+// Wavefronts that share a SIMD get different priorities: with equal ones they reach their softmax together and neither covers the other's
+// (4 participants of 100..900 tokens, 8/2 heads of 128, a local and a sync block: 117.7 -> 110.3 us; all of the above 120 -> 104).
+// Two query sub-tiles per wavefront (32 rows per workgroup): 2 to 17 % slower in ten layouts of 1 x 1024 to 8 x 1000 tokens but one,
+// bidirectional with 16 heads, 4 % faster.
+template <int DP>
+__global__ __launch_bounds__(256, 2) void prefill_f32_keys_kernel(PrefillArgs a) {
+  constexpr int DS = DP / 16;              // 16-wide slices of the head dimension
+  constexpr int C4 = DP / 64, C2 = DP % 64 / 32;
+  constexpr int CH = DP / 4;               // 16-byte chunks per row
+  constexpr int ROWB = DP * 4, SLICEB = 16 * ROWB;
+  constexpr int UNIT = 4 * 17;             // 16-byte pieces of a merge unit: 4 groups of 16 lanes, padded (conflict-free by rows and by pieces)
+  extern __shared__ __attribute__((aligned(1024))) unsigned char keys_lds[];   // [wave][2] K slices, in the end [wave][DS] merge units
+  __shared__ float ml_s[4][2][16];
+  __shared__ uint32_t odd_s;               // rows that came out not finite
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, kg = lane >> 4;
+  const lds_cptr lds0 = (lds_cptr)(lds_void_ptr)(keys_lds + wave * 2 * SLICEB);
+  const uint32_t lds_base = lds_addr_of(keys_lds) + wave * 2 * SLICEB;
+
+  const int Hq = a.Hq, Hkv = a.Hkv, D = a.D;
+  const int G = Hq / Hkv;
+  const int N = a.seg.n, T = a.n_q_tiles;
+  const SegTab seg_tab = load_seg_tab(a.seg.seg_off, lane, N);
+  const SegTab tile_tab = load_seg_tab(a.seg.tile_cum, lane, N);
+  const SegTab order_tab = load_seg_tab(a.seg.pair_cum, lane, N);
+  const int order_lo = a.seg_order[lane], order_hi = a.seg_order[lane + 64];
+
+  // workgroup -> (KV head, head of its group, query tile), in the order of prefill_f32_kernel
+  const int g = blockIdx.x % Hkv;
+  const int rest = blockIdx.x / Hkv;
+  const int head = g * G + rest % G;
+  const int p = rest / G;
+  const int block = blockIdx.y;
+  const bool is_sync = a.sync_override >= 0 ? (a.sync_override != 0)
+                                            : sync_block_rule(a.sync_interval, a.block_idx0 + block);
+  const bool causal = a.causal != 0;
+  const bool sparse = is_sync && a.keep_chunks != nullptr;
+  const int rank = a.short_half_ascending && p >= (T + 1) / 2 ? T - 1 - (p - (T + 1) / 2) : p;  // 0: longest walk
+  int tile;
+  if (is_sync) {
+    tile = T - 1 - rank;
+  } else {
+    const int s = seg_tab_find(order_tab, rank, N);
+    const int n = s < 64 ? __builtin_amdgcn_readlane(order_lo, s) : __builtin_amdgcn_readlane(order_hi, s - 64);
+    tile = seg_tab_at(tile_tab, n + 1) - 1 - (rank - seg_tab_at(order_tab, s));
+  }
+  const KvWalk w = make_kv_walk(a, seg_tab, tile_tab, tile, is_sync, sparse);
+  const int row0 = w.q0;
+
+  const float* qp = reinterpret_cast<const float*>(a.q) + (int64_t)block * a.q_block_stride;
+  const float* kp = reinterpret_cast<const float*>(a.k) + (int64_t)block * a.kv_block_stride + g * D;
+  const float* vp = reinterpret_cast<const float*>(a.v) + (int64_t)block * a.kv_block_stride + g * D;
+  const float* kp_list = reinterpret_cast<const float*>(a.k_list) + g * D;
+  const float* vp_list = reinterpret_cast<const float*>(a.v_list) + g * D;
+  float* op = reinterpret_cast<float*>(a.out) + (int64_t)block * a.q_block_stride;
+  const int row_elems = Hkv * D;
+
+  // 16-key slices of the walk: four per listed 64-row tile (the last ones may be empty), then the dense range
+  const int n_list = 4 * w.n_list;
+  const int ns = n_list + (w.dhi - w.dlo + 15) / 16;
+  struct Slice {
+    const float *k, *v;    // first row to load
+    int kv0, len, load_len;
+    bool causal_slice;
+  };
+  auto slice_at = [&](int i) __attribute__((always_inline)) {
+    Slice t;
+    int first;
+    if (i < n_list) {
+      const int i4 = i >> 2, off = 16 * (i & 3);
+      const int2 e = a.kept_tiles[i4 < w.la_n ? i4 : w.lb0 + (i4 - w.la_n)];
+      const int lo = __builtin_amdgcn_readfirstlane(e.x), left = __builtin_amdgcn_readfirstlane(e.y) - off;
+      t.kv0 = lo + off;
+      t.len = min(max(left, 0), 16);
+      first = left > 0 ? t.kv0 : lo;       // an empty slice loads the tile's first row, unseen
+      t.load_len = max(t.len, 1);
+      t.causal_slice = false;
+    } else {
+      t.kv0 = first = w.dlo + 16 * (i - n_list);
+      t.len = t.load_len = min(w.dhi - t.kv0, 16);
+      t.causal_slice = causal;
+    }
+    t.k = (i < n_list ? kp_list : kp) + (int64_t)first * row_elems;
+    t.v = (i < n_list ? vp_list : vp) + (int64_t)first * row_elems;
+    return t;
+  };
+
+  // Rows of K and V are D <= DP long: pieces past the end re-read the last one (K meets a zero of Q there, V makes
+  // outputs that are not stored).
+  // Offsets of a full slice are worked out once: next to fp32 MFMAs every vector instruction counts (above).
+  // K slice -> this wavefront's LDS buffer; slot (row, cp) receives chunk cp ^ (row mod 8)
+  constexpr int KINST = SLICEB / 1024;
+  auto k_slot = [&](int i, int rows) __attribute__((always_inline)) {
+    const int row = (i * 64 + lane) / CH, chunk = min(((i * 64 + lane) % CH) ^ (row & 7), D / 4 - 1);
+    return (uint32_t)(min(row, rows - 1) * row_elems + chunk * 4) * 4u;
+  };
+  // piece c of V row 4 kg + e; c = C4: the last 32 elements
+  auto v_slot = [&](int e, int c, int rows) __attribute__((always_inline)) {
+    return (uint32_t)(min(4 * kg + e, rows - 1) * row_elems + (c < C4 ? min(64 * c + 4 * l16, D - 4) : min(64 * C4 + 2 * l16, D - 2))) * 4u;
+  };
+  uint32_t k_full[KINST], v_full[4][C4 + C2];
+#pragma unroll
+  for (int i = 0; i < KINST; ++i) k_full[i] = k_slot(i, 16);
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+#pragma unroll
+    for (int c = 0; c < C4 + C2; ++c) v_full[e][c] = v_slot(e, c, 16);
+  auto fetch_k = [&](const Slice& t, int b) __attribute__((always_inline)) {
+    if (t.load_len == 16) {
+#pragma unroll
+      for (int i = 0; i < KINST; ++i) lds_dma_16(t.k, k_full[i], lds_base + b * SLICEB + i * 1024);
+    } else {
+#pragma unroll
+      for (int i = 0; i < KINST; ++i) lds_dma_16(t.k, k_slot(i, t.load_len), lds_base + b * SLICEB + i * 1024);
+    }
+  };
+  f32x4 v4[4][C4 == 0 ? 1 : C4];
+  f32x2 v2[4];
+  auto load_v = [&](const Slice& t) __attribute__((always_inline)) {
+    const char* base = reinterpret_cast<const char*>(t.v);
+    uint32_t at[4][C4 + C2];
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int c = 0; c < C4 + C2; ++c) at[e][c] = v_full[e][c];
+    if (t.load_len < 16) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int c = 0; c < C4 + C2; ++c) at[e][c] = v_slot(e, c, t.load_len);
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+#pragma unroll
+      for (int c = 0; c < C4; ++c) v4[e][c] = *reinterpret_cast<const f32x4*>(base + at[e][c]);
+      if constexpr (C2 != 0) v2[e] = *reinterpret_cast<const f32x2*>(base + at[e][C4]);
+    }
+  };
+  constexpr int VLOADS = 4 * (C4 + C2);
+  int k_off[DS];   // LDS -> A operand of S^T: chunk 4 st + kg of row l16
+#pragma unroll
+  for (int st = 0; st < DS; ++st) k_off[st] = l16 * ROWB + (((4 * st + kg) ^ (l16 & 7)) << 4);
+
+  // Q (B operand of S^T): lane (query l16, kg) holds Q[query][16 s + 4 kg .. +4]
+  f32x4 q[DS];
+  const float* qrow = qp + ((int64_t)min(row0 + l16, w.seg_hi - 1) * Hq + head) * D;
+#pragma unroll
+  for (int s = 0; s < DS; ++s) {
+    const int d = 16 * s + 4 * kg;
+    q[s] = *reinterpret_cast<const f32x4*>(qrow + (s < DS - 2 ? d : min(d, D - 4)));
+  }
+  Slice cur = slice_at(min(wave, ns - 1));
+  fetch_k(cur, 0);
+
+  f32x4 o[DS];
+  float m_run = -INFINITY, l_run = 0.f;
+#pragma unroll
+  for (int dt = 0; dt < DS; ++dt) o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const float sc = a.scale * kLog2e;
+#pragma unroll
+  for (int s = DS - 2; s < DS; ++s)
+    if (16 * s + 4 * kg >= D) q[s] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  // One slice, in K buffer b.  K of the next slice and V of this one are requested first; V, the younger of the two, is
+  // waited for behind the softmax, and K of this slice, which is older than both, here.
+  auto step = [&](auto more, auto buffer, const Slice& cur, const Slice& nxt) __attribute__((always_inline)) {
+    constexpr bool MORE = decltype(more)::value;
+    constexpr int b = decltype(buffer)::value;
+    if constexpr (MORE) fetch_k(nxt, b ^ 1);
+    load_v(cur);
+    wait_loads<(MORE ? KINST : 0) + VLOADS>();
+    f32x4 kf[DS];
+#pragma unroll
+    for (int st = 0; st < DS; ++st)
+      kf[st] = *reinterpret_cast<const __attribute__((address_space(3))) f32x4*>(lds0 + (k_off[st] + b * SLICEB));
+    f32x4 s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int st = 0; st < DS; ++st)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[st][e], q[st][e], s, 0, 0, 0);
+    if (cur.len < 16 || (cur.causal_slice && cur.kv0 + 15 > row0)) {
+      int lim = cur.len;
+      if (cur.causal_slice) lim = min(lim, row0 + l16 - cur.kv0 + 1);
+      lim -= 4 * kg;
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (e >= lim) s[e] = -INFINITY;
+    }
+    const float m_cand = max_over_kgroups(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]))) * sc;
+    if (__builtin_amdgcn_ballot_w64(m_cand > m_run + kRescaleThreshold) != 0) {
+      const float m_new = fmaxf(m_run, m_cand);
+      const float alpha = __builtin_amdgcn_exp2f(m_run - ((m_new == -INFINITY) ? 0.f : m_new));
+      m_run = m_new;
+      l_run *= alpha;
+#pragma unroll
+      for (int dt = 0; dt < DS; ++dt) o[dt] *= alpha;
+    }
+    const float m_use = (m_run == -INFINITY) ? 0.f : m_run;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) s[e] = __builtin_amdgcn_exp2f(fmaf(s[e], sc, -m_use));
+    l_run += (s[0] + s[1]) + (s[2] + s[3]);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+#pragma unroll
+      for (int c = 0; c < C4; ++c)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) o[4 * c + j] = __builtin_amdgcn_mfma_f32_16x16x4f32(v4[e][c][j], s[e], o[4 * c + j], 0, 0, 0);
+      if constexpr (C2 != 0)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) o[4 * C4 + j] = __builtin_amdgcn_mfma_f32_16x16x4f32(v2[e][j], s[e], o[4 * C4 + j], 0, 0, 0);
+    }
+  };
+  priority_by_slot();
+  using std::true_type;
+  using B0 = std::integral_constant<int, 0>;
+  using B1 = std::integral_constant<int, 1>;
+  if (wave < ns) {
+    int i = wave + 4;
+    for (; i + 4 < ns; i += 8) {
+      const Slice n1 = slice_at(i), n2 = slice_at(i + 4);
+      step(true_type{}, B0{}, cur, n1);
+      step(true_type{}, B1{}, n1, n2);
+      cur = n2;
+    }
+    if (i < ns) {
+      const Slice n1 = slice_at(i);
+      step(true_type{}, B0{}, cur, n1);
+      step(std::false_type{}, B1{}, n1, n1);
+    } else {
+      step(std::false_type{}, B0{}, cur, cur);
+    }
+  }
+  wait_loads<0>();
+  lds_barrier();   // the merge reuses the K buffers
+
+  // ---- merge: unit u of a wavefront holds, at piece 17 kg + l16, the four elements from d = 64 (u / 4) + 16 kg + 4 (u mod 4)
+  // on (last 32: 64 C4 + 8 kg + 4 (u mod 4)) of row l16; then every thread takes whole pieces of output rows ----------------------
+  f32x4* const units = reinterpret_cast<f32x4*>(keys_lds);
+  if (tid == 0) odd_s = 0;
+  const float l = sum_over_kgroups(l_run);
+  if (kg == 0) {
+    ml_s[wave][0][l16] = m_run;
+    ml_s[wave][1][l16] = l;
+  }
+  f32x4* const xo = units + wave * DS * UNIT + 17 * kg + l16;
+#pragma unroll
+  for (int c = 0; c < C4; ++c)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) xo[(4 * c + r) * UNIT] = f32x4{o[4 * c][r], o[4 * c + 1][r], o[4 * c + 2][r], o[4 * c + 3][r]};
+  if constexpr (C2 != 0)
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+      xo[(4 * C4 + r) * UNIT] = f32x4{o[4 * C4][2 * r], o[4 * C4 + 1][2 * r], o[4 * C4][2 * r + 1], o[4 * C4 + 1][2 * r + 1]};
+  lds_barrier();
+  const int D4 = D / 4;
+  for (int idx = tid; idx < 16 * D4; idx += 256) {
+    const int r = idx / D4, d4 = idx - r * D4;
+    const bool tail = C2 != 0 && d4 >= 16 * C4;
+    const int u = 4 * (d4 >> 4) + (tail ? d4 & 1 : d4 & 3), k = tail ? (d4 & 15) >> 1 : (d4 & 15) >> 2;
+    float mm = -INFINITY, den = 0.f;
+#pragma unroll
+    for (int x = 0; x < 4; ++x) mm = fmaxf(mm, ml_s[x][0][r]);
+    const float mu = (mm == -INFINITY) ? 0.f : mm;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+      const float f = __builtin_amdgcn_exp2f(ml_s[x][0][r] - mu);
+      den = fmaf(ml_s[x][1][r], f, den);
+      acc += units[(x * DS + u) * UNIT + 17 * k + r] * f;
+    }
+    acc *= den > 0.f ? 1.f / den : 0.f;
+    if (row0 + r < w.seg_hi) {
+      __builtin_nontemporal_store(acc, reinterpret_cast<f32x4*>(op + ((int64_t)(row0 + r) * Hq + head) * D + 4 * d4));
+      FiniteCheck fin;
+      fin.add4(acc);
+      if (fin.failed()) atomicOr(&odd_s, 1u << r);
+    }
+  }
+  lds_barrier();
+  const uint32_t odd = __builtin_amdgcn_readfirstlane(odd_s);
+  if (__builtin_expect(odd != 0, 0)) redo_prefill_rows<float, 4>(row0, odd, head, [](int) { return true; });
+}
+
 template <int DP, int NQ, int KS>
 hipError_t launch_prefill_f32_t(const PrefillArgs& a, int n_blocks, hipStream_t s) {
   constexpr int smem = 2 * kKvTile * DP * 4;
@@ -312,17 +620,30 @@ hipError_t launch_prefill_f32_t(const PrefillArgs& a, int n_blocks, hipStream_t 
 }
 
 template <int DP>
+hipError_t launch_prefill_f32_keys(const PrefillArgs& a, int n_blocks, hipStream_t s) {
+  constexpr int merge = 4 * (DP / 16) * 4 * 17 * 16, keys = 4 * 2 * 16 * DP * 4;
+  constexpr int smem = merge > keys ? merge : keys;
+  static std::atomic<uint64_t> attr_done{0};
+  hipError_t e = set_max_dynamic_lds_once(attr_done, reinterpret_cast<const void*>(&prefill_f32_keys_kernel<DP>), smem);
+  if (e != hipSuccess) return e;
+  dim3 grid((unsigned)(a.n_q_tiles * a.Hq), (unsigned)n_blocks);
+  hipLaunchKernelGGL(prefill_f32_keys_kernel<DP>, grid, dim3(256), smem, s, a);
+  return hipGetLastError();
+}
+
+template <int DP>
 hipError_t launch_prefill_f32_d(PrefillArgs& a, int n_blocks, hipStream_t s) {
   constexpr int NQ = DP > 128 ? 1 : 2;
-  const F32Launch plan = choose_f32_launch(a.seg.seg_off, a.seg.n, a.Hq, a.Hkv, a.D, n_blocks, a.n_cus);
-  a.heads_per_wg = plan == kF32Shared ? heads_in_common(a.Hq / a.Hkv) : 1;
-  lay_out_query_tiles(a, plan == kF32Narrow ? 16 : 16 * NQ * (4 / (plan == kF32Shared ? a.heads_per_wg : 4)));
+  const bool shared = choose_f32_launch(a.seg.seg_off, a.seg.n, a.Hq, a.Hkv, a.D, n_blocks, a.n_cus) == kF32Shared;
+  a.heads_per_wg = shared ? heads_in_common(a.Hq / a.Hkv) : 1;
+  lay_out_query_tiles(a, shared ? 16 * NQ * (4 / a.heads_per_wg) : 16);
   const int64_t wgs = (int64_t)a.n_q_tiles * a.Hkv * (a.Hq / a.Hkv / a.heads_per_wg) * n_blocks;
   if (wgs / n_blocks > 0x7fffffffLL) return hipErrorInvalidValue;
   a.short_half_ascending = wgs <= 2 * (int64_t)a.n_cus ? 1 : 0;
   order_segments_by_length(a);
-  if (plan == kF32Shared) return launch_prefill_f32_t<DP, NQ, 1>(a, n_blocks, s);
-  return plan == kF32Narrow ? launch_prefill_f32_t<DP, 1, 4>(a, n_blocks, s) : launch_prefill_f32_t<DP, NQ, 4>(a, n_blocks, s);
+  if (shared) return launch_prefill_f32_t<DP, NQ, 1>(a, n_blocks, s);
+  if constexpr (DP <= 128) return launch_prefill_f32_keys<DP>(a, n_blocks, s);
+  else return launch_prefill_f32_t<DP, 1, 4>(a, n_blocks, s);
 }
 
 }  // namespace

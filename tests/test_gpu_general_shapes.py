@@ -37,6 +37,19 @@ def test_f32_prefill(layout, D):
         check(got[rows, heads], ref, F32, what)
 
 
+@pytest.mark.parametrize("D", [8, 24, 32, 56, 64, 96, 104, 128])
+def test_f32_prefill_ends_of_key_slices(D):
+    """Walks that end on, before and behind a 16-key slice and leave one to four wavefronts without one, every row checked."""
+    lens, Hq, Hkv = [1, 15, 16, 17, 0, 31, 33, 48, 63, 64, 65, 80, 129], 3, 1
+    seg = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    q, k, v = rand_block(44, int(seg[-1]), Hq, Hkv, D, bf16=False)
+    for sync, causal in [(0, True), (1, True), (0, False), (1, False)]:
+        what = "f32 slice ends D=%d sync=%d causal=%d" % (D, sync, causal)
+        say(what)
+        got = prefill(q, k, v, seg, Hq=Hq, Hkv=Hkv, D=D, H=0, block=0, dtype=F32, causal=causal, sync_override=sync)
+        check(got, oracle.attend_block(q, k, v, seg, is_sync=bool(sync), causal=causal), F32, what)
+
+
 # one head per workgroup with split keys, on short and long walks (head dimensions beyond 128: 4-wave workgroups, in an
 # order if causal); 4-wave workgroups, one tile each, heaviest first (the other launches: test_bf16_prefill_every_launch)
 BF16_LAYOUTS = {"short": ([70, 0, 63, 1, 258], 4, 1), "long": ([1100, 0, 1003], 6, 3), "four": ([3101, 2, 3137], 32, 8)}
