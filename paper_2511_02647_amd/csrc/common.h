@@ -47,21 +47,28 @@ struct PrefillArgs {
   int32_t sync_interval;
   int32_t sync_override;    // -1 rule, 0 local, 1 sync
   int32_t causal;
-  int32_t heads_per_wg;     // MFMA kernel: query heads of one KV group handled by one workgroup
+  int32_t heads_per_wg;     // query heads of one KV group handled by one workgroup: 1, 2 or 4
+  int32_t group;            // Hq / Hkv
+  int32_t head_sets;        // workgroups per query tile and KV head: group / heads_per_wg
+  int32_t kv_shift, set_shift;   // log2 of Hkv and head_sets, -1 where they are not powers of two
   int32_t q_tile_rows;      // MFMA kernel: query rows per workgroup
   int32_t n_q_tiles;
   int32_t n_cus;            // compute units of the device (launch shape heuristics)
   float scale;              // softmax scale
-  int32_t n_ordered;        // > 0: one workgroup per query tile, workgroup p takes tile_order[p] (MFMA kernel)
+  int32_t n_listed;         // > 0: the host has listed the query tiles of the workgroups (tile_list); else they are worked out
+  int32_t listed_pairs;     // MFMA kernel: workgroup p takes the tiles 2 p and 2 p + 1 of the list, else tile p
+  int32_t late_from;        // MFMA kernel: listed workgroups from here on start a little later
   int32_t warm_kv;          // MFMA kernel: every workgroup pulls the K, V rows of its own query rows into L2 first
   int32_t one_tile_heavy_first;  // MFMA kernel, causal launch of several rounds of workgroups: one query tile per
                                  // workgroup, heaviest first (seg.pair_cum then counts tiles in seg_order's order)
-  int32_t short_half_ascending;  // fp32 kernel: workgroups of the shorter half of the walks in ascending order
+  int32_t short_half_ascending;  // split and fp32 kernels: workgroups of the shorter half of the walks in ascending order
   SegLayout seg;
-  uint16_t tile_order[kMaxOrderedTiles];
+  uint32_t tile_list[kMaxListedTiles / 2];   // two entries each: segment | tile inside the segment << 7; kNoTile: none
   uint8_t seg_order[kMaxP];      // participants by decreasing length (local blocks of a heavy-first launch)
 };
 
+constexpr uint32_t kNoTile = 0xffff;
+static_assert(kMaxP <= 128 && kMaxListedTiles <= 512, "a list entry has 7 bits for the segment and 9 for its tile");
 static_assert(sizeof(PrefillArgs) <= 4096, "kernel arguments are limited to 4 KB");
 
 struct DecodeArgs {
@@ -140,6 +147,46 @@ inline void order_segments_by_length(PrefillArgs& a) {
     run += a.seg.tile_cum[order[i] + 1] - a.seg.tile_cum[order[i]];
   }
   a.seg.pair_cum[N] = run;
+}
+
+// Host side: what the workgroups' place in a launch is found with (heads_per_wg is final).
+inline int log2_or_none(int x) {
+  int s = 0;
+  while ((1 << s) < x) ++s;
+  return (1 << s) == x ? s : -1;
+}
+inline void lay_out_heads(PrefillArgs& a) {
+  a.group = a.Hq / a.Hkv;
+  a.head_sets = a.group / a.heads_per_wg;
+  a.kv_shift = log2_or_none(a.Hkv);
+  a.set_shift = log2_or_none(a.head_sets);
+}
+
+// Host side: the list of query tiles that the workgroups of a launch of one block take.  A workgroup without a list finds its
+// tile in the segment tables: about 300 instructions, 0.6 us at the start of a launch.  kMaxListedTiles is what fits beside the tables in
+// the argument block; launches with more tiles have several rounds of workgroups, whose starts hide behind one another.
+struct TileList {
+  PrefillArgs& a;
+  explicit TileList(PrefillArgs& args) : a(args) { a.n_listed = 0; }
+  static bool fits(const PrefillArgs& a, int per_wg) { return (int64_t)a.n_q_tiles * per_wg <= kMaxListedTiles; }
+  void put(int i, uint32_t e) {
+    a.tile_list[i >> 1] = (i & 1) ? (a.tile_list[i >> 1] & 0xffffu) | e << 16 : (a.tile_list[i >> 1] & 0xffff0000u) | e;
+  }
+  static uint32_t entry(int n, int t) { return (uint32_t)(n | t << 7); }
+  int tiles(int n) const { return a.seg.tile_cum[n + 1] - a.seg.tile_cum[n]; }
+};
+
+// Longest walks first: sync block from the end of the sequence; local block the participants in seg_order, each from its last tile.
+inline void list_heavy_first(PrefillArgs& a, bool is_sync) {
+  TileList l(a);
+  if (!TileList::fits(a, 1)) return;
+  const int N = a.seg.n, T = a.n_q_tiles, half = a.short_half_ascending ? (T + 1) / 2 : T;
+  int i = 0;
+  for (int x = 0; x < N; ++x) {
+    const int n = is_sync ? N - 1 - x : a.seg_order[x];
+    for (int t = l.tiles(n) - 1; t >= 0; --t, ++i) l.put(i < half ? i : T - 1 - (i - half), TileList::entry(n, t));
+  }
+  a.n_listed = T;
 }
 
 // Host-side launchers (one per kernel family); each returns the hipError_t of the launch.

@@ -9,7 +9,7 @@ namespace fedattn {
 
 constexpr int kKvTile = 64;            // KV rows per tile; also the keep-list tile
 constexpr int kWaveRows = 32;          // query rows per wavefront in the bf16 prefill kernels
-constexpr int kMaxOrderedTiles = 512;  // query tiles of a launch that assigns them through an explicit order
+constexpr int kMaxListedTiles = 512;   // query tiles of a launch whose workgroups find theirs in a list
 constexpr int kCombineAtOnce = 64;     // chunks up to which the decode combine kernel makes one round trip
 constexpr int kMaxSegments = 128;      // participants at most
 
@@ -110,7 +110,7 @@ inline PrefillLaunch choose_prefill_launch(const PrefillShape& a, bool is_sync) 
   const bool causal = a.causal;
   const int per_tile = a.Hkv * (a.Hq / a.Hkv / a.heads_per_wg);
   const QueryTiles q = count_query_tiles(a.seg_off, a.n, a.q_tile_rows);
-  const PrefillLaunch four = causal && q.tiles <= kMaxOrderedTiles && q.tiles * per_tile <= 2 * (int64_t)a.n_cus ? kFourOrdered : kFour;
+  const PrefillLaunch four = causal && q.tiles <= kMaxListedTiles && q.tiles * per_tile <= 2 * (int64_t)a.n_cus ? kFourOrdered : kFour;
   if (a.D > 128) return four;   // the others' tiles do not fit LDS
   const Paces& p = paces(a.D);
   const Walks four_walks = count_walks(a, is_sync, a.q_tile_rows, kKvTile, per_tile);

@@ -57,37 +57,19 @@ __global__ __launch_bounds__(256, DP > 128 ? 1 : 2) void prefill_f32_kernel(Pref
   const uint32_t lds_base = lds_addr_of(kv_lds);
 
   const int Hq = a.Hq, Hkv = a.Hkv, D = a.D;
-  const int G = Hq / Hkv;
-  const int HS = a.heads_per_wg, HG = G / HS;
-  const int N = a.seg.n, T = a.n_q_tiles;
-  const SegTab seg_tab = load_seg_tab(a.seg.seg_off, lane, N);
-  const SegTab tile_tab = load_seg_tab(a.seg.tile_cum, lane, N);
-  const SegTab order_tab = load_seg_tab(a.seg.pair_cum, lane, N);
-  const int order_lo = a.seg_order[lane], order_hi = a.seg_order[lane + 64];
+  const int HS = a.heads_per_wg;
 
-  // workgroup -> (KV head, head subgroup, query tile): KV head fastest, so that the workgroups of
-  // one KV head share an XCD's L2 when there are 8; longest walks first (sync block: from the end
-  // of the sequence; local block: participants by decreasing length, each from its last tile)
-  const int g = blockIdx.x % Hkv;
-  const int rest = blockIdx.x / Hkv;
-  const int hsub = rest % HG;
-  const int p = rest / HG;
+  // longest walks first (sync block: from the end of the sequence; local block: participants by
+  // decreasing length, each from its last tile)
+  const WgPlace wg = find_wg_place(a);
+  const int g = wg.g;
   const int block = blockIdx.y;
   const bool is_sync = a.sync_override >= 0 ? (a.sync_override != 0)
                                             : sync_block_rule(a.sync_interval, a.block_idx0 + block);
   const bool sparse = is_sync && a.keep_chunks != nullptr;
-  const int rank = a.short_half_ascending && p >= (T + 1) / 2 ? T - 1 - (p - (T + 1) / 2) : p;  // 0: longest walk
-  int tile;
-  if (is_sync) {
-    tile = T - 1 - rank;
-  } else {
-    const int s = seg_tab_find(order_tab, rank, N);
-    const int n = s < 64 ? __builtin_amdgcn_readlane(order_lo, s) : __builtin_amdgcn_readlane(order_hi, s - 64);
-    tile = seg_tab_at(tile_tab, n + 1) - 1 - (rank - seg_tab_at(order_tab, s));
-  }
-  const KvWalk w = make_kv_walk(a, seg_tab, tile_tab, tile, is_sync, sparse);
+  const KvWalk w = make_kv_walk(a, place_heavy_first(a, wg.p, is_sync, lane), is_sync, sparse);
   const int row0 = w.q0 + 16 * NQ * (qg / HS);   // this wavefront's first query row
-  const int head = g * G + hsub * HS + qg % HS;
+  const int head = g * a.group + wg.set * HS + qg % HS;
 
   const float* qp = reinterpret_cast<const float*>(a.q) + (int64_t)block * a.q_block_stride;
   const float* kp = reinterpret_cast<const float*>(a.k) + (int64_t)block * a.kv_block_stride + g * D;
@@ -345,33 +327,16 @@ __global__ __launch_bounds__(256, 2) void prefill_f32_keys_kernel(PrefillArgs a)
   const uint32_t lds_base = lds_addr_of(keys_lds) + wave * 2 * SLICEB;
 
   const int Hq = a.Hq, Hkv = a.Hkv, D = a.D;
-  const int G = Hq / Hkv;
-  const int N = a.seg.n, T = a.n_q_tiles;
-  const SegTab seg_tab = load_seg_tab(a.seg.seg_off, lane, N);
-  const SegTab tile_tab = load_seg_tab(a.seg.tile_cum, lane, N);
-  const SegTab order_tab = load_seg_tab(a.seg.pair_cum, lane, N);
-  const int order_lo = a.seg_order[lane], order_hi = a.seg_order[lane + 64];
 
   // workgroup -> (KV head, head of its group, query tile), in the order of prefill_f32_kernel
-  const int g = blockIdx.x % Hkv;
-  const int rest = blockIdx.x / Hkv;
-  const int head = g * G + rest % G;
-  const int p = rest / G;
+  const WgPlace wg = find_wg_place(a);
+  const int g = wg.g, head = g * a.group + wg.set;
   const int block = blockIdx.y;
   const bool is_sync = a.sync_override >= 0 ? (a.sync_override != 0)
                                             : sync_block_rule(a.sync_interval, a.block_idx0 + block);
   const bool causal = a.causal != 0;
   const bool sparse = is_sync && a.keep_chunks != nullptr;
-  const int rank = a.short_half_ascending && p >= (T + 1) / 2 ? T - 1 - (p - (T + 1) / 2) : p;  // 0: longest walk
-  int tile;
-  if (is_sync) {
-    tile = T - 1 - rank;
-  } else {
-    const int s = seg_tab_find(order_tab, rank, N);
-    const int n = s < 64 ? __builtin_amdgcn_readlane(order_lo, s) : __builtin_amdgcn_readlane(order_hi, s - 64);
-    tile = seg_tab_at(tile_tab, n + 1) - 1 - (rank - seg_tab_at(order_tab, s));
-  }
-  const KvWalk w = make_kv_walk(a, seg_tab, tile_tab, tile, is_sync, sparse);
+  const KvWalk w = make_kv_walk(a, place_heavy_first(a, wg.p, is_sync, lane), is_sync, sparse);
   const int row0 = w.q0;
 
   const float* qp = reinterpret_cast<const float*>(a.q) + (int64_t)block * a.q_block_stride;
@@ -640,7 +605,10 @@ hipError_t launch_prefill_f32_d(PrefillArgs& a, int n_blocks, hipStream_t s) {
   const int64_t wgs = (int64_t)a.n_q_tiles * a.Hkv * (a.Hq / a.Hkv / a.heads_per_wg) * n_blocks;
   if (wgs / n_blocks > 0x7fffffffLL) return hipErrorInvalidValue;
   a.short_half_ascending = wgs <= 2 * (int64_t)a.n_cus ? 1 : 0;
+  lay_out_heads(a);
   order_segments_by_length(a);
+  // blocks of one launch may be of both kinds
+  if (n_blocks == 1) list_heavy_first(a, a.sync_override >= 0 ? a.sync_override != 0 : sync_block_rule(a.sync_interval, a.block_idx0));
   if (shared) return launch_prefill_f32_t<DP, NQ, 1>(a, n_blocks, s);
   if constexpr (DP <= 128) return launch_prefill_f32_keys<DP>(a, n_blocks, s);
   else return launch_prefill_f32_t<DP, 1, 4>(a, n_blocks, s);

@@ -73,25 +73,9 @@ __global__ __launch_bounds__(256 * NG, DP > 128 ? 1 : DP > 64 ? 2 : 3) void pref
   const uint32_t lds_base = lds_addr_of(kv_lds) + grp * 4 * TILEB;
 
   const int Hq = a.Hq, Hkv = a.Hkv;
-  const int G = Hq / Hkv;
   const int HS = a.heads_per_wg;
-  const int HG = G / HS;
-  const int N = a.seg.n;
-  const int T = a.n_q_tiles;
-
-  const SegTab seg_tab = load_seg_tab(a.seg.seg_off, lane, N);
-  const SegTab tile_tab = load_seg_tab(a.seg.tile_cum, lane, N);
-  const SegTab pair_tab = load_seg_tab(a.seg.pair_cum, lane, N);
-  const int order_lo = a.seg_order[lane], order_hi = a.seg_order[lane + 64];
-
-  // workgroup -> (kv head, head subgroup, query tile pair); kv head fastest so that the
-  // workgroups of one KV head land on one XCD (8 XCDs, round-robin dispatch) and its
-  // K/V stay in that XCD's L2; heaviest work first.
-  const int id = blockIdx.x;
-  const int g = id % Hkv;
-  const int rest = id / Hkv;
-  const int hsub = rest % HG;
-  const int p = rest / HG;
+  const WgPlace wg = find_wg_place(a);
+  const int g = wg.g, p = wg.p;
   const int block = blockIdx.y;
 
   const bool is_sync = a.sync_override >= 0 ? (a.sync_override != 0)
@@ -102,43 +86,60 @@ __global__ __launch_bounds__(256 * NG, DP > 128 ? 1 : DP > 64 ? 2 : 3) void pref
   // Causal work grows along the sequence (sync block) or along each segment (local
   // block); a workgroup takes one query tile, dispatched in an order that the host lays out or
   // longest walks first, or a heavy tile and then its light mirror image.
-  int tile_a = -1, tile_b = -1;  // heavy tile, then its light partner (or none)
-  if (a.n_ordered > 0) {
-    // small causal launch: one query tile per workgroup, in the order the host laid out
-    if (p >= a.n_ordered) return;
-    tile_a = a.tile_order[p];
-    // the light half waits about a microsecond: its loads then queue behind those of the heavy
-    // half, whose workgroups set the length of the launch (the light ones have time to spare)
-    if (p >= (a.n_ordered + 1) / 2) __builtin_amdgcn_s_sleep(32);
-  } else if (!causal) {
-    if (p >= T) return;
-    tile_a = T - 1 - p;
-  } else if (a.one_tile_heavy_first) {
-    // One tile per workgroup, dispatched heaviest first: in a launch of several rounds of workgroups
-    // the short walks at the end of the list fill the gaps that equal-sized pairs would leave in
-    // the last round, in a launch of one round each walk is half a pair's.  Sync block: work
-    // grows with the position in the sequence.  Local block: the participants in order of
-    // decreasing length, each one's tiles from its last to its first.
-    if (p >= T) return;
-    if (is_sync) {
-      tile_a = T - 1 - p;
+  TilePlace place_a, place_b;  // heavy tile, then its light partner
+  bool two = false;            // there is one
+  if (a.n_listed > 0) {
+    if (a.listed_pairs) {
+      place_a = place_listed(a, list_entry(a, 2 * p));
+      const uint32_t e = list_entry(a, 2 * p + 1);
+      two = e != kNoTile;
+      place_b = place_listed(a, two ? e : 0);
     } else {
-      const int s = seg_tab_find(pair_tab, p, N);   // position in the length order
-      const int pi = p - seg_tab_at(pair_tab, s);
-      const int n = s < 64 ? __builtin_amdgcn_readlane(order_lo, s) : __builtin_amdgcn_readlane(order_hi, s - 64);
-      tile_a = seg_tab_at(tile_tab, n + 1) - 1 - pi;
+      place_a = place_b = place_listed(a, list_entry(a, p));
     }
-  } else if (is_sync) {
-    if (p >= (T + 1) / 2) return;
-    tile_a = T - 1 - p;
-    if (p < T - 1 - p) tile_b = p;
+    // small causal launch: the light half waits about a microsecond: its loads then queue behind those of the heavy
+    // half, whose workgroups set the length of the launch (the light ones have time to spare)
+    if (p >= a.late_from) __builtin_amdgcn_s_sleep(32);
   } else {
-    if (p >= seg_tab_at(pair_tab, N)) return;
-    const int n = seg_tab_find(pair_tab, p, N);
-    const int pi = p - seg_tab_at(pair_tab, n);
-    const int t0 = seg_tab_at(tile_tab, n), tn = seg_tab_at(tile_tab, n + 1) - t0;
-    tile_a = t0 + tn - 1 - pi;
-    if (pi < tn - 1 - pi) tile_b = t0 + pi;
+    const int N = a.seg.n, T = a.n_q_tiles;
+    const SegTab seg_tab = load_seg_tab(a.seg.seg_off, lane, N);
+    const SegTab tile_tab = load_seg_tab(a.seg.tile_cum, lane, N);
+    const SegTab pair_tab = load_seg_tab(a.seg.pair_cum, lane, N);
+    int tile_a, tile_b = -1;
+    if (!causal) {
+      if (p >= T) return;
+      tile_a = T - 1 - p;
+    } else if (a.one_tile_heavy_first) {
+      // One tile per workgroup, dispatched heaviest first: in a launch of several rounds of workgroups
+      // the short walks at the end of the list fill the gaps that equal-sized pairs would leave in
+      // the last round, in a launch of one round each walk is half a pair's.  Sync block: work
+      // grows with the position in the sequence.  Local block: the participants in order of
+      // decreasing length, each one's tiles from its last to its first.
+      if (p >= T) return;
+      if (is_sync) {
+        tile_a = T - 1 - p;
+      } else {
+        const int order_lo = a.seg_order[lane], order_hi = a.seg_order[lane + 64];
+        const int s = seg_tab_find(pair_tab, p, N);   // position in the length order
+        const int pi = p - seg_tab_at(pair_tab, s);
+        const int n = s < 64 ? __builtin_amdgcn_readlane(order_lo, s) : __builtin_amdgcn_readlane(order_hi, s - 64);
+        tile_a = seg_tab_at(tile_tab, n + 1) - 1 - pi;
+      }
+    } else if (is_sync) {
+      if (p >= (T + 1) / 2) return;
+      tile_a = T - 1 - p;
+      if (p < T - 1 - p) tile_b = p;
+    } else {
+      if (p >= seg_tab_at(pair_tab, N)) return;
+      const int n = seg_tab_find(pair_tab, p, N);
+      const int pi = p - seg_tab_at(pair_tab, n);
+      const int t0 = seg_tab_at(tile_tab, n), tn = seg_tab_at(tile_tab, n + 1) - t0;
+      tile_a = t0 + tn - 1 - pi;
+      if (pi < tn - 1 - pi) tile_b = t0 + pi;
+    }
+    place_a = place_b = place_in_tables(a, seg_tab, tile_tab, tile_a);
+    two = tile_b >= 0;
+    if (two) place_b = place_in_tables(a, seg_tab, tile_tab, tile_b);
   }
 
   const uint16_t* qp = reinterpret_cast<const uint16_t*>(a.q) + (int64_t)block * a.q_block_stride;
@@ -156,9 +157,10 @@ __global__ __launch_bounds__(256 * NG, DP > 128 ? 1 : DP > 64 ? 2 : 3) void pref
   struct Walk : KvWalk {
     int row0w;  // first query row of this wavefront
   };
-  auto make_walk = [&](int tile, Walk& w) __attribute__((always_inline)) {
-    static_cast<KvWalk&>(w) = make_kv_walk(a, seg_tab, tile_tab, tile, is_sync, sparse);
-    w.row0w = w.q0 + kWaveRows * (wave / HS);
+  const int wave_head = wave & (HS - 1), wave_rows = wave >> (HS >> 1);   // HS = 1, 2 or 4
+  auto make_walk = [&](const TilePlace& tp, Walk& w) __attribute__((always_inline)) {
+    static_cast<KvWalk&>(w) = make_kv_walk(a, tp, is_sync, sparse);
+    w.row0w = w.q0 + kWaveRows * wave_rows;
   };
   // K and V tile `it` of walk w into the stage at byte offset st of this group
   auto fetch_tile = [&](const Walk& w, int it, int st) __attribute__((always_inline)) {
@@ -169,7 +171,7 @@ __global__ __launch_bounds__(256 * NG, DP > 128 ? 1 : DP > 64 ? 2 : 3) void pref
     tile_io.template dma<false>((listed ? kp_list : kp) + (int64_t)kv0 * row_elems, lds_base + st, len);
     tile_io.template dma<true>((listed ? vp_list : vp) + (int64_t)kv0 * row_elems, lds_base + 2 * TILEB + st, len);
   };
-  const int head = g * G + hsub * HS + (wave % HS);
+  const int head = g * a.group + wg.set * HS + wave_head;
   // Q fragments (B operand of S^T): lane (q row = l32, half hf) holds
   // Q[row][16*step + 8*hf .. +8].
   auto load_q = [&](const Walk& w, bf16x8 (&qf)[KSTEPS]) __attribute__((always_inline)) {
@@ -218,15 +220,14 @@ __global__ __launch_bounds__(256 * NG, DP > 128 ? 1 : DP > 64 ? 2 : 3) void pref
   // first walk into the second, whose first tile and Q fragments are fetched while
   // the first walk finishes.
   Walk cur, nxt;
-  make_walk(tile_a, cur);
+  make_walk(place_a, cur);
   bf16x8 qf[KSTEPS];
   fetch_q_lds(cur);
   if (grp < cur.nt) fetch_tile(cur, grp, 0);
   nxt = cur;
-  const bool two = tile_b >= 0;
   unsigned warm = 0;
   if (two) {
-    make_walk(tile_b, nxt);
+    make_walk(place_b, nxt);
     // pull the second walk's Q rows into L2 now (one dword per 128-byte line)
     const int row_ld = min(nxt.row0w + l32, nxt.seg_hi - 1);
     warm = *reinterpret_cast<const unsigned*>(qp + ((int64_t)row_ld * Hq + head) * D + (hf * 64) % D);
@@ -239,10 +240,10 @@ __global__ __launch_bounds__(256 * NG, DP > 128 ? 1 : DP > 64 ? 2 : 3) void pref
   unsigned warm_k = 0;
   if (!EXACT && a.warm_kv && grp == 0) {
     constexpr int LPR = TL::ROWB / 128;  // 128-byte lines per K/V row
-    const int sub = wave % HS;
+    const int sub = wave_head;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      if (i % HS != sub || (i >= 2 && !two)) continue;   // wave-uniform
+      if ((i & (HS - 1)) != sub || (i >= 2 && !two)) continue;   // wave-uniform
       const Walk& w = i >= 2 ? nxt : cur;
       const int row = min(w.row0w + lane / LPR, w.seg_hi - 1);
       const uint16_t* base = (i & 1) ? vp : kp;
@@ -632,7 +633,9 @@ hipError_t launch_prefill_exact(const PrefillArgs& a, bool wide, dim3 grid, hipS
 hipError_t launch_prefill_mfma(const PrefillArgs& a_in, int n_blocks, hipStream_t s) {
   if (a_in.n_q_tiles == 0 || n_blocks == 0) return hipSuccess;
   PrefillArgs a = a_in;
-  a.n_ordered = 0;
+  lay_out_heads(a);
+  TileList list(a);
+  a.late_from = INT32_MAX;
   // one block whose K and V of a KV head are at most 2 MB: the workgroups pull them into L2 up front
   a.warm_kv = (n_blocks == 1 && a.keep_chunks == nullptr && (int64_t)a.total * a.D * 4 <= (2 << 20)) ? 1 : 0;
   const int G = a.Hq / a.Hkv;
@@ -656,26 +659,46 @@ hipError_t launch_prefill_mfma(const PrefillArgs& a_in, int n_blocks, hipStream_
       // All workgroups are resident at once, two per CU.  Order: heavy half first, heaviest first;
       // then the light half, lightest first, so that the workgroups that come to share a CU
       // (index p and p + half, dispatched in order) carry about the same load together.
-      struct Item { int tile, work; };
-      Item items[kMaxOrderedTiles];
+      struct Item { int n, t, work; };
+      Item items[kMaxListedTiles];
       int cnt = 0;
       for (int n = 0; n < a.seg.n; ++n) {
         const int lo = a.seg.seg_off[n], hi = a.seg.seg_off[n + 1];
-        for (int t = a.seg.tile_cum[n]; t < a.seg.tile_cum[n + 1]; ++t) {
-          const int last = min(lo + (t - a.seg.tile_cum[n] + 1) * a.q_tile_rows, hi);  // one past the tile's last row
-          items[cnt++] = Item{t, (last - (is_sync ? 0 : lo) + kKvTile - 1) / kKvTile};
+        for (int t = 0; t < list.tiles(n); ++t) {
+          const int last = min(lo + (t + 1) * a.q_tile_rows, hi);  // one past the tile's last row
+          items[cnt++] = Item{n, t, (last - (is_sync ? 0 : lo) + kKvTile - 1) / kKvTile};
         }
       }
       std::stable_sort(items, items + cnt, [](const Item& x, const Item& y) { return x.work > y.work; });
       const int half = (cnt + 1) / 2;
-      for (int i = 0; i < half; ++i) a.tile_order[i] = (uint16_t)items[i].tile;
-      for (int i = half; i < cnt; ++i) a.tile_order[i] = (uint16_t)items[cnt - 1 - (i - half)].tile;
-      a.n_ordered = cnt;
+      for (int i = 0; i < cnt; ++i) list.put(i < half ? i : cnt - 1 - (i - half), TileList::entry(items[i].n, items[i].t));
+      a.n_listed = cnt;
+      a.late_from = half;
       grid.x = (unsigned)(cnt * per_tile);
-    } else if (plan != kEightPairs && a.causal) {
-      a.one_tile_heavy_first = 1;
-      if (!is_sync) order_segments_by_length(a);
+    } else if (plan == kEightPairs) {
+      if (TileList::fits(a, 2)) {   // at most as many pairs as tiles
+        const int T = a.n_q_tiles;
+        int cnt = 0;
+        uint32_t all[kMaxListedTiles];
+        for (int n = 0, i = 0; n < a.seg.n; ++n)
+          for (int t = 0; t < list.tiles(n); ++t) all[i++] = TileList::entry(n, t);
+        const auto pair_up = [&](int t0, int tn) {   // tiles [t0, t0 + tn): the last with the first and so on
+          for (int i = 0; i < (tn + 1) / 2; ++i, ++cnt) {
+            list.put(2 * cnt, all[t0 + tn - 1 - i]);
+            list.put(2 * cnt + 1, i < tn - 1 - i ? all[t0 + i] : kNoTile);
+          }
+        };
+        if (is_sync) pair_up(0, T);
+        else for (int n = 0; n < a.seg.n; ++n) pair_up(a.seg.tile_cum[n], list.tiles(n));
+        a.n_listed = cnt;
+        a.listed_pairs = 1;
+        grid.x = (unsigned)(cnt * per_tile);
+      }
+    } else {
+      if (a.causal) a.one_tile_heavy_first = 1;
+      if (a.causal && !is_sync) order_segments_by_length(a);
       grid.x = (unsigned)(a.n_q_tiles * per_tile);
+      list_heavy_first(a, is_sync || !a.causal);
     }
   }
   if (exact) {

@@ -56,31 +56,14 @@ __global__ __launch_bounds__(64 * kSplitWaves, DP > 64 ? 2 : 4) void prefill_spl
 
   const int Hq = a.Hq, Hkv = a.Hkv;
   const int D = EXACT ? a.D : DP;
-  const int G = Hq / Hkv;
-  const int N = a.seg.n, T = a.n_q_tiles;
-  const SegTab seg_tab = load_seg_tab(a.seg.seg_off, lane, N);
-  const SegTab tile_tab = load_seg_tab(a.seg.tile_cum, lane, N);
-  const SegTab order_tab = load_seg_tab(a.seg.pair_cum, lane, N);
-  const int order_lo = a.seg_order[lane], order_hi = a.seg_order[lane + 64];
 
   // workgroup -> (KV head, head of its group, query tile), longest walks first
-  const int g = blockIdx.x % Hkv;
-  const int rest = blockIdx.x / Hkv;
-  const int head = g * G + rest % G;
-  const int p = rest / G;
+  const WgPlace wg = find_wg_place(a);
+  const int g = wg.g, head = g * a.group + wg.set;
   const bool is_sync = a.sync_override >= 0 ? (a.sync_override != 0) : sync_block_rule(a.sync_interval, a.block_idx0);
   const bool causal = a.causal != 0;
   const bool sparse = is_sync && a.keep_chunks != nullptr;
-  const int rank = a.short_half_ascending && p >= (T + 1) / 2 ? T - 1 - (p - (T + 1) / 2) : p;  // 0: longest walk
-  int tile;
-  if (is_sync) {
-    tile = T - 1 - rank;
-  } else {
-    const int s = seg_tab_find(order_tab, rank, N);
-    const int n = s < 64 ? __builtin_amdgcn_readlane(order_lo, s) : __builtin_amdgcn_readlane(order_hi, s - 64);
-    tile = seg_tab_at(tile_tab, n + 1) - 1 - (rank - seg_tab_at(order_tab, s));
-  }
-  const KvWalk w = make_kv_walk(a, seg_tab, tile_tab, tile, is_sync, sparse);
+  const KvWalk w = make_kv_walk(a, place_heavy_first(a, wg.p, is_sync, lane), is_sync, sparse);
   const int row0 = w.q0;
 
   const uint16_t* qp = reinterpret_cast<const uint16_t*>(a.q);
@@ -307,8 +290,11 @@ hipError_t launch_split_t(const PrefillArgs& a, hipStream_t s) {
 hipError_t launch_prefill_split(const PrefillArgs& a_in, bool fold, hipStream_t s) {
   PrefillArgs a = a_in;
   lay_out_query_tiles(a, kWaveRows);
+  a.heads_per_wg = 1;
+  lay_out_heads(a);
   order_segments_by_length(a);
   a.short_half_ascending = (int64_t)a.n_q_tiles * a.Hq <= 2 * (int64_t)a.n_cus ? 1 : 0;
+  list_heavy_first(a, a.sync_override >= 0 ? a.sync_override != 0 : sync_block_rule(a.sync_interval, a.block_idx0));
   if (a.D == 128) return fold ? launch_split_t<128, true, false>(a, s) : launch_split_t<128, false, false>(a, s);
   if (a.D == 64) return fold ? launch_split_t<64, true, false>(a, s) : launch_split_t<64, false, false>(a, s);
   if (a.D <= 32) return launch_split_t<32, false, true>(a, s);

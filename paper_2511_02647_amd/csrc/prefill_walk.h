@@ -1,7 +1,11 @@
 // Where a query tile's workgroup finds its segment and which KV tiles it walks: shared by the
 // prefill kernels on the matrix cores.
 //
-// The segment tables sit in the kernel-argument buffer.  Walking them entry by entry costs
+// In launches with few tiles the host has listed them (tile_list in the argument block), and a workgroup reads its entry and its
+// segment's two ends; otherwise it searches the segment tables.  A workgroup alone on its SIMDs takes 4 to 5 cycles per instruction,
+// so what counts at the start of a short launch is how many there are, divisions by head counts included.
+//
+// The segment tables sit in the kernel-argument buffer, too.  Walking them entry by entry costs
 // one scalar-cache miss after another while nothing else is in flight, so every lane
 // fetches the entries of segment `lane` (and `lane + 64`) of all tables in one go and the
 // searches run on ballots.  Entry 0 of every table is 0.
@@ -36,22 +40,74 @@ __device__ __attribute__((always_inline)) inline int seg_tab_find(const SegTab& 
   return n;
 }
 
+// Workgroup -> (KV head, set of heads of its group, position in the launch): KV head fastest, so that the workgroups of one
+// KV head share an XCD's L2 when there are 8 (round-robin dispatch over 8 XCDs).
+struct WgPlace {
+  int g, set, p;
+};
+__device__ __attribute__((always_inline)) inline WgPlace find_wg_place(const PrefillArgs& a) {
+  const unsigned id = blockIdx.x;
+  const unsigned rest = a.kv_shift >= 0 ? id >> a.kv_shift : id / (unsigned)a.Hkv;
+  const unsigned p = a.set_shift >= 0 ? rest >> a.set_shift : rest / (unsigned)a.head_sets;
+  return WgPlace{(int)(id - rest * a.Hkv), (int)(rest - p * a.head_sets), (int)p};
+}
+
+// A query tile: its segment, the segment's ends, the tile's first row.
+struct TilePlace {
+  int n, seg_lo, seg_hi, q0;
+};
+// entry i of the host's list
+__device__ __attribute__((always_inline)) inline uint32_t list_entry(const PrefillArgs& a, int i) { return a.tile_list[i >> 1] >> (16 * (i & 1)) & 0xffffu; }
+__device__ __attribute__((always_inline)) inline TilePlace place_listed(const PrefillArgs& a, uint32_t e) {
+  TilePlace t;
+  t.n = e & 127;
+  t.seg_lo = a.seg.seg_off[t.n];
+  t.seg_hi = a.seg.seg_off[t.n + 1];
+  t.q0 = t.seg_lo + (int)(e >> 7) * a.q_tile_rows;
+  return t;
+}
+// tile of a launch without a list
+__device__ __attribute__((always_inline)) inline TilePlace place_in_tables(const PrefillArgs& a, const SegTab& seg_tab, const SegTab& tile_tab, int tile) {
+  TilePlace t;
+  t.n = seg_tab_find(tile_tab, tile, a.seg.n);
+  t.seg_lo = seg_tab_at(seg_tab, t.n);
+  t.seg_hi = seg_tab_at(seg_tab, t.n + 1);
+  t.q0 = t.seg_lo + (tile - seg_tab_at(tile_tab, t.n)) * a.q_tile_rows;
+  return t;
+}
+// One tile per workgroup, longest walks first (split and fp32 kernels): tile of position p.
+__device__ __attribute__((always_inline)) inline TilePlace place_heavy_first(const PrefillArgs& a, int p, bool is_sync, int lane) {
+  if (a.n_listed > 0) return place_listed(a, list_entry(a, p));
+  const int N = a.seg.n, T = a.n_q_tiles;
+  const SegTab seg_tab = load_seg_tab(a.seg.seg_off, lane, N);
+  const SegTab tile_tab = load_seg_tab(a.seg.tile_cum, lane, N);
+  const SegTab order_tab = load_seg_tab(a.seg.pair_cum, lane, N);
+  const int order_lo = a.seg_order[lane], order_hi = a.seg_order[lane + 64];
+  const int rank = a.short_half_ascending && p >= (T + 1) / 2 ? T - 1 - (p - (T + 1) / 2) : p;  // 0: longest walk
+  int tile;
+  if (is_sync) {
+    tile = T - 1 - rank;
+  } else {
+    const int s = seg_tab_find(order_tab, rank, N);
+    const int n = s < 64 ? __builtin_amdgcn_readlane(order_lo, s) : __builtin_amdgcn_readlane(order_hi, s - 64);
+    tile = seg_tab_at(tile_tab, n + 1) - 1 - (rank - seg_tab_at(order_tab, s));
+  }
+  return place_in_tables(a, seg_tab, tile_tab, tile);
+}
+
 // One query tile's walk through its KV tiles (all members wave-uniform): two runs of the
 // kept-tile list (sparse exchange: remote participants before and after the own one), then a
 // dense range [dlo, dhi).
 struct KvWalk {
   int seg_hi, q0, la_n, lb0, n_list, dlo, dhi, nt;
 };
-__device__ __attribute__((always_inline)) inline KvWalk make_kv_walk(const PrefillArgs& a, const SegTab& seg_tab,
-                                                                     const SegTab& tile_tab, int tile, bool is_sync,
-                                                                     bool sparse) {
+__device__ __attribute__((always_inline)) inline KvWalk make_kv_walk(const PrefillArgs& a, const TilePlace& tp, bool is_sync, bool sparse) {
   const int N = a.seg.n, BM = a.q_tile_rows;
   const bool causal = a.causal != 0;
   KvWalk w;
-  const int n = seg_tab_find(tile_tab, tile, N);
-  const int seg_lo = seg_tab_at(seg_tab, n);
-  w.seg_hi = seg_tab_at(seg_tab, n + 1);
-  w.q0 = seg_lo + (tile - seg_tab_at(tile_tab, n)) * BM;
+  const int n = tp.n, seg_lo = tp.seg_lo;
+  w.seg_hi = tp.seg_hi;
+  w.q0 = tp.q0;
   const int i_last = min(w.q0 + BM, w.seg_hi) - 1;
   int la_n = 0, lb0 = 0, lb_n = 0;
   if (sparse) {

@@ -142,6 +142,21 @@ def test_decode_other_shapes_fused_blocks_equal_single_calls(dtype, D):
     assert torch.equal(one, many)
 
 
+@pytest.mark.parametrize("dtype,Hq,Hkv,D,tiles", [(BF16, 4, 1, 64, 32), (BF16, 1, 1, 64, 32), (BF16, 2, 1, 128, 64), (BF16, 3, 1, 96, 32), (F32, 1, 1, 64, 16)])
+@pytest.mark.parametrize("extra", [0, 1])
+def test_prefill_with_as_many_query_tiles_as_listed_and_one_more(dtype, Hq, Hkv, D, tiles, extra):
+    """512 query tiles (of 32, 64 or 16 rows) are listed by the host, more are found in the segment tables."""
+    lens = [tiles * 300, 0, tiles * 3 - 5, tiles * 209 + extra]
+    seg = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    q, k, v = rand_block(45, int(seg[-1]), Hq, Hkv, D, bf16=dtype == BF16)
+    rows, heads = fi.sample_rows(seg, Hq, 96, fi.DEFAULT_SEED, salt=D, tile=tiles, max_boundary_rows=150)
+    for sync, causal in [(0, True), (1, True), (1, False)]:
+        what = "%d tiles D=%d sync=%d causal=%d" % (512 + extra, D, sync, causal)
+        say(what)
+        got = prefill(q, k, v, seg, Hq=Hq, Hkv=Hkv, D=D, H=0, block=0, dtype=dtype, causal=causal, sync_override=sync)
+        check(got[rows, heads], oracle.attend_rows(q, k, v, seg, rows, heads, is_sync=bool(sync), causal=causal), dtype, what)
+
+
 # bf16 with head dimension 64 / 128: ragged layouts, named after the launch of their causal sync block, with empty and
 # one-token segments
 PLAN_LAYOUTS = {"split": ([70, 0, 63, 1, 258], 4, 1), "split-long": ([1, 1999, 33], 2, 1), "eight-short": ([100, 1, 0, 301, 33], 64, 16),
