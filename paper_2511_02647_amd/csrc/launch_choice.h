@@ -72,9 +72,7 @@ inline Walks count_walks(const PrefillShape& a, bool is_sync, int rows, int keys
       // Remote rows under a keep-list: their number is known to the device only, half are taken to be kept.
       // Every launch forced on 8 layouts (4 to 16 participants of 100..2000 tokens, 2 to 32 heads of 64, 96 and 128)
       // at shares of 0.1, 0.25, 0.5 and 1: kFour, kEight and kSplit were taken where they are the fastest, or within
-      // 4 % of it at a quarter and a half, 11 % at 0.1, 13 % at 1.  kEightPairs, whose two walks are taken to
-      // add up to the same, is overrated under a keep-list: taken in two of the layouts and slower at every share
-      // (at 0.1, 8 x 454..823 tokens, 16/8 heads of 64: 51 us, kFour 31; 16 x 207..786, 8/2 heads of 96: 105, kEight 76).
+      // 4 % of it at a quarter and a half, 11 % at 0.1, 13 % at 1.
       const double before = is_sync ? (a.keep ? off / 2 : off) : 0;
       most = before + len;
       mean = before + (len + fmin(rows, len)) / 2;
@@ -106,7 +104,7 @@ inline double estimate(const Pace& p, const Walks& w, bool causal, int cus) {
   return fmax(path, work);
 }
 
-inline PrefillLaunch choose_prefill_launch(const PrefillShape& a, bool is_sync) {
+inline PrefillLaunch choose_prefill_launch(const PrefillShape& a, bool is_sync, bool with_pairs = true) {
   const bool causal = a.causal;
   const int per_tile = a.Hkv * (a.Hq / a.Hkv / a.heads_per_wg);
   const QueryTiles q = count_query_tiles(a.seg_off, a.n, a.q_tile_rows);
@@ -125,8 +123,8 @@ inline PrefillLaunch choose_prefill_launch(const PrefillShape& a, bool is_sync) 
     }
   };
   consider(kEight, estimate(p.eight, eight, causal, a.n_cus));
-  if (causal) {   // half as many workgroups, each with a heavy and a light walk
-    const double pairs = (double)(q.pairs * per_tile);
+  const double pairs = (double)(q.pairs * per_tile);
+  if (causal && with_pairs) {   // half as many workgroups, each with a heavy and a light walk
     eight.longest = is_sync ? 2 * eight.total / eight.wgs : eight.longest + 1;
     eight.wgs = pairs;
     Pace pp = p.eight;
@@ -135,6 +133,22 @@ inline PrefillLaunch choose_prefill_launch(const PrefillShape& a, bool is_sync) 
   }
   consider(kSplit, estimate(p.split, split, causal, a.n_cus));
   return best;
+}
+
+// The launch that is taken: the estimate's choice, but pairs in one round of workgroups only.  Pairs are of about one size and alone on
+// their CUs, so a second round takes as long as the first, be it for 16 of 272 workgroups, where the estimate spreads its work over the chip.
+// Pairs and the next best launch, us: sync blocks of 4 x 516 tokens, 32/8 heads of 128 (272 pairs) 78.4 and 50.3, 5 x 516 (344)
+// 94.2 and 61.8, 8 x 454..823, 16/4 heads of 128 (320) 158 and 117, 3 x 3233, 12/4 heads of 64 (306) 195 and 169, half kept, 8 x
+// 454..823, 16/8 heads of 64 (320) 84 and 63; local blocks of 2 x 2239, 16/2 heads of 128 (280) 84 and 55, 4 x 774..1290, 24/8
+// heads of 64 (432) 36 and 26, 2 x 1004..3348, 16/2 heads of 96 (304) 120 and 103; the one of 11 where pairs were faster: 6 x 2373..3956,
+// 6/2 heads of 64 (444) 76.3 and 79.2.  In one round: 4 x 500, 32/8 heads of 128, a tenth kept 26.2 and 29.1.
+// can_pair: false where a workgroup's two tiles may not be of different participants.
+inline PrefillLaunch launch_to_take(const PrefillShape& a, bool is_sync, bool can_pair = true) {
+  const PrefillLaunch plan = choose_prefill_launch(a, is_sync, can_pair);
+  if (plan != kEightPairs) return plan;
+  const QueryTiles q = count_query_tiles(a.seg_off, a.n, a.q_tile_rows);
+  const int64_t wgs = (is_sync ? (q.tiles + 1) / 2 : q.pairs) * a.Hkv * (a.Hq / a.Hkv / a.heads_per_wg);
+  return wgs <= a.n_cus ? plan : choose_prefill_launch(a, is_sync, false);
 }
 
 // ---- fp32 prefill ----------------------------------------------------------------------------

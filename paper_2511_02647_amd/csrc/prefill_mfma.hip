@@ -651,7 +651,7 @@ hipError_t launch_prefill_mfma(const PrefillArgs& a_in, int n_blocks, hipStream_
   bool wide = (int64_t)grid.x * grid.y < 2 * (int64_t)a.n_cus && a.D <= 128;
   if (n_blocks == 1) {
     const bool is_sync = a.sync_override >= 0 ? a.sync_override != 0 : sync_block_rule(a.sync_interval, a.block_idx0);
-    const PrefillLaunch plan = choose_prefill_launch(PrefillShape{a.seg.seg_off, a.seg.n, a.Hq, a.Hkv, a.D, a.causal != 0, a.keep_chunks != nullptr,
+    const PrefillLaunch plan = launch_to_take(PrefillShape{a.seg.seg_off, a.seg.n, a.Hq, a.Hkv, a.D, a.causal != 0, a.keep_chunks != nullptr,
                                                                   a.heads_per_wg, a.q_tile_rows, a.n_cus}, is_sync);
     if (plan == kSplit) return launch_prefill_split(a_in, fold, s);
     wide = plan == kEight || plan == kEightPairs;

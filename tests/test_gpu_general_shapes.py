@@ -142,6 +142,30 @@ def test_decode_other_shapes_fused_blocks_equal_single_calls(dtype, D):
     assert torch.equal(one, many)
 
 
+# sync blocks that are taken as pairs, also under a keep-list: at most 256 of them, an odd and an even number of tiles
+PAIRS = {"odd": ([513, 1, 450, 600, 350], 32, 8), "even": ([512, 512, 512, 512], 32, 8), "one": ([2030], 32, 8)}
+PAIRS_DIMS = [64, 96, 128]
+
+
+@pytest.mark.parametrize("layout", sorted(PAIRS))
+@pytest.mark.parametrize("D", PAIRS_DIMS)
+@pytest.mark.parametrize("chunk", [0, 64, 7])
+def test_bf16_prefill_in_pairs(layout, D, chunk):
+    lens, Hq, Hkv = PAIRS[layout]
+    seg = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    total = int(seg[-1])
+    q, k, v = rand_block(46, total, Hq, Hkv, D)
+    flags = keep = None
+    if chunk:
+        flags = (np.random.default_rng(8).random(int(fi.chunk_counts(np.diff(seg), chunk).sum())) < 0.5).astype(np.uint8)
+        keep = oracle.expand_keep_chunks(flags, seg, chunk)
+    rows, heads = fi.sample_rows(seg, Hq, 64, fi.DEFAULT_SEED, salt=D, tile=32, max_boundary_rows=150)
+    what = "pairs %s D=%d chunk=%d" % (layout, D, chunk)
+    say(what)
+    got = prefill(q, k, v, seg, Hq=Hq, Hkv=Hkv, D=D, H=0, block=0, dtype=BF16, sync_override=1, keep_chunks=flags, chunk_tokens=chunk)
+    check(got[rows, heads], oracle.attend_rows(q, k, v, seg, rows, heads, is_sync=True, keep_tok=keep), BF16, what)
+
+
 @pytest.mark.parametrize("dtype,Hq,Hkv,D,tiles", [(BF16, 4, 1, 64, 32), (BF16, 1, 1, 64, 32), (BF16, 2, 1, 128, 64), (BF16, 3, 1, 96, 32), (F32, 1, 1, 64, 16)])
 @pytest.mark.parametrize("extra", [0, 1])
 def test_prefill_with_as_many_query_tiles_as_listed_and_one_more(dtype, Hq, Hkv, D, tiles, extra):

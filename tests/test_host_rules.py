@@ -58,3 +58,16 @@ def test_the_layouts_of_the_gpu_tests_take_the_launches_they_name(tmp_path):
 
 def test_chunk_length_of_wide_sync_blocks_is_that_of_the_full_search(tmp_path):
     assert "clean" in run(tmp_path, "wide_chunks")
+
+
+def test_pairs_are_taken_in_one_round_of_workgroups_only(tmp_path):
+    """At 256 and 272 pairs, with and without a keep-list, local and sync; the GPU test of pairs has layouts that take them."""
+    import test_gpu_general_shapes as g
+    shapes = ["128 32 8 1 1 %d 256 %s" % (keep, " ".join(["512"] * 4 if one else ["516"] * 4)) for keep in (0, 1) for one in (1, 0)]
+    shapes += ["128 16 8 1 0 0 256 1019 1019 1019 1019", "128 16 2 1 0 0 256 2239 2239"]
+    for lens, Hq, Hkv in g.PAIRS.values():
+        shapes += ["%d %d %d 1 1 %d 256 %s" % (D, Hq, Hkv, keep, " ".join(map(str, lens))) for D in g.PAIRS_DIMS for keep in (0, 1)]
+    got = [l.split() for l in run(tmp_path, "launch_taken", "\n".join(shapes)).splitlines()]
+    assert [taken == "eight-pairs" for _, taken in got[:6]] == [True, False, True, False, True, False]
+    assert all(choice == "eight-pairs" for choice, _ in got[:6])
+    assert all(taken == "eight-pairs" for _, taken in got[6:])
