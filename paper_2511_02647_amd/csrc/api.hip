@@ -104,7 +104,10 @@ size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 // prefill workspace: [kept_cum: (kMaxP+1) int32, padded][kept_tiles: int2 per 64-row tile]
 // and, for keep chunks finer than a tile where a tile kernel runs: [packed K][packed V]
+// The first 1024 bytes also hold, behind the kept_cum of at most kMaxApart participants, the table of where their matrices are.
 constexpr size_t kKeptCumBytes = 1024;
+constexpr size_t kOwnTableOff = 520;
+static_assert(sizeof(int32_t) * (kMaxApart + 1) <= kOwnTableOff && kOwnTableOff + 2 * kMaxApart * sizeof(void*) <= kKeptCumBytes, "");
 struct PrefillWs {
   size_t tiles_off, list_end, k_off, v_off, total;
 };
@@ -164,10 +167,17 @@ size_t local_kv_copy_bytes(const fedattn_params* p, int32_t tokens) {
   return align_up((size_t)tokens * (size_t)p->n_kv_heads * (size_t)p->head_dim * (p->dtype == FEDATTN_BF16 ? 2 : 4), 256);
 }
 
+// Sparse exchange from matrices that lie apart: where they are (entries as in PrefillArgs::own_kv), and room for the kept rows.
+struct ApartKv {
+  const void* own[2 * kMaxApart];
+  unsigned char *k_packed, *v_packed;
+};
+
 fedattn_status run_prefill(const fedattn_params* p, int32_t block_idx0, int32_t n_blocks, const void* q,
                            const void* k, const void* v, void* out, int64_t q_stride, int64_t kv_stride,
                            const int32_t* seg, const uint8_t* keep_chunks, int32_t chunk_tokens,
-                           int32_t sync_override, void* workspace, size_t workspace_bytes, void* stream) {
+                           int32_t sync_override, void* workspace, size_t workspace_bytes, void* stream,
+                           const ApartKv* apart = nullptr) {
   fedattn_status st = check_params(p);
   if (st != FEDATTN_OK) return st;
   st = check_offsets(p, seg);
@@ -243,10 +253,30 @@ fedattn_status run_prefill(const fedattn_params* p, int32_t block_idx0, int32_t 
       a.kept_cum = kept_cum;
       a.kept_tiles = kept_tiles;
       hipError_t e;
-      if (needs_row_packing(chunk_tokens)) {
-        a.k_list = ws + w.k_off;
-        a.v_list = ws + w.v_off;
-        e = launch_pack_kept_rows(a, a.Hkv * a.D * elem_bytes(p), ws + w.k_off, ws + w.v_off, kept_tiles, kept_cum, s);
+      if (apart || needs_row_packing(chunk_tokens)) {
+        PackArgs pack;
+        unsigned char *k_packed = apart ? apart->k_packed : ws + w.k_off, *v_packed = apart ? apart->v_packed : ws + w.v_off;
+        a.k_list = k_packed;
+        a.v_list = v_packed;
+        pack.keep_chunks = keep_chunks;
+        pack.chunk_tokens = chunk_tokens;
+        pack.n = N;
+        pack.row_vecs = a.Hkv * a.D * elem_bytes(p) / 16;
+        pack.k_packed = reinterpret_cast<uint4*>(k_packed);
+        pack.v_packed = reinterpret_cast<uint4*>(v_packed);
+        pack.kept_tiles = kept_tiles;
+        pack.kept_cum = kept_cum;
+        pack.k = k;
+        pack.v = v;
+        pack.own_kv = nullptr;
+        if (apart) {
+          pack.own_kv = reinterpret_cast<const void**>(ws + kOwnTableOff);
+          memcpy(pack.own, apart->own, sizeof(pack.own));
+          a.own_kv = pack.own_kv;
+        }
+        memcpy(pack.seg_off, a.seg.seg_off, sizeof(pack.seg_off));
+        memcpy(pack.chunk_cum, a.seg.chunk_cum, sizeof(pack.chunk_cum));
+        e = launch_pack_kept_rows(pack, s);
       } else {
         e = launch_build_kept_tiles(a, kept_tiles, kept_cum, s);
       }
@@ -347,6 +377,19 @@ fedattn_status fedattn_prefill_sync_local_kv(const fedattn_params* params, const
   // nothing there can fail short of a launch error, so the copy is enqueued only for valid calls
   if (!q || !out || !aligned16(q) || !aligned16(out)) return fail(FEDATTN_EINVAL, "q and out must be non-NULL and 16-byte aligned");
   if (keep_chunks && chunk_tokens <= 0) return fail(FEDATTN_EINVAL, "chunk_tokens must be positive with a keep-list");
+  if (!in_place && keep_chunks && N <= kMaxApart && use_mfma_prefill(params)) {
+    // the kept rows are packed from where they are, and every participant's own rows are read there; the packed ones
+    // take the place of the aggregated copy, whose address stands for the matrices in the checks
+    ApartKv apart;
+    apart.k_packed = const_cast<unsigned char*>(k_base);
+    apart.v_packed = const_cast<unsigned char*>(v_base);
+    for (int n = 0; n < kMaxApart; ++n)
+      for (int kv = 0; kv < 2; ++kv) {
+        const bool has_rows = n < N && seg_offsets[n + 1] > seg_offsets[n];
+        apart.own[2 * n + kv] = has_rows ? reinterpret_cast<const unsigned char*>((kv ? v_local : k_local)[n]) - (int64_t)seg_offsets[n] * row_bytes : nullptr;
+      }
+    return run_prefill(params, 0, 1, q, k_base, v_base, out, 0, 0, seg_offsets, keep_chunks, chunk_tokens, 1, ws, ws_left, stream, &apart);
+  }
   if (!in_place) {
     st = fedattn_aggregate_kv(params, k_local, v_local, seg_offsets, const_cast<unsigned char*>(k_base),
                               const_cast<unsigned char*>(v_base), stream);

@@ -16,6 +16,7 @@ namespace fedattn {
 constexpr int kMaxP = FEDATTN_MAX_PARTICIPANTS;
 static_assert(kMaxP == kMaxSegments, "the launch rules hold one entry per participant");
 constexpr int kMaxFusedBlocks = 64;    // blocks of one fused decode launch
+constexpr int kMaxApart = 31;          // participants whose matrices a sparse sync block reads where they are (their table: api.hip)
 constexpr int kMergeBatch = 8;         // chunks whose partials a decode merge has in flight at once
 
 // Segment layout of the global sequence, passed by value in the kernel arguments
@@ -40,6 +41,8 @@ struct PrefillArgs {
   const void* v_list;           // are whole tiles, else the packed copies of the kept rows (workspace)
   const int2* kept_tiles;       // device (workspace): (first row, valid rows) of kept 64-row tiles
   const int32_t* kept_cum;      // device (workspace): kept tiles of participants < n, [N+1]
+  const void* const* own_kv;    // device (workspace), or nullptr: where the participants' own matrices lie, entries 2 n and 2 n + 1 such
+                                // that global row r of K and V is at entry + r rows (bf16 with D = 64 or 128); nullptr: in k and v
   int32_t chunk_tokens;
   int32_t total;
   int32_t Hq, Hkv, D;
@@ -70,6 +73,22 @@ struct PrefillArgs {
 constexpr uint32_t kNoTile = 0xffff;
 static_assert(kMaxP <= 128 && kMaxListedTiles <= 512, "a list entry has 7 bits for the segment and 9 for its tile");
 static_assert(sizeof(PrefillArgs) <= 4096, "kernel arguments are limited to 4 KB");
+
+// Packing of the kept rows of a sync block.
+struct PackArgs {
+  const uint8_t* keep_chunks;
+  int32_t chunk_tokens, n;
+  int32_t row_vecs, span;       // 16-byte pieces of a row; rows per workgroup
+  uint4 *k_packed, *v_packed;
+  int2* kept_tiles;
+  int32_t* kept_cum;
+  const void* k;                // rows of all participants back to back, or, with own_kv set,
+  const void* v;                // nothing: every participant's matrices on their own
+  const void** own_kv;          // device, written: see PrefillArgs
+  const void* own[2 * kMaxApart];   // its entries
+  int32_t seg_off[kMaxP + 1];
+  int32_t chunk_cum[kMaxP + 1];
+};
 
 struct DecodeArgs {
   const void* q;
@@ -196,8 +215,7 @@ hipError_t launch_prefill_split(const PrefillArgs& a, bool fold, hipStream_t s);
 hipError_t launch_prefill_f32(const PrefillArgs& a, int n_blocks, hipStream_t s);
 hipError_t launch_build_kept_tiles(const PrefillArgs& a, int2* kept_tiles, int32_t* kept_cum,
                                    hipStream_t s);
-hipError_t launch_pack_kept_rows(const PrefillArgs& a, int row_bytes, void* k_packed, void* v_packed, int2* kept_tiles,
-                                 int32_t* kept_cum, hipStream_t s);
+hipError_t launch_pack_kept_rows(PackArgs& a, hipStream_t s);
 hipError_t launch_decode(const DecodeArgs& a, int dtype, bool split, int n_z, hipStream_t s);
 hipError_t launch_decode_f32(const DecodeArgs& a, bool pieces, int n_z, hipStream_t s);
 hipError_t launch_aggregate(const AggregateArgs& a, hipStream_t s);

@@ -154,6 +154,12 @@ __global__ __launch_bounds__(256 * NG, DP > 128 ? 1 : DP > 64 ? 2 : 3) void pref
   TL tile_io;
   tile_io.init(lane, wave, row_elems, D / 8 - 1);
 
+  // participants' matrices apart (sparse exchange, no pairs then): the dense range of the walk is the own one's rows
+  if (!EXACT && a.own_kv != nullptr) {
+    kp = own_matrix(a, place_a.n, 0) + g * D;
+    vp = own_matrix(a, place_a.n, 1) + g * D;
+  }
+
   struct Walk : KvWalk {
     int row0w;  // first query row of this wavefront
   };
@@ -520,23 +526,26 @@ __global__ __launch_bounds__(64 * kListWaves) void build_kept_tiles_kernel(Prefi
 // segment, so that this stays a few reads per flag.  The workgroups of the last x write the tile list.
 // (8 participants of 300..1500 rows of 1 KB, single tokens: a scan, a list and a gather kernel took
 // 4.8 + 4.8 + 5.2 us under a profiler that shows 4 us for an empty one; now one launch.)
+// Matrices that lie apart are read where they are: the copy holds kept rows only, and the table for the attention kernels, whose
+// workgroups read their own participant's rows there, is written beside the list (an aggregated copy of all rows before it was a launch
+// of its own: 8 participants of 300..1500 rows, 16/4 heads of 128, single tokens, 30 % kept: 103.6 -> 95.5 us).
 constexpr int kPackThreads = 512;
-__global__ __launch_bounds__(kPackThreads) void pack_kept_rows_kernel(PrefillArgs a, int row_vecs, int span, uint4* __restrict__ k_packed,
-                                                                      uint4* __restrict__ v_packed, int2* kept_tiles, int32_t* kept_cum) {
+__global__ __launch_bounds__(kPackThreads) void pack_kept_rows_kernel(PackArgs a) {
   constexpr int NW = kPackThreads / 64;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int N = a.seg.n;
+  const int N = a.n, row_vecs = a.row_vecs, span = a.span;
   if (blockIdx.x == gridDim.x - 1) {
     // packed rows of participant n: [seg_off[n], + kept rows), in tiles of 64 of which the last is ragged
     __shared__ int cnt[kMaxP + 1], rows[kMaxP];
     if (blockIdx.y != 0 || blockIdx.z != 0) return;
     if (tid <= kMaxP) cnt[tid] = 0;
+    if (a.own_kv != nullptr && tid < 2 * N) a.own_kv[tid] = a.own[tid];
     __syncthreads();
     for (int n = wave; n < N; n += NW) {
-      const uint8_t* keep = a.keep_chunks + a.seg.chunk_cum[n];
-      const int nc = a.seg.chunk_cum[n + 1] - a.seg.chunk_cum[n];
+      const uint8_t* keep = a.keep_chunks + a.chunk_cum[n];
+      const int nc = a.chunk_cum[n + 1] - a.chunk_cum[n];
       int kept = lane_flags(keep, nc, lane) * a.chunk_tokens;
-      if (nc > 0 && lane == 0 && keep[nc - 1]) kept -= nc * a.chunk_tokens - (a.seg.seg_off[n + 1] - a.seg.seg_off[n]);
+      if (nc > 0 && lane == 0 && keep[nc - 1]) kept -= nc * a.chunk_tokens - (a.seg_off[n + 1] - a.seg_off[n]);
       kept = wave_sum_int(kept);
       if (lane == 0) {
         rows[n] = kept;
@@ -544,11 +553,11 @@ __global__ __launch_bounds__(kPackThreads) void pack_kept_rows_kernel(PrefillArg
       }
     }
     __syncthreads();
-    if (wave == 0) sum_before(cnt, N, lane, kept_cum);
+    if (wave == 0) sum_before(cnt, N, lane, a.kept_cum);
     __syncthreads();
     for (int n = wave; n < N; n += NW) {
-      const int lo = a.seg.seg_off[n];
-      for (int i = lane; i * kKvTile < rows[n]; i += 64) kept_tiles[cnt[n] + i] = make_int2(lo + i * kKvTile, min(kKvTile, rows[n] - i * kKvTile));
+      const int lo = a.seg_off[n];
+      for (int i = lane; i * kKvTile < rows[n]; i += 64) a.kept_tiles[cnt[n] + i] = make_int2(lo + i * kKvTile, min(kKvTile, rows[n] - i * kKvTile));
     }
     return;
   }
@@ -556,13 +565,13 @@ __global__ __launch_bounds__(kPackThreads) void pack_kept_rows_kernel(PrefillArg
   __shared__ int wave_cnt[NW];
   __shared__ int from[kPackThreads];   // kept rows of this round
   const int m = blockIdx.y;
-  const int lo = a.seg.seg_off[m], hi = a.seg.seg_off[m + 1];
+  const int lo = a.seg_off[m], hi = a.seg_off[m + 1];
   const int64_t first64 = lo + (int64_t)blockIdx.x * span;
   if (first64 >= hi) return;
   const int first = (int)first64, last = min(first64 + span, (int64_t)hi);
-  const uint8_t* keep = a.keep_chunks + a.seg.chunk_cum[m];
-  const uint4* __restrict__ src = reinterpret_cast<const uint4*>(blockIdx.z == 0 ? a.k : a.v);
-  uint4* __restrict__ dst = blockIdx.z == 0 ? k_packed : v_packed;
+  const uint8_t* keep = a.keep_chunks + a.chunk_cum[m];
+  const uint4* __restrict__ src = reinterpret_cast<const uint4*>(a.own_kv != nullptr ? a.own[2 * m + blockIdx.z] : blockIdx.z == 0 ? a.k : a.v);
+  uint4* __restrict__ dst = blockIdx.z == 0 ? a.k_packed : a.v_packed;
 
   const int c_first = (first - lo) / a.chunk_tokens;   // chunk of the first row; those before it are whole
   int n = 0;
@@ -602,14 +611,12 @@ __global__ __launch_bounds__(kPackThreads) void pack_kept_rows_kernel(PrefillArg
 
 }  // namespace
 
-hipError_t launch_pack_kept_rows(const PrefillArgs& a, int row_bytes, void* k_packed, void* v_packed, int2* kept_tiles,
-                                 int32_t* kept_cum, hipStream_t s) {
+hipError_t launch_pack_kept_rows(PackArgs& a, hipStream_t s) {
   int max_len = 1;
-  for (int n = 0; n < a.seg.n; ++n) max_len = max(max_len, a.seg.seg_off[n + 1] - a.seg.seg_off[n]);
-  const int span = (max_len - 1) / 4096 * 64 + 64;
-  const dim3 grid((unsigned)((max_len - 1) / span + 2), (unsigned)a.seg.n, 2);
-  hipLaunchKernelGGL(pack_kept_rows_kernel, grid, dim3(kPackThreads), 0, s, a, row_bytes / 16, span,
-                     reinterpret_cast<uint4*>(k_packed), reinterpret_cast<uint4*>(v_packed), kept_tiles, kept_cum);
+  for (int n = 0; n < a.n; ++n) max_len = max(max_len, a.seg_off[n + 1] - a.seg_off[n]);
+  a.span = (max_len - 1) / 4096 * 64 + 64;
+  const dim3 grid((unsigned)((max_len - 1) / a.span + 2), (unsigned)a.n, 2);
+  hipLaunchKernelGGL(pack_kept_rows_kernel, grid, dim3(kPackThreads), 0, s, a);
   return hipGetLastError();
 }
 
@@ -652,7 +659,7 @@ hipError_t launch_prefill_mfma(const PrefillArgs& a_in, int n_blocks, hipStream_
   if (n_blocks == 1) {
     const bool is_sync = a.sync_override >= 0 ? a.sync_override != 0 : sync_block_rule(a.sync_interval, a.block_idx0);
     const PrefillLaunch plan = launch_to_take(PrefillShape{a.seg.seg_off, a.seg.n, a.Hq, a.Hkv, a.D, a.causal != 0, a.keep_chunks != nullptr,
-                                                                  a.heads_per_wg, a.q_tile_rows, a.n_cus}, is_sync);
+                                                                  a.heads_per_wg, a.q_tile_rows, a.n_cus}, is_sync, a.own_kv == nullptr);
     if (plan == kSplit) return launch_prefill_split(a_in, fold, s);
     wide = plan == kEight || plan == kEightPairs;
     if (plan == kFourOrdered) {

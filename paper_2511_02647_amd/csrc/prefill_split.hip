@@ -63,7 +63,8 @@ __global__ __launch_bounds__(64 * kSplitWaves, DP > 64 ? 2 : 4) void prefill_spl
   const bool is_sync = a.sync_override >= 0 ? (a.sync_override != 0) : sync_block_rule(a.sync_interval, a.block_idx0);
   const bool causal = a.causal != 0;
   const bool sparse = is_sync && a.keep_chunks != nullptr;
-  const KvWalk w = make_kv_walk(a, place_heavy_first(a, wg.p, is_sync, lane), is_sync, sparse);
+  const TilePlace place = place_heavy_first(a, wg.p, is_sync, lane);
+  const KvWalk w = make_kv_walk(a, place, is_sync, sparse);
   const int row0 = w.q0;
 
   const uint16_t* qp = reinterpret_cast<const uint16_t*>(a.q);
@@ -71,6 +72,10 @@ __global__ __launch_bounds__(64 * kSplitWaves, DP > 64 ? 2 : 4) void prefill_spl
   const uint16_t* vp = reinterpret_cast<const uint16_t*>(a.v) + g * D;
   const uint16_t* kp_list = reinterpret_cast<const uint16_t*>(a.k_list) + g * D;
   const uint16_t* vp_list = reinterpret_cast<const uint16_t*>(a.v_list) + g * D;
+  if (!EXACT && a.own_kv != nullptr) {   // matrices apart: the dense range is the own participant's rows
+    kp = own_matrix(a, place.n, 0) + g * D;
+    vp = own_matrix(a, place.n, 1) + g * D;
+  }
   uint16_t* op = reinterpret_cast<uint16_t*>(a.out);
   const float sc = a.scale * kLog2e;
   const int row_elems = Hkv * D;

@@ -95,6 +95,13 @@ __device__ __attribute__((always_inline)) inline TilePlace place_heavy_first(con
   return place_in_tables(a, seg_tab, tile_tab, tile);
 }
 
+// Where participant n's own K (kv = 0) or V matrix lies (PrefillArgs::own_kv).
+__device__ __attribute__((always_inline)) inline const uint16_t* own_matrix(const PrefillArgs& a, int n, int kv) {
+  const uint64_t x = reinterpret_cast<uint64_t>(a.own_kv[2 * n + kv]);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)x), hi = __builtin_amdgcn_readfirstlane((uint32_t)(x >> 32));
+  return reinterpret_cast<const uint16_t*>((uint64_t)hi << 32 | lo);
+}
+
 // One query tile's walk through its KV tiles (all members wave-uniform): two runs of the
 // kept-tile list (sparse exchange: remote participants before and after the own one), then a
 // dense range [dlo, dhi).
