@@ -104,10 +104,7 @@ size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 // prefill workspace: [kept_cum: (kMaxP+1) int32, padded][kept_tiles: int2 per 64-row tile]
 // and, for keep chunks finer than a tile where a tile kernel runs: [packed K][packed V]
-// The first 1024 bytes also hold, behind the kept_cum of at most kMaxApart participants, the table of where their matrices are.
 constexpr size_t kKeptCumBytes = 1024;
-constexpr size_t kOwnTableOff = 520;
-static_assert(sizeof(int32_t) * (kMaxApart + 1) <= kOwnTableOff && kOwnTableOff + 2 * kMaxApart * sizeof(void*) <= kKeptCumBytes, "");
 struct PrefillWs {
   size_t tiles_off, list_end, k_off, v_off, total;
 };
@@ -167,7 +164,7 @@ size_t local_kv_copy_bytes(const fedattn_params* p, int32_t tokens) {
   return align_up((size_t)tokens * (size_t)p->n_kv_heads * (size_t)p->head_dim * (p->dtype == FEDATTN_BF16 ? 2 : 4), 256);
 }
 
-// Sparse exchange from matrices that lie apart: where they are (entries as in PrefillArgs::own_kv), and room for the kept rows.
+// Sync block on matrices that lie apart: where they are (entries as in PrefillArgs::own), and room for the kept rows of a sparse exchange.
 struct ApartKv {
   const void* own[2 * kMaxApart];
   unsigned char *k_packed, *v_packed;
@@ -212,6 +209,10 @@ fedattn_status run_prefill(const fedattn_params* p, int32_t block_idx0, int32_t 
   a.scale = resolve_scale(p);
   a.seg.n = N;
 
+  if (apart) {
+    a.apart = 1;
+    memcpy(a.own, apart->own, sizeof(a.own));
+  }
   const bool mfma = use_mfma_prefill(p);
   a.k_list = k;
   a.v_list = v;
@@ -268,12 +269,8 @@ fedattn_status run_prefill(const fedattn_params* p, int32_t block_idx0, int32_t 
         pack.kept_cum = kept_cum;
         pack.k = k;
         pack.v = v;
-        pack.own_kv = nullptr;
-        if (apart) {
-          pack.own_kv = reinterpret_cast<const void**>(ws + kOwnTableOff);
-          memcpy(pack.own, apart->own, sizeof(pack.own));
-          a.own_kv = pack.own_kv;
-        }
+        pack.apart = a.apart;
+        if (apart) memcpy(pack.own, apart->own, sizeof(pack.own));
         memcpy(pack.seg_off, a.seg.seg_off, sizeof(pack.seg_off));
         memcpy(pack.chunk_cum, a.seg.chunk_cum, sizeof(pack.chunk_cum));
         e = launch_pack_kept_rows(pack, s);
@@ -377,9 +374,15 @@ fedattn_status fedattn_prefill_sync_local_kv(const fedattn_params* params, const
   // nothing there can fail short of a launch error, so the copy is enqueued only for valid calls
   if (!q || !out || !aligned16(q) || !aligned16(out)) return fail(FEDATTN_EINVAL, "q and out must be non-NULL and 16-byte aligned");
   if (keep_chunks && chunk_tokens <= 0) return fail(FEDATTN_EINVAL, "chunk_tokens must be positive with a keep-list");
-  if (!in_place && keep_chunks && N <= kMaxApart && use_mfma_prefill(params)) {
-    // the kept rows are packed from where they are, and every participant's own rows are read there; the packed ones
-    // take the place of the aggregated copy, whose address stands for the matrices in the checks
+  const auto dense_apart = [&] {   // scales that are folded only: the kernels that read dense tiles apart are of that kind
+    const int heads = heads_in_common(params->n_q_heads / params->n_kv_heads);
+    return folds_scale(resolve_scale(params), params->head_dim) &&
+           read_apart(PrefillShape{seg_offsets, N, params->n_q_heads, params->n_kv_heads, params->head_dim, params->causal != 0, false, heads,
+                                   kWaveRows * (4 / heads), device_cus()});
+  };
+  if (!in_place && N <= kMaxApart && use_mfma_prefill(params) && (keep_chunks || dense_apart())) {
+    // Every participant's rows are read where they are, or, the kept ones of a sparse exchange, packed from there; these
+    // take the place of the aggregated copy, whose address stands for the matrices in the checks.
     ApartKv apart;
     apart.k_packed = const_cast<unsigned char*>(k_base);
     apart.v_packed = const_cast<unsigned char*>(v_base);

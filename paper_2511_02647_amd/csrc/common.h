@@ -16,7 +16,7 @@ namespace fedattn {
 constexpr int kMaxP = FEDATTN_MAX_PARTICIPANTS;
 static_assert(kMaxP == kMaxSegments, "the launch rules hold one entry per participant");
 constexpr int kMaxFusedBlocks = 64;    // blocks of one fused decode launch
-constexpr int kMaxApart = 31;          // participants whose matrices a sparse sync block reads where they are (their table: api.hip)
+constexpr int kMaxApart = 31;          // participants whose matrices a sync block reads where they are (what fits the argument block)
 constexpr int kMergeBatch = 8;         // chunks whose partials a decode merge has in flight at once
 
 // Segment layout of the global sequence, passed by value in the kernel arguments
@@ -41,8 +41,6 @@ struct PrefillArgs {
   const void* v_list;           // are whole tiles, else the packed copies of the kept rows (workspace)
   const int2* kept_tiles;       // device (workspace): (first row, valid rows) of kept 64-row tiles
   const int32_t* kept_cum;      // device (workspace): kept tiles of participants < n, [N+1]
-  const void* const* own_kv;    // device (workspace), or nullptr: where the participants' own matrices lie, entries 2 n and 2 n + 1 such
-                                // that global row r of K and V is at entry + r rows (bf16 with D = 64 or 128); nullptr: in k and v
   int32_t chunk_tokens;
   int32_t total;
   int32_t Hq, Hkv, D;
@@ -65,6 +63,8 @@ struct PrefillArgs {
   int32_t one_tile_heavy_first;  // MFMA kernel, causal launch of several rounds of workgroups: one query tile per
                                  // workgroup, heaviest first (seg.pair_cum then counts tiles in seg_order's order)
   int32_t short_half_ascending;  // split and fp32 kernels: workgroups of the shorter half of the walks in ascending order
+  int32_t apart;                 // bf16 with D = 64 or 128, sync blocks: the participants' matrices are not in k and v but where `own` says
+  const void* own[2 * kMaxApart];   // entries 2 n and 2 n + 1: global row r of K and V is at entry + r rows
   SegLayout seg;
   uint32_t tile_list[kMaxListedTiles / 2];   // two entries each: segment | tile inside the segment << 7; kNoTile: none
   uint8_t seg_order[kMaxP];      // participants by decreasing length (local blocks of a heavy-first launch)
@@ -82,10 +82,10 @@ struct PackArgs {
   uint4 *k_packed, *v_packed;
   int2* kept_tiles;
   int32_t* kept_cum;
-  const void* k;                // rows of all participants back to back, or, with own_kv set,
+  const void* k;                // rows of all participants back to back, or, with `apart` set,
   const void* v;                // nothing: every participant's matrices on their own
-  const void** own_kv;          // device, written: see PrefillArgs
-  const void* own[2 * kMaxApart];   // its entries
+  int32_t apart;
+  const void* own[2 * kMaxApart];   // see PrefillArgs
   int32_t seg_off[kMaxP + 1];
   int32_t chunk_cum[kMaxP + 1];
 };

@@ -88,6 +88,9 @@ inline Walks count_walks(const PrefillShape& a, bool is_sync, int rows, int keys
   return w;
 }
 
+// Whether the softmax scale is folded into the Q operand of the bf16 kernels: up to the usual 1/sqrt(D), as its rounding error grows with it.
+inline bool folds_scale(float scale, int D) { return (double)scale * (double)scale * D <= 1.0 + 1e-6; }
+
 // Microseconds of the launch without what every launch costs: the longer of its longest walk, which
 // shares its CU with average ones, and the work of a CU (bidirectional blocks have walks of one length
 // that fill no gaps: whole workgroups count).
@@ -149,6 +152,23 @@ inline PrefillLaunch launch_to_take(const PrefillShape& a, bool is_sync, bool ca
   const QueryTiles q = count_query_tiles(a.seg_off, a.n, a.q_tile_rows);
   const int64_t wgs = (is_sync ? (q.tiles + 1) / 2 : q.pairs) * a.Hkv * (a.Hq / a.Hkv / a.heads_per_wg);
   return wgs <= a.n_cus ? plan : choose_prefill_launch(a, is_sync, false);
+}
+
+// Dense sync blocks whose participants' matrices lie apart: whether they are read where they are or aggregated first, which costs a
+// launch and a copy.  Read where they are, a tile that crosses a segment's end is loaded by a longer way (every lane picks its row's
+// matrix), and the 4- and 8-wavefront kernels take 1 to 4 % longer even without.  Aggregated and read apart, us:
+//  - split launch, unless a CU's workgroups load many such tiles (one 32-row tile in total / (32 n) is) or, at head dimension 128, several ends
+//    lie in a tile: 20 x 1..28 tokens, 8/2 heads of 64 14.7 and 12.3, 2 x 109, 1/1 heads of 64 8.6 and 5.7, 13 x 83..277, 9/3 heads
+//    of 128 36.9 and 32.6, bidirectional 6 x 1..900, 16/16 heads of 64 (3.6 such tiles a CU) 74 and 67; 18 x 1..46, 16/4 heads of 128 15.6 and 17.1;
+//  - others, unless segments are short or the launch is long or loads many such tiles (of 64 rows): bidirectional 6 x 300..900, 16/16 heads of 128
+//    (10.8 a CU) 119 and 113; 25 x 209, 3/1 heads of 128 (14.7) 81.7 and 88.0, 16 x 20..60, 32/8 heads of 128 20.3 and 23.9, 8 x
+//    500..1500, 32/8 heads of 128 431 and 436, 31 x 200..600, 16/4 580 and 605.
+inline bool read_apart(const PrefillShape& a) {
+  const double total = a.seg_off[a.n];
+  if (launch_to_take(a, true) == kSplit)
+    return (a.D == 64 || total >= 32.0 * a.n) && count_walks(a, true, kWaveRows, 256, a.Hq).total * kWaveRows * a.n <= 4.5 * a.n_cus * total;
+  const double tiles = count_walks(a, true, a.q_tile_rows, kKvTile, a.Hkv * (a.Hq / a.Hkv / a.heads_per_wg)).total / a.n_cus;
+  return total >= 128.0 * a.n && tiles <= 150 && tiles * kKvTile * a.n <= 12 * total;
 }
 
 // ---- fp32 prefill ----------------------------------------------------------------------------

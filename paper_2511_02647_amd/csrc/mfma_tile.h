@@ -57,6 +57,17 @@ __device__ inline void lds_dma_16(const void* base, uint32_t off, uint32_t lds_a
         : "memory", "m0");
 }
 
+// The same from addresses of the lanes' own.
+__device__ inline void lds_dma_16_at(const void* p, uint32_t lds_addr) {
+  asm volatile(
+      "s_mov_b32 m0, %0\n\t"
+      "s_nop 0\n\t"
+      "global_load_lds_dwordx4 %1, off"
+      :
+      : "s"(lds_addr), "v"(p)
+      : "memory", "m0");
+}
+
 __device__ inline uint32_t lds_addr_of(const void* p) { return (uint32_t)(uintptr_t)(lds_void_ptr)p; }
 
 // Waits until at most `n` of this wavefront's loads are outstanding (vmcnt only).
@@ -212,6 +223,17 @@ struct KvTile {
         const uint32_t o2 = (uint32_t)(min(row, len - 1) * row_elems + col) * 2u;
         lds_dma_16<STREAM>(tile_base, o2, lds_stage + (wave * IPW + i) * 1024);
       }
+    }
+  }
+
+  // The same with a matrix for every row: at(row) is where tile row `row` starts.
+  template <bool IS_V, typename RowAt>
+  __device__ __attribute__((always_inline)) void dma_rows(uint32_t lds_stage, int len, const RowAt& at) const {
+#pragma unroll
+    for (int i = 0; i < IPW; ++i) {
+      int row, col;
+      dma_slot(i, IS_V, row, col);
+      lds_dma_16_at(at(min(row, len - 1)) + col, lds_stage + (wave * IPW + i) * 1024);
     }
   }
 

@@ -54,7 +54,8 @@ namespace {
 // Its matrix work is (1 + 3) / 2 times that of the other kind: 8 x 2000 tokens, 32/8 heads, sync:
 // 590 useful TFLOP/s at head dimension 96 (1160 at 128 without EXACT).  A local and a sync block of
 // 4 x 1000..2500 tokens, 8/2 heads of 96: 190 us.
-template <int DP, int NG, bool FOLD, bool EXACT>
+// APART: a dense sync block whose participants' matrices lie apart, its tiles loaded from where they are.
+template <int DP, int NG, bool FOLD, bool EXACT, bool APART>
 __global__ __launch_bounds__(256 * NG, DP > 128 ? 1 : DP > 64 ? 2 : 3) void prefill_mfma_kernel(PrefillArgs a) {
   using TL = KvTile<DP, 1, 4, kKvTile, EXACT>;
   const int D = EXACT ? a.D : DP;
@@ -154,8 +155,8 @@ __global__ __launch_bounds__(256 * NG, DP > 128 ? 1 : DP > 64 ? 2 : 3) void pref
   TL tile_io;
   tile_io.init(lane, wave, row_elems, D / 8 - 1);
 
-  // participants' matrices apart (sparse exchange, no pairs then): the dense range of the walk is the own one's rows
-  if (!EXACT && a.own_kv != nullptr) {
+  // participants' matrices apart: with a sparse exchange (no pairs then) the dense range of the walk is the own one's rows
+  if (!EXACT && a.apart) {
     kp = own_matrix(a, place_a.n, 0) + g * D;
     vp = own_matrix(a, place_a.n, 1) + g * D;
   }
@@ -169,10 +170,18 @@ __global__ __launch_bounds__(256 * NG, DP > 128 ? 1 : DP > 64 ? 2 : 3) void pref
     w.row0w = w.q0 + kWaveRows * wave_rows;
   };
   // K and V tile `it` of walk w into the stage at byte offset st of this group
+  ApartRows apart_rows;
+  if constexpr (APART) apart_rows.init(a, lane);
   auto fetch_tile = [&](const Walk& w, int it, int st) __attribute__((always_inline)) {
     int kv0, len;
     bool ct;
     kv_tile_desc(a, w, it, kv0, len, ct);
+    if constexpr (APART) {
+      apart_rows.enter(a, g, kv0);
+      apart_rows.template load<false>(a, tile_io, g, kv0, len, lds_base + st);
+      apart_rows.template load<true>(a, tile_io, g, kv0, len, lds_base + 2 * TILEB + st);
+      return;
+    }
     const bool listed = it < w.n_list;
     tile_io.template dma<false>((listed ? kp_list : kp) + (int64_t)kv0 * row_elems, lds_base + st, len);
     tile_io.template dma<true>((listed ? vp_list : vp) + (int64_t)kv0 * row_elems, lds_base + 2 * TILEB + st, len);
@@ -526,9 +535,8 @@ __global__ __launch_bounds__(64 * kListWaves) void build_kept_tiles_kernel(Prefi
 // segment, so that this stays a few reads per flag.  The workgroups of the last x write the tile list.
 // (8 participants of 300..1500 rows of 1 KB, single tokens: a scan, a list and a gather kernel took
 // 4.8 + 4.8 + 5.2 us under a profiler that shows 4 us for an empty one; now one launch.)
-// Matrices that lie apart are read where they are: the copy holds kept rows only, and the table for the attention kernels, whose
-// workgroups read their own participant's rows there, is written beside the list (an aggregated copy of all rows before it was a launch
-// of its own: 8 participants of 300..1500 rows, 16/4 heads of 128, single tokens, 30 % kept: 103.6 -> 95.5 us).
+// Matrices that lie apart are read where they are: the copy holds kept rows only, and the attention kernels' workgroups read
+// their own participant's rows there, too (an aggregated copy of all rows before it was a launch of its own: 8 participants of 300..1500 rows, 16/4 heads of 128, single tokens, 30 % kept: 103.6 -> 95.5 us).
 constexpr int kPackThreads = 512;
 __global__ __launch_bounds__(kPackThreads) void pack_kept_rows_kernel(PackArgs a) {
   constexpr int NW = kPackThreads / 64;
@@ -539,7 +547,6 @@ __global__ __launch_bounds__(kPackThreads) void pack_kept_rows_kernel(PackArgs a
     __shared__ int cnt[kMaxP + 1], rows[kMaxP];
     if (blockIdx.y != 0 || blockIdx.z != 0) return;
     if (tid <= kMaxP) cnt[tid] = 0;
-    if (a.own_kv != nullptr && tid < 2 * N) a.own_kv[tid] = a.own[tid];
     __syncthreads();
     for (int n = wave; n < N; n += NW) {
       const uint8_t* keep = a.keep_chunks + a.chunk_cum[n];
@@ -570,7 +577,7 @@ __global__ __launch_bounds__(kPackThreads) void pack_kept_rows_kernel(PackArgs a
   if (first64 >= hi) return;
   const int first = (int)first64, last = min(first64 + span, (int64_t)hi);
   const uint8_t* keep = a.keep_chunks + a.chunk_cum[m];
-  const uint4* __restrict__ src = reinterpret_cast<const uint4*>(a.own_kv != nullptr ? a.own[2 * m + blockIdx.z] : blockIdx.z == 0 ? a.k : a.v);
+  const uint4* __restrict__ src = reinterpret_cast<const uint4*>(a.apart ? a.own[2 * m + blockIdx.z] : blockIdx.z == 0 ? a.k : a.v);
   uint4* __restrict__ dst = blockIdx.z == 0 ? a.k_packed : a.v_packed;
 
   const int c_first = (first - lo) / a.chunk_tokens;   // chunk of the first row; those before it are whole
@@ -620,13 +627,13 @@ hipError_t launch_pack_kept_rows(PackArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int DP, int NG, bool FOLD, bool EXACT>
+template <int DP, int NG, bool FOLD, bool EXACT, bool APART = false>
 hipError_t launch_prefill_mfma_t(const PrefillArgs& a, dim3 grid, hipStream_t s) {
   constexpr int smem = NG * 4 * KvTile<DP, 1>::TILEB;
   static std::atomic<uint64_t> attr_done{0};
-  hipError_t e0 = set_max_dynamic_lds_once(attr_done, reinterpret_cast<const void*>(&prefill_mfma_kernel<DP, NG, FOLD, EXACT>), smem);
+  hipError_t e0 = set_max_dynamic_lds_once(attr_done, reinterpret_cast<const void*>(&prefill_mfma_kernel<DP, NG, FOLD, EXACT, APART>), smem);
   if (e0 != hipSuccess) return e0;
-  hipLaunchKernelGGL((prefill_mfma_kernel<DP, NG, FOLD, EXACT>), grid, dim3(256 * NG), smem, s, a);
+  hipLaunchKernelGGL((prefill_mfma_kernel<DP, NG, FOLD, EXACT, APART>), grid, dim3(256 * NG), smem, s, a);
   return hipGetLastError();
 }
 
@@ -652,16 +659,17 @@ hipError_t launch_prefill_mfma(const PrefillArgs& a_in, int n_blocks, hipStream_
   dim3 grid((unsigned)((a.causal ? a.seg.pair_cum[a.seg.n] : a.n_q_tiles) * per_tile), (unsigned)n_blocks, 1);
   // scale folded into Q only up to the usual 1/sqrt(D): its rounding error grows with the scale
   const bool exact = a.D != 64 && a.D != 128;
-  const bool fold = !exact && (double)a.scale * (double)a.scale * a.D <= 1.0 + 1e-6;
+  const bool fold = !exact && folds_scale(a.scale, a.D);
   // several blocks in one launch (local and sync ones mixed): pairs, in 8-wavefront workgroups where
   // there would be fewer than two 4-wavefront ones per CU
   bool wide = (int64_t)grid.x * grid.y < 2 * (int64_t)a.n_cus && a.D <= 128;
   if (n_blocks == 1) {
     const bool is_sync = a.sync_override >= 0 ? a.sync_override != 0 : sync_block_rule(a.sync_interval, a.block_idx0);
     const PrefillLaunch plan = launch_to_take(PrefillShape{a.seg.seg_off, a.seg.n, a.Hq, a.Hkv, a.D, a.causal != 0, a.keep_chunks != nullptr,
-                                                                  a.heads_per_wg, a.q_tile_rows, a.n_cus}, is_sync, a.own_kv == nullptr);
+                                                                  a.heads_per_wg, a.q_tile_rows, a.n_cus}, is_sync, !(a.apart && a.keep_chunks));
     if (plan == kSplit) return launch_prefill_split(a_in, fold, s);
     wide = plan == kEight || plan == kEightPairs;
+    if (a.apart && plan == kEightPairs) a.warm_kv = 0;   // it looks for a pair's rows in one participant's matrices
     if (plan == kFourOrdered) {
       // All workgroups are resident at once, two per CU.  Order: heavy half first, heaviest first;
       // then the light half, lightest first, so that the workgroups that come to share a CU
@@ -719,6 +727,10 @@ hipError_t launch_prefill_mfma(const PrefillArgs& a_in, int n_blocks, hipStream_
       case 7: return launch_prefill_exact<224>(a, wide, grid, s);
       default: return launch_prefill_exact<256>(a, wide, grid, s);
     }
+  }
+  if (a.apart && a.keep_chunks == nullptr) {   // scales that are folded only
+    if (a.D == 128) return wide ? launch_prefill_mfma_t<128, 2, true, false, true>(a, grid, s) : launch_prefill_mfma_t<128, 1, true, false, true>(a, grid, s);
+    return wide ? launch_prefill_mfma_t<64, 2, true, false, true>(a, grid, s) : launch_prefill_mfma_t<64, 1, true, false, true>(a, grid, s);
   }
   if (a.D == 128) {
     if (fold) return wide ? launch_prefill_mfma_t<128, 2, true, false>(a, grid, s) : launch_prefill_mfma_t<128, 1, true, false>(a, grid, s);

@@ -35,7 +35,7 @@ __device__ inline void wait_loads() {
 __device__ inline void wait_lds_reads() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
 // FOLD, EXACT, DP: as in prefill_mfma.hip
-template <int DP, bool FOLD, bool EXACT>
+template <int DP, bool FOLD, bool EXACT, bool APART>
 __global__ __launch_bounds__(64 * kSplitWaves, DP > 64 ? 2 : 4) void prefill_split_kernel(PrefillArgs a) {
   constexpr int KS = kSplitWaves;
   using TL = KvTile<DP, 1, 1, kSplitRows, EXACT>;
@@ -72,7 +72,7 @@ __global__ __launch_bounds__(64 * kSplitWaves, DP > 64 ? 2 : 4) void prefill_spl
   const uint16_t* vp = reinterpret_cast<const uint16_t*>(a.v) + g * D;
   const uint16_t* kp_list = reinterpret_cast<const uint16_t*>(a.k_list) + g * D;
   const uint16_t* vp_list = reinterpret_cast<const uint16_t*>(a.v_list) + g * D;
-  if (!EXACT && a.own_kv != nullptr) {   // matrices apart: the dense range is the own participant's rows
+  if (!EXACT && a.apart) {   // matrices apart: the dense range is the own participant's rows
     kp = own_matrix(a, place.n, 0) + g * D;
     vp = own_matrix(a, place.n, 1) + g * D;
   }
@@ -112,6 +112,18 @@ __global__ __launch_bounds__(64 * kSplitWaves, DP > 64 ? 2 : 4) void prefill_spl
     return t;
   };
 
+  ApartRows apart_rows;
+  if constexpr (APART) apart_rows.init(a, lane);
+  auto load_k = [&](const Tile& t) __attribute__((always_inline)) {
+    if constexpr (APART) apart_rows.enter(a, g, t.kv0);
+    if constexpr (APART) apart_rows.template load<false>(a, tile_io, g, t.kv0, t.load_len, lds_base);
+    else tile_io.template dma<false>(t.k, lds_base, t.load_len);
+  };
+  auto load_v = [&](const Tile& t) __attribute__((always_inline)) {
+    if constexpr (APART) apart_rows.template load<true>(a, tile_io, g, t.kv0, t.load_len, lds_base + TILEB);   // of the tile K was loaded of last
+    else tile_io.template dma<true>(t.v, lds_base + TILEB, t.load_len);
+  };
+
   // Q tile (whole rows, K's swizzled layout): the wavefronts share the loads out among them
   constexpr int QTILEB = kWaveRows * ROWB;
 #pragma unroll
@@ -127,8 +139,8 @@ __global__ __launch_bounds__(64 * kSplitWaves, DP > 64 ? 2 : 4) void prefill_spl
   }
   Tile cur = tile_at(min(wave, nt - 1));
   if (wave < nt) {
-    tile_io.template dma<false>(cur.k, lds_base, cur.load_len);
-    tile_io.template dma<true>(cur.v, lds_base + TILEB, cur.load_len);
+    load_k(cur);
+    load_v(cur);
     wait_loads<2 * TL::IPW>();
   } else {
     wait_loads<0>();
@@ -170,7 +182,7 @@ __global__ __launch_bounds__(64 * kSplitWaves, DP > 64 ? 2 : 4) void prefill_spl
     for (int st = 0; st < KSTEPS; ++st) s[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[st], qf[st], s[0], 0, 0, 0);
     if constexpr (MORE) {
       wait_lds_reads();
-      tile_io.template dma<false>(nx.k, lds_base, nx.load_len);
+      load_k(nx);
     }
     if (t.len < kSplitRows || (t.causal_tile && t.kv0 + kSplitRows - 1 > row0)) {
       int lim = t.len;
@@ -214,7 +226,7 @@ __global__ __launch_bounds__(64 * kSplitWaves, DP > 64 ? 2 : 4) void prefill_spl
     }
     if constexpr (MORE) {
       wait_lds_reads();
-      tile_io.template dma<true>(nx.v, lds_base + TILEB, nx.load_len);
+      load_v(nx);
     }
   };
   if (wave < nt) {
@@ -278,14 +290,14 @@ __global__ __launch_bounds__(64 * kSplitWaves, DP > 64 ? 2 : 4) void prefill_spl
   }
 }
 
-template <int DP, bool FOLD, bool EXACT>
+template <int DP, bool FOLD, bool EXACT, bool APART = false>
 hipError_t launch_split_t(const PrefillArgs& a, hipStream_t s) {
   constexpr int smem = (2 * kSplitWaves + 1) * KvTile<DP, 1, 1, kSplitRows>::TILEB;
   static std::atomic<uint64_t> attr_done{0};
-  hipError_t e = set_max_dynamic_lds_once(attr_done, reinterpret_cast<const void*>(&prefill_split_kernel<DP, FOLD, EXACT>), smem);
+  hipError_t e = set_max_dynamic_lds_once(attr_done, reinterpret_cast<const void*>(&prefill_split_kernel<DP, FOLD, EXACT, APART>), smem);
   if (e != hipSuccess) return e;
   dim3 grid((unsigned)(a.n_q_tiles * a.Hq));
-  hipLaunchKernelGGL((prefill_split_kernel<DP, FOLD, EXACT>), grid, dim3(64 * kSplitWaves), smem, s, a);
+  hipLaunchKernelGGL((prefill_split_kernel<DP, FOLD, EXACT, APART>), grid, dim3(64 * kSplitWaves), smem, s, a);
   return hipGetLastError();
 }
 
@@ -300,6 +312,9 @@ hipError_t launch_prefill_split(const PrefillArgs& a_in, bool fold, hipStream_t 
   order_segments_by_length(a);
   a.short_half_ascending = (int64_t)a.n_q_tiles * a.Hq <= 2 * (int64_t)a.n_cus ? 1 : 0;
   list_heavy_first(a, a.sync_override >= 0 ? a.sync_override != 0 : sync_block_rule(a.sync_interval, a.block_idx0));
+  if (a.apart && a.keep_chunks == nullptr) {
+    return a.D == 128 ? launch_split_t<128, true, false, true>(a, s) : launch_split_t<64, true, false, true>(a, s);
+  }
   if (a.D == 128) return fold ? launch_split_t<128, true, false>(a, s) : launch_split_t<128, false, false>(a, s);
   if (a.D == 64) return fold ? launch_split_t<64, true, false>(a, s) : launch_split_t<64, false, false>(a, s);
   if (a.D <= 32) return launch_split_t<32, false, true>(a, s);

@@ -95,12 +95,55 @@ __device__ __attribute__((always_inline)) inline TilePlace place_heavy_first(con
   return place_in_tables(a, seg_tab, tile_tab, tile);
 }
 
-// Where participant n's own K (kv = 0) or V matrix lies (PrefillArgs::own_kv).
+// Where participant n's own K (kv = 0) or V matrix lies.
 __device__ __attribute__((always_inline)) inline const uint16_t* own_matrix(const PrefillArgs& a, int n, int kv) {
-  const uint64_t x = reinterpret_cast<uint64_t>(a.own_kv[2 * n + kv]);
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)x), hi = __builtin_amdgcn_readfirstlane((uint32_t)(x >> 32));
-  return reinterpret_cast<const uint16_t*>((uint64_t)hi << 32 | lo);
+  return reinterpret_cast<const uint16_t*>(a.own[2 * n + kv]);
 }
+// Tiles of the global sequence from matrices that lie apart.  A tile inside one segment is loaded as from one matrix, whose place is kept
+// from tile to tile; in one that crosses an end every lane picks its row's matrix.
+struct ApartRows {
+  int ends;         // lane n: the end of participant n's segment, INT_MAX past the last
+  int m, lo, hi;    // the segment the last tile began in
+  const uint16_t *k, *v;
+
+  __device__ __attribute__((always_inline)) void init(const PrefillArgs& a, int lane) {
+    static_assert(kMaxApart < 64, "one participant per lane");
+    ends = lane < a.seg.n ? a.seg.seg_off[lane + 1] : INT_MAX;
+    lo = hi = 0;
+  }
+  __device__ __attribute__((always_inline)) void enter(const PrefillArgs& a, int g, int kv0) {
+    if (kv0 >= lo && kv0 < hi) return;
+    m = __builtin_popcountll(__builtin_amdgcn_ballot_w64(kv0 >= ends));
+    lo = a.seg.seg_off[m];
+    hi = a.seg.seg_off[m + 1];
+    k = own_matrix(a, m, 0) + g * a.D;
+    v = own_matrix(a, m, 1) + g * a.D;
+  }
+  template <bool IS_V, typename TL>
+  __device__ __attribute__((always_inline)) void load(const PrefillArgs& a, const TL& tile_io, int g, int kv0, int len, uint32_t stage) const {
+    const int64_t row_elems = tile_io.row_elems;
+    const uint16_t* base = IS_V ? v : k;
+    if (kv0 + len <= hi) {
+      tile_io.template dma<IS_V>(base + kv0 * row_elems, stage, len);
+      return;
+    }
+    if (kv0 + len <= a.seg.seg_off[m + 2]) {   // one end, as nearly always
+      const uint16_t* next = own_matrix(a, m + 1, IS_V) + g * a.D;
+      tile_io.template dma_rows<IS_V>(stage, len, [&](int row) __attribute__((always_inline)) {
+        return (kv0 + row >= hi ? next : base) + (kv0 + row) * row_elems;
+      });
+      return;
+    }
+    tile_io.template dma_rows<IS_V>(stage, len, [&](int row) __attribute__((always_inline)) {
+      const uint16_t* p = base;
+      for (int x = m + 1; a.seg.seg_off[x] < kv0 + len; ++x) {
+        const uint16_t* q = own_matrix(a, x, IS_V) + g * a.D;
+        p = kv0 + row >= a.seg.seg_off[x] ? q : p;
+      }
+      return p + (kv0 + row) * row_elems;
+    });
+  }
+};
 
 // One query tile's walk through its KV tiles (all members wave-uniform): two runs of the
 // kept-tile list (sparse exchange: remote participants before and after the own one), then a

@@ -793,11 +793,12 @@ def test_decode_blocks_fused_equals_decode_blocks(lens):
 
 
 @pytest.mark.parametrize("N,Hq,Hkv,D,hi", [(5, 8, 2, 128, 300), (31, 4, 4, 64, 70), (32, 4, 4, 64, 70), (3, 32, 8, 128, 1500), (6, 16, 8, 64, 900),
-                                             (4, 32, 8, 128, 0)])   # hi = 0: 500 tokens each, taken in pairs from one matrix
-@pytest.mark.parametrize("chunk", [1, 20, 64, 192])
+                                             (4, 32, 8, 128, 0),    # hi = 0: 500 tokens each, taken in pairs from one matrix
+                                             (20, 8, 2, 64, 28), (7, 16, 16, 64, 500), (9, 4, 1, 128, 40)])
+@pytest.mark.parametrize("chunk", [0, 1, 20, 64, 192])   # 0: dense
 @pytest.mark.parametrize("causal", [True, False])
-def test_sparse_exchange_from_matrices_that_lie_apart(N, Hq, Hkv, D, hi, chunk, causal):
-    """Kept rows packed from where they are, own rows read there (up to 31 participants; more: from an aggregated copy): the same
+def test_sync_block_from_matrices_that_lie_apart(N, Hq, Hkv, D, hi, chunk, causal):
+    """Rows read where they are, kept rows packed from there (up to 31 participants; more: from an aggregated copy): the same
     bits as from one matrix where that is not taken in pairs, with NaN around every participant's rows and nothing written behind the workspace."""
     g = np.random.default_rng(N + chunk)
     lens = [int(x) for x in g.integers(1, hi, N)] if hi else [500] * N
@@ -806,7 +807,9 @@ def test_sparse_exchange_from_matrices_that_lie_apart(N, Hq, Hkv, D, hi, chunk, 
     seg = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
     t = int(seg[-1])
     q, k, v = (torch.randn(t, h, D, dtype=BF16, device="cuda") for h in (Hq, Hkv, Hkv))
-    flags = torch.from_numpy((g.random(int(fi.chunk_counts(np.diff(seg), chunk).sum())) < 0.4).astype(np.uint8)).cuda()
+    flags = None
+    if chunk:
+        flags = torch.from_numpy((g.random(int(fi.chunk_counts(np.diff(seg), chunk).sum())) < 0.4).astype(np.uint8)).cuda()
     p = fa.make_params(N, Hq, Hkv, D, 1, BF16, causal=causal)
 
     def apart(x):
@@ -820,13 +823,13 @@ def test_sparse_exchange_from_matrices_that_lie_apart(N, Hq, Hkv, D, hi, chunk, 
     need = fa.fedattn_workspace_bytes(p, fa.FEDATTN_OP_PREFILL_SYNC_LOCAL_KV, t, chunk)
     buf = torch.full((need + 4096,), 0xFF, dtype=torch.uint8, device="cuda")
     ref, out = torch.full_like(q, float("nan")), torch.full_like(q, float("nan"))
-    say("sparse exchange, apart, N=%d D=%d chunk=%d causal=%d" % (N, D, chunk, causal))
+    say("matrices apart, N=%d D=%d chunk=%d causal=%d" % (N, D, chunk, causal))
     fa.fedattn_prefill(p, 0, q, k, v, ref, seg, keep_chunks=flags, chunk_tokens=chunk, sync_override=1, workspace=buf[:need])
     torch.cuda.synchronize()
     buf.fill_(0xFF)
     fa.fedattn_prefill_sync_local_kv(p, q, apart(k), apart(v), out, seg, keep_chunks=flags, chunk_tokens=chunk, workspace=buf[:need])
     torch.cuda.synchronize()
-    if hi:
+    if hi or not chunk:
         assert torch.equal(out, ref)
     else:   # other sums' order: each side's weights and outputs are rounded to 2^-9 of their value
         assert float((out.float() - ref.float()).abs().max()) <= 2e-2
