@@ -3,6 +3,7 @@
 // and nothing is kept between calls.
 #include <math.h>
 #include <stdarg.h>
+#include <stddef.h>
 #include <stdio.h>
 #include <stdlib.h>
 #include <string.h>
@@ -194,7 +195,7 @@ fedattn_status run_prefill(const fedattn_params* p, int32_t block_idx0, int32_t 
   if (has_keep && chunk_tokens <= 0) return fail(FEDATTN_EINVAL, "chunk_tokens must be positive with a keep-list");
 
   PrefillArgs a;
-  memset(&a, 0, sizeof(a));
+  memset(&a, 0, offsetof(PrefillArgs, own));   // what lies behind is written where it is read: entries past the participants' and tiles' count are not
   a.q = q; a.k = k; a.v = v; a.out = out;
   a.q_block_stride = q_stride;
   a.kv_block_stride = kv_stride;

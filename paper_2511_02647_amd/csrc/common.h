@@ -208,11 +208,12 @@ inline void list_heavy_first(PrefillArgs& a, bool is_sync) {
   a.n_listed = T;
 }
 
-// Host-side launchers (one per kernel family); each returns the hipError_t of the launch.
+// Host-side launchers (one per kernel family); each returns the hipError_t of the launch.  Those that take the block
+// for writing finish it: a caller has no use for it afterwards.
 hipError_t launch_prefill_generic(const PrefillArgs& a, int n_blocks, int dtype, hipStream_t s);
-hipError_t launch_prefill_mfma(const PrefillArgs& a, int n_blocks, hipStream_t s);
-hipError_t launch_prefill_split(const PrefillArgs& a, bool fold, hipStream_t s);
-hipError_t launch_prefill_f32(const PrefillArgs& a, int n_blocks, hipStream_t s);
+hipError_t launch_prefill_mfma(PrefillArgs& a, int n_blocks, hipStream_t s);
+hipError_t launch_prefill_split(PrefillArgs& a, bool fold, hipStream_t s);
+hipError_t launch_prefill_f32(PrefillArgs& a, int n_blocks, hipStream_t s);
 hipError_t launch_build_kept_tiles(const PrefillArgs& a, int2* kept_tiles, int32_t* kept_cum,
                                    hipStream_t s);
 hipError_t launch_pack_kept_rows(PackArgs& a, hipStream_t s);
@@ -228,6 +229,14 @@ hipError_t launch_swiglu(const void* gate_up, void* out, int64_t rows, int F, hi
 hipError_t launch_residual_add(float* x, const void* y, int64_t n, hipStream_t s);
 hipError_t launch_stream_probe(const void* src, int64_t bytes, int n_wgs, int pattern, float* sink, hipStream_t s);
 hipError_t launch_mfma_probe(float* sink, int n_wgs, int iters, hipStream_t s);
+
+// One launch with its argument block where it is: the launch syntax copies the block (up to 4 KB) once more on the way.
+template <typename Args>
+inline hipError_t launch_with(void (*kernel)(Args), dim3 grid, dim3 block, int smem, hipStream_t s, const Args& a) {
+  void* args[] = {const_cast<Args*>(&a)};
+  const hipError_t e = hipLaunchKernel(reinterpret_cast<const void*>(kernel), grid, block, args, (size_t)smem, s);
+  return e == hipSuccess ? hipSuccess : (void(hipGetLastError()), e);   // reported here, not by the next caller's look
+}
 
 // A kernel's dynamic-LDS limit is a per-device attribute: set it the first time the kernel is
 // launched on a device (`done` holds one bit per device; setting it twice is harmless).

@@ -478,8 +478,7 @@ hipError_t launch_stream_stages(const DecodeArgs& a, dim3 grid, hipStream_t s) {
   const auto kernel = &decode_stream_kernel<DP, COLSPLIT, EXACT, PIECES, STAGES>;
   hipError_t e0 = set_max_dynamic_lds_once(attr_done, reinterpret_cast<const void*>(kernel), smem);
   if (e0 != hipSuccess) return e0;
-  hipLaunchKernelGGL(kernel, grid, dim3(COLSPLIT ? 512 : 256), smem, s, a);
-  return hipGetLastError();
+  return launch_with(kernel, grid, dim3(COLSPLIT ? 512 : 256), smem, s, a);
 }
 
 template <int DP, bool COLSPLIT, bool EXACT, bool PIECES = false>
@@ -512,11 +511,7 @@ template <typename T>
 hipError_t launch_decode_combine(const DecodeArgs& a, bool pieces, int n_z, hipStream_t s) {
   const dim3 grid((unsigned)((a.is_sync ? 1 : a.N) * launch_heads(a, pieces) * launch_cols(a, pieces)), (unsigned)n_z);
   const dim3 block((unsigned)((a.D + 63) / 64 * 64));
-  if (pieces)
-    hipLaunchKernelGGL((decode_combine_kernel<T, true>), grid, block, 0, s, a);
-  else
-    hipLaunchKernelGGL((decode_combine_kernel<T, false>), grid, block, 0, s, a);
-  return hipGetLastError();
+  return launch_with(pieces ? &decode_combine_kernel<T, true> : &decode_combine_kernel<T, false>, grid, block, 0, s, a);
 }
 
 }  // namespace

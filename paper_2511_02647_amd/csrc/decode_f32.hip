@@ -246,8 +246,7 @@ hipError_t launch_decode_f32_t(const DecodeArgs& a, int n_z, hipStream_t s) {
   if (e != hipSuccess) return e;
   const int heads = PIECES ? a.n_g : a.Hkv, cols = PIECES ? a.n_cols : a.cols;
   dim3 grid((unsigned)(a.n_chunks * heads), (unsigned)((cols + 16 * NQ - 1) / (16 * NQ)), (unsigned)n_z);
-  hipLaunchKernelGGL(kernel, grid, dim3(256), f32_smem_bytes<DP>(), s, a);
-  return hipGetLastError();
+  return launch_with(kernel, grid, dim3(256), f32_smem_bytes<DP>(), s, a);
 }
 
 // Query columns per workgroup, 16 NQ: a tile costs a workgroup NQ times the matrix work, and the more columns

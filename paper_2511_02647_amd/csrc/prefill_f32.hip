@@ -580,8 +580,7 @@ hipError_t launch_prefill_f32_t(const PrefillArgs& a, int n_blocks, hipStream_t 
   hipError_t e = set_max_dynamic_lds_once(attr_done, reinterpret_cast<const void*>(&prefill_f32_kernel<DP, NQ, KS>), smem);
   if (e != hipSuccess) return e;
   dim3 grid((unsigned)(a.n_q_tiles * a.Hkv * (a.Hq / a.Hkv / a.heads_per_wg)), (unsigned)n_blocks);
-  hipLaunchKernelGGL((prefill_f32_kernel<DP, NQ, KS>), grid, dim3(256), smem, s, a);
-  return hipGetLastError();
+  return launch_with(&prefill_f32_kernel<DP, NQ, KS>, grid, dim3(256), smem, s, a);
 }
 
 template <int DP>
@@ -592,8 +591,7 @@ hipError_t launch_prefill_f32_keys(const PrefillArgs& a, int n_blocks, hipStream
   hipError_t e = set_max_dynamic_lds_once(attr_done, reinterpret_cast<const void*>(&prefill_f32_keys_kernel<DP>), smem);
   if (e != hipSuccess) return e;
   dim3 grid((unsigned)(a.n_q_tiles * a.Hq), (unsigned)n_blocks);
-  hipLaunchKernelGGL(prefill_f32_keys_kernel<DP>, grid, dim3(256), smem, s, a);
-  return hipGetLastError();
+  return launch_with(&prefill_f32_keys_kernel<DP>, grid, dim3(256), smem, s, a);
 }
 
 template <int DP>
@@ -616,8 +614,7 @@ hipError_t launch_prefill_f32_d(PrefillArgs& a, int n_blocks, hipStream_t s) {
 
 }  // namespace
 
-hipError_t launch_prefill_f32(const PrefillArgs& a_in, int n_blocks, hipStream_t s) {
-  PrefillArgs a = a_in;
+hipError_t launch_prefill_f32(PrefillArgs& a, int n_blocks, hipStream_t s) {
   if (a.D <= 32) return launch_prefill_f32_d<32>(a, n_blocks, s);
   if (a.D <= 64) return launch_prefill_f32_d<64>(a, n_blocks, s);
   if (a.D <= 96) return launch_prefill_f32_d<96>(a, n_blocks, s);

@@ -623,8 +623,7 @@ hipError_t launch_pack_kept_rows(PackArgs& a, hipStream_t s) {
   for (int n = 0; n < a.n; ++n) max_len = max(max_len, a.seg_off[n + 1] - a.seg_off[n]);
   a.span = (max_len - 1) / 4096 * 64 + 64;
   const dim3 grid((unsigned)((max_len - 1) / a.span + 2), (unsigned)a.n, 2);
-  hipLaunchKernelGGL(pack_kept_rows_kernel, grid, dim3(kPackThreads), 0, s, a);
-  return hipGetLastError();
+  return launch_with(&pack_kept_rows_kernel, grid, dim3(kPackThreads), 0, s, a);
 }
 
 template <int DP, int NG, bool FOLD, bool EXACT, bool APART = false>
@@ -633,8 +632,7 @@ hipError_t launch_prefill_mfma_t(const PrefillArgs& a, dim3 grid, hipStream_t s)
   static std::atomic<uint64_t> attr_done{0};
   hipError_t e0 = set_max_dynamic_lds_once(attr_done, reinterpret_cast<const void*>(&prefill_mfma_kernel<DP, NG, FOLD, EXACT, APART>), smem);
   if (e0 != hipSuccess) return e0;
-  hipLaunchKernelGGL((prefill_mfma_kernel<DP, NG, FOLD, EXACT, APART>), grid, dim3(256 * NG), smem, s, a);
-  return hipGetLastError();
+  return launch_with(&prefill_mfma_kernel<DP, NG, FOLD, EXACT, APART>, grid, dim3(256 * NG), smem, s, a);
 }
 
 template <int DP>
@@ -644,9 +642,8 @@ hipError_t launch_prefill_exact(const PrefillArgs& a, bool wide, dim3 grid, hipS
   return launch_prefill_mfma_t<DP, 1, false, true>(a, grid, s);
 }
 
-hipError_t launch_prefill_mfma(const PrefillArgs& a_in, int n_blocks, hipStream_t s) {
-  if (a_in.n_q_tiles == 0 || n_blocks == 0) return hipSuccess;
-  PrefillArgs a = a_in;
+hipError_t launch_prefill_mfma(PrefillArgs& a, int n_blocks, hipStream_t s) {
+  if (a.n_q_tiles == 0 || n_blocks == 0) return hipSuccess;
   lay_out_heads(a);
   TileList list(a);
   a.late_from = INT32_MAX;
@@ -667,7 +664,7 @@ hipError_t launch_prefill_mfma(const PrefillArgs& a_in, int n_blocks, hipStream_
     const bool is_sync = a.sync_override >= 0 ? a.sync_override != 0 : sync_block_rule(a.sync_interval, a.block_idx0);
     const PrefillLaunch plan = launch_to_take(PrefillShape{a.seg.seg_off, a.seg.n, a.Hq, a.Hkv, a.D, a.causal != 0, a.keep_chunks != nullptr,
                                                                   a.heads_per_wg, a.q_tile_rows, a.n_cus}, is_sync, !(a.apart && a.keep_chunks));
-    if (plan == kSplit) return launch_prefill_split(a_in, fold, s);
+    if (plan == kSplit) return launch_prefill_split(a, fold, s);
     wide = plan == kEight || plan == kEightPairs;
     if (a.apart && plan == kEightPairs) a.warm_kv = 0;   // it looks for a pair's rows in one participant's matrices
     if (plan == kFourOrdered) {

@@ -297,15 +297,13 @@ hipError_t launch_split_t(const PrefillArgs& a, hipStream_t s) {
   hipError_t e = set_max_dynamic_lds_once(attr_done, reinterpret_cast<const void*>(&prefill_split_kernel<DP, FOLD, EXACT, APART>), smem);
   if (e != hipSuccess) return e;
   dim3 grid((unsigned)(a.n_q_tiles * a.Hq));
-  hipLaunchKernelGGL((prefill_split_kernel<DP, FOLD, EXACT, APART>), grid, dim3(64 * kSplitWaves), smem, s, a);
-  return hipGetLastError();
+  return launch_with(&prefill_split_kernel<DP, FOLD, EXACT, APART>, grid, dim3(64 * kSplitWaves), smem, s, a);
 }
 
 }  // namespace
 
 // one block; head dimension at most 128
-hipError_t launch_prefill_split(const PrefillArgs& a_in, bool fold, hipStream_t s) {
-  PrefillArgs a = a_in;
+hipError_t launch_prefill_split(PrefillArgs& a, bool fold, hipStream_t s) {
   lay_out_query_tiles(a, kWaveRows);
   a.heads_per_wg = 1;
   lay_out_heads(a);
