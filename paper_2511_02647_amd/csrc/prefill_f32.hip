@@ -61,13 +61,14 @@ __global__ __launch_bounds__(256, DP > 128 ? 1 : 2) void prefill_f32_kernel(Pref
 
   // longest walks first (sync block: from the end of the sequence; local block: participants by
   // decreasing length, each from its last tile)
+  const ListTab list = load_list(a, lane);
   const WgPlace wg = find_wg_place(a);
   const int g = wg.g;
   const int block = blockIdx.y;
   const bool is_sync = a.sync_override >= 0 ? (a.sync_override != 0)
                                             : sync_block_rule(a.sync_interval, a.block_idx0 + block);
   const bool sparse = is_sync && a.keep_chunks != nullptr;
-  const KvWalk w = make_kv_walk(a, place_heavy_first(a, wg.p, is_sync, lane), is_sync, sparse);
+  const KvWalk w = make_kv_walk(a, place_heavy_first(a, list, wg.p, is_sync, lane), is_sync, sparse);
   const int row0 = w.q0 + 16 * NQ * (qg / HS);   // this wavefront's first query row
   const int head = g * a.group + wg.set * HS + qg % HS;
 
@@ -329,6 +330,7 @@ __global__ __launch_bounds__(256, 2) void prefill_f32_keys_kernel(PrefillArgs a)
   const int Hq = a.Hq, Hkv = a.Hkv, D = a.D;
 
   // workgroup -> (KV head, head of its group, query tile), in the order of prefill_f32_kernel
+  const ListTab list = load_list(a, lane);
   const WgPlace wg = find_wg_place(a);
   const int g = wg.g, head = g * a.group + wg.set;
   const int block = blockIdx.y;
@@ -336,7 +338,7 @@ __global__ __launch_bounds__(256, 2) void prefill_f32_keys_kernel(PrefillArgs a)
                                             : sync_block_rule(a.sync_interval, a.block_idx0 + block);
   const bool causal = a.causal != 0;
   const bool sparse = is_sync && a.keep_chunks != nullptr;
-  const KvWalk w = make_kv_walk(a, place_heavy_first(a, wg.p, is_sync, lane), is_sync, sparse);
+  const KvWalk w = make_kv_walk(a, place_heavy_first(a, list, wg.p, is_sync, lane), is_sync, sparse);
   const int row0 = w.q0;
 
   const float* qp = reinterpret_cast<const float*>(a.q) + (int64_t)block * a.q_block_stride;

@@ -75,6 +75,7 @@ __global__ __launch_bounds__(256 * NG, DP > 128 ? 1 : DP > 64 ? 2 : 3) void pref
 
   const int Hq = a.Hq, Hkv = a.Hkv;
   const int HS = a.heads_per_wg;
+  const ListTab list = load_list(a, lane);
   const WgPlace wg = find_wg_place(a);
   const int g = wg.g, p = wg.p;
   const int block = blockIdx.y;
@@ -91,19 +92,19 @@ __global__ __launch_bounds__(256 * NG, DP > 128 ? 1 : DP > 64 ? 2 : 3) void pref
   bool two = false;            // there is one
   if (a.n_listed > 0) {
     if (a.listed_pairs) {
-      place_a = place_listed(a, list_entry(a, 2 * p));
-      const uint32_t e = list_entry(a, 2 * p + 1);
+      place_a = place_listed(a, list, list_entry(list, 2 * p));
+      const uint32_t e = list_entry(list, 2 * p + 1);
       two = e != kNoTile;
-      place_b = place_listed(a, two ? e : 0);
+      place_b = place_listed(a, list, two ? e : 0);
     } else {
-      place_a = place_b = place_listed(a, list_entry(a, p));
+      place_a = place_b = place_listed(a, list, list_entry(list, p));
     }
     // small causal launch: the light half waits about a microsecond: its loads then queue behind those of the heavy
     // half, whose workgroups set the length of the launch (the light ones have time to spare)
     if (p >= a.late_from) __builtin_amdgcn_s_sleep(32);
   } else {
     const int N = a.seg.n, T = a.n_q_tiles;
-    const SegTab seg_tab = load_seg_tab(a.seg.seg_off, lane, N);
+    const SegTab seg_tab = list.seg;
     const SegTab tile_tab = load_seg_tab(a.seg.tile_cum, lane, N);
     const SegTab pair_tab = load_seg_tab(a.seg.pair_cum, lane, N);
     int tile_a, tile_b = -1;

@@ -58,12 +58,13 @@ __global__ __launch_bounds__(64 * kSplitWaves, DP > 64 ? 2 : 4) void prefill_spl
   const int D = EXACT ? a.D : DP;
 
   // workgroup -> (KV head, head of its group, query tile), longest walks first
+  const ListTab list = load_list(a, lane);
   const WgPlace wg = find_wg_place(a);
   const int g = wg.g, head = g * a.group + wg.set;
   const bool is_sync = a.sync_override >= 0 ? (a.sync_override != 0) : sync_block_rule(a.sync_interval, a.block_idx0);
   const bool causal = a.causal != 0;
   const bool sparse = is_sync && a.keep_chunks != nullptr;
-  const TilePlace place = place_heavy_first(a, wg.p, is_sync, lane);
+  const TilePlace place = place_heavy_first(a, list, wg.p, is_sync, lane);
   const KvWalk w = make_kv_walk(a, place, is_sync, sparse);
   const int row0 = w.q0;
 

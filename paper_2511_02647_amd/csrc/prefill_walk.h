@@ -56,13 +56,32 @@ __device__ __attribute__((always_inline)) inline WgPlace find_wg_place(const Pre
 struct TilePlace {
   int n, seg_lo, seg_hi, q0;
 };
-// entry i of the host's list
-__device__ __attribute__((always_inline)) inline uint32_t list_entry(const PrefillArgs& a, int i) { return a.tile_list[i >> 1] >> (16 * (i & 1)) & 0xffffu; }
-__device__ __attribute__((always_inline)) inline TilePlace place_listed(const PrefillArgs& a, uint32_t e) {
+// The host's list and the segments' ends, requested with the first instructions of the kernel: together with the other arguments one
+// round trip to memory (entry, then segment, by scalar loads: two more, 0.3 us of a launch).
+struct ListTab {
+  uint32_t w[kMaxListedTiles / 128];   // word 64 x + lane
+  SegTab seg;
+};
+__device__ __attribute__((always_inline)) inline ListTab load_list(const PrefillArgs& a, int lane) {
+  ListTab t;
+#pragma unroll
+  for (int x = 0; x < kMaxListedTiles / 128; ++x) t.w[x] = a.tile_list[64 * x + lane];
+  t.seg = load_seg_tab(a.seg.seg_off, lane, a.seg.n);
+  return t;
+}
+// entry i
+__device__ __attribute__((always_inline)) inline uint32_t list_entry(const ListTab& t, int i) {
+  const int word = i >> 1, lane = word & 63;
+  uint32_t w = __builtin_amdgcn_readlane(t.w[0], lane);
+#pragma unroll
+  for (int x = 1; x < kMaxListedTiles / 128; ++x) w = word >> 6 == x ? __builtin_amdgcn_readlane(t.w[x], lane) : w;
+  return w >> (16 * (i & 1)) & 0xffffu;
+}
+__device__ __attribute__((always_inline)) inline TilePlace place_listed(const PrefillArgs& a, const ListTab& l, uint32_t e) {
   TilePlace t;
   t.n = e & 127;
-  t.seg_lo = a.seg.seg_off[t.n];
-  t.seg_hi = a.seg.seg_off[t.n + 1];
+  t.seg_lo = seg_tab_at(l.seg, t.n);
+  t.seg_hi = seg_tab_at(l.seg, t.n + 1);
   t.q0 = t.seg_lo + (int)(e >> 7) * a.q_tile_rows;
   return t;
 }
@@ -76,10 +95,10 @@ __device__ __attribute__((always_inline)) inline TilePlace place_in_tables(const
   return t;
 }
 // One tile per workgroup, longest walks first (split and fp32 kernels): tile of position p.
-__device__ __attribute__((always_inline)) inline TilePlace place_heavy_first(const PrefillArgs& a, int p, bool is_sync, int lane) {
-  if (a.n_listed > 0) return place_listed(a, list_entry(a, p));
+__device__ __attribute__((always_inline)) inline TilePlace place_heavy_first(const PrefillArgs& a, const ListTab& list, int p, bool is_sync, int lane) {
+  if (a.n_listed > 0) return place_listed(a, list, list_entry(list, p));
   const int N = a.seg.n, T = a.n_q_tiles;
-  const SegTab seg_tab = load_seg_tab(a.seg.seg_off, lane, N);
+  const SegTab seg_tab = list.seg;
   const SegTab tile_tab = load_seg_tab(a.seg.tile_cum, lane, N);
   const SegTab order_tab = load_seg_tab(a.seg.pair_cum, lane, N);
   const int order_lo = a.seg_order[lane], order_hi = a.seg_order[lane + 64];
