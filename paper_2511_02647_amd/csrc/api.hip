@@ -452,7 +452,7 @@ static bool blocks_apart(const fedattn_params* p, int32_t n_blocks, const void* 
   const int64_t esize = elem_bytes(p);
   if (q_block_stride < q_elems) return false;   // output blocks overlap one another
   const auto end = [&](const void* base, int64_t stride, int64_t elems) {
-    return reinterpret_cast<uintptr_t>(base) + (uintptr_t)(((n_blocks - 1) * stride + elems) * esize);
+    return reinterpret_cast<uintptr_t>(base) + ((uintptr_t)(n_blocks - 1) * (uintptr_t)stride + (uintptr_t)elems) * (uintptr_t)esize;
   };
   const uintptr_t out_lo = reinterpret_cast<uintptr_t>(out), out_hi = end(out, q_block_stride, q_elems);
   const auto hits = [&](const void* base, int64_t stride, int64_t elems) {
@@ -624,12 +624,17 @@ static fedattn_status run_decode(bool fused, const fedattn_params* params, int32
   }
   if (shared) {
     for (int kind = 0; kind < 2; ++kind) {
+      // launches of about one size: 24 blocks with room for 23 as 12 and 12
+      int of_kind = 0;
+      for (int b = 0; b < n_blocks; ++b) of_kind += (block_is_sync(b) ? 1 : 0) == kind ? 1 : 0;
+      if (of_kind == 0) continue;
+      const int launches = (of_kind + slices[kind] - 1) / slices[kind], at_once = (of_kind + launches - 1) / launches;
       int first = 0;
       while (first < n_blocks) {
         int cnt = 0;
         DecodeArgs& a = args[kind];
         int b = first;
-        for (; b < n_blocks && cnt < slices[kind]; ++b) {
+        for (; b < n_blocks && cnt < at_once; ++b) {
           if ((block_is_sync(b) ? 1 : 0) != kind) continue;
           a.block_list[cnt++] = (uint16_t)b;
         }

@@ -14,8 +14,6 @@
 // KS = 4, head dimensions above 128; the others run prefill_f32_keys_kernel below.
 #include <type_traits>
 
-#include <type_traits>
-
 #include "common.h"
 #include "mfma_tile.h"
 #include "prefill_walk.h"
