@@ -76,6 +76,11 @@ __global__ __launch_bounds__(256 * NG, DP > 128 ? 1 : DP > 64 ? 2 : 3) void pref
   const int Hq = a.Hq, Hkv = a.Hkv;
   const int HS = a.heads_per_wg;
   const ListTab list = load_list(a, lane);
+  // the tables of launches without a list with them: a second round trip there is 0.3 to 0.5 % of a launch of many rounds
+  const SegTab tile_tab = load_seg_tab(a.seg.tile_cum, lane, a.seg.n);
+  const SegTab pair_tab = load_seg_tab(a.seg.pair_cum, lane, a.seg.n);
+  const int order_lo = a.seg_order[lane], order_hi = a.seg_order[lane + 64];
+  asm volatile("" ::"v"(tile_tab.lo), "v"(pair_tab.lo), "v"(order_lo));   // not moved to where they are used
   const WgPlace wg = find_wg_place(a);
   const int g = wg.g, p = wg.p;
   const int block = blockIdx.y;
@@ -105,8 +110,6 @@ __global__ __launch_bounds__(256 * NG, DP > 128 ? 1 : DP > 64 ? 2 : 3) void pref
   } else {
     const int N = a.seg.n, T = a.n_q_tiles;
     const SegTab seg_tab = list.seg;
-    const SegTab tile_tab = load_seg_tab(a.seg.tile_cum, lane, N);
-    const SegTab pair_tab = load_seg_tab(a.seg.pair_cum, lane, N);
     int tile_a, tile_b = -1;
     if (!causal) {
       if (p >= T) return;
@@ -121,7 +124,6 @@ __global__ __launch_bounds__(256 * NG, DP > 128 ? 1 : DP > 64 ? 2 : 3) void pref
       if (is_sync) {
         tile_a = T - 1 - p;
       } else {
-        const int order_lo = a.seg_order[lane], order_hi = a.seg_order[lane + 64];
         const int s = seg_tab_find(pair_tab, p, N);   // position in the length order
         const int pi = p - seg_tab_at(pair_tab, s);
         const int n = s < 64 ? __builtin_amdgcn_readlane(order_lo, s) : __builtin_amdgcn_readlane(order_hi, s - 64);
