@@ -140,7 +140,8 @@ FEDATTN_API fedattn_status fedattn_prefill(const fedattn_params* params, int32_t
  * no copy, no extra launch.  Otherwise the matrices are first aggregated into the workspace
  * (fedattn_aggregate_kv) and the attention reads the copy, or, with bf16, D = 64 or 128 and up to 31
  * participants, the attention reads them (with a keep-list the packed copy of the kept rows is made from them) where they
- * are, if that is faster.  The workspace is asked for all the same.  Always a sync block (the caller
+ * are, if that is faster and `out` overlaps none of them.  So out may lie over matrices that do not lie back to back (not over
+ * those that do, which are read in place).  The workspace is asked for all the same.  Always a sync block (the caller
  * decides which blocks are, e.g. with fedattn_is_sync_block); results equal
  * fedattn_aggregate_kv + fedattn_prefill with sync_override = 1.
  *   q,out          device [total,Hq,D].

@@ -62,6 +62,9 @@ bool use_mfma_prefill(const fedattn_params* p) {
   return p->dtype == FEDATTN_BF16 && (p->head_dim == 64 || p->head_dim == 128);
 }
 
+// Whether two address ranges have a byte in common.
+bool ranges_meet(uintptr_t a, size_t a_bytes, uintptr_t b, size_t b_bytes) { return a < b + b_bytes && b < a + a_bytes; }
+
 int elem_bytes(const fedattn_params* p) { return p->dtype == FEDATTN_BF16 ? 2 : 4; }
 
 // keep chunks that are not whole 64-row tiles: the tile kernels pack the kept rows first
@@ -334,7 +337,8 @@ fedattn_status fedattn_prefill_sync_local_kv(const fedattn_params* params, const
   // aggregated matrices exist as they are and the attention reads them in place.
   const unsigned char* k_base = nullptr;
   const unsigned char* v_base = nullptr;
-  bool in_place = true;
+  bool in_place = true, under_out = false;   // under_out: the output lies over a matrix
+  const size_t out_bytes = (size_t)total * (size_t)params->n_q_heads * (size_t)params->head_dim * (size_t)elem_bytes(params);
   for (int n = 0; n < N; ++n) {
     if (seg_offsets[n + 1] == seg_offsets[n]) continue;
     if (!k_local[n] || !v_local[n]) return fail(FEDATTN_EINVAL, "local K/V of participant %d is NULL", n);
@@ -348,6 +352,9 @@ fedattn_status fedattn_prefill_sync_local_kv(const fedattn_params* params, const
     } else if (kb != k_base || vb != v_base) {
       in_place = false;
     }
+    const size_t bytes = (size_t)(seg_offsets[n + 1] - seg_offsets[n]) * (size_t)row_bytes;
+    for (const void* m : {k_local[n], v_local[n]})
+      under_out = under_out || ranges_meet(reinterpret_cast<uintptr_t>(m), bytes, reinterpret_cast<uintptr_t>(out), out_bytes);
   }
   unsigned char* ws = reinterpret_cast<unsigned char*>(workspace);
   size_t ws_left = workspace ? workspace_bytes : 0;
@@ -381,9 +388,10 @@ fedattn_status fedattn_prefill_sync_local_kv(const fedattn_params* params, const
            read_apart(PrefillShape{seg_offsets, N, params->n_q_heads, params->n_kv_heads, params->head_dim, params->causal != 0, false, heads,
                                    kWaveRows * (4 / heads), device_cus()});
   };
-  if (!in_place && N <= kMaxApart && use_mfma_prefill(params) && (keep_chunks || dense_apart())) {
+  if (!in_place && !under_out && N <= kMaxApart && use_mfma_prefill(params) && (keep_chunks || dense_apart())) {
     // Every participant's rows are read where they are, or, the kept ones of a sparse exchange, packed from there; these
-    // take the place of the aggregated copy, whose address stands for the matrices in the checks.
+    // take the place of the aggregated copy, whose address stands for the matrices in the checks.  Not where the output
+    // lies over a matrix: workgroups write rows of it while others still read.
     ApartKv apart;
     apart.k_packed = const_cast<unsigned char*>(k_base);
     apart.v_packed = const_cast<unsigned char*>(v_base);

@@ -1,0 +1,90 @@
+// The library's host side with its launchers replaced by ones that write down what they are asked to launch: which
+// kernels a call takes and what it hands them, without a device.  Pointers stand for device memory and are never read.
+#include <cstdio>
+#include <cstring>
+#include <string>
+#include <vector>
+
+#include "common.h"
+
+namespace fedattn {
+struct Launch {
+  std::string kernel;
+  PrefillArgs prefill;
+};
+static std::vector<Launch> launched;
+static hipError_t note(const char* kernel, const PrefillArgs* a = nullptr) {
+  launched.emplace_back();
+  launched.back().kernel = kernel;
+  if (a) std::memcpy(static_cast<void*>(&launched.back().prefill), a, sizeof(*a));
+  return hipSuccess;
+}
+hipError_t launch_prefill_generic(const PrefillArgs& a, int, int, hipStream_t) { return note("generic", &a); }
+hipError_t launch_prefill_mfma(PrefillArgs& a, int, hipStream_t) { return note("mfma", &a); }
+hipError_t launch_prefill_f32(PrefillArgs& a, int, hipStream_t) { return note("f32", &a); }
+hipError_t launch_build_kept_tiles(const PrefillArgs& a, int2*, int32_t*, hipStream_t) { return note("list", &a); }
+hipError_t launch_pack_kept_rows(PackArgs&, hipStream_t) { return note("pack"); }
+hipError_t launch_decode(const DecodeArgs&, int, bool, int, hipStream_t) { return note("decode"); }
+hipError_t launch_aggregate(const AggregateArgs&, hipStream_t) { return note("aggregate"); }
+hipError_t launch_rmsnorm(const float*, void*, int64_t, int, float, hipStream_t) { return note("rmsnorm"); }
+hipError_t launch_residual_add_rmsnorm(float*, const void*, void*, int64_t, int, float, hipStream_t) { return note("rmsnorm"); }
+hipError_t launch_rope_split(const void*, const int32_t*, void*, void*, void*, int64_t, int, int, int, float, hipStream_t) { return note("rope"); }
+hipError_t launch_swiglu(const void*, void*, int64_t, int, hipStream_t) { return note("swiglu"); }
+hipError_t launch_residual_add(float*, const void*, int64_t, hipStream_t) { return note("add"); }
+hipError_t launch_stream_probe(const void*, int64_t, int, int, float*, hipStream_t) { return note("probe"); }
+hipError_t launch_mfma_probe(float*, int, int, hipStream_t) { return note("probe"); }
+}  // namespace fedattn
+
+using namespace fedattn;
+
+static int failures = 0;
+#define EXPECT(what)                                                                     \
+  do {                                                                                   \
+    if (!(what)) {                                                                       \
+      std::printf("line %d: %s (%s)\n", __LINE__, #what, fedattn_last_error());          \
+      ++failures;                                                                        \
+    }                                                                                    \
+  } while (0)
+
+static std::string kernels() {
+  std::string s;
+  for (const Launch& l : launched) s += (s.empty() ? "" : " ") + l.kernel;
+  return s;
+}
+
+// Sync block on matrices that lie apart, `out` over them or beside them: read where they are only if nobody can write them meanwhile.
+static void output_over_matrices() {
+  const fedattn_params p = {3, 8, 2, 128, 1, 1, FEDATTN_BF16, 0.f};
+  const std::vector<int32_t> seg = {0, 130, 130, 300};
+  const size_t row = 2 * 128 * 2, q_bytes = 300 * 8 * 128 * 2;
+  char* base = reinterpret_cast<char*>(0x7000000000ull);
+  const char *k[3] = {base, nullptr, base + (1 << 20)}, *v[3] = {base + (2 << 20), nullptr, base + (3 << 20)};
+  const void *kp[3] = {k[0], k[1], k[2]}, *vp[3] = {v[0], v[1], v[2]};
+  void* ws = base + (64 << 20);
+  struct { const char* m; size_t rows; } const mats[] = {{k[0], 130}, {k[2], 170}, {v[0], 130}, {v[2], 170}};
+  const uint8_t* const keeps[] = {nullptr, reinterpret_cast<const uint8_t*>(base + (8 << 20))};
+  for (const uint8_t* keep : keeps) {
+    const int chunk = keep ? 16 : 0;
+    const size_t need = fedattn_workspace_bytes(&p, FEDATTN_OP_PREFILL_SYNC_LOCAL_KV, 300, chunk);
+    const auto call = [&](const char* out) {
+      launched.clear();
+      EXPECT(fedattn_prefill_sync_local_kv(&p, base + (16 << 20), kp, vp, const_cast<char*>(out), seg.data(), keep, chunk, ws, need, nullptr) == FEDATTN_OK);
+      return kernels();
+    };
+    const std::string where_they_are = keep ? "pack mfma" : "mfma", copied = keep ? "aggregate pack mfma" : "aggregate mfma";
+    EXPECT(call(base + (32 << 20)) == where_they_are && launched.back().prefill.apart == 1);
+    for (const auto& m : mats) {
+      EXPECT(call(m.m) == copied && launched.back().prefill.apart == 0);
+      EXPECT(call(m.m + m.rows * row - 16) == copied && launched.back().prefill.apart == 0);
+      EXPECT(call(m.m + m.rows * row) == (m.m + m.rows * row + q_bytes <= m.m + (1 << 20) ? where_they_are : copied));
+    }
+    EXPECT(call(k[0] - q_bytes) == where_they_are);
+    EXPECT(call(k[0] - q_bytes + 16) == copied);
+  }
+}
+
+int main() {
+  output_over_matrices();
+  std::puts(failures ? "wrong" : "clean");
+  return failures != 0;
+}

@@ -836,6 +836,37 @@ def test_sync_block_from_matrices_that_lie_apart(N, Hq, Hkv, D, hi, chunk, causa
     assert int(buf[need:].min()) == 0xFF
 
 
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("chunk", [0, 16])
+def test_sync_block_whose_output_lies_over_the_matrices(D, chunk):
+    """Matrices in another order than the participants', in the buffer that the output then takes: copied before anything is written."""
+    N, Hq, Hkv, lens = 4, 8, 2, [300, 0, 171, 260]
+    seg = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    t = int(seg[-1])
+    q, k, v = (torch.randn(t, h, D, dtype=BF16, device="cuda") for h in (Hq, Hkv, Hkv))
+    flags = None
+    if chunk:
+        flags = torch.from_numpy((np.random.default_rng(D).random(int(fi.chunk_counts(np.diff(seg), chunk).sum())) < 0.4).astype(np.uint8)).cuda()
+    p = fa.make_params(N, Hq, Hkv, D, 1, BF16)
+    ws = torch.empty(fa.fedattn_workspace_bytes(p, fa.FEDATTN_OP_PREFILL_SYNC_LOCAL_KV, t, chunk), dtype=torch.uint8, device="cuda")
+    want = torch.full_like(q, float("nan"))
+    say("output over the matrices, D=%d chunk=%d" % (D, chunk))
+    fa.fedattn_prefill(p, 0, q, k, v, want, seg, keep_chunks=flags, chunk_tokens=chunk, sync_override=1, workspace=ws)
+    torch.cuda.synchronize()
+    for rep in range(5):
+        out = torch.full_like(q, float("nan"))
+        rows = out.view(-1, Hkv, D)
+        at, local = 0, ([], [])
+        for n in (3, 2, 1, 0):
+            for x, views in zip((k, v), local):
+                views.insert(0, rows[at:at + lens[n]])
+                views[0].copy_(x[seg[n]:seg[n + 1]])
+                at += lens[n] + 3
+        fa.fedattn_prefill_sync_local_kv(p, q, local[0], local[1], out, seg, keep_chunks=flags, chunk_tokens=chunk, workspace=ws)
+        torch.cuda.synchronize()
+        assert torch.equal(out, want), rep
+
+
 # ------------------------------------------------------------------ aggregate
 def test_hip_graph_replays_match_eager():
     """A sequence of the library's launches (aggregate, local and sync prefill, sparse prefill with

@@ -16,6 +16,19 @@ def run(tmp_path, name, stdin=""):
     return p.stdout
 
 
+def test_routes_of_calls(tmp_path):
+    """Which launches calls take (tests/host/routes.cpp)."""
+    hipcc = "/opt/rocm/bin/hipcc"
+    if not os.path.exists(hipcc):
+        pytest.skip("hipcc not found")
+    exe = str(tmp_path / "routes")
+    subprocess.check_call([hipcc, "--offload-arch=gfx950", "-O1", "-std=c++17", "-w", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+                           "-I" + os.path.join(ROOT, "include"), "-I" + CSRC, "-o", exe, os.path.join(CSRC, "api.hip"),
+                           "-x", "hip", os.path.join(ROOT, "tests", "host", "routes.cpp")])
+    p = subprocess.run([exe], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=60)
+    assert p.returncode == 0 and "clean" in p.stdout, p.stdout
+
+
 def test_halves_of_a_listed_tile_stay_inside_it(tmp_path):
     assert "clean" in run(tmp_path, "half_tile")
 
