@@ -145,9 +145,8 @@ inline PrefillLaunch choose_prefill_launch(const PrefillShape& a, bool is_sync, 
 // 454..823, 16/8 heads of 64 (320) 84 and 63; local blocks of 2 x 2239, 16/2 heads of 128 (280) 84 and 55, 4 x 774..1290, 24/8
 // heads of 64 (432) 36 and 26, 2 x 1004..3348, 16/2 heads of 96 (304) 120 and 103; the one of 11 where pairs were faster: 6 x 2373..3956,
 // 6/2 heads of 64 (444) 76.3 and 79.2.  In one round: 4 x 500, 32/8 heads of 128, a tenth kept 26.2 and 29.1.
-// can_pair: false where a workgroup's two tiles may not be of different participants.
-inline PrefillLaunch launch_to_take(const PrefillShape& a, bool is_sync, bool can_pair = true) {
-  const PrefillLaunch plan = choose_prefill_launch(a, is_sync, can_pair);
+inline PrefillLaunch launch_to_take(const PrefillShape& a, bool is_sync) {
+  const PrefillLaunch plan = choose_prefill_launch(a, is_sync);
   if (plan != kEightPairs) return plan;
   const QueryTiles q = count_query_tiles(a.seg_off, a.n, a.q_tile_rows);
   const int64_t wgs = (is_sync ? (q.tiles + 1) / 2 : q.pairs) * a.Hkv * (a.Hq / a.Hkv / a.heads_per_wg);

@@ -158,11 +158,14 @@ __global__ __launch_bounds__(256 * NG, DP > 128 ? 1 : DP > 64 ? 2 : 3) void pref
   TL tile_io;
   tile_io.init(lane, wave, row_elems, D / 8 - 1);
 
-  // participants' matrices apart: with a sparse exchange (no pairs then) the dense range of the walk is the own one's rows
-  if (!EXACT && a.apart) {
-    kp = own_matrix(a, place_a.n, 0) + g * D;
-    vp = own_matrix(a, place_a.n, 1) + g * D;
-  }
+  // participants' matrices apart: with a sparse exchange the dense range of a walk is the own one's rows, which in a pair may be
+  // two participants' (4 x 500 tokens, 32/8 heads of 128, a tenth of the 64-token chunks kept: 31.0 us from an aggregated copy, 29.0 in
+  // pairs from where they are, 30.9 by the next best launch; 651, 1169 and 1628 tokens, 8/2 heads: 52.0 and 47.0 in pairs)
+  const auto use_own_matrices = [&](int n) __attribute__((always_inline)) {
+    kp = own_matrix(a, n, 0) + g * D;
+    vp = own_matrix(a, n, 1) + g * D;
+  };
+  if (!EXACT && a.apart) use_own_matrices(place_a.n);
 
   struct Walk : KvWalk {
     int row0w;  // first query row of this wavefront
@@ -310,8 +313,10 @@ __global__ __launch_bounds__(256 * NG, DP > 128 ? 1 : DP > 64 ? 2 : 3) void pref
       const int st_nxt = TILEB - st_cur;
       if (it + 1 < n_it) {
         if (j + NG < cur.nt) fetch_tile(cur, j + NG, st_nxt);
-      } else if (more && grp < nxt.nt) {
-        fetch_tile(nxt, grp, st_nxt);  // last iteration of the first walk: start on the second walk
+      } else if (more) {  // last iteration of the first walk: start on the second walk
+        if constexpr (NG == 2 && !EXACT && !APART)   // pairs of one block are of this kind
+          if (a.apart) use_own_matrices(place_b.n);
+        if (grp < nxt.nt) fetch_tile(nxt, grp, st_nxt);
       }
 
       if (j < cur.nt) {
@@ -666,7 +671,7 @@ hipError_t launch_prefill_mfma(PrefillArgs& a, int n_blocks, hipStream_t s) {
   if (n_blocks == 1) {
     const bool is_sync = a.sync_override >= 0 ? a.sync_override != 0 : sync_block_rule(a.sync_interval, a.block_idx0);
     const PrefillLaunch plan = launch_to_take(PrefillShape{a.seg.seg_off, a.seg.n, a.Hq, a.Hkv, a.D, a.causal != 0, a.keep_chunks != nullptr,
-                                                                  a.heads_per_wg, a.q_tile_rows, a.n_cus}, is_sync, !(a.apart && a.keep_chunks));
+                                                                  a.heads_per_wg, a.q_tile_rows, a.n_cus}, is_sync);
     if (plan == kSplit) return launch_prefill_split(a, fold, s);
     wide = plan == kEight || plan == kEightPairs;
     if (a.apart && plan == kEightPairs) a.warm_kv = 0;   // it looks for a pair's rows in one participant's matrices
