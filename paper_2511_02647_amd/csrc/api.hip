@@ -649,7 +649,8 @@ static fedattn_status run_decode(bool fused, const fedattn_params* params, int32
         first = b;
         if (cnt == 0) continue;
         a.q = q; a.out = out; a.k_cache = k_cache; a.v_cache = v_cache;
-        a.ticket = ticket;   // the other kind's launches lay the workspace out differently
+        a.ticket = counters_ready[kind] ? 0 : ticket;   // no later launch of this kind has more blocks than the first
+        counters_ready[kind] = true;
         hipError_t e = launch(a, cnt);
         if (e != hipSuccess) return fail(FEDATTN_ELAUNCH, "decode (%d blocks at once): %s", cnt, hipGetErrorString(e));
       }

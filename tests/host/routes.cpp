@@ -11,6 +11,8 @@ namespace fedattn {
 struct Launch {
   std::string kernel;
   PrefillArgs prefill;
+  DecodeArgs decode;
+  int blocks;
 };
 static std::vector<Launch> launched;
 static hipError_t note(const char* kernel, const PrefillArgs* a = nullptr) {
@@ -24,7 +26,12 @@ hipError_t launch_prefill_mfma(PrefillArgs& a, int, hipStream_t) { return note("
 hipError_t launch_prefill_f32(PrefillArgs& a, int, hipStream_t) { return note("f32", &a); }
 hipError_t launch_build_kept_tiles(const PrefillArgs& a, int2*, int32_t*, hipStream_t) { return note("list", &a); }
 hipError_t launch_pack_kept_rows(PackArgs&, hipStream_t) { return note("pack"); }
-hipError_t launch_decode(const DecodeArgs&, int, bool, int, hipStream_t) { return note("decode"); }
+hipError_t launch_decode(const DecodeArgs& a, int, bool, int n_z, hipStream_t) {
+  note("decode");
+  launched.back().decode = a;
+  launched.back().blocks = n_z;
+  return hipSuccess;
+}
 hipError_t launch_aggregate(const AggregateArgs&, hipStream_t) { return note("aggregate"); }
 hipError_t launch_rmsnorm(const float*, void*, int64_t, int, float, hipStream_t) { return note("rmsnorm"); }
 hipError_t launch_residual_add_rmsnorm(float*, const void*, void*, int64_t, int, float, hipStream_t) { return note("rmsnorm"); }
@@ -83,7 +90,35 @@ static void output_over_matrices() {
   }
 }
 
+// Decoding: which blocks share a launch, and which launches set their chunk counters up (a round trip for every workgroup): the
+// first one of a kind, as every launch leaves its counters at zero and no later one has more blocks.
+static void decode_launches() {
+  char* base = reinterpret_cast<char*>(0x7000000000ull);
+  for (int rows : {1512, 100}) {   // workspace with room for one block of a kind, and for all
+    const fedattn_params p = {1, 8, 8, 128, 2, 1, FEDATTN_BF16, 0.f};
+    const std::vector<int32_t> seg = {0, rows}, lens = {rows};
+    const int64_t q = 8 * 128, cache = (int64_t)rows * 8 * 128;
+    const size_t need = fedattn_workspace_bytes(&p, FEDATTN_OP_DECODE, rows, 0);
+    for (int out_at : {16, 2}) {   // output apart from the queries; over those of the next blocks
+      launched.clear();
+      EXPECT(fedattn_decode_blocks(&p, 0, 6, base, base + (32 << 20), base + (96 << 20), base + (out_at == 16 ? 16 << 20 : q * 2), q, cache, seg.data(),
+                                   lens.data(), nullptr, -1, base + (200 << 20), need, nullptr) == FEDATTN_OK);
+      bool seen[2] = {false, false};
+      int blocks[2] = {0, 0};
+      for (const Launch& l : launched) {
+        EXPECT((l.decode.ticket != 0) == !seen[l.decode.is_sync]);
+        EXPECT(l.blocks >= 1 && (out_at == 16 || l.blocks == 1));
+        seen[l.decode.is_sync] = true;
+        blocks[l.decode.is_sync] += l.blocks;
+      }
+      EXPECT(blocks[0] == 3 && blocks[1] == 3);
+      EXPECT(launched.size() == (out_at == 16 && rows == 100 ? 2u : 6u));
+    }
+  }
+}
+
 int main() {
+  decode_launches();
   output_over_matrices();
   std::puts(failures ? "wrong" : "clean");
   return failures != 0;
