@@ -487,8 +487,10 @@ hipError_t launch_stream_mode(const DecodeArgs& a, int n_z, hipStream_t s) {
   dim3 grid((unsigned)(a.n_chunks * launch_heads(a, PIECES)), (unsigned)((launch_cols(a, PIECES) + qcols - 1) / qcols), (unsigned)n_z);
   // More than one workgroup per CU: a third stage would keep the second one off the CU until the first has ended, and with
   // two resident one streams while the other starts or merges (6 blocks of 16 x 1152 rows, 32/8 heads, in one
-  // launch: 92 us with three stages, 84 with two).
-  if constexpr (DP == 128)
+  // launch: 92 us with three stages, 84 with two).  Padded to 96, where two with three stages do fit a CU, three with two are
+  // faster, too (2 and 4 blocks of 1427 and 1517 rows, 8/8 heads of 96: 16.7 and 28.8 us with three, 9.8 and 14.0 with two; a launch per
+  // block 17.4 and 35).
+  if constexpr (DP == 96 || DP == 128)
     if ((int64_t)grid.x * grid.y * grid.z > a.n_cus) return launch_stream_stages<DP, COLSPLIT, EXACT, PIECES, 2>(a, grid, s);
   return launch_stream_stages<DP, COLSPLIT, EXACT, PIECES, decode_stages<DP>()>(a, grid, s);
 }

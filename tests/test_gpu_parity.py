@@ -729,7 +729,7 @@ def test_decode_blocks_equals_per_block_calls():
 
 @pytest.mark.parametrize("N,Hq,Hkv,D,n_lens,H", [(4, 8, 2, 128, 90, 2),      # local and sync blocks, each kind in one launch
                                                  (16, 32, 8, 128, 300, 4),   # partials of one sync block fill the workspace
-                                                 (5, 16, 8, 128, 1500, 1),   # more workgroups than CUs: two ring stages
+                                                 (5, 16, 8, 128, 1500, 1), (5, 16, 8, 96, 1500, 1), (5, 16, 8, 72, 1500, 6),   # more workgroups than CUs: two ring stages
                                                  (3, 4, 2, 64, 130, 3), (3, 4, 2, 96, 130, 2)])
 def test_decode_blocks_share_launches(N, Hq, Hkv, D, n_lens, H):
     """Blocks whose memory is apart share launches inside a workspace of the size for one; bit-equal to a call per block,
