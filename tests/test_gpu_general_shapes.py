@@ -275,6 +275,23 @@ def test_keep_list_compaction(layout, chunk):
             check(got[rows, heads], ref, BF16, what)
 
 
+@pytest.mark.parametrize("lens", [[1 + 5 * (i % 7) for i in range(fa.FEDATTN_MAX_PARTICIPANTS)], [300, 0, 1, 64, 65, 130, 17, 16, 90], [33, 70, 1, 129]])
+@pytest.mark.parametrize("D", [24, 64, 96, 128])
+@pytest.mark.parametrize("chunk,share", [(1, 0.1), (1, 0.6), (20, 0.5), (64, 0.5), (192, 1.0), (1, 0.0)])
+def test_f32_keep_lists_of_short_tiles(lens, D, chunk, share):
+    """Lists of none to 127 tiles of 1 to 64 rows: empty slices left out (from four participants on, from eight with chunks of a tile and more) or walked."""
+    Hq, Hkv = 2, 1
+    seg = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    q, k, v = rand_block(49, int(seg[-1]), Hq, Hkv, D, bf16=False)
+    flags = (np.random.default_rng(9).random(int(fi.chunk_counts(np.diff(seg), chunk).sum())) < share).astype(np.uint8)
+    keep = oracle.expand_keep_chunks(flags, seg, chunk)
+    for causal in (True, False):
+        what = "f32 short tiles N=%d D=%d chunk=%d share=%.1f causal=%d" % (len(lens), D, chunk, share, causal)
+        say(what)
+        got = prefill(q, k, v, seg, Hq=Hq, Hkv=Hkv, D=D, H=1, block=0, dtype=F32, causal=causal, keep_chunks=flags, chunk_tokens=chunk)
+        check(got, oracle.attend_block(q, k, v, seg, is_sync=True, causal=causal, keep_tok=keep), F32, what)
+
+
 @pytest.mark.parametrize("dtype,D", [(BF16, 128), (BF16, 64), (BF16, 72), (F32, 64)])
 @pytest.mark.parametrize("chunk", [1, 20, 64])
 @pytest.mark.parametrize("tail", [1, 31, 32, 33])
