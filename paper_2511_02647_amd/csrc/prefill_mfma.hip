@@ -162,6 +162,7 @@ __global__ __launch_bounds__(256 * NG, DP > 128 ? 1 : DP > 64 ? 2 : 3) void pref
   // two participants' (4 x 500 tokens, 32/8 heads of 128, a tenth of the 64-token chunks kept: 31.0 us from an aggregated copy, 29.0 in
   // pairs from where they are, 30.9 by the next best launch; 651, 1169 and 1628 tokens, 8/2 heads: 52.0 and 47.0 in pairs)
   const auto use_own_matrices = [&](int n) __attribute__((always_inline)) {
+    asm volatile("");   // a branch around it, no lookup by every workgroup
     kp = own_matrix(a, n, 0) + g * D;
     vp = own_matrix(a, n, 1) + g * D;
   };
