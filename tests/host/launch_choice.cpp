@@ -26,8 +26,8 @@ int main() {
     } else {
       static const char* const names[] = {"four", "four-ordered", "eight", "eight-pairs", "split"};
       const int heads = heads_in_common(Hq / Hkv);
-      std::puts(names[choose_prefill_launch(PrefillShape{seg.data(), n, Hq, Hkv, D, causal != 0, keep != 0, heads,
-                                                         kWaveRows * (4 / heads), cus}, sync != 0)]);
+      std::puts(names[launch_to_take(PrefillShape{seg.data(), n, Hq, Hkv, D, causal != 0, keep != 0, heads,
+                                                  kWaveRows * (4 / heads), cus}, sync != 0)]);
     }
   }
   return 0;

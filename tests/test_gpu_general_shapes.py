@@ -184,7 +184,7 @@ def test_prefill_with_as_many_query_tiles_as_listed_and_one_more(dtype, Hq, Hkv,
 # bf16 with head dimension 64 / 128: ragged layouts, named after the launch of their causal sync block, with empty and
 # one-token segments
 PLAN_LAYOUTS = {"split": ([70, 0, 63, 1, 258], 4, 1), "split-long": ([1, 1999, 33], 2, 1), "eight-short": ([100, 1, 0, 301, 33], 64, 16),
-                "eight": ([129, 0, 700, 1, 1203], 16, 4), "eight-pairs": ([513, 1, 450, 600, 500], 32, 8), "four": ([3101, 2, 3137], 32, 8)}
+                "eight": ([129, 0, 700, 1, 1203], 16, 4), "eight-pairs": ([578, 866, 0, 1, 502], 32, 8), "four": ([3101, 2, 3137], 32, 8)}
 
 
 @pytest.mark.parametrize("layout", sorted(PLAN_LAYOUTS))
@@ -206,8 +206,10 @@ def test_bf16_prefill_launches(layout, D, scale):
 # it, at every padded head dimension that has it
 ALL_D = (32, 40, 64, 72, 120, 128)
 LAUNCHES = [("eight", 1, False, [1, 0, 160, 181, 168, 199], 32, 8, ALL_D), ("eight", 0, True, [67, 36, 0, 82, 99, 1], 32, 8, ALL_D),
-            ("eight", 1, True, [214, 1, 259, 0, 262, 263], 32, 8, ALL_D), ("eight-pairs", 0, True, [724, 0, 1, 856, 843], 24, 8, ALL_D),
-            ("eight-pairs", 1, True, [542, 1, 0, 528, 834, 394], 24, 8, ALL_D), ("four", 1, False, [378, 340, 392, 1, 0, 363], 32, 8, ALL_D + (160, 224)),
+            ("eight", 1, True, [214, 1, 259, 0, 262, 263], 32, 8, ALL_D), ("eight-pairs", 0, True, [1249, 1276, 1260, 1275, 1, 0], 12, 4, ALL_D),
+            ("eight-pairs", 1, True, [578, 866, 0, 1, 502], 32, 8, ALL_D),
+            ("eight-pairs", 1, True, [0, 2136, 1885, 1745, 1, 2311], 8, 2, (64, 72, 120, 128)),    # 255 tiles: one without a partner
+            ("four", 1, False, [378, 340, 392, 1, 0, 363], 32, 8, ALL_D + (160, 224)),
             ("four", 0, True, [967, 965, 1, 0, 1050, 955], 24, 8, ALL_D + (192,)), ("four", 1, True, [1101, 1062, 1075, 1192, 0, 1], 24, 8, ALL_D + (256,)),
             ("four-ordered", 0, True, [34, 60, 50, 48, 0, 1], 32, 8, (32, 40, 72, 120, 160, 184)),
             ("four-ordered", 0, True, [450, 1, 574, 569, 541, 0], 24, 8, (64, 128)), ("four-ordered", 1, True, [47, 48, 48, 0, 44, 1], 32, 8, (128, 208, 256)),
@@ -367,8 +369,8 @@ def test_decode_sync_blocks_that_fill_the_chip(dtype, D, Hq):
 # what a masked key holds must not reach the rows that do not see it: layouts for every tile kernel of the shapes outside
 # bf16 x 64 / 128 (16-row, key-split and shared fp32 tiles; split, 8-wave and 4-wave bf16 launches)
 HIDDEN = [("narrow", F32, 64), ("narrow", F32, 40), ("split", F32, 128), ("split", F32, 256), ("shared", F32, 32), ("short", BF16, 72),
-          ("short", BF16, 96), ("eight", BF16, 72), ("eight-pairs", BF16, 72), ("long", BF16, 160), ("four", BF16, 40), ("four", BF16, 256)]
-HIDDEN_LAYOUTS = dict(LAYOUTS, **BF16_LAYOUTS, **{"eight": ([214, 1, 259, 0, 262, 263], 32, 8), "eight-pairs": ([542, 1, 528, 0, 834, 394], 24, 8)})
+          ("short", BF16, 96), ("eight", BF16, 72), ("eight-pairs", BF16, 72), ("local-pairs", BF16, 72), ("long", BF16, 160), ("four", BF16, 40), ("four", BF16, 256)]
+HIDDEN_LAYOUTS = dict(LAYOUTS, **BF16_LAYOUTS, **{"eight": ([214, 1, 259, 0, 262, 263], 32, 8), "eight-pairs": ([578, 1, 502, 0, 866], 32, 8), "local-pairs": ([1249, 1276, 1260, 1275, 1, 0], 12, 4)})   # the poisoned token is in a second walk
 
 
 @pytest.mark.parametrize("layout,dtype,D", HIDDEN)

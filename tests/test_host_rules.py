@@ -56,9 +56,9 @@ def test_the_layouts_of_the_gpu_tests_take_the_launches_they_name(tmp_path):
     for D in (8, 40, 64, 88, 128, 136, 256):
         for name, (lens, Hq, Hkv) in g.LAYOUTS.items():
             add("split" if name == "narrow" and D > 128 else name, "f32", D, Hq, Hkv, 1, 1, lens)
-    for name in ("eight", "eight-pairs"):
-        lens, Hq, Hkv = g.HIDDEN_LAYOUTS[name]
-        add(name, "bf16", 72, Hq, Hkv, 1, 1, lens)
+    for layout, name, sync in (("eight", "eight", 1), ("eight-pairs", "eight-pairs", 1), ("local-pairs", "eight-pairs", 0)):
+        lens, Hq, Hkv = g.HIDDEN_LAYOUTS[layout]
+        add(name, "bf16", 72, Hq, Hkv, 1, sync, lens)
     got = run(tmp_path, "launch_choice", "\n".join(shapes)).split()
     assert len(got) == len(want)
     assert not [(s, w, x) for s, w, x in zip(shapes, want, got) if w != x]
