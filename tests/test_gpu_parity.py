@@ -760,8 +760,8 @@ def test_decode_blocks_share_launches(N, Hq, Hkv, D, n_lens, H):
 
 @pytest.mark.parametrize("lens", [[200, 150, 1, 77], [130, 0, 64, 200]])
 def test_decode_blocks_fused_equals_decode_blocks(lens):
-    """Blocks of one kind sharing launches (every block in flight in its own workspace slice):
-    bit-equal to one launch per block, whatever the number of slices the workspace holds; with
+    """Blocks of one kind sharing launches (every block in flight in its own workspace slice), by either entry point:
+    bit-equal to a call per block, whatever the number of slices the workspace holds; with
     and without empty caches (chunks merged in the streaming kernel / by the combine kernel)."""
     N, Hq, Hkv, D, cap, M, H = 4, 8, 2, 128, 200, 9, 4
     seg = (np.arange(N + 1) * cap).astype(np.int32)
@@ -777,17 +777,18 @@ def test_decode_blocks_fused_equals_decode_blocks(lens):
     prompt = np.minimum(lens, 100).astype(np.int32)
     for override, rl in [(-1, None), (-1, prompt), (0, None), (1, None)]:
         ref = torch.full_like(tq, float("nan"))
-        fa.fedattn_decode_blocks(p, 0, M, tq, tk, tv, ref, tq[0].numel(), tk[0].numel(), seg, lens, remote_lens=rl,
-                                 sync_override=override, workspace=ws1)
+        for b in range(M):
+            fa.fedattn_decode(p, b, tq[b], tk[b], tv[b], ref[b], seg, lens, remote_lens=rl, sync_override=override, workspace=ws1)
         torch.cuda.synchronize()
         for n_slices in (1, 3, 9):
             ws = torch.full((one + (n_slices - 1) * slice_bytes,), 0xFF, dtype=torch.uint8, device="cuda")
-            out = torch.full_like(tq, float("nan"))
-            say("decode_blocks_fused lens=%s override=%d remote=%s slices=%d" % (lens.tolist(), override, rl is not None, n_slices))
-            fa.fedattn_decode_blocks_fused(p, 0, M, tq, tk, tv, out, tq[0].numel(), tk[0].numel(), seg, lens,
-                                           remote_lens=rl, sync_override=override, workspace=ws)
-            torch.cuda.synchronize()
-            assert torch.equal(out, ref), "fused decode differs (override %d, %d slices)" % (override, n_slices)
+            for entry in (fa.fedattn_decode_blocks, fa.fedattn_decode_blocks_fused):
+                out = torch.full_like(tq, float("nan"))
+                ws.fill_(0xFF)
+                say("%s lens=%s override=%d remote=%s slices=%d" % (entry.__name__, lens.tolist(), override, rl is not None, n_slices))
+                entry(p, 0, M, tq, tk, tv, out, tq[0].numel(), tk[0].numel(), seg, lens, remote_lens=rl, sync_override=override, workspace=ws)
+                torch.cuda.synchronize()
+                assert torch.equal(out, ref), "%s differs (override %d, %d slices)" % (entry.__name__, override, n_slices)
     b = 3
     check(host(ref[b]), oracle.decode_step(q[b], kc[b], vc[b], seg, lens, is_sync=True), BF16, "decode block 3 (forced sync)")
 
