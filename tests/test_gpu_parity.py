@@ -835,6 +835,41 @@ def test_sync_block_from_matrices_that_lie_apart(N, Hq, Hkv, D, hi, chunk, causa
     assert int(buf[need:].min()) == 0xFF
 
 
+# dense sync blocks from matrices apart: (launch, causal, lengths, Hq, Hkv, D); that they are read where they are, by the launch
+# named, is checked by tests/test_host_rules.py
+APART = [("four", True, [1201, 1271, 1116, 0, 1], 32, 8, 64), ("four", False, [950, 614, 0, 1073, 1, 966], 16, 4, 64),
+         ("four", True, [617, 562, 604, 628, 670, 595], 24, 8, 128), ("four", False, [1001, 714, 0, 776, 834, 1], 16, 8, 128),
+         ("eight", True, [1309, 919, 1116, 0, 876, 1370, 1], 16, 8, 64), ("eight", False, [400, 409, 433, 1, 399], 16, 8, 64),
+         ("eight", True, [589, 577, 601, 0, 602, 589, 612, 1], 12, 4, 128), ("eight", False, [304, 1, 62, 361], 16, 8, 128),
+         ("eight-pairs", True, [1040, 1100, 1102, 1043, 1067], 12, 3, 64), ("eight-pairs", True, [1265, 1343, 0, 1411], 16, 8, 128),
+         ("split", True, [6, 56, 28, 0, 23, 33, 1, 46, 40, 55], 2, 1, 64), ("split", False, [180, 690, 442, 0, 75, 182, 516, 1], 3, 1, 128),
+         ("split", True, [269, 1, 271, 268, 0, 271], 16, 4, 128), ("split", False, [29, 31, 17, 0, 26, 1, 35], 8, 4, 64),
+         ("copied", True, [16 + i for i in range(28)], 24, 8, 128)]
+
+
+@pytest.mark.parametrize("launch,causal,lens,Hq,Hkv,D", APART)
+def test_dense_sync_block_read_apart_by_every_launch(launch, causal, lens, Hq, Hkv, D):
+    """The same bits as from one matrix, with NaN around every participant's rows."""
+    seg = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    t, N = int(seg[-1]), len(lens)
+    q, k, v = (torch.randn(t, h, D, dtype=BF16, device="cuda") for h in (Hq, Hkv, Hkv))
+    p = fa.make_params(N, Hq, Hkv, D, 1, BF16, causal=causal)
+    local = []
+    for x in (k, v):
+        bufs = [torch.full((n + 130, Hkv, D), float("nan"), dtype=BF16, device="cuda") for n in lens]
+        for n in range(N):
+            bufs[n][65:65 + lens[n]] = x[seg[n]:seg[n + 1]]
+        local.append([b[65:65 + n] for b, n in zip(bufs, lens)])
+    ws = torch.full((fa.fedattn_workspace_bytes(p, fa.FEDATTN_OP_PREFILL_SYNC_LOCAL_KV, t, 0),), 0xFF, dtype=torch.uint8, device="cuda")
+    ref, out = torch.full_like(q, float("nan")), torch.full_like(q, float("nan"))
+    say("read apart, %s D=%d causal=%d" % (launch, D, causal))
+    fa.fedattn_prefill(p, 0, q, k, v, ref, seg, sync_override=1)
+    fa.fedattn_prefill_sync_local_kv(p, q, local[0], local[1], out, seg, workspace=ws)
+    torch.cuda.synchronize()
+    assert torch.equal(out, ref)
+    assert (int(ws.min()) == 0xFF) == (launch != "copied")   # nothing is copied
+
+
 @pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("chunk", [0, 16])
 def test_sync_block_whose_output_lies_over_the_matrices(D, chunk):

@@ -81,6 +81,16 @@ def test_pairs_are_taken_in_one_round_of_workgroups_only(tmp_path):
     for lens, Hq, Hkv in g.PAIRS.values():
         shapes += ["%d %d %d 1 1 %d 256 %s" % (D, Hq, Hkv, keep, " ".join(map(str, lens))) for D in g.PAIRS_DIMS for keep in (0, 1)]
     got = [l.split() for l in run(tmp_path, "launch_taken", "\n".join(shapes)).splitlines()]
-    assert [taken == "eight-pairs" for _, taken in got[:6]] == [True, False, True, False, True, False]
-    assert all(choice == "eight-pairs" for choice, _ in got[:6])
-    assert all(taken == "eight-pairs" for _, taken in got[6:])
+    assert [taken == "eight-pairs" for _, taken, _ in got[:6]] == [True, False, True, False, True, False]
+    assert all(choice == "eight-pairs" for choice, _, _ in got[:6])
+    assert all(taken == "eight-pairs" for _, taken, _ in got[6:])
+
+
+def test_dense_layouts_apart_are_read_where_they_are_by_the_launches_they_name(tmp_path):
+    """Every launch that the rule has read matrices apart, at both head dimensions, and one layout that is copied first."""
+    import test_gpu_parity as g
+    shapes = ["%d %d %d %d 1 0 256 %s" % (D, Hq, Hkv, causal, " ".join(map(str, lens))) for _, causal, lens, Hq, Hkv, D in g.APART]
+    got = [l.split()[1:] for l in run(tmp_path, "launch_taken", "\n".join(shapes)).splitlines()]
+    want = [["four", "copied"] if launch == "copied" else [launch, "apart"] for launch, *_ in g.APART]
+    assert not [(s, w, x) for s, w, x in zip(shapes, want, got) if w != x] and len(got) == len(want)
+    assert {(launch, D) for launch, _, _, _, _, D in g.APART} >= {(l, D) for l in ("four", "eight", "eight-pairs", "split") for D in (64, 128)}
