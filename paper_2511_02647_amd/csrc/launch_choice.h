@@ -171,25 +171,17 @@ inline bool read_apart(const PrefillShape& a) {
 }
 
 // ---- fp32 prefill ----------------------------------------------------------------------------
-// (TFLOP/s measured at 8 x 1000 to 8 x 2000 tokens unless stated):
-//  - kF32Shared, at least 6 workgroups per CU: the wavefronts take different heads, each K and V
-//    tile is staged once for all of them (32/8 heads of 128, sync: 137; with the keys shared out among the wavefronts 119, 4 % slower
-//    in a sync block already at 4 workgroups per CU, but 8 % faster in a local one);
-//  - kF32KeySplit: the keys shared out among the 4 wavefronts of 16 query rows of one head, more workgroups and walks four
-//    times shorter (8/2 heads of 128, sync: 112 against 91); kF32Narrow: the same kernel, where 32-row tiles would make fewer
-//    than 2 workgroups per CU.  If all workgroups are resident at once, the short half is dispatched shortest first, so that workgroups
-//    that come to share a CU carry about the same load together (1000 tokens, 8 heads: 59 against 51; with
-//    more workgroups than fit, longest first is better: 80 against 73).
-enum F32Launch { kF32Shared, kF32KeySplit, kF32Narrow };
 // Query heads of a KV group that a workgroup of 4 wavefronts takes.
 inline int heads_in_common(int group) { return group % 4 == 0 ? 4 : (group % 2 == 0 ? 2 : 1); }
-inline F32Launch choose_f32_launch(const int32_t* seg_off, int n_seg, int Hq, int Hkv, int D, int n_blocks, int n_cus) {
+// Whether the wavefronts of a workgroup take different heads, each K and V tile staged once for all of them, rather than the keys of
+// one head's 16 query rows: from 6 workgroups per CU on.  Keys shared out and heads shared, us, 32/8 heads of 128: 8 x 1000 tokens (8 per CU)
+// sync 4257 and 3891 (137 TFLOP/s), local 664 and 661; 6 x 1000 (6) 2416 and 2281, local 497 and 502; of 64: 1199 and 1180, local 232 and 275.
+// With fewer it depends on how evenly the workgroups fill the rounds: 4 x 1000 (4), heads of 64 543 and 572, bidirectional 1065
+// and 1027; 4 x 700 (2.8), of 128 557 and 548, local 176 and 180; 6 x 1000, 8/2 heads of 128 (1.5) 621 and 882; 1000 tokens, 8/2 heads 27 and 133.
+inline bool f32_heads_shared(const int32_t* seg_off, int n_seg, int Hq, int Hkv, int D, int n_blocks, int n_cus) {
   const int nq = D > 128 ? 1 : 2;   // 16-row sub-tiles per wavefront
   const int group = Hq / Hkv, common = heads_in_common(group);
-  const int64_t shared = count_query_tiles(seg_off, n_seg, 16 * nq * (4 / common)).tiles * Hkv * (group / common) * n_blocks;
-  if (shared >= 6 * (int64_t)n_cus) return kF32Shared;
-  const int64_t split = count_query_tiles(seg_off, n_seg, 16 * nq).tiles * Hq * n_blocks;
-  return nq > 1 && split < 2 * (int64_t)n_cus ? kF32Narrow : kF32KeySplit;
+  return count_query_tiles(seg_off, n_seg, 16 * nq * (4 / common)).tiles * Hkv * (group / common) * n_blocks >= 6 * (int64_t)n_cus;
 }
 
 // ---- decode ----------------------------------------------------------------------------------

@@ -21,8 +21,7 @@ int main() {
     while (in >> len) seg.push_back(seg.back() + len);
     const int n = (int)seg.size() - 1;
     if (dtype == "f32") {
-      static const char* const names[] = {"shared", "split", "narrow"};
-      std::puts(names[choose_f32_launch(seg.data(), n, Hq, Hkv, D, 1, cus)]);
+      std::puts(f32_heads_shared(seg.data(), n, Hq, Hkv, D, 1, cus) ? "shared" : "keys");
     } else {
       static const char* const names[] = {"four", "four-ordered", "eight", "eight-pairs", "split"};
       const int heads = heads_in_common(Hq / Hkv);

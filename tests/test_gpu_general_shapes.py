@@ -15,8 +15,8 @@ pytestmark = pytest.mark.gpu
 BF16, F32 = torch.bfloat16, torch.float32
 
 # Which launch a layout takes on 256 CUs is checked by tests/test_host_rules.py: those called by a launch's name take it.
-# (lengths, Hq, Hkv): 16-row tiles (head dimensions up to 128); 32-row tiles with the keys split over a workgroup (at least 512
-# of them on 256 CUs); heads sharing a workgroup (at least 1536 of them).  Ragged ends, an empty and
+# (lengths, Hq, Hkv), fp32: the keys of 16 query rows of a head split over a workgroup, few workgroups and more than are resident at
+# once; heads sharing a workgroup (at least 1536 workgroups on 256 CUs).  Ragged ends, an empty and
 # a one-token segment, groups of 1, 2 and 4 heads per KV head.
 LAYOUTS = {"narrow": ([70, 0, 63, 1, 258], 4, 1), "split": ([500, 33, 484], 16, 8), "shared": ([3101, 2, 3137], 32, 8)}
 
@@ -367,7 +367,7 @@ def test_decode_sync_blocks_that_fill_the_chip(dtype, D, Hq):
 
 
 # what a masked key holds must not reach the rows that do not see it: layouts for every tile kernel of the shapes outside
-# bf16 x 64 / 128 (16-row, key-split and shared fp32 tiles; split, 8-wave and 4-wave bf16 launches)
+# bf16 x 64 / 128 (fp32: keys split, few and many workgroups, and heads sharing tiles; bf16: split, 8-wave and 4-wave launches)
 HIDDEN = [("narrow", F32, 64), ("narrow", F32, 40), ("split", F32, 128), ("split", F32, 256), ("shared", F32, 32), ("short", BF16, 72),
           ("short", BF16, 96), ("eight", BF16, 72), ("eight-pairs", BF16, 72), ("local-pairs", BF16, 72), ("long", BF16, 160), ("four", BF16, 40), ("four", BF16, 256)]
 HIDDEN_LAYOUTS = dict(LAYOUTS, **BF16_LAYOUTS, **{"eight": ([214, 1, 259, 0, 262, 263], 32, 8), "eight-pairs": ([578, 1, 502, 0, 866], 32, 8), "local-pairs": ([1249, 1276, 1260, 1275, 1, 0], 12, 4)})   # the poisoned token is in a second walk

@@ -55,7 +55,7 @@ def test_the_layouts_of_the_gpu_tests_take_the_launches_they_name(tmp_path):
             add("four", "bf16", D, *g.BF16_LAYOUTS["four"][1:], 1, sync, g.BF16_LAYOUTS["four"][0])
     for D in (8, 40, 64, 88, 128, 136, 256):
         for name, (lens, Hq, Hkv) in g.LAYOUTS.items():
-            add("split" if name == "narrow" and D > 128 else name, "f32", D, Hq, Hkv, 1, 1, lens)
+            add("shared" if name == "shared" else "keys", "f32", D, Hq, Hkv, 1, 1, lens)
     for layout, name, sync in (("eight", "eight", 1), ("eight-pairs", "eight-pairs", 1), ("local-pairs", "eight-pairs", 0)):
         lens, Hq, Hkv = g.HIDDEN_LAYOUTS[layout]
         add(name, "bf16", 72, Hq, Hkv, 1, sync, lens)
