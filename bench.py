@@ -280,8 +280,9 @@ def prefill_leg(pb: PrefillBench, H: int, ms_step: np.ndarray, pmc_key: str | No
 
 
 class DecodeBench:
-    """cfg4: N participants, one query each per step, all M blocks of a step through
-    fedattn_decode_blocks (one host call per step, blocks of one kind share launches)."""
+    """cfg4: N participants, one query each per step, the M blocks of a step one after the other, as the blocks of a
+    model follow one another (fedattn_decode, a call per block), or all at hand at once (fedattn_decode_blocks, whose
+    blocks of one kind share launches, with a workspace for one block or for all of them)."""
 
     def __init__(self, name: str = "cfg4_decode"):
         self.w = fi.workload(name)
@@ -314,18 +315,23 @@ class DecodeBench:
         rows = w.n_participants * (self.prompt + step + 1)
         return float(rows * w.n_kv_heads * w.head_dim * 2 * 2)
 
-    def run_step(self, step: int, sync_override: int = -1, fused: bool = False):
+    def run_step(self, step: int, sync_override: int = -1, how: str = "each"):
         lens = np.full(self.w.n_participants, self.prompt + step + 1, dtype=np.int32)
         q = self.q[step % self.nq]
-        if fused and self.ws_fused is None:   # one workspace slice per block in flight
+        if how == "each":
+            for b in range(self.M):
+                fa.fedattn_decode(self.p, b, q[b], self.kc[b], self.vc[b], self.out[b], self.seg, lens, sync_override=sync_override,
+                                  workspace=self.ws)
+            return
+        if how == "fused" and self.ws_fused is None:   # one workspace slice per block in flight
             one = self.ws.numel()
             self.ws_fused = torch.empty(one + (self.M - 1) * ((one + 255) // 256 * 256), dtype=torch.uint8, device="cuda")
         fa.fedattn_decode_blocks(self.p, 0, self.M, q, self.kc, self.vc, self.out, q[0].numel(), self.kc[0].numel(),
                                  self.seg, lens, sync_override=sync_override,
-                                 workspace=self.ws_fused if fused else self.ws, fused=fused)
+                                 workspace=self.ws_fused if how == "fused" else self.ws, fused=how == "fused")
 
-    def graphs(self, steps, sync_override: int = -1, fused: bool = False):
-        return [capture(lambda s=s: self.run_step(s, sync_override, fused), self.out) for s in steps]
+    def graphs(self, steps, sync_override: int = -1, how: str = "each"):
+        return [capture(lambda s=s: self.run_step(s, sync_override, how), self.out) for s in steps]
 
 
 def decode_leg(iterations: int, n_steps: int | None = None) -> dict:
@@ -346,12 +352,12 @@ def decode_leg(iterations: int, n_steps: int | None = None) -> dict:
     med = float(np.median(ms))
     gbs = total_bytes / (med * 1e-3) / 1e9
     n_launch = len(all_steps) * db.M
-    # the two kinds of block-step on their own, and the bound without launch effects, on 8 sampled steps
+    # the two kinds of block-step on their own, and steps whose blocks are at hand at once, on 8 sampled steps
     sample = sorted(set(int(s) for s in np.linspace(0, w.decode_steps - 1, 8)))
     sample_bytes = sum(db.bytes_block_step(s) * db.M for s in sample)
     kinds = {}
-    for name, override, fused in (("local", 0, False), ("sync", 1, False), ("blocks_fused", -1, True)):
-        gs = db.graphs(sample, override, fused)
+    for name, override, how in (("local", 0, "each"), ("sync", 1, "each"), ("blocks_shared", -1, "shared"), ("blocks_fused", -1, "fused")):
+        gs = db.graphs(sample, override, how)
         _, m = timed_replays([lambda gs=gs: [g.replay() for g in gs]], max(5, iterations // 2), 1)
         kinds[name] = float(np.median(m))
         del gs
@@ -359,7 +365,7 @@ def decode_leg(iterations: int, n_steps: int | None = None) -> dict:
     pmc = PMC["decode"]
     return {"workload": "%s: N = %d, prompt %d, %d decoding steps x %d blocks, H = %d" % (
                 w.name, w.n_participants, db.prompt, w.decode_steps, db.M, w.sync_interval),
-            "launch": "fedattn_decode_blocks: one host call per decoding step, blocks of a kind share launches; each "
+            "launch": "fedattn_decode, block after block; each "
                       "step replayed from its own HIP graph, all %d steps in order per iteration" % len(all_steps),
             "steps_timed": len(all_steps), "blocks": db.M, "iterations": iterations,
             "gbytes_per_run": total_bytes / 1e9, "ms_per_run": med, "ms_per_run_wall": wall * 1e3,
@@ -373,7 +379,7 @@ def decode_leg(iterations: int, n_steps: int | None = None) -> dict:
                          "local_GBps": rate(kinds["local"]), "sync_GBps": rate(kinds["sync"]),
                          "avg_local_us": kinds["local"] * 1e3 / (len(sample) * db.M),
                          "avg_sync_us": kinds["sync"] * 1e3 / (len(sample) * db.M),
-                         "blocks_fused_GBps": rate(kinds["blocks_fused"]),
+                         "blocks_shared_GBps": rate(kinds["blocks_shared"]), "blocks_fused_GBps": rate(kinds["blocks_fused"]),
                          "kinds_measured_on_steps": sample}}
 
 
@@ -618,9 +624,9 @@ def main() -> int:
     if "decode" in legs_req:
         decode = decode_leg(args.decode_iterations, args.decode_steps)
         log("decode: %.0f GB/s over %d steps x %d blocks (%.1f%% of HBM peak; local block-steps %.0f, sync %.0f, "
-            "blocks sharing launches %.0f GB/s)" % (decode["value"], decode["steps_timed"], decode["blocks"],
+            "blocks sharing launches %.0f GB/s, with room for all of them %.0f)" % (decode["value"], decode["steps_timed"], decode["blocks"],
             100 * decode["frac_of_hbm_peak"], decode["roofline"]["local_GBps"], decode["roofline"]["sync_GBps"],
-            decode["roofline"]["blocks_fused_GBps"]))
+            decode["roofline"]["blocks_shared_GBps"], decode["roofline"]["blocks_fused_GBps"]))
         torch.cuda.empty_cache()
 
     peaks = None
