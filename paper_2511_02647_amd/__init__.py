@@ -217,7 +217,7 @@ def fedattn_decode_blocks(params: fedattn_params, block_idx0: int, n_blocks: int
                           k_cache: torch.Tensor, v_cache: torch.Tensor, out: torch.Tensor, q_block_stride: int,
                           cache_block_stride: int, seg_offsets, seg_lens, remote_lens=None, sync_override: int = -1,
                           workspace: Optional[torch.Tensor] = None, stream=None, fused: bool = False) -> None:
-    """fused=True calls fedattn_decode_blocks_fused (blocks of one kind share launches)."""
+    """fused=True calls fedattn_decode_blocks_fused (blocks of one kind share launches without a look at their addresses)."""
     _check(_calls().decode_blocks(params, block_idx0, n_blocks, q, k_cache, v_cache, out, q_block_stride,
                                    cache_block_stride, seg_offsets, seg_lens, remote_lens, sync_override, workspace,
                                    stream, fused))

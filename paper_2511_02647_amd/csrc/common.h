@@ -98,7 +98,7 @@ struct DecodeArgs {
   float* part_o;            // [Hkv, n_chunks, cols, D] fp32: sum_j p_j v_j with p_j = 2^(s_j - m), unnormalised
   float* part_ml;           // [Hkv, n_chunks, cols, 2] (m in log2 domain, l)
   uint64_t* counters;       // [Hkv, N] chunks counted in per (KV head, segment), sync block: [Hkv, 0]; zero after a launch
-  uint64_t ticket;          // first launch of a call: the call's number, 48 bits, marks the counters as set up; later ones: 0
+  uint64_t ticket;          // a call's first launch of a kind (local / sync): the call's number, 48 bits, marks the counters as set up; later ones: 0
   int32_t merge_in_kernel;  // the split kernel writes the output rows itself (no combine launch)
   int32_t N, Hq, Hkv, D;
   int32_t n_cus;            // compute units of the device (launch shape heuristics)
@@ -109,8 +109,8 @@ struct DecodeArgs {
   int32_t has_remote;       // remote_lens given
   float scale;
   // several blocks in one launch (grid z, or y for the combine): block z is block_list[z]
-  // blocks of block_stride bytes away from q/out and the caches, and works in its own slice
-  // of the workspace (slice_bytes apart, partials and counters laid out alike in every slice)
+  // blocks of q_block_bytes / cache_block_bytes away from q, out and the caches, and works in its own slice
+  // of the workspace (slice_bytes apart, partials and counters laid out alike in every slice of a kind)
   int64_t q_block_bytes;
   int64_t cache_block_bytes;
   int64_t slice_bytes;

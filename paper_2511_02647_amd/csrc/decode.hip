@@ -4,9 +4,10 @@
 // Split-KV: a workgroup takes one chunk of one participant's cache segment for
 // one KV head and ALL query rows that may see it - the G query heads of that
 // participant in a local block, the N*G rows of all participants in a sync block
-// (the aggregated cache is read once for everybody).  The chunk streams through a
-// 3-stage LDS ring of 64-row K/V tiles filled by direct HBM -> LDS loads (two
-// tiles in flight per workgroup, one workgroup per CU).  Every wavefront works on
+// (the aggregated cache is read once for everybody).  The chunk streams through an
+// LDS ring of 64-row K/V tiles filled by direct HBM -> LDS loads: three stages, two tiles in
+// flight, where every CU has at most one workgroup, else (head dimensions padded to 96 or 128) two
+// stages, so that more workgroups are resident.  Every wavefront works on
 // every tile: wavefront w takes tile rows 16w..16w+15 against all query columns,
 // S^T[kv][q] = K Q^T on v_mfma_f32_16x16x32_bf16 and O^T[d][q] += V^T P^T on
 // v_mfma_f32_16x16x16_bf16, whose k-slots are exactly the 4 rows per lane that the
@@ -27,7 +28,7 @@ namespace {
 // Three stages of 64-row K/V tiles (96 KB per workgroup, two tiles in flight while one is
 // worked on): measured against four stages (three in flight), the deeper ring only lengthens
 // the queue in front of the memory system; a block-step of 16 x 1152 rows takes 17.4 instead
-// of 18.0 us.
+// of 18.0 us.  Launches of more workgroups than CUs: launch_stream_mode.
 // (Rows of more than 192 elements: two, three do not fit LDS.)
 template <int D>
 constexpr int decode_stages() { return D > 192 ? 2 : 3; }

@@ -51,7 +51,7 @@ __device__ __attribute__((always_inline)) inline DecodeChunk find_decode_chunk(c
 // Chunks whose partials are merged into the same output rows: those of a segment (local block) or all
 // (sync block).  The workgroup that finishes the last of them merges.  Their counter holds (ticket of the
 // call) << 16 | chunks counted in, and every launch leaves it at zero.  What it holds before a call does not
-// matter: in a call's first launch (ticket set) the first workgroups put the ticket there.
+// matter: in a call's first launch of a kind (ticket set) the first workgroups put the ticket there.
 struct MergeSet {
   int first, count;
   uint64_t* cnt;

@@ -77,7 +77,7 @@ __device__ inline void wait_vmcnt() {
   __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
 }
 
-// Gives the wavefronts that share a SIMD different issue priorities for good, by the slot each of them has there.  
+// Gives the wavefronts that share a SIMD different issue priorities for good, by the slot each of them has there.
 __device__ inline void priority_by_slot() {
   switch (__builtin_amdgcn_s_getreg((1 << 11) | 4)) {   // HW_ID: low two bits of the slot
     case 1: __builtin_amdgcn_s_setprio(1); break;

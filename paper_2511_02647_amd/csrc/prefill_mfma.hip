@@ -39,8 +39,8 @@ namespace {
 // sits between the two products that depend on it, and spreading it under the MFMAs of the
 // neighbouring tiles instead measured slower).  Three wavefronts per SIMD where the registers allow
 // it (head dimension up to 64: 8 x 2000 tokens, 32/8 heads, sync 1132 -> 1032 us against two).
-// NG = 2, for grids that would
-// leave one workgroup per CU: 8 wavefronts = two groups of 4 on the same query rows;
+// NG = 2, where the estimate of choose_prefill_launch takes it to be faster (few workgroups per
+// CU): 8 wavefronts = two groups of 4 on the same query rows;
 // group g takes the KV tiles j with j mod 2 == g through its own LDS stages and the two
 // partial results are merged at the end (split-KV inside the workgroup).
 // FOLD: the softmax scale (and the change to base 2) is folded into the Q operand and the
