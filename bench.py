@@ -57,11 +57,11 @@ PEAK_HBM_GBS = 8000.0       # MI355X HBM3E
 #   mfma_util      SQ_VALU_MFMA_BUSY_CYCLES / (4 SIMDs x SQ_BUSY_CU_CYCLES): share of the cycles a
 #                  busy CU's matrix pipes were busy
 PMC = {
-    "cfg3": {"source": "profiles/hbm_traffic_pmc.txt, profiles/prefill_pmc_counters.txt", "traffic_bytes": 553101325, "mfma_util": 0.581},
-    "cfg3_H4": {"source": "profiles/hbm_traffic_pmc.txt, profiles/prefill_pmc_counters.txt", "traffic_bytes": 500240550, "mfma_util": 0.571},
-    "cfg5": {"source": "profiles/hbm_traffic_pmc.txt, profiles/prefill_pmc_counters.txt", "traffic_bytes": 1165436734, "mfma_util": 0.524},
-    "cfg2": {"source": "profiles/hbm_traffic_pmc.txt, profiles/prefill_pmc_counters.txt", "traffic_bytes": 42180319, "mfma_util": 0.291},
-    "decode": {"source": "profiles/hbm_traffic_pmc.txt", "traffic_bytes": 81643417},
+    "cfg3": {"source": "profiles/hbm_traffic_pmc.txt, profiles/prefill_pmc_counters.txt", "traffic_bytes": 551285316, "mfma_util": 0.575},
+    "cfg3_H4": {"source": "profiles/hbm_traffic_pmc.txt, profiles/prefill_pmc_counters.txt", "traffic_bytes": 498965680, "mfma_util": 0.566},
+    "cfg5": {"source": "profiles/hbm_traffic_pmc.txt, profiles/prefill_pmc_counters.txt", "traffic_bytes": 1166154266, "mfma_util": 0.518},
+    "cfg2": {"source": "profiles/hbm_traffic_pmc.txt, profiles/prefill_pmc_counters.txt", "traffic_bytes": 42203350, "mfma_util": 0.295},
+    "decode": {"source": "profiles/hbm_traffic_pmc.txt", "traffic_bytes": 81654040},
 }
 
 CFG3_SWEEP = (1, 4, 8, 32)
