@@ -182,9 +182,10 @@ inline void lay_out_heads(PrefillArgs& a) {
 }
 
 // Host side: the list of query tiles that the workgroups of a launch of one block take.  A workgroup without a list finds its
-// tile in the segment tables: about 300 instructions at 4 to 5 cycles each before its first load (bf16, head dimension 96, 4 x 100..900 tokens,
-// 8/2 heads, two launches 40.2 and 39.8 us; small blocks up to 10 % of the call).  kMaxListedTiles is what fits beside the tables in the
-// argument block; launches with more tiles have several rounds of workgroups, whose starts hide behind one another.
+// tile in the segment tables, 0.3 to 0.4 us before its first load.  Without and with a list, us: 39 and 22 tokens, 6/2 heads of 64 4.45 and 4.02, 64 and
+// 76 tokens, 8/8 heads of 128 6.03 and 5.72, 4 x 100..900 tokens, 8/2 heads of 96, two launches 38.9 and 37.7, 4 x 512, 32/8 heads of 128, four
+// launches 94.5 and 94.2.  kMaxListedTiles is what fits beside the tables in the argument block; launches with more tiles have several
+// rounds of workgroups, whose starts hide behind one another (16 x 4096 tokens: no difference).
 struct TileList {
   PrefillArgs& a;
   explicit TileList(PrefillArgs& args) : a(args) { a.n_listed = 0; }
