@@ -167,8 +167,9 @@ inline PrefillLaunch launch_to_take(const PrefillShape& a, bool is_sync) {
 // 1.32 (median 1.05; 19 x 431..458, 4/4 heads of 64, 5.2: 65.9 and 57.7); others, below the limit 0.97 to 1.17, beyond it 0.93 to 1.15 (median 1.02).
 inline bool read_apart(const PrefillShape& a) {
   const double total = a.seg_off[a.n];
+  if (a.D != 64 && total < 32.0 * a.n) return false;   // whichever launch it is; such calls are bound by the host (27 x 1..19 tokens: 18.9 and 18.6 us)
   if (launch_to_take(a, true) == kSplit)
-    return (a.D == 64 || total >= 32.0 * a.n) && count_walks(a, true, kWaveRows, 256, a.Hq).total * kWaveRows * a.n <= 4.5 * a.n_cus * total;
+    return count_walks(a, true, kWaveRows, 256, a.Hq).total * kWaveRows * a.n <= 4.5 * a.n_cus * total;
   const double tiles = count_walks(a, true, a.q_tile_rows, kKvTile, a.Hkv * (a.Hq / a.Hkv / a.heads_per_wg)).total / a.n_cus;
   return total >= 128.0 * a.n && tiles <= 150 && tiles * kKvTile * a.n <= 12 * total;
 }
