@@ -278,8 +278,8 @@ def test_keep_list_compaction(layout, chunk):
 
 
 @pytest.mark.parametrize("lens", [[1 + 5 * (i % 7) for i in range(fa.FEDATTN_MAX_PARTICIPANTS)], [300, 0, 1, 64, 65, 130, 17, 16, 90], [33, 70, 1, 129]])
-@pytest.mark.parametrize("D", [24, 64, 96, 128])
-@pytest.mark.parametrize("chunk,share", [(1, 0.1), (1, 0.6), (20, 0.5), (64, 0.5), (192, 1.0), (1, 0.0)])
+@pytest.mark.parametrize("D", [24, 96, 128])
+@pytest.mark.parametrize("chunk,share", [(1, 0.1), (20, 0.6), (64, 0.5), (1, 0.0)])
 def test_f32_keep_lists_of_short_tiles(lens, D, chunk, share):
     """Lists of none to 127 tiles of 1 to 64 rows: empty slices left out (from four participants on, from eight with chunks of a tile and more) or walked."""
     Hq, Hkv = 2, 1
