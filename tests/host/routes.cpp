@@ -1,6 +1,7 @@
 // The library's host side with its launchers replaced by ones that write down what they are asked to launch: which
 // kernels a call takes and what it hands them, without a device.  Pointers stand for device memory and are never read.
 #include <cstdio>
+#include <cstdlib>
 #include <cstring>
 #include <string>
 #include <vector>
@@ -117,8 +118,80 @@ static void decode_launches() {
   }
 }
 
+// Random decode calls: every launch's partials and chunk counters lie inside the workspace, and those of the blocks that share it apart.
+static void decode_workspaces() {
+  std::srand(7);
+  char* base = reinterpret_cast<char*>(0x7000000000ull);
+  char* ws = base + (1ull << 40);
+  for (int t = 0; t < 4000; ++t) {
+    static const int kv[] = {1, 2, 3, 8, 16}, groups[] = {1, 2, 3, 4, 8}, dims[] = {8, 64, 72, 96, 128, 200, 256};
+    const int N = 1 + std::rand() % (std::rand() % 2 ? 8 : 128), Hkv = kv[std::rand() % 5], Hq = Hkv * groups[std::rand() % 5], D = dims[std::rand() % 7];
+    const int most = 1 << (std::rand() % 13), M = 1 + std::rand() % 40;
+    const fedattn_params p = {N, Hq, Hkv, D, 1 + std::rand() % 4, 1, std::rand() % 2 ? FEDATTN_BF16 : FEDATTN_F32, 0.f};
+    std::vector<int32_t> seg = {0}, lens, remote;
+    for (int n = 0; n < N; ++n) {
+      lens.push_back(std::rand() % (most + 1));
+      remote.push_back(std::rand() % (lens[n] + 3));
+      seg.push_back(seg[n] + lens[n] + 2);
+    }
+    const size_t need = fedattn_workspace_bytes(&p, FEDATTN_OP_DECODE, seg[N], 0), extra = std::rand() % 3 ? 0 : (size_t)(std::rand() % 5) * need + std::rand() % 4096;
+    const size_t bytes = need + extra / 16 * 16;
+    const int64_t q = (int64_t)N * Hq * D, cache = (int64_t)seg[N] * Hkv * D;
+    launched.clear();
+    const auto call = std::rand() % 2 ? fedattn_decode_blocks : fedattn_decode_blocks_fused;
+    EXPECT(call(&p, 0, M, base, base + (1ull << 36), base + (2ull << 36), base + (3ull << 36), q, cache, seg.data(), lens.data(),
+                std::rand() % 2 ? remote.data() : nullptr, -1, ws, bytes, nullptr) == FEDATTN_OK);
+    for (const Launch& l : launched) {
+      const DecodeArgs& a = l.decode;
+      if (a.part_o == nullptr) continue;   // one wavefront per participant and head: no partials
+      const size_t rows = (size_t)a.n_g * a.n_chunks * a.n_cols;
+      const size_t o = (size_t)(reinterpret_cast<char*>(a.part_o) - ws), ml = (size_t)(reinterpret_cast<char*>(a.part_ml) - ws);
+      const size_t cnt = (size_t)(reinterpret_cast<char*>(a.counters) - ws), last = (size_t)(l.blocks - 1) * (size_t)a.slice_bytes;
+      const size_t end = cnt + (size_t)Hkv * N * sizeof(uint64_t);
+      EXPECT(o + rows * D * 4 <= ml && ml + rows * 8 <= cnt);
+      EXPECT(l.blocks >= 1 && l.blocks <= kMaxFusedBlocks && last + end <= bytes);
+      EXPECT(l.blocks == 1 || end <= (size_t)a.slice_bytes);
+      EXPECT(ml % 8 == 0 && cnt % 8 == 0 && (l.blocks == 1 || a.slice_bytes % 16 == 0));
+    }
+    if (failures) return;
+  }
+}
+
+// The list of query tiles names, for every workgroup, the tile that the search of the segment tables finds.
+static void listed_tiles() {
+  std::srand(8);
+  for (int t = 0; t < 4000; ++t) {
+    PrefillArgs a;
+    std::memset(static_cast<void*>(&a), 0, sizeof(a));
+    const int N = a.seg.n = 1 + std::rand() % (std::rand() % 2 ? 6 : kMaxP), most = 1 << (std::rand() % 14), rows = 16 << (std::rand() % 4);
+    const bool sync = std::rand() % 2 != 0;
+    a.short_half_ascending = std::rand() % 2;
+    for (int n = 0; n < N; ++n) a.seg.seg_off[n + 1] = a.seg.seg_off[n] + (std::rand() % 5 == 0 ? 0 : std::rand() % (most + 1));
+    lay_out_query_tiles(a, rows);
+    order_segments_by_length(a);   // pair_cum: tiles in that order
+    list_heavy_first(a, sync);
+    const int T = a.n_q_tiles, half = (T + 1) / 2;
+    EXPECT(a.n_listed == (T <= kMaxListedTiles ? T : 0));
+    for (int p = 0; p < a.n_listed; ++p) {
+      const int rank = a.short_half_ascending && p >= half ? T - 1 - (p - half) : p;
+      int n = 0, tile = T - 1 - rank;
+      if (!sync) {
+        int s = 0;
+        while (rank >= a.seg.pair_cum[s + 1]) ++s;
+        tile = a.seg.tile_cum[a.seg_order[s] + 1] - 1 - (rank - a.seg.pair_cum[s]);
+      }
+      while (tile >= a.seg.tile_cum[n + 1]) ++n;
+      const uint32_t e = a.tile_list[p >> 1] >> (16 * (p & 1)) & 0xffffu;
+      EXPECT((int)(e & 127) == n && (int)(e >> 7) == tile - a.seg.tile_cum[n]);
+    }
+    if (failures) return;
+  }
+}
+
 int main() {
+  listed_tiles();
   decode_launches();
+  decode_workspaces();
   output_over_matrices();
   std::puts(failures ? "wrong" : "clean");
   return failures != 0;

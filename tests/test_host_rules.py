@@ -17,7 +17,7 @@ def run(tmp_path, name, stdin=""):
 
 
 def test_routes_of_calls(tmp_path):
-    """Which launches calls take (tests/host/routes.cpp)."""
+    """Which launches calls take, and what they hand them: workspaces, lists of tiles (tests/host/routes.cpp)."""
     hipcc = "/opt/rocm/bin/hipcc"
     if not os.path.exists(hipcc):
         pytest.skip("hipcc not found")
